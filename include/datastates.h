@@ -174,7 +174,8 @@ typedef struct ds_plan_stats {
   uint64_t chunk_bytes;   /* image bytes per work-group chunk                     */
   uint64_t n_strided;     /* shards that are not one contiguous run               */
   uint64_t align;
-  uint64_t n_general_chunks; /* chunks that take the kernel's general path (the lean path takes the rest) */
+  uint64_t n_general_chunks; /* chunks the lean path does not take (the general path does, or the block route
+                                of views with runs shorter than 16 bytes) */
   uint64_t n_files;       /* 1 for a plan of ds_plan_create                       */
 } ds_plan_stats;
 
@@ -234,10 +235,13 @@ int ds_unpack(const ds_plan *plan, const void *src_dev, uint64_t img_lo, uint64_
  * Limit: the tables (168 bytes per non-empty shard, 36 bytes per work-group
  * chunk of the image, i.e. about 2.3 KiB per MiB of image) must fit the array:
  * an image of about 1.7 GB with few shards does, DS_ETOOBIG otherwise
- * (returned before anything is enqueued).  All calls on one GPU share the one
- * array and it keeps the last call's tables: calls on the same stream are
- * ordered by it, calls that may overlap on one GPU (different streams, or
- * different threads) race and are the caller's to serialise.  Arguments and
+ * (returned before anything is enqueued).  Views with runs shorter than
+ * 16 bytes are moved in blocks if the tables of those (176 bytes per such view,
+ * 8 per block, 36 per other chunk) fit behind the rest, unit by unit if not.
+ * All calls on one GPU share the one array and it keeps the last call's tables:
+ * calls on the same stream are ordered by it, calls that may overlap on one GPU
+ * (different streams, or different threads) race and are the caller's to
+ * serialise.  Arguments and
  * the other errors as for ds_pack; the current device is the one that runs it.
  */
 #define DS_PACK_NOALLOC_TABLE_BYTES (4u << 20)

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "datastates.h"
+#include "ds_perm.h"
 
 // A tile is one non-empty shard in device form: the view is normalised to
 // "outer index -> start of a contiguous run of run_bytes".  Its place in the
@@ -32,17 +33,19 @@ struct DsTileHot {
   uint64_t nbytes;   // payload bytes
   uint64_t stride0;  // distance between runs in bytes (views with one outer dimension)
   uint32_t run;      // run length in bytes, views with one outer dimension (0 otherwise)
-  uint32_t meta;     // n_outer | log2(itemsize) << 8.  n_outer is given as 2 for a view with one outer
-                     // dimension whose runs do not fit 32 bits: it then takes the routes of the N-D views
+  uint32_t meta;     // n_outer | log2(itemsize) << 8 | DS_HOT_PERM.  n_outer is given as 2 for a view with one
+                     // outer dimension whose runs do not fit 32 bits: it then takes the routes of the N-D views
 };
+enum : uint32_t { DS_HOT_PERM = 1u << 17 };  // the view's whole units are moved in blocks (ds_perm.h)
 static_assert(sizeof(DsTileHot) == 40, "five 8-byte words");
 
 // What the kernel's lean path needs to move one whole chunk, in one 32-byte load.
 // Chunks that are not "simple" (a tile boundary, the end of a payload or
 // padding inside the chunk, more than one outer dimension, rows shorter than
 // 16 bytes) are of kind DS_CHUNK_GENERAL and take the general path; their
-// record names the tiles they hold (tile, col0).
-enum : uint32_t { DS_CHUNK_CONTIG = 0, DS_CHUNK_ROWS = 1, DS_CHUNK_GENERAL = 2 };
+// record names the tiles they hold (tile, col0).  DS_CHUNK_PERM: the whole chunk is whole units of one view that is
+// moved in blocks (ds_perm.h); its record is that of a general chunk, for launches without the block tables.
+enum : uint32_t { DS_CHUNK_CONTIG = 0, DS_CHUNK_ROWS = 1, DS_CHUNK_GENERAL = 2, DS_CHUNK_PERM = 3 };
 // CONTIG only, bit 8 of `kind`: the tensor side of the chunk is not 16-byte aligned, and the tensor has at least
 // 16 more bytes on either side of it, so the gather may read the 16-byte aligned units that cover the chunk's
 // bytes (one more than the chunk has) without leaving the tensor.
@@ -105,7 +108,12 @@ struct ds_plan {
   std::vector<DsTileHot> hot;              // n_tiles + 1 entries, image order, last = sentinel
   std::vector<uint32_t> first_tile;        // n_chunks + 1 entries, last = n_tiles
   std::vector<DsChunkRec> recs;            // one per chunk
-  uint64_t n_general = 0;                  // chunks of kind DS_CHUNK_GENERAL
+  std::vector<DsPerm> perms;               // views moved in blocks, image order
+  std::vector<DsPermItem> perm_items;      // their blocks, view by view
+  std::vector<uint32_t> perm_first;        // perms.size() + 1 entries: a view's first block
+  std::vector<uint32_t> rest_ids;          // if there are such views: the chunks that are not of kind DS_CHUNK_PERM ...
+  std::vector<DsChunkRec> rest_recs;       // ... and their records, so that a launch has no empty work items
+  uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL and DS_CHUNK_PERM)
   // device copies (one allocation)
   int device = -1;
   void *dev_blob = nullptr;
@@ -113,6 +121,10 @@ struct ds_plan {
   const DsTileHot *d_hot = nullptr;
   const uint32_t *d_first_tile = nullptr;
   const DsChunkRec *d_recs = nullptr;
+  const DsPerm *d_perms = nullptr;
+  const DsPermItem *d_perm_items = nullptr;
+  const uint32_t *d_rest_ids = nullptr;
+  const DsChunkRec *d_rest_recs = nullptr;
   uint64_t n_chunks() const { return first_tile.empty() ? 0 : first_tile.size() - 1; }
 };
 

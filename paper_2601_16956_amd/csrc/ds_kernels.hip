@@ -41,6 +41,7 @@
 // for runs shorter than 16 bytes, moved element by element, so no byte outside
 // the described views is ever read or written.
 
+#include <algorithm>
 #include <mutex>
 
 #include "ds_internal.h"
@@ -68,11 +69,12 @@ struct MoveArgs {
 
 struct LeanArgs {
   const DsChunkRec *recs;
+  const uint32_t *ids; // LIST launches: the chunk a record belongs to
   uint8_t *img;        // points at image byte img_lo
   uint64_t img_lo;
   uint32_t chunk_log2;
-  uint32_t c_lo;       // first whole chunk inside [img_lo, img_hi)
-  uint32_t n_chunks;   // whole chunks inside the range
+  uint32_t c_lo;       // record of the first whole chunk inside [img_lo, img_hi)
+  uint32_t n_chunks;   // records of whole chunks inside the range
   uint32_t xcd_span;   // chunks per XCD (ceil(n_chunks / 8)); 0 = work-group i takes chunk i
 };
 
@@ -375,7 +377,8 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 // of a 2-D view), padding, and units cut by the end of a run of at least 16 bytes are handled in the phases;
 // only the rest (runs shorter than 16 bytes, views with several outer dimensions) goes one by one through
 // move_unit afterwards.
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST>
+// LIST: a launch of blocks moves the views marked DS_HOT_PERM.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST>
 __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t t0, uint32_t t1, GenLds *g) {
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & (kWave - 1);
@@ -410,6 +413,10 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
         meta = h->meta;
         const uint64_t te = h[1].img_off;  // the entry behind the last tile is a sentinel
         lo = tb > cb ? tb : cb;
+        if (LIST && (meta & DS_HOT_PERM)) {  // its whole units are moved in blocks: what is left is the cut unit and padding
+          const uint64_t rest = tb + (nbytes & ~(uint64_t)15);
+          lo = rest > lo ? rest : lo;
+        }
         hi = te < ce ? te : ce;
         if (hi < lo) hi = lo;
       }
@@ -633,7 +640,9 @@ __device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd
 // Work item ci of a launch: moves its chunk if the chunk is lean and returns false; for a general chunk it
 // moves nothing, says which chunk and tiles (c, t0, t1) and returns true: the caller sends it down the general
 // path (one call site, so that the general path is in the kernel once).
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST>
+// LIST: the launch's records are not those of all its chunks, and `ids` names the chunk of each.  A template
+// parameter and not a test of the pointer: the test alone made a 23 MB gather 0.9 us slower.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST>
 __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint64_t &c_gen, uint32_t &t0, uint32_t &t1) {
   const uint32_t tid = threadIdx.x;
   {
@@ -646,10 +655,10 @@ __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint6
       cm = (ci & 7u) * a.xcd_span + (ci >> 3);
       if (cm >= a.n_chunks) return false;
     }
-    const uint32_t c = a.c_lo + cm;
-    const DsChunkRec r = a.recs[c];
+    const DsChunkRec r = a.recs[a.c_lo + cm];
+    const uint32_t c = LIST ? a.ids[a.c_lo + cm] : a.c_lo + cm;
     const uint32_t kind = r.kind & 0xFF;  // bits 8.. hold log2(itemsize)
-    if (kind == DS_CHUNK_GENERAL) {
+    if (kind >= DS_CHUNK_GENERAL) {
       // its record names the tiles it holds: one load away from them, and in place among its neighbours
       c_gen = c;
       t0 = r.tile;
@@ -782,7 +791,7 @@ __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint6
 // more of it -- five for the gather, whose registers allow no more, six for the scatter (measured on tables
 // where every chunk is general: +8 to +10 % both ways with five, another +6 to +10 % for the scatter of tiny
 // tensors with six), while the lean path loses 2 to 5 % there.
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES>
+template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, bool LIST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
                                                                                                      MoveArgs ma) {
   __shared__ GenLds s_gen;
@@ -793,7 +802,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES)))
     uint32_t t0 = 0, t1 = 0;
     bool general = true;
     if (wi < n_lean) {
-      general = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST>(la, wi, c, t0, t1);
+      general = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST, LIST>(la, wi, c, t0, t1);
     } else {
       // a chunk cut by the range: the general path clips to the range, whatever the chunk's kind
       c = ma.extra[wi - n_lean];
@@ -803,17 +812,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES)))
       t1 = ma.first_tile[c + 1];
       if (ma.hot[t1].img_off >= c_end) --t1;  // that tile starts where this chunk ends
     }
-    if (general) general_chunk<PACK, 256, 4, NTL, NTS, BUFST>(ma, c, t0, t1, &s_gen);
+    if (general) general_chunk<PACK, 256, 4, NTL, NTS, BUFST, LIST>(ma, c, t0, t1, &s_gen);
   }
 }
 
-template <bool PACK, bool NTL, bool NTS, bool BUFST, int WAVES = 4>
+template <bool PACK, bool NTL, bool NTS, bool BUFST, int WAVES = 4, bool LIST = false>
 int launch_move(uint32_t chunk_log2, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, hipStream_t stream) {
   uint32_t grid = (la.xcd_span ? la.xcd_span * 8 : la.n_chunks) + ma.n_extra;
   if (grid == 0) return DS_OK;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
 #define DS_MOVE(UN) \
-  hipLaunchKernelGGL((ds_move_kernel<PACK, UN, NTL, NTS, BUFST, WAVES>), dim3(grid), dim3(256), 0, stream, la, ma)
+  hipLaunchKernelGGL((ds_move_kernel<PACK, UN, NTL, NTS, BUFST, WAVES, LIST>), dim3(grid), dim3(256), 0, stream, la, ma)
   switch (chunk_log2) {
     case 13: DS_MOVE(2); break;
     case 14: DS_MOVE(4); break;
@@ -821,6 +830,80 @@ int launch_move(uint32_t chunk_log2, const LeanArgs &la, const MoveArgs &ma, uin
     default: return DS_EINVAL;
   }
 #undef DS_MOVE
+  DS_HIP_TRY(hipGetLastError());
+  return DS_OK;
+}
+
+// ---- views with runs shorter than 16 bytes, in blocks through LDS (ds_perm.h) ---------------------------
+// Bound by the memory system's handling of 128-byte pieces: a block reads (scatter: writes) 128 bytes at a time
+// along a, one row of the tensor after the other, and 256 bytes and more along b.  Measured, gather / scatter
+// (two thirds of the working set in the last-level cache, launch included): bf16 4096 x 4120 transposed 18.0 / 16.8
+// us = 3.8 / 4.0 TB/s, odd extents 28 / 25 us, four transposed 4096 x 1024 experts 16.2 / 16.4 us, every second
+// fp32 column 10.9 / 14.4 us; unit by unit the table of such views of perf/cases.py took 460 / 524 us, now
+// 103 / 109.  Blocks are numbered along b first: along a first costs 15 % of the gather.  Five wavefronts per
+// SIMD hold the 16 loads of a thread without scratch; four and six measure 3 to 8 % slower.
+struct PermArgs {
+  const DsPerm *perms;
+  const DsPermItem *items;  // the launch's first block
+  uint32_t n_items;
+  uint32_t xcd_span;        // blocks per XCD, as in LeanArgs
+  uint8_t *img;             // points at image byte img_lo
+  uint64_t img_lo, img_hi;
+};
+
+template <typename E, typename W, bool PACK>
+__device__ __forceinline__ void move_perm_block(const DsPerm &d, const DsPermBlock &k, const PermArgs &a, uint8_t *lds) {
+  const uint32_t tid = threadIdx.x;
+  if (PACK) {
+    ds_perm_tensor_side<E, W, true>(d, k, lds, tid);
+    __syncthreads();
+    // rows that end inside a line leave its rest to another block: the line is better kept in the L2 until then
+    // (bytes transposed into rows of 112: 16.1 us streaming, 12.1 us cached; rows of whole lines 16.2 and 17.7)
+    // (Two loops: one loop with both stores is compiled to one store, the cached one.)
+    if (d.flags & kPermLines)
+      ds_perm_image_store<E>(d, k, lds, a.img, a.img_lo, tid, [](uint64_t p, const DsPermUnit &v) {
+        st16_aligned<true>((uint8_t *)p, u32x4{v.w[0], v.w[1], v.w[2], v.w[3]});
+      });
+    else
+      ds_perm_image_store<E>(d, k, lds, a.img, a.img_lo, tid, [](uint64_t p, const DsPermUnit &v) {
+        st16_aligned<false>((uint8_t *)p, u32x4{v.w[0], v.w[1], v.w[2], v.w[3]});
+      });
+  } else {
+    ds_perm_image_load(d, k, lds, a.img, a.img_lo, tid, [](uint64_t p) {
+      const u32x4 v = ld16_aligned<false>((const uint8_t *)p);
+      return DsPermUnit{{v.x, v.y, v.z, v.w}};
+    });
+    __syncthreads();
+    ds_perm_tensor_side<E, W, false>(d, k, lds, tid);
+  }
+}
+
+template <bool PACK>
+__global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t s_block[kPermLdsBytes];
+  const uint32_t n = a.xcd_span ? a.xcd_span * 8u : a.n_items;
+  for (uint32_t wi = blockIdx.x; wi < n; wi += gridDim.x) {
+    const uint32_t i = a.xcd_span ? (wi & 7u) * a.xcd_span + (wi >> 3) : wi;
+    if (i >= a.n_items) continue;
+    const DsPermItem item = a.items[i];
+    const DsPerm &d = a.perms[item.perm];
+    DsPermBlock k;
+    if (!ds_perm_block(d, item.tile, a.img_lo, a.img_hi, PACK, k)) continue;
+    switch (d.flags & 0xFFu) {
+      case 0: move_perm_block<uint8_t, uint32_t, PACK>(d, k, a, s_block); break;
+      case 1: move_perm_block<uint16_t, uint32_t, PACK>(d, k, a, s_block); break;
+      case 2: move_perm_block<uint32_t, uint32_t, PACK>(d, k, a, s_block); break;
+      default: move_perm_block<uint64_t, uint64_t, PACK>(d, k, a, s_block); break;
+    }
+    __syncthreads();  // the block in LDS has been used
+  }
+}
+
+int launch_perm(bool pack, const PermArgs &a, uint32_t grid_limit, hipStream_t stream) {
+  uint32_t grid = a.xcd_span ? a.xcd_span * 8 : a.n_items;
+  if (grid_limit && grid > grid_limit) grid = grid_limit;
+  if (pack) hipLaunchKernelGGL(ds_perm_kernel<true>, dim3(grid), dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(ds_perm_kernel<false>, dim3(grid), dim3(256), 0, stream, a);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
@@ -1030,9 +1113,14 @@ struct DeviceTables {
   const DsTileHot *hot;
   const uint32_t *first_tile;
   const DsChunkRec *recs;
+  const DsPerm *perms;             // null: no block tables, the general path takes those views
+  const DsPermItem *perm_items;
+  const uint32_t *rest_ids;        // the chunks left beside them
+  const DsChunkRec *rest_recs;
 };
 
-int launch_move_with(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_t *img, uint64_t img_lo,
+// The chunks of the range, lean and general, in one launch.
+int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_t *img, uint64_t img_lo,
                      uint64_t img_hi, uint32_t grid_limit, hipStream_t stream) {
   const uint32_t lg = plan->chunk_log2;
   const uint64_t C = (uint64_t)1 << lg;
@@ -1044,11 +1132,20 @@ int launch_move_with(const ds_plan *plan, const DeviceTables &tb, bool pack, uin
   if (img_hi == plan->total_bytes) w_hi = n_total;  // the last chunk may be short; its record says 'general' then
   LeanArgs la;
   la.recs = tb.recs;
+  la.ids = nullptr;
   la.img = img;
   la.img_lo = img_lo;
   la.chunk_log2 = lg;
   la.c_lo = (uint32_t)w_lo;
   la.n_chunks = w_hi > w_lo ? (uint32_t)(w_hi - w_lo) : 0;
+  if (tb.perms && la.n_chunks) {
+    const auto first = std::lower_bound(plan->rest_ids.begin(), plan->rest_ids.end(), (uint32_t)w_lo);
+    const auto last = std::lower_bound(first, plan->rest_ids.end(), (uint32_t)w_hi);
+    la.recs = tb.rest_recs;
+    la.ids = tb.rest_ids;
+    la.c_lo = (uint32_t)(first - plan->rest_ids.begin());
+    la.n_chunks = (uint32_t)(last - first);
+  }
   la.xcd_span = ds_cfg_variant() == 3 ? 0 : (la.n_chunks + 7) / 8;
   // ... and the one or two chunks cut by the ends of the range, clipped by the general path
   MoveArgs ma;
@@ -1072,6 +1169,9 @@ int launch_move_with(const ds_plan *plan, const DeviceTables &tb, bool pack, uin
     if (c_last >= w_hi) ma.extra[ma.n_extra++] = (uint32_t)c_last;
   }
   const uint64_t variant = ds_cfg_variant();
+  if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
+    return pack ? launch_move<true, true, true, true, 4, true>(lg, la, ma, grid_limit, stream)
+                : launch_move<false, true, true, false, 4, true>(lg, la, ma, grid_limit, stream);
   if (variant == 1) {  // plain loads and stores
     return pack ? launch_move<true, false, false, false>(lg, la, ma, grid_limit, stream)
                 : launch_move<false, false, false, false>(lg, la, ma, grid_limit, stream);
@@ -1090,6 +1190,28 @@ int launch_move_with(const ds_plan *plan, const DeviceTables &tb, bool pack, uin
               : launch_move<false, true, true, false>(lg, la, ma, grid_limit, stream);
 }
 
+int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *img, uint64_t img_lo, uint64_t img_hi,
+                     uint32_t grid_limit, hipStream_t stream) {
+  const uint64_t variant = ds_cfg_variant();
+  if (variant == 1 || variant == 2 || variant == 5) tb.perms = nullptr;
+  const int rc = launch_chunks(plan, tb, pack, img, img_lo, img_hi, grid_limit, stream);
+  if (rc != DS_OK || !tb.perms) return rc;
+  // the views that are moved in blocks and have a whole unit in the range
+  size_t v0 = 0, v1 = plan->perms.size();
+  while (v0 < v1 && plan->perms[v0].end16 <= img_lo) ++v0;
+  while (v1 > v0 && plan->perms[v1 - 1].img >= img_hi) --v1;
+  if (v0 == v1) return DS_OK;
+  PermArgs a;
+  a.perms = tb.perms;
+  a.items = tb.perm_items + plan->perm_first[v0];
+  a.n_items = plan->perm_first[v1] - plan->perm_first[v0];
+  a.xcd_span = variant == 3 ? 0 : (a.n_items + 7) / 8;
+  a.img = img;
+  a.img_lo = img_lo;
+  a.img_hi = img_hi;
+  return launch_perm(pack, a, grid_limit, stream);
+}
+
 }  // namespace
 
 int ds_launch_move(const ds_plan *plan, bool pack, uint8_t *img, uint64_t img_lo, uint64_t img_hi,
@@ -1098,7 +1220,8 @@ int ds_launch_move(const ds_plan *plan, bool pack, uint8_t *img, uint64_t img_lo
   int dev = -1;
   DS_HIP_TRY(hipGetDevice(&dev));
   if (dev != plan->device) return DS_ESTATE;
-  const DeviceTables tb = {plan->d_tiles, plan->d_hot, plan->d_first_tile, plan->d_recs};
+  const DeviceTables tb = {plan->d_tiles, plan->d_hot, plan->d_first_tile, plan->d_recs, plan->d_perms,
+                           plan->d_perm_items, plan->d_rest_ids, plan->d_rest_recs};
   return launch_move_with(plan, tb, pack, img, img_lo, img_hi, grid_limit, stream);
 }
 
@@ -1163,8 +1286,29 @@ extern "C" int ds_pack_noalloc(const ds_plan *plan, void *dst_dev, uint64_t img_
                             plan->first_tile.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st));
   DS_HIP_TRY(hipMemcpyAsync(base + b_tiles + b_off + b_first, plan->recs.data(),
                             plan->recs.size() * sizeof(DsChunkRec), hipMemcpyHostToDevice, st));
-  const DeviceTables tb = {(const DsTile *)base, (const DsTileHot *)(base + b_tiles),
-                           (const uint32_t *)(base + b_tiles + b_off),
-                           (const DsChunkRec *)(base + b_tiles + b_off + b_first)};
+  DeviceTables tb = {(const DsTile *)base, (const DsTileHot *)(base + b_tiles),
+                     (const uint32_t *)(base + b_tiles + b_off),
+                     (const DsChunkRec *)(base + b_tiles + b_off + b_first), nullptr, nullptr, nullptr, nullptr};
+  // the block tables where they fit behind the others; without them the general path takes those views
+  const size_t b_perms = round_up_128(plan->perms.size() * sizeof(DsPerm));
+  const size_t b_items = round_up_128(plan->perm_items.size() * sizeof(DsPermItem));
+  const size_t b_ids = round_up_128(plan->rest_ids.size() * sizeof(uint32_t));
+  const size_t b_rest = plan->rest_recs.size() * sizeof(DsChunkRec);
+  uint8_t *at = base + b_tiles + b_off + b_first + b_recs;
+  if (!plan->perms.empty() && (size_t)(at - base) + b_perms + b_items + b_ids + b_rest <= kScratchBytes) {
+    DS_HIP_TRY(hipMemcpyAsync(at, plan->perms.data(), plan->perms.size() * sizeof(DsPerm), hipMemcpyHostToDevice, st));
+    DS_HIP_TRY(hipMemcpyAsync(at + b_perms, plan->perm_items.data(), plan->perm_items.size() * sizeof(DsPermItem),
+                              hipMemcpyHostToDevice, st));
+    tb.perms = (const DsPerm *)at;
+    tb.perm_items = (const DsPermItem *)(at + b_perms);
+    at += b_perms + b_items;
+    if (b_rest) {
+      DS_HIP_TRY(hipMemcpyAsync(at, plan->rest_ids.data(), plan->rest_ids.size() * sizeof(uint32_t),
+                                hipMemcpyHostToDevice, st));
+      DS_HIP_TRY(hipMemcpyAsync(at + b_ids, plan->rest_recs.data(), b_rest, hipMemcpyHostToDevice, st));
+      tb.rest_ids = (const uint32_t *)at;
+      tb.rest_recs = (const DsChunkRec *)(at + b_ids);
+    }
+  }
   return launch_move_with(plan, tb, true, (uint8_t *)dst_dev, img_lo, img_hi, 0, st);
 }

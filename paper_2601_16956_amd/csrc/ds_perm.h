@@ -1,0 +1,488 @@
+// Views whose contiguous runs are shorter than 16 bytes (transposed and permuted matrices, channels-last
+// weights, every k-th column): moved in two-dimensional blocks through LDS instead of unit by unit.
+//
+// In image order the elements of such a view lie a stride apart, so a 16-byte image unit touches as many
+// lines of the tensor as it has elements, and every one of those lines again for the neighbouring rows.  A
+// block takes `ta` steps along the dimension whose elements are closest to each other in the TENSOR (a) and
+// `tb` steps along the last dimension, whose elements are neighbours in the IMAGE (b); it is read along one
+// of them, kept in LDS in image order, and written along the other, so that both sides see whole lines.
+//
+// What moves is a granule: the largest power of two up to 8 bytes that divides the runs, the strides and the
+// base address.
+//
+// The file compiles for the device and, unchanged, for the host: a CPU test runs the same phases thread by
+// thread, with every access checked (DS_PERM_TOUCH).
+#pragma once
+
+#include <stdint.h>
+#include <string.h>
+
+#if defined(__HIPCC__)
+#define DS_PERM_FN __host__ __device__ __forceinline__
+#else
+#define DS_PERM_FN static inline
+#endif
+#if defined(__HIP_DEVICE_COMPILE__)
+#define DS_PERM_GLOBAL __attribute__((address_space(1)))
+#else
+#define DS_PERM_GLOBAL
+#endif
+#ifndef DS_PERM_TOUCH  // the CPU test's hook: (kind, address or LDS offset, bytes, alignment)
+#define DS_PERM_TOUCH(kind, at, n, align)
+#endif
+
+constexpr uint32_t kPermThreads = 256;
+constexpr uint32_t kPermLdsBytes = 21504;
+constexpr uint32_t kPermMaxBatch = 4;      // dimensions beside a and b (DS_MAX_DIMS - 2)
+// Smaller views, and views whose blocks would hold less, stay with the general path, which takes 64 tiles at a time.
+// Gather of 20 000 square bf16 views, blocks / general path: of 512 bytes 62 / 40 us, of 1152 bytes 69 / 81, of 2048
+// bytes 76 / 92, of 4608 bytes 112 / 258; of 2000 views the blocks win from 512 bytes on (10.5 / 25 us).
+constexpr uint64_t kPermMinBytes = 1024;
+constexpr int kPermUnroll = 8;             // granules a thread has in flight
+
+enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11 };
+
+// Steps along a of the usual block, by granule: at least a 128-byte line of the tensor.
+// Its columns are what LDS has room for: a thread's 16 granules (words of up to 4 bytes), all in flight at once.
+DS_PERM_FN constexpr uint32_t ds_perm_full_a(uint32_t granule) { return granule == 1 ? 128 : granule == 8 ? 32 : 64; }
+DS_PERM_FN constexpr uint32_t ds_perm_full_b(uint32_t granule) { return granule < 4 ? 128 : 64; }
+
+struct DsPerm {
+  uint64_t src;    // address of element (0,...,0)
+  uint64_t img;    // image offset of the view's first byte
+  uint64_t end16;  // image offset where its whole 16-byte units end (the cut unit and padding are the general path's)
+  uint64_t sa, sb; // tensor distance between neighbours along a and b, bytes
+  uint64_t da;     // image distance between neighbours along a (along b it is `run`)
+  uint64_t bsrc[kPermMaxBatch], bimg[kPermMaxBatch];  // the other dimensions, slowest first
+  uint32_t bext[kPermMaxBatch];
+  uint32_t n_batch;
+  uint32_t ea, eb;            // extents
+  uint32_t run;               // bytes of a run
+  uint32_t ta, tb;            // block size
+  uint32_t tiles_a, tiles_b;  // blocks along a and b
+  uint32_t pitch;             // LDS bytes between rows of the block
+  uint32_t lanes_log2;        // threads that share a row on the image side
+  uint32_t flags;             // log2(granule) | kPermAlongA (tensor side walked along a) | kPermFlat | kPermFull (the
+                              // usual block) | kPermLines (rows are whole 128-byte lines of the image)
+  uint32_t pad_[1];
+};
+static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
+
+struct DsPermItem {
+  uint32_t perm, tile;  // which view, which block of it
+};
+
+// One block, as the phases need it.  A "row" is the block's part of one step along a; with kPermFlat the
+// rows follow each other without a gap in the image and the whole block counts as one row.  Positions are
+// 32-bit: tensor offsets count from src0, image offsets from the 16-byte unit that holds the block's first byte.
+struct DsPermBlock {
+  uint64_t src0;       // tensor address of the block's first element
+  uint64_t unit0;      // image offset of the unit that holds the block's first byte
+  uint32_t skew;       // where in that unit the byte lies
+  uint32_t lo, hi;     // image offsets to move (the call's range, cut to the view's whole units): multiples of 16
+  uint32_t da, sa, sb; // distances as in DsPerm
+  uint32_t na, nb;     // elements of the block
+  uint32_t nbx;        // gather: columns read, up to 15 bytes more than nb where the next block starts inside a unit
+  bool first_b, last_b;  // does the block hold the first / the last column of its rows?
+  bool inside;         // do all its bytes lie in [lo, hi)?
+};
+
+DS_PERM_FN uint32_t ds_perm_min(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
+// i / d for i, d < 2^15 with m = 2^32 / d rounded up (d > 1)
+DS_PERM_FN uint32_t ds_perm_magic(uint32_t d) { return 0xFFFFFFFFu / d + 1u; }
+DS_PERM_FN uint32_t ds_perm_div(uint32_t i, uint32_t d, uint32_t m) {
+  return d == 1 ? i : (uint32_t)(((uint64_t)i * m) >> 32);
+}
+
+DS_PERM_FN uint32_t ds_perm_offset(uint64_t x, uint64_t from) {  // x - from, cut to 0 .. 2^31
+  return x <= from ? 0u : x - from < (1ull << 31) ? (uint32_t)(x - from) : 1u << 31;
+}
+
+// Block t of the view; false if none of it lies in image bytes [img_lo, img_hi).
+DS_PERM_FN bool ds_perm_block(const DsPerm &d, uint32_t t, uint64_t img_lo, uint64_t img_hi, bool pack, DsPermBlock &k) {
+  const uint32_t rest = t / d.tiles_b, tb = t - rest * d.tiles_b;
+  uint32_t batch = rest / d.tiles_a;
+  const uint32_t ta = rest - batch * d.tiles_a;
+  uint64_t src0 = d.src, img0 = d.img;
+  for (int j = (int)d.n_batch - 1; j >= 0; --j) {
+    const uint32_t q = batch / d.bext[j], r = batch - q * d.bext[j];
+    src0 += r * d.bsrc[j];
+    img0 += r * d.bimg[j];
+    batch = q;
+  }
+  const uint32_t a0 = ta * d.ta, b0 = tb * d.tb;
+  k.src0 = src0 + a0 * d.sa + b0 * d.sb;
+  img0 += a0 * d.da + (uint64_t)b0 * d.run;
+  k.skew = (uint32_t)img0 & 15u;
+  k.unit0 = img0 - k.skew;
+  k.da = (uint32_t)d.da;
+  k.sa = (uint32_t)d.sa;
+  k.sb = (uint32_t)d.sb;
+  k.na = ds_perm_min(d.ta, d.ea - a0);
+  k.nb = ds_perm_min(d.tb, d.eb - b0);
+  k.first_b = b0 == 0;
+  k.last_b = b0 + k.nb == d.eb;
+  const bool units = ((k.skew | k.da | k.nb * d.run) & 15u) == 0;  // every row is whole 16-byte units
+  k.nbx = pack && !k.last_b && !units ? ds_perm_min(k.nb + (14 + d.run) / d.run, d.eb - b0) : k.nb;
+  k.lo = ds_perm_offset(img_lo > d.img ? img_lo : d.img, k.unit0);
+  k.hi = ds_perm_offset(img_hi < d.end16 ? img_hi : d.end16, k.unit0);
+  const uint32_t end = k.skew + (k.na - 1) * k.da + k.nbx * d.run;
+  k.inside = k.skew >= k.lo && end <= k.hi;
+  return k.skew < k.hi && end > k.lo;
+}
+
+// Where row a of the block starts in the image, and in LDS: a row lies in LDS at the same position inside a
+// 16-byte unit as in the image.
+DS_PERM_FN uint32_t ds_perm_row_image(const DsPermBlock &k, uint32_t a) { return k.skew + a * k.da; }
+DS_PERM_FN uint32_t ds_perm_row_lds(const DsPerm &d, const DsPermBlock &k, uint32_t a) {
+  if (d.flags & kPermFlat) return ds_perm_row_image(k, a);
+  return a * d.pitch + (ds_perm_row_image(k, a) & 15u);
+}
+
+// ---- tensor side: granules of type E -------------------------------------------------------------------
+// Addresses are the block's (one for the work-group) plus a 32-bit offset.  Gather: every load of a batch is
+// issued before the first is used; indices beyond the block are pulled back to its last element, which is then
+// moved twice, so that no load hangs on a condition.  Scatter: only what lies in [lo, hi) is stored.
+template <typename T>
+DS_PERM_FN T ds_perm_load(uint64_t base, uint32_t off, uint32_t align) {
+  DS_PERM_TOUCH('r', base + off, sizeof(T), align);
+  T v;
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef T any __attribute__((aligned(1)));
+  v = *(const DS_PERM_GLOBAL any *)(base + off);
+#else
+  memcpy(&v, (const void *)(uintptr_t)(base + off), sizeof(T));
+#endif
+  (void)align;
+  return v;
+}
+template <typename T>
+DS_PERM_FN void ds_perm_store(uint64_t base, uint32_t off, T v, uint32_t align) {
+  DS_PERM_TOUCH('w', base + off, sizeof(T), align);
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef T any __attribute__((aligned(1)));
+  *(DS_PERM_GLOBAL any *)(base + off) = v;
+#else
+  memcpy((void *)(uintptr_t)(base + off), &v, sizeof(T));
+#endif
+  (void)align;
+}
+template <typename E>
+DS_PERM_FN E ds_perm_get(const uint8_t *lds, uint32_t at) {
+  DS_PERM_TOUCH('l', at, sizeof(E), sizeof(E));
+  return *(const E *)(lds + at);
+}
+template <typename E>
+DS_PERM_FN void ds_perm_put(uint8_t *lds, uint32_t at, E v) {
+  DS_PERM_TOUCH('l', at, sizeof(E), sizeof(E));
+  *(E *)(lds + at) = v;
+}
+
+// Walk along a, the usual block: ds_perm_full_a<E>() steps along a, one granule per run.  Neighbouring threads take
+// neighbours along a, V granules of type E each as one access of type W (V > 1: dense along a, whole groups of V);
+// a thread goes down b at a fixed step, so that its places in LDS are its first one plus constants.  LDS rows have
+// room for whole batches: columns beyond the block are loaded from its last one and never used.
+template <typename E, typename W, bool PACK>
+DS_PERM_FN void ds_perm_full(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  constexpr uint32_t S = (uint32_t)sizeof(E), V = (uint32_t)(sizeof(W) / sizeof(E));
+  constexpr uint32_t lanes = ds_perm_full_a(S) / V, step = kPermThreads / lanes;
+  constexpr int U = ds_perm_full_b(S) / step < 16 ? ds_perm_full_b(S) / step : 16;
+  const uint32_t n_cols = PACK ? k.nbx : k.nb;
+  const uint32_t a = (tid & (lanes - 1)) * V, ac = ds_perm_min(a, k.na - V);
+  const uint32_t first = ac * k.sa, last = first + (n_cols - 1) * k.sb;
+  uint32_t row[V];
+#pragma unroll
+  for (uint32_t i = 0; i < V; ++i) row[i] = ds_perm_row_lds(d, k, ac + i) + (tid / lanes) * S;
+  if (PACK) {
+#pragma unroll 1
+    for (uint32_t b0 = 0; b0 < n_cols; b0 += U * step) {
+      W v[U];
+      uint32_t off = first + (b0 + tid / lanes) * k.sb;
+#pragma unroll
+      for (int j = 0; j < U; ++j, off += step * k.sb) v[j] = ds_perm_load<W>(k.src0, ds_perm_min(off, last), S);
+#pragma unroll
+      for (int j = 0; j < U; ++j)
+#pragma unroll
+        for (uint32_t i = 0; i < V; ++i)
+          ds_perm_put<E>(lds, row[i] + b0 * S + (uint32_t)j * step * S, (E)(v[j] >> (8 * S * i)));
+    }
+  } else if (a < k.na) {
+    // the columns whose bytes lie in [lo, hi): granules are never cut
+    const uint32_t image = ds_perm_row_image(k, ac);
+    const uint32_t c0 = k.inside || k.lo <= image ? 0u : (k.lo - image + S - 1) / S;
+    const uint32_t c1 = k.inside ? n_cols : k.hi <= image ? 0u : ds_perm_min((k.hi - image) / S, n_cols);
+#pragma unroll 4
+    for (uint32_t c = tid / lanes; c < c1; c += step) {
+      W v = 0;
+#pragma unroll
+      for (uint32_t i = 0; i < V; ++i) v |= (W)((W)ds_perm_get<E>(lds, row[i] + (c - tid / lanes) * S) << (8 * S * i));
+      if (c >= c0) ds_perm_store<W>(k.src0, first + c * k.sb, v, S);
+    }
+  }
+}
+
+// Walk along a, any block (d.ta is a power of two).
+template <typename E, bool PACK>
+DS_PERM_FN void ds_perm_along_a(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  const uint32_t n_cols = PACK ? k.nbx : k.nb;
+  const uint32_t step = kPermThreads / d.ta, a = tid & (d.ta - 1), ac = ds_perm_min(a, k.na - 1);
+  const uint32_t first = ac * k.sa, row = ds_perm_row_lds(d, k, ac);
+  const uint32_t image = ds_perm_row_image(k, ac);
+#pragma unroll 1
+  for (uint32_t b = tid / d.ta; b < n_cols; b += kPermUnroll * step)
+#pragma unroll 1
+    for (uint32_t in_run = 0; in_run < d.run; in_run += (uint32_t)sizeof(E)) {
+      if (PACK) {
+        E v[kPermUnroll];
+#pragma unroll
+        for (int j = 0; j < kPermUnroll; ++j) {
+          const uint32_t c = ds_perm_min(b + (uint32_t)j * step, n_cols - 1);
+          v[j] = ds_perm_load<E>(k.src0, first + c * k.sb + in_run, sizeof(E));
+        }
+#pragma unroll
+        for (int j = 0; j < kPermUnroll; ++j) {
+          const uint32_t c = ds_perm_min(b + (uint32_t)j * step, n_cols - 1);
+          ds_perm_put<E>(lds, row + c * d.run + in_run, v[j]);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < kPermUnroll; ++j) {
+          const uint32_t c = b + (uint32_t)j * step, in_row = c * d.run + in_run;
+          if (a < k.na && c < n_cols && (k.inside || (image + in_row >= k.lo && image + in_row < k.hi)))
+            ds_perm_store<E>(k.src0, first + c * k.sb + in_run, ds_perm_get<E>(lds, row + in_row), sizeof(E));
+        }
+      }
+    }
+}
+
+// Walk along b: granule i of the block, rows one behind the other.
+template <typename E, bool PACK>
+DS_PERM_FN void ds_perm_along_b(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  const uint32_t K = d.run / (uint32_t)sizeof(E);
+  const uint32_t per_row = (PACK ? k.nbx : k.nb) * K, total = k.na * per_row;
+  const uint32_t m_row = ds_perm_magic(per_row > 1 ? per_row : 2), m_run = ds_perm_magic(K > 1 ? K : 2);
+#pragma unroll 1
+  for (uint32_t i = tid; i < total; i += kPermUnroll * kPermThreads) {
+    uint32_t from[kPermUnroll], at[kPermUnroll], image[kPermUnroll];
+#pragma unroll
+    for (int j = 0; j < kPermUnroll; ++j) {
+      const uint32_t x = ds_perm_min(i + (uint32_t)j * kPermThreads, total - 1);
+      const uint32_t a = ds_perm_div(x, per_row, m_row), r = x - a * per_row;
+      const uint32_t c = ds_perm_div(r, K, m_run);
+      const uint32_t in_row = r * (uint32_t)sizeof(E);  // the granules of a row are dense in the image
+      from[j] = a * k.sa + c * k.sb + (r - c * K) * (uint32_t)sizeof(E);
+      at[j] = ds_perm_row_lds(d, k, a) + in_row;
+      image[j] = ds_perm_row_image(k, a) + in_row;
+    }
+    if (PACK) {
+      E v[kPermUnroll];
+#pragma unroll
+      for (int j = 0; j < kPermUnroll; ++j) v[j] = ds_perm_load<E>(k.src0, from[j], sizeof(E));
+#pragma unroll
+      for (int j = 0; j < kPermUnroll; ++j) ds_perm_put<E>(lds, at[j], v[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < kPermUnroll; ++j)
+        if (i + (uint32_t)j * kPermThreads < total && (k.inside || (image[j] >= k.lo && image[j] < k.hi)))
+          ds_perm_store<E>(k.src0, from[j], ds_perm_get<E>(lds, at[j]), sizeof(E));
+    }
+  }
+}
+
+template <typename E, typename W, bool PACK>
+DS_PERM_FN void ds_perm_tensor_side(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  constexpr uint32_t V = (uint32_t)(sizeof(W) / sizeof(E));
+  if (!(d.flags & kPermAlongA)) ds_perm_along_b<E, PACK>(d, k, lds, tid);
+  else if (!(d.flags & kPermFull)) ds_perm_along_a<E, PACK>(d, k, lds, tid);
+  else if (V > 1 && d.sa == sizeof(E) && k.na % V == 0 && (PACK || k.inside)) ds_perm_full<E, W, PACK>(d, k, lds, tid);
+  else ds_perm_full<E, E, PACK>(d, k, lds, tid);
+}
+
+// ---- image side ---------------------------------------------------------------------------------------------
+// The bytes of the row a work-group writes (gather), relative to the start of the 16-byte unit that holds the
+// row's first byte.  Inside a row, blocks meet at unit boundaries, so a unit is written whole by one block;
+// only where a row starts or ends inside a unit are its two parts written by two rows.
+DS_PERM_FN void ds_perm_window(const DsPerm &d, const DsPermBlock &k, uint32_t unit, uint32_t skew, uint32_t &w0, uint32_t &w1) {
+  if (d.flags & kPermFlat) {
+    w0 = skew;
+    w1 = skew + k.na * k.da;
+  } else {
+    const uint32_t read_end = skew + k.nbx * d.run;
+    w0 = k.first_b ? skew : ds_perm_min((skew + 15u) & ~15u, read_end);
+    w1 = k.last_b ? read_end : ds_perm_min((skew + k.nb * d.run + 15u) & ~15u, read_end);
+  }
+  if (k.inside) return;
+  if (k.lo > unit + w0) w0 = k.lo - unit < w1 ? k.lo - unit : w1;
+  if (k.hi < unit + w1) w1 = k.hi > unit ? k.hi - unit : 0u;
+}
+
+struct DsPermUnit {
+  uint32_t w[4];
+};
+
+// Gather: LDS -> image, `img` pointing at image byte img_lo.
+template <typename E, typename StoreUnit>
+DS_PERM_FN void ds_perm_image_store(const DsPerm &d, const DsPermBlock &k, const uint8_t *lds, uint8_t *img, uint64_t img_lo,
+                                    uint32_t tid, StoreUnit store_unit) {
+  const uint32_t lanes = 1u << d.lanes_log2, rows = d.flags & kPermFlat ? 1u : k.na;
+  const uint64_t base = (uint64_t)(uintptr_t)img + (k.unit0 - img_lo);
+#pragma unroll 1
+  for (uint32_t a = tid >> d.lanes_log2; a < rows; a += kPermThreads >> d.lanes_log2) {
+    const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = a * d.pitch;
+    uint32_t w0, w1;
+    ds_perm_window(d, k, unit, skew, w0, w1);
+    for (uint32_t x = (w0 & ~15u) + 16u * (tid & (lanes - 1)); x < w1; x += 16u * lanes) {
+      if (x >= w0 && x + 16u <= w1) {
+        DsPermUnit v;
+        DS_PERM_TOUCH('l', row + x, 16, 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v.w[j] = *(const uint32_t *)(lds + row + x + 4 * j);
+        DS_PERM_TOUCH('i', base + (unit + x), 16, 16);
+        store_unit(base + (unit + x), v);
+      } else {
+        const uint32_t x1 = ds_perm_min(w1, x + 16u);
+        for (uint32_t y = w0 > x ? w0 : x; y < x1; y += (uint32_t)sizeof(E)) {
+          DS_PERM_TOUCH('i', base + (unit + y), sizeof(E), sizeof(E));
+          *(DS_PERM_GLOBAL E *)(base + (unit + y)) = ds_perm_get<E>(lds, row + y);
+        }
+      }
+    }
+  }
+}
+
+// Scatter: image -> LDS, every unit of the range that holds bytes of the block's rows.
+template <typename LoadUnit>
+DS_PERM_FN void ds_perm_image_load(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, const uint8_t *img, uint64_t img_lo,
+                                   uint32_t tid, LoadUnit load_unit) {
+  const uint32_t lanes = 1u << d.lanes_log2, flat = d.flags & kPermFlat, rows = flat ? 1u : k.na;
+  const uint64_t base = (uint64_t)(uintptr_t)img + (k.unit0 - img_lo);
+#pragma unroll 1
+  for (uint32_t a = tid >> d.lanes_log2; a < rows; a += kPermThreads >> d.lanes_log2) {
+    const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = a * d.pitch;
+    const uint32_t end = skew + (flat ? k.na * k.da : k.nb * d.run);
+    for (uint32_t x = 16u * (tid & (lanes - 1)); x < end; x += 16u * lanes) {
+      if (unit + x < k.lo || unit + x >= k.hi) continue;
+      DS_PERM_TOUCH('j', base + (unit + x), 16, 16);
+      const DsPermUnit v = load_unit(base + (unit + x));
+      DS_PERM_TOUCH('l', row + x, 16, 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *(uint32_t *)(lds + row + x + 4 * j) = v.w[j];
+    }
+  }
+}
+
+// ---- the plan's side (host) -----------------------------------------------------------------------------------
+// Fills `d` for a view of `n_outer` outer dimensions (slowest first, strides in bytes) of runs of `run` bytes at
+// image offset `img`; returns the number of blocks, or 0 if the view is not one of this route's: one contiguous
+// run, runs of 16 bytes and more (a unit then lies in at most two runs: the row and general paths move it with
+// whole 16-byte accesses), less than kPermMinBytes, extents that leave a block nearly empty or exceed 31 bits.
+static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes, uint64_t run, uint32_t n_outer,
+                                    const uint64_t *extent, const uint64_t *stride, DsPerm *d) {
+  if (n_outer == 0 || run >= 16 || nbytes < kPermMinBytes) return 0;
+  uint64_t bits = src | run;
+  for (uint32_t j = 0; j < n_outer; ++j) {
+    if (extent[j] >= (1ull << 31)) return 0;
+    bits |= stride[j];
+  }
+  memset(d, 0, sizeof(*d));
+  d->src = src;
+  d->img = img;
+  d->end16 = img + (nbytes & ~(uint64_t)15);
+  d->run = (uint32_t)run;
+  uint32_t g_log2 = 0;
+  while (g_log2 < 3 && !(bits & (1u << g_log2))) ++g_log2;
+  const uint32_t g = 1u << g_log2;
+  uint64_t image_stride[8];
+  uint64_t at = run;
+  for (int j = (int)n_outer - 1; j >= 0; --j) {
+    image_stride[j] = at;
+    at *= extent[j];
+  }
+  const uint32_t b = n_outer - 1;
+  uint32_t a = n_outer;  // the dimension closest in the tensor, the one before b if that is b itself
+  for (uint32_t j = 0; j < b; ++j)
+    if (stride[j] < stride[b] && (a == n_outer || stride[j] < stride[a])) a = j;
+  const bool along_a = a != n_outer;
+  if (!along_a && b > 0) a = b - 1;
+  d->eb = (uint32_t)extent[b];
+  d->sb = stride[b];
+  d->ea = a == n_outer ? 1u : (uint32_t)extent[a];
+  d->sa = a == n_outer ? 0u : stride[a];
+  d->da = a == n_outer ? run * extent[b] : image_stride[a];
+  uint64_t batches = 1, image_bits = img | d->da;  // where in a unit rows can start
+  for (uint32_t j = 0; j < b; ++j)
+    if (j != a) {
+      d->bext[d->n_batch] = (uint32_t)extent[j];
+      d->bsrc[d->n_batch] = stride[j];
+      d->bimg[d->n_batch] = image_stride[j];
+      image_bits |= image_stride[j];
+      ++d->n_batch;
+      batches *= extent[j];
+    }
+  // Rows of less than 512 bytes that are neighbours in the image are taken as one piece, unless they are whole
+  // units at unit boundaries anyway.
+  const uint64_t row_bytes = run * d->eb;
+  const bool neighbours = a == n_outer || a + 1 == b;
+  const bool flat = neighbours && row_bytes < 512 && ((row_bytes | img) & 15);
+  uint32_t ta, tb;
+  if (flat) {
+    tb = d->eb;
+    ta = (uint32_t)(16384 / row_bytes);
+    if (!along_a && ta > d->ea) ta = d->ea;
+  } else if (along_a) {
+    // a line or more along a; along b what 16 KiB leave, less the 15 bytes that rows which are not whole units are
+    // read further
+    ta = ds_perm_full_a(g);
+    while (ta > 1 && ta / 2 >= d->ea) ta /= 2;
+    tb = (uint32_t)((16384 / ta) / run);
+    if (tb == 0) tb = 1;
+    if (tb > d->eb) tb = d->eb;
+    else if ((image_bits & 15) && tb * run >= 128) tb -= (uint32_t)(16 / g);
+  } else {
+    tb = (uint32_t)(4096 / run);
+    if (tb > d->eb) tb = d->eb;
+    ta = (uint32_t)(16384 / (tb * run));
+    if (ta > d->ea) ta = d->ea;
+    tb = (uint32_t)(16384 / (ta * run));
+    if (tb > d->eb) tb = d->eb;
+  }
+  if (along_a) {  // a power of two, of at most one step along a per thread
+    uint32_t p = 1;
+    while (2 * p <= ta && 2 * p <= kPermThreads && p < d->ea) p *= 2;
+    ta = p;
+  }
+  // LDS rows are an odd number of words (of granules of 8 bytes) apart, so that a wavefront's granules along a
+  // fall into different banks; a row needs its position inside the unit (up to 15 bytes), the columns up to the
+  // next unit (up to 15 bytes and a run more), and whole 16-byte units to its end.
+  const uint32_t word = g == 8 ? 8 : 4;
+  bool full = along_a && !flat && run == g && ta == ds_perm_full_a(g);
+  for (;;) {
+    uint32_t cols = tb + (uint32_t)((14 + run) / run);
+    if (((image_bits | tb * run) & 15) == 0 || tb == d->eb) cols = tb;
+    if (full && cols > ds_perm_full_b(g)) full = false;
+    if (full) cols = ds_perm_full_b(g);
+    d->pitch = (uint32_t)(cols * run + 30 + word - 1) / word * word;
+    if (!(d->pitch / word & 1)) d->pitch += word;
+    if (flat || ta * d->pitch <= kPermLdsBytes) break;
+    if (full) full = false;
+    else if (ta > 1) ta /= 2;
+    else return 0;
+  }
+  // inside a block, positions on either side are 32-bit
+  while (ta > 1 && (ta * d->da >= (1ull << 31) || ta * d->sa >= (1ull << 31))) ta /= 2, full = false;
+  while (tb > 1 && (uint64_t)(tb + 16) * d->sb >= (1ull << 31)) tb /= 2;
+  if ((uint64_t)(tb + 16) * d->sb >= (1ull << 31) || d->da >= (1ull << 31)) return 0;
+  if (flat && tb != d->eb) return 0;
+  if ((uint64_t)(ta < d->ea ? ta : d->ea) * tb * run < kPermMinBytes) return 0;
+  d->ta = ta;
+  d->tb = tb;
+  d->tiles_a = (d->ea + ta - 1) / ta;
+  d->tiles_b = (d->eb + tb - 1) / tb;
+  const uint32_t units = (uint32_t)((flat ? kPermThreads * 16 : tb * run) / 16);
+  while (d->lanes_log2 < 8 && (2u << d->lanes_log2) <= units) ++d->lanes_log2;
+  d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
+             (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u);
+  const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
+  return tiles < (1u << 31) ? (uint64_t)tiles : 0;
+}

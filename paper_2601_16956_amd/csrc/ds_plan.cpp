@@ -151,7 +151,11 @@ int upload(ds_plan *p) {
   const size_t b_hot = round_up(p->hot.size() * sizeof(DsTileHot), 128);
   const size_t b_first = round_up(p->first_tile.size() * sizeof(uint32_t), 128);
   const size_t b_recs = round_up(p->recs.size() * sizeof(DsChunkRec), 128);
-  const size_t total = std::max<size_t>(b_tiles + b_hot + b_first + b_recs, 128);
+  const size_t b_perms = round_up(p->perms.size() * sizeof(DsPerm), 128);
+  const size_t b_items = round_up(p->perm_items.size() * sizeof(DsPermItem), 128);
+  const size_t b_ids = round_up(p->rest_ids.size() * sizeof(uint32_t), 128);
+  const size_t b_rest = p->rest_recs.size() * sizeof(DsChunkRec);
+  const size_t total = std::max<size_t>(b_tiles + b_hot + b_first + b_recs + b_perms + b_items + b_ids + b_rest, 128);
   DS_HIP_TRY(hipMalloc(&p->dev_blob, total));
   uint8_t *base = (uint8_t *)p->dev_blob;
   p->d_tiles = (const DsTile *)base;
@@ -165,6 +169,21 @@ int upload(ds_plan *p) {
   if (!p->recs.empty())
     DS_HIP_TRY(hipMemcpy(base + b_tiles + b_hot + b_first, p->recs.data(), p->recs.size() * sizeof(DsChunkRec),
                          hipMemcpyHostToDevice));
+  if (!p->perms.empty()) {
+    uint8_t *at = base + b_tiles + b_hot + b_first + b_recs;
+    p->d_perms = (const DsPerm *)at;
+    p->d_perm_items = (const DsPermItem *)(at + b_perms);
+    DS_HIP_TRY(hipMemcpy(at, p->perms.data(), p->perms.size() * sizeof(DsPerm), hipMemcpyHostToDevice));
+    DS_HIP_TRY(hipMemcpy(at + b_perms, p->perm_items.data(), p->perm_items.size() * sizeof(DsPermItem),
+                         hipMemcpyHostToDevice));
+    if (!p->rest_ids.empty()) {
+      p->d_rest_ids = (const uint32_t *)(at + b_perms + b_items);
+      p->d_rest_recs = (const DsChunkRec *)(at + b_perms + b_items + b_ids);
+      DS_HIP_TRY(hipMemcpy(at + b_perms + b_items, p->rest_ids.data(), p->rest_ids.size() * sizeof(uint32_t),
+                           hipMemcpyHostToDevice));
+      DS_HIP_TRY(hipMemcpy(at + b_perms + b_items + b_ids, p->rest_recs.data(), b_rest, hipMemcpyHostToDevice));
+    }
+  }
   return DS_OK;
 }
 
@@ -408,7 +427,18 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
             else n_outer = 2;
           }
           h.meta = n_outer | (tl.es_log2 << 8);
+          DsPerm perm;
+          const uint64_t blocks = ds_perm_make(tl.src, h.img_off, tl.nbytes, tl.run_bytes, tl.n_outer, tl.extent,
+                                               tl.stride, &perm);
+          if (blocks && p->perm_items.size() + blocks < (1u << 31)) {
+            h.meta |= DS_HOT_PERM;
+            p->perm_first.push_back((uint32_t)p->perm_items.size());
+            for (uint64_t b = 0; b < blocks; ++b)
+              p->perm_items.push_back({(uint32_t)p->perms.size(), (uint32_t)b});
+            p->perms.push_back(perm);
+          }
         }
+        p->perm_first.push_back((uint32_t)p->perm_items.size());
         const uint64_t chunk = ds_cfg_chunk_bytes();
         p->chunk_log2 = (uint32_t)__builtin_ctzll(chunk);
         const uint64_t n_chunks = (p->total_bytes + chunk - 1) >> p->chunk_log2;
@@ -453,15 +483,21 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
                 // length once here instead of once per unit in the kernel
                 const uint64_t step = 4096;
                 r.tile = (uint32_t)(((step / tl.run_bytes) << 16) | (step % tl.run_bytes));
+              } else if (p->hot[ti].meta & DS_HOT_PERM) {
+                r.kind = DS_CHUNK_PERM;
               }
             }
-            if ((r.kind & 0xFF) == DS_CHUNK_GENERAL) {
+            if ((r.kind & 0xFF) >= DS_CHUNK_GENERAL) {
               // the tiles the chunk holds, so that the kernel is one load away from them
               uint32_t t1 = p->first_tile[c + 1];
               const uint64_t c_end = std::min(ce, p->total_bytes);
               if (p->tile_off[t1] >= c_end) --t1;  // that tile starts where this chunk ends
               r.col0 = t1 - ti;
               ++p->n_general;
+            }
+            if (!p->perms.empty() && r.kind != DS_CHUNK_PERM) {
+              p->rest_ids.push_back((uint32_t)c);
+              p->rest_recs.push_back(r);
             }
           }
         }

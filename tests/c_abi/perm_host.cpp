@@ -1,0 +1,72 @@
+// Host build of the block route for views with short runs (csrc/ds_perm.h, included unchanged): every block of a
+// view is moved thread by thread, phase by phase, and every access is counted, so that a CPU test can see that
+// exactly the bytes of the view and of the image range are read and written, and that LDS is not left.
+#include <stdint.h>
+
+static unsigned char *g_arena_hits, *g_image_hits;  // accesses per byte
+static uint64_t g_arena, g_arena_len, g_image, g_image_len;
+static long g_bad;
+static void touch(char kind, uint64_t at, uint64_t n, uint64_t align);
+#define DS_PERM_TOUCH(kind, at, n, align) touch(kind, at, n, align)
+#include "ds_perm.h"
+
+static void touch(char kind, uint64_t at, uint64_t n, uint64_t align) {
+  if (kind == 'l') {
+    if (at + n > kPermLdsBytes || at % align) ++g_bad;
+    return;
+  }
+  const bool arena = kind == 'r' || kind == 'w';
+  const uint64_t base = arena ? g_arena : g_image, len = arena ? g_arena_len : g_image_len;
+  if (at < base || at + n > base + len || at % align) {
+    ++g_bad;
+    return;
+  }
+  for (uint64_t i = at - base; i < at - base + n; ++i)
+    if ((arena ? g_arena_hits : g_image_hits)[i] < 255) ++(arena ? g_arena_hits : g_image_hits)[i];
+}
+
+template <typename E, typename W>
+static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigned char *img, uint64_t lo, uint8_t *lds) {
+  const auto store = [](uint64_t p, const DsPermUnit &v) { memcpy((void *)(uintptr_t)p, v.w, 16); };
+  const auto load = [](uint64_t p) {
+    DsPermUnit v;
+    memcpy(v.w, (const void *)(uintptr_t)p, 16);
+    return v;
+  };
+  memset(lds, 0xCD, kPermLdsBytes);
+  for (uint32_t t = 0; t < kPermThreads; ++t)
+    if (pack) ds_perm_tensor_side<E, W, true>(d, k, lds, t);
+    else ds_perm_image_load(d, k, lds, img, lo, t, load);
+  for (uint32_t t = 0; t < kPermThreads; ++t)
+    if (pack) ds_perm_image_store<E>(d, k, lds, img, lo, t, store);
+    else ds_perm_tensor_side<E, W, false>(d, k, lds, t);
+}
+
+// Moves image bytes [lo, hi) of one view at image offset `at`; `img` holds byte lo.  Returns the number of blocks
+// (0: not this route's), or -1 if an access was out of bounds or not aligned.
+extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_t offset, uint64_t at, uint64_t nbytes,
+                               uint64_t run, uint32_t n_outer, const uint64_t *extent, const uint64_t *stride, int pack,
+                               uint64_t lo, uint64_t hi, unsigned char *img, unsigned char *arena_hits,
+                               unsigned char *image_hits) {
+  g_arena = (uint64_t)(uintptr_t)arena;
+  g_arena_len = arena_len;
+  g_image = (uint64_t)(uintptr_t)img;
+  g_image_len = hi - lo;
+  g_arena_hits = arena_hits;
+  g_image_hits = image_hits;
+  g_bad = 0;
+  alignas(16) static uint8_t lds[kPermLdsBytes];
+  DsPerm d;
+  const uint64_t n = ds_perm_make(g_arena + offset, at, nbytes, run, n_outer, extent, stride, &d);
+  for (uint64_t t = 0; t < n; ++t) {
+    DsPermBlock k;
+    if (!ds_perm_block(d, (uint32_t)t, lo, hi, pack, k)) continue;
+    switch (d.flags & 0xFFu) {
+      case 0: move_block<uint8_t, uint32_t>(d, k, pack, img, lo, lds); break;
+      case 1: move_block<uint16_t, uint32_t>(d, k, pack, img, lo, lds); break;
+      case 2: move_block<uint32_t, uint32_t>(d, k, pack, img, lo, lds); break;
+      default: move_block<uint64_t, uint64_t>(d, k, pack, img, lo, lds); break;
+    }
+  }
+  return g_bad ? -1 : (long)n;
+}

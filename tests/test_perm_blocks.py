@@ -1,0 +1,179 @@
+"""The block route for views with runs shorter than 16 bytes (csrc/ds_perm.h): on the CPU thread by thread with
+every access counted, and on the GPU against the oracle."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import ds_oracle as orc
+from workloads.configs import DTYPES, Shard, Workload
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# (dtype, shape, strides in elements): blocks whole and cut on either side, rows that start anywhere in a unit, rows
+# shorter than a unit, runs of several granules, batches, both walks, strides that do not nest
+VIEWS = [
+    ("bf16", (64, 128), (1, 64)), ("bf16", (129, 257), (1, 130)), ("bf16", (65, 1031), (1, 67)),
+    ("f32", (64, 64), (1, 64)), ("f32", (63, 129), (1, 63)), ("f32", (200, 9), (1, 200)), ("f32", (7, 500), (1, 9)),
+    ("u8", (128, 128), (1, 128)), ("u8", (131, 259), (1, 133)), ("u8", (300, 33), (1, 301)),
+    ("i64", (32, 64), (1, 32)), ("i64", (33, 65), (1, 35)), ("i64", (2, 700), (1, 3)),
+    ("bf16", (3, 70, 40), (70 * 40, 1, 70)), ("f32", (5, 37, 3, 3), (37 * 9, 1, 111, 37)),
+    ("f32", (40, 48, 3, 3), (48 * 9, 1, 144, 48)), ("u8", (2, 3, 2, 25, 2, 60), (20000, 6100, 3000, 1, 1500, 25)),
+    ("f32", (2100,), (2,)), ("u8", (5000,), (3,)), ("bf16", (70, 300), (800, 2)), ("i64", (3, 400), (900, 2)),
+    ("bf16", (700, 6), (16, 1)), ("u8", (900, 11), (13, 1)), ("f32", (500, 3), (4, 1)), ("bf16", (60, 30, 6), (6, 400, 1)),
+    ("u8", (90, 40, 5), (5, 460, 1)), ("f32", (33, 70, 2), (2, 66, 1)), ("u8", (40, 100, 1), (1, 41, 1)),
+    ("bf16", (700, 2), (2, 3)), ("bf16", (64, 3, 2, 32), (1, 64, 192, 384)),
+    ("bf16", (70, 8, 301), (1, 70, 560)),
+]
+
+
+def _normal(dtype, shape, strides):
+    """What the plan makes of a view: outer extents and byte strides, run length."""
+    es, dims = DTYPES[dtype][1], []
+    for e, s in zip(shape, strides):
+        if e == 1:
+            continue
+        if dims and dims[-1][1] == e * s:
+            dims[-1] = (dims[-1][0] * e, s)
+        else:
+            dims.append((e, s))
+    run = es
+    if dims and dims[-1][1] == 1:
+        run *= dims.pop()[0]
+    return [e for e, _ in dims], [s * es for _, s in dims], run
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("perm") / "perm_host.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-fPIC", "-shared", "-I",
+                    os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c_abi", "perm_host.cpp"), "-o", so], check=True)
+    fn = ctypes.CDLL(so).perm_host_move
+    u64, vp = ctypes.c_uint64, ctypes.c_void_p
+    fn.restype = ctypes.c_long
+    fn.argtypes = [vp, u64, u64, u64, u64, u64, ctypes.c_uint32, vp, vp, ctypes.c_int, u64, u64, vp, vp, vp]
+    return fn
+
+
+def _check(host, dtype, shape, strides, shift, at, rng):
+    es = DTYPES[dtype][1]
+    extent, stride, run = _normal(dtype, shape, strides)
+    ext, st = (ctypes.c_uint64 * 6)(*extent), (ctypes.c_uint64 * 6)(*stride)
+    nbytes = int(np.prod(shape)) * es
+    idx = np.zeros(shape, dtype=np.int64)
+    for j, (e, s) in enumerate(zip(shape, strides)):
+        idx += (np.arange(e) * s).reshape([-1 if i == j else 1 for i in range(len(shape))])
+    byte = (idx.reshape(-1, 1) * es + np.arange(es)).reshape(-1) + shift * es      # of every image byte
+    room = np.empty(int(byte.max()) + 64, dtype=np.uint8)
+    start = -room.ctypes.data % 16
+    arena = room[start:start + int(byte.max()) + 1]
+    whole = nbytes & ~15
+    for lo, hi in ((at, at + whole), (0, at + nbytes + 64), (at + 16, at + whole - 16),
+                   (at + (whole // 3 & ~15), at + (whole // 2 & ~15))):
+        inside = np.arange(max(lo, at), min(hi, at + whole))
+        arena[:] = rng.integers(0, 256, arena.size)
+        raw = np.empty(hi - lo + 16, dtype=np.uint8)
+        img = raw[-raw.ctypes.data % 16:][:hi - lo]
+        want_hits = np.zeros(arena.size, dtype=bool)
+        want_hits[byte[inside - at]] = True
+        for pack in (1, 0):
+            ah, ih = np.zeros(arena.size, dtype=np.uint8), np.zeros(hi - lo, dtype=np.uint8)
+            if pack:
+                img[:] = 0xAA
+                want = img.copy()
+                want[inside - lo] = arena[byte[inside - at]]
+            else:
+                img[:] = rng.integers(0, 256, hi - lo)
+                want = arena.copy()
+                want[byte[inside - at]] = img[inside - lo]
+            n = host(arena.ctypes.data, arena.size, shift * es, at, nbytes, run, len(extent), ext, st, pack, lo, hi,
+                     img.ctypes.data, ah.ctypes.data, ih.ctypes.data)
+            assert n >= 0, "an access out of bounds"
+            if n == 0:
+                return 0
+            if pack:
+                assert np.array_equal(img, want)
+                assert not ah[np.setdiff1d(np.arange(arena.size), byte)].any(), "read outside the view"
+                assert np.array_equal(np.flatnonzero(ih), inside - lo) and ih.max(initial=0) <= 1, "image bytes written once each"
+            else:
+                assert np.array_equal(arena, want)
+                assert np.array_equal(ah > 0, want_hits) and ah.max(initial=0) <= 1, "view bytes written once each"
+    return n
+
+
+@pytest.mark.parametrize("k", range(len(VIEWS)))
+def test_blocks_move_exactly_the_view(host, k):
+    dtype, shape, strides = VIEWS[k]
+    rng = np.random.default_rng(k)
+    for shift, at in ((0, 0), (1, 16), (3, 4096)):
+        assert _check(host, dtype, shape, strides, shift, at, rng) > 0
+
+
+def test_random_permuted_views(host):
+    """Slices and permutations of dense parents of one to six dimensions: whatever the route accepts it moves
+    exactly; what it leaves to the other paths it does not touch."""
+    rng = np.random.default_rng(11)
+    taken = 0
+    for trial in range(150):
+        nd = int(rng.integers(1, 7))
+        dtype = list(DTYPES)[trial % 5]
+        full = [max(1, int(round((30000 ** (1 / nd)) * rng.uniform(0.3, 2)))) for _ in range(nd)]
+        strides = [int(np.prod(full[j + 1:], dtype=np.int64)) for j in range(nd)]
+        shape, step = list(full), [int(rng.integers(1, 3)) if rng.random() < 0.3 else 1 for _ in range(nd)]
+        shape = [max(1, (e - int(rng.integers(0, max(1, e // 3)))) // s) for e, s in zip(shape, step)]
+        strides = [s * t for s, t in zip(strides, step)]
+        order = rng.permutation(nd)
+        taken += _check(host, dtype, tuple(shape[j] for j in order), tuple(strides[j] for j in order),
+                        int(rng.integers(0, 4)), 16 * int(rng.integers(0, 9)), rng) > 0
+    assert taken > 30
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("chunk_bytes", [16384, 8192, 32768])
+def test_gather_and_scatter_of_permuted_views(chunk_bytes):
+    """The same views in one table, with a large one of each walk, whole and in ranges that cut blocks."""
+    import paper_2601_16956_amd as ds
+    import gpu_util as gu
+    import torch
+    rng = np.random.default_rng(5)
+    big = [("bf16", (1000, 1531), (1, 1000)), ("f32", (333, 1111), (2222, 2)), ("u8", (700, 901), (1, 701)),
+           ("i64", (130, 513), (1, 131))]
+    shards, at = [], 0
+    for k, (dtype, shape, strides) in enumerate(VIEWS + big + [("u8", (777,), (1,))]):
+        es = DTYPES[dtype][1]
+        span = (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+        start = -(-at // 256) * 256 + es * int(rng.integers(0, 4))
+        shards.append(Shard(f"p{k}", dtype, shape, strides, start, k))
+        at = start + span
+    arena = rng.integers(0, 256, size=at + 64, dtype=np.uint8)
+    w = Workload("perm", 64, 0, arena, shards)
+    want, offs, tab = gu.oracle_image(w)
+    old = ds.ds_config_get("chunk_bytes")
+    ds.ds_config_set("chunk_bytes", chunk_bytes)
+    try:
+        dw = gu.DeviceWorkload(w)
+        try:
+            print(f"[case] permuted views chunk={chunk_bytes} image={dw.total}", flush=True)
+            got = dw.pack()
+            assert gu.first_mismatch(got, want) is None, gu.first_mismatch(got, want)
+            cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, dw.total // 16, 9)) + [dw.total]
+            ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+            for lo, hi in ranges:
+                assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+            out = torch.full((dw.total,), 0xFF, dtype=torch.uint8, device="cuda")
+            ds.ds_pack_noalloc(dw.plan, out.data_ptr(), 0, dw.total, torch.cuda.current_stream().cuda_stream)
+            assert gu.first_mismatch(out.cpu().numpy(), want) is None
+            w.arena[:] = 0x5A
+            orc.unpack(tab, len(shards), want)
+            for parts in ([(0, dw.total)], ranges):
+                dw.arena.fill_(0x5A)
+                for lo, hi in parts:
+                    dw.unpack(want, lo, hi)
+                assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+        finally:
+            dw.close()
+    finally:
+        ds.ds_config_set("chunk_bytes", old)
