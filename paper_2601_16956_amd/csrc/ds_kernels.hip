@@ -967,76 +967,137 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
 }
 
 // ---- block elision of an image (the compressed-snapshot experiment) ------------------------------------
-// keep[k] = 1 if some 16-byte unit of block k differs from the block's first unit.  One work-group looks at
-// 1024 units (16 KiB), which lie in one block (the block size is a power of two of at least 16 KiB).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void ds_constant_blocks_kernel(
-    const u32x4 *__restrict__ img, uint64_t n_units, uint32_t units_per_block_log2, uint32_t *__restrict__ keep) {
-  const uint32_t n_groups = (uint32_t)((n_units + 1023) / 1024), span = (n_groups + 7) / 8;
-  const uint32_t g = (blockIdx.x & 7u) * span + (blockIdx.x >> 3);
-  if (g >= n_groups) return;
-  const uint64_t first = (uint64_t)g * 1024;
-  const uint64_t left = n_units - first;
-  const uint32_t mine = left < 1024 ? (uint32_t)left : 1024u;
-  const uint64_t block = first >> units_per_block_log2;
-  const u32x4 ref = img[block << units_per_block_log2];
-  u32x4 x[4];
+// Bound by HBM: the kept blocks are read and written once, the constant ones read once.  A block that is kept
+// usually shows it in its first 4 KiB, so the flags cost little more than the constant blocks' bytes and the image
+// is read once in all, not twice.  1 GiB of which 30 % is constant, in blocks of 64 KiB: flags, scan and dense
+// copy together 603 us with every byte read by both passes (275 + 280 us) and a scan of 256 entries at a time
+// (46 us).
+//
+// One work-group looks at one segment: a whole block of up to 64 KiB, or 64 KiB of a larger one (WHOLE = false; the
+// flags are cleared before).  keep[k] = 1 if some 16-byte unit of block k differs from the block's first unit.
+constexpr uint32_t kSegmentUnitsLog2 = 12;
+template <bool WHOLE>
+__global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *__restrict__ img, uint64_t n_units,
+                                                                   uint32_t units_per_block_log2,
+                                                                   uint32_t units_per_segment_log2,
+                                                                   uint32_t *__restrict__ keep, u32x4 *__restrict__ patterns) {
+  const uint32_t segments = (uint32_t)((n_units + (1ull << units_per_segment_log2) - 1) >> units_per_segment_log2);
+  // Work-group i takes segment i, round-robin over the XCDs: constant blocks come in long runs, which in the lean
+  // path's order would be the work of one or two of them (99 us instead of 61, with 22 % of the image in one run).
+  const uint32_t g = blockIdx.x, tid = threadIdx.x;
+  if (g >= segments) return;
+  const uint64_t first = (uint64_t)g << units_per_segment_log2, left = n_units - first;
+  const uint32_t n = left < (1ull << units_per_segment_log2) ? (uint32_t)left : 1u << units_per_segment_log2;
+  const uint64_t block = first >> units_per_block_log2, block_first = block << units_per_block_log2;
+  const u32x4 ref = img[block_first];
+  u32x4 x = ref;
+  if (tid < n) x = __builtin_nontemporal_load(img + first + tid);
+  u32x4 d = x ^ ref;
+  int any = __syncthreads_or((d.x | d.y | d.z | d.w) != 0);
+  for (uint32_t base = 256; base < n && !any; base += 1024) {
+    u32x4 y[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (threadIdx.x + 256u * i < mine) x[i] = __builtin_nontemporal_load(img + first + threadIdx.x + 256 * i);
-  uint32_t diff = 0;
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t u = base + 256u * i + tid;
+      y[i] = __builtin_nontemporal_load(img + first + (u < n ? u : n - 1));
+    }
+    uint32_t diff = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (threadIdx.x + 256u * i < mine) {
-      const u32x4 d = x[i] ^ ref;
+    for (int i = 0; i < 4; ++i) {
+      d = y[i] ^ ref;
       diff |= d.x | d.y | d.z | d.w;
     }
-  if (__ballot(diff != 0) != 0 && (threadIdx.x & (kWave - 1)) == 0) atomicOr(keep + block, 1u);
+    any = __syncthreads_or(diff != 0);
+  }
+  if (tid == 0) {
+    if (WHOLE) keep[block] = any ? 1u : 0u;
+    else if (any) atomicOr(keep + block, 1u);
+    if (first == block_first) patterns[block] = ref;
+  }
 }
 
-// pos[k] = keep[0] + ... + keep[k-1], pos[n] = the sum.  One work-group walks the array 256 entries at a time.
-__global__ __launch_bounds__(256) void ds_exclusive_scan_kernel(const uint32_t *__restrict__ keep, uint32_t *__restrict__ pos,
-                                                                 uint64_t n) {
-  __shared__ uint32_t wave_sum[4];
+// pos[k] = keep[0] + ... + keep[k-1], pos[n] = the sum.  One work-group walks the array 16 Ki entries at a time, a
+// wavefront 1024 neighbouring ones: at that width one step covers a 1 GiB image of 64 KiB blocks (7 us; 16 entries
+// per thread one behind the other, each load of a wavefront on 64 lines, 17 us).
+constexpr uint32_t kScanThreads = 1024, kScanQuads = 4;  // quads of entries per thread and step
+__global__ __launch_bounds__(kScanThreads) void ds_exclusive_scan_kernel(const uint32_t *__restrict__ keep,
+                                                                         uint32_t *__restrict__ pos, uint64_t n) {
+  __shared__ uint32_t wave_sum[kScanThreads / kWave];
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   uint32_t carry = 0;
-  for (uint64_t base = 0; base < n; base += 256) {
-    const uint64_t i = base + tid;
-    const uint32_t x = i < n ? keep[i] : 0u;
-    const uint32_t incl = wave_inclusive_scan(x, lane);
-    if (lane == kWave - 1) wave_sum[wv] = incl;
+  for (uint64_t base = 0; base < n; base += kScanThreads * kScanQuads * 4) {
+    const uint64_t at = base + (uint64_t)wv * (kWave * kScanQuads * 4) + lane * 4;
+    u32x4 x[kScanQuads];
+#pragma unroll
+    for (uint32_t j = 0; j < kScanQuads; ++j) {
+      const uint64_t i = at + j * (kWave * 4);
+      x[j] = u32x4{0, 0, 0, 0};
+      if (i + 4 <= n) x[j] = ld16_any<false>((const uint8_t *)(keep + i));
+      else
+        for (uint32_t e = 0; e < 3; ++e)
+          if (i + e < n) x[j][e] = keep[i + e];
+    }
+    uint32_t before[kScanQuads], sum = 0;  // of the wavefront's entries, those before the quad
+#pragma unroll
+    for (uint32_t j = 0; j < kScanQuads; ++j) {
+      const uint32_t mine = x[j].x + x[j].y + x[j].z + x[j].w;
+      const uint32_t incl = wave_inclusive_scan(mine, lane);
+      before[j] = sum + incl - mine;
+      sum += __shfl(incl, kWave - 1, kWave);
+    }
+    if (lane == 0) wave_sum[wv] = sum;
     __syncthreads();
-    uint32_t before = carry;
-    for (uint32_t w = 0; w < wv; ++w) before += wave_sum[w];
-    if (i < n) pos[i] = before + incl - x;
-    carry += wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+    const uint32_t other = lane < kScanThreads / kWave ? wave_sum[lane] : 0u;
+    const uint32_t waves = wave_inclusive_scan(other, lane);
+    const uint32_t start = carry + __shfl(waves - other, wv, kWave);
+    carry += __shfl(waves, kWave - 1, kWave);
+#pragma unroll
+    for (uint32_t j = 0; j < kScanQuads; ++j) {
+      const uint64_t i = at + j * (kWave * 4);
+      u32x4 v;
+      v.x = start + before[j];
+      v.y = v.x + x[j].x;
+      v.z = v.y + x[j].y;
+      v.w = v.z + x[j].z;
+      if (i + 4 <= n) st16_any<false>((uint8_t *)(pos + i), v);
+      else
+        for (uint32_t e = 0; e < 3; ++e)
+          if (i + e < n) pos[i + e] = v[e];
+    }
     __syncthreads();
   }
   if (tid == 0) pos[n] = carry;
 }
 
-// Kept blocks go to their slots in `packed`, one behind the other; every block leaves its first unit in
-// `patterns`.  Same work-group shape as above.
+// Kept blocks go to their slots in `packed`, one behind the other.  One work-group takes 1024 units (16 KiB), which
+// lie in one block (the block size is a power of two of at least 16 KiB).
+constexpr uint32_t kStripeLog2 = 6;  // work-groups
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void ds_pack_kept_blocks_kernel(
     const u32x4 *__restrict__ img, uint64_t n_units, uint32_t units_per_block_log2, const uint32_t *__restrict__ keep,
-    const uint32_t *__restrict__ pos, u32x4 *__restrict__ patterns, u32x4 *__restrict__ packed) {
-  const uint32_t n_groups = (uint32_t)((n_units + 1023) / 1024), span = (n_groups + 7) / 8;
-  const uint32_t g = (blockIdx.x & 7u) * span + (blockIdx.x >> 3);
+    const uint32_t *__restrict__ pos, u32x4 *__restrict__ packed) {
+  const uint32_t n_groups = (uint32_t)((n_units + 1023) / 1024);
+  // an XCD takes every eighth stripe of 1 MiB: neighbours share an L2, and runs of constant blocks, which leave
+  // nothing to do, are dealt evenly (241 us; one contiguous eighth per XCD 271 us)
+  const uint32_t i8 = blockIdx.x >> 3;
+  const uint32_t g = ((i8 >> kStripeLog2) * 8 + (blockIdx.x & 7u)) << kStripeLog2 | (i8 & ((1u << kStripeLog2) - 1));
   if (g >= n_groups) return;
   const uint64_t first = (uint64_t)g * 1024;
   const uint64_t left = n_units - first;
   const uint32_t mine = left < 1024 ? (uint32_t)left : 1024u;
   const uint64_t block = first >> units_per_block_log2;
   const uint64_t in_block = first - (block << units_per_block_log2);
-  if (in_block == 0 && threadIdx.x == 0) patterns[block] = img[first];
+  const uint32_t slot = pos[block];
   if (!keep[block]) return;
-  u32x4 *out = packed + ((uint64_t)pos[block] << units_per_block_log2) + in_block;
   u32x4 x[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
     if (threadIdx.x + 256u * i < mine) x[i] = __builtin_nontemporal_load(img + first + threadIdx.x + 256 * i);
+  __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(packed + ((uint64_t)slot << units_per_block_log2) + in_block,
+                                                                 0, (int)(mine * 16u), 0x00020000);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    if (threadIdx.x + 256u * i < mine) __builtin_nontemporal_store(x[i], out + threadIdx.x + 256 * i);
+    if (threadIdx.x + 256u * i < mine)
+      __builtin_amdgcn_raw_buffer_store_b128(x[i], out, (int)(16u * (threadIdx.x + 256u * i)), 0, kStorePolicySc0Sc1Nt);
 }
 
 }  // namespace
@@ -1055,17 +1116,25 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   if (groups > 0x7FFFFFF0ull) return DS_ERANGE;
   const uint64_t n_blocks = (nbytes + block_bytes - 1) / block_bytes;
   const uint32_t upb_log2 = (uint32_t)__builtin_ctzll(block_bytes >> 4);
-  const uint32_t grid = (uint32_t)(((groups + 7) / 8) * 8);
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(ds_clear_flags_kernel, dim3((uint32_t)((n_blocks + 255) / 256)), dim3(256), 0, st, keep_dev, n_blocks);
+  const uint32_t ups_log2 = upb_log2 < kSegmentUnitsLog2 ? upb_log2 : kSegmentUnitsLog2;
+  const uint64_t segments = (n_units + (1ull << ups_log2) - 1) >> ups_log2;
+  const dim3 seg_grid((uint32_t)segments);
+  const uint64_t stripes = (((groups + (1u << kStripeLog2) - 1) >> kStripeLog2) + 7) / 8 * 8;
+  if (ups_log2 == upb_log2) {
+    hipLaunchKernelGGL(ds_constant_segments_kernel<true>, seg_grid, dim3(256), 0, st, (const u32x4 *)image_dev, n_units,
+                       upb_log2, ups_log2, keep_dev, (u32x4 *)patterns_dev);
+  } else {
+    hipLaunchKernelGGL(ds_clear_flags_kernel, dim3((uint32_t)((n_blocks + 255) / 256)), dim3(256), 0, st, keep_dev, n_blocks);
+    DS_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(ds_constant_segments_kernel<false>, seg_grid, dim3(256), 0, st, (const u32x4 *)image_dev, n_units,
+                       upb_log2, ups_log2, keep_dev, (u32x4 *)patterns_dev);
+  }
   DS_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(ds_constant_blocks_kernel, dim3(grid), dim3(256), 0, st, (const u32x4 *)image_dev, n_units, upb_log2,
-                     keep_dev);
+  hipLaunchKernelGGL(ds_exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, keep_dev, pos_dev, n_blocks);
   DS_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(ds_exclusive_scan_kernel, dim3(1), dim3(256), 0, st, keep_dev, pos_dev, n_blocks);
-  DS_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(ds_pack_kept_blocks_kernel, dim3(grid), dim3(256), 0, st, (const u32x4 *)image_dev, n_units, upb_log2,
-                     keep_dev, pos_dev, (u32x4 *)patterns_dev, (u32x4 *)packed_dev);
+  hipLaunchKernelGGL(ds_pack_kept_blocks_kernel, dim3((uint32_t)(stripes << kStripeLog2)), dim3(256), 0, st,
+                     (const u32x4 *)image_dev, n_units, upb_log2, keep_dev, pos_dev, (u32x4 *)packed_dev);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }

@@ -1,0 +1,60 @@
+"""ds_image_compress where its kernels can go wrong: blocks around the size one work-group looks at (64 KiB), a
+difference in the last unit of each part of such a look, and more blocks than one step of the scan (16 384)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(img, block):
+    import paper_2601_16956_amd as ds
+    import torch
+    n_blocks = -(-img.numel() // block)
+    keep = torch.full((n_blocks,), 9, dtype=torch.int32, device="cuda")
+    pos = torch.full((n_blocks + 1,), 9, dtype=torch.int32, device="cuda")
+    pats = torch.full((n_blocks, 16), 0xCC, dtype=torch.uint8, device="cuda")
+    packed = torch.full((n_blocks * block,), 0xCC, dtype=torch.uint8, device="cuda")
+    ds.ds_image_compress(img.data_ptr(), img.numel(), block, keep.data_ptr(), pos.data_ptr(), pats.data_ptr(),
+                         packed.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return keep.cpu().numpy(), pos.cpu().numpy(), pats.cpu().numpy(), packed.cpu().numpy()
+
+
+@pytest.mark.parametrize("block", [16384, 32768, 65536, 131072, 1 << 21])
+def test_a_difference_anywhere_in_a_block_keeps_it(block):
+    import torch
+    from oracle import image_compress as ic
+    rng = np.random.default_rng(block)
+    # the only unit that differs: the first ones of a look of 4 KiB, of a step of 16 KiB, of a segment, the last ones
+    at = sorted({u for u in (1, 255, 256, 1023, 1024, 1279, 1280, 4095, 4096, 4097, 8191, block // 16 - 1, block // 16 - 2)
+                 if 0 < u < block // 16})
+    blocks = []
+    for u in at:
+        b = np.tile(rng.integers(0, 256, 16, dtype=np.uint8), block // 16)
+        blocks += [b.copy(), b]
+        b[16 * u + int(rng.integers(0, 16))] ^= 1
+    for tail in (16, 4096, block - 16, block):
+        img = np.concatenate(blocks + [np.tile(np.arange(16, dtype=np.uint8), tail // 16)])
+        for last in (0, 1):
+            img[-1] ^= last
+            keep_w, pos_w, pat_w, packed_w = ic.compress(img, block)
+            print(f"[case] compress block={block} tail={tail} last={last}", flush=True)
+            keep, pos, pats, packed = _run(torch.from_numpy(img).cuda(), block)
+            assert keep.tolist() == keep_w.tolist() and pos.tolist() == pos_w.tolist() and np.array_equal(pats, pat_w)
+            n = int(pos_w[-1]) * block - (block - tail if keep_w[-1] else 0)
+            assert np.array_equal(packed[:n], packed_w[:n]) and np.all(packed[n:] == 0xCC)
+
+
+@pytest.mark.parametrize("n_blocks", [16383, 16384, 16385, 40000])
+def test_more_blocks_than_one_step_of_the_scan(n_blocks):
+    import torch
+    block = 16384
+    kept = torch.from_numpy(np.random.default_rng(n_blocks).random(n_blocks) < 0.4).cuda()
+    img = torch.zeros(n_blocks, block // 4, dtype=torch.int32, device="cuda")
+    img[:, -1] = kept.int() * torch.arange(1, n_blocks + 1, device="cuda", dtype=torch.int32)
+    print(f"[case] compress {n_blocks} blocks", flush=True)
+    keep, pos, pats, packed = _run(img.view(torch.uint8).reshape(-1), block)
+    want = kept.cpu().numpy().astype(np.int64)
+    assert np.array_equal(keep, want) and np.array_equal(pos, np.concatenate([[0], np.cumsum(want)])) and not pats.any()
+    last = packed[:int(want.sum()) * block].view(np.int32).reshape(-1, block // 4)
+    assert np.array_equal(last[:, -1], np.flatnonzero(want) + 1) and not last[:, :-1].any()
