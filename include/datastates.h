@@ -672,11 +672,12 @@ int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_t block_byt
  *                   work-group i takes chunk i (no XCD-contiguous order), 4 = default, but plans made
  *                   under it do not mark chunks for the gather's aligned-load route (tensors at
  *                   addresses that are not multiples of 16 are then read with unaligned loads),
- *                   5 = default, but a plan in which most chunks take the general path is launched
- *                   with four wavefronts per SIMD like any other (by default it gets five for the
- *                   gather and six for the scatter)
+ *                   5 = every launch is of work-groups of 16 KiB at four wavefronts per SIMD that know all
+ *                   kinds of chunks (by default the scatter's take 8 KiB at six, a plan of mostly general
+ *                   chunks gets five for the gather, and plans of contiguous shards and views with runs
+ *                   shorter than 16 bytes have kernels of their own)
  *   "grid_limit"    work-groups per launch of ds_pack / ds_unpack (each then walks several chunks);
- *                   0 = one per chunk (default).  Engines have their own pack_grid_limit
+ *                   0 = one per chunk or part of one (default).  Engines have their own pack_grid_limit
  *   "drop_pinned_cache"   (set only) a non-zero value frees the pinned ring and the device staging the
  *                   library keeps from the last destroyed engine for the next one (see ds_engine_create)
  *   "io_uring_available"  (get only) 1 if this process can set up an io_uring, else 0

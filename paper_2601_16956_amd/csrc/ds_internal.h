@@ -45,7 +45,9 @@ static_assert(sizeof(DsTileHot) == 40, "five 8-byte words");
 // 16 bytes) are of kind DS_CHUNK_GENERAL and take the general path; their
 // record names the tiles they hold (tile, col0).  DS_CHUNK_PERM: the whole chunk is whole units of one view that is
 // moved in blocks (ds_perm.h); its record is that of a general chunk, for launches without the block tables.
-enum : uint32_t { DS_CHUNK_CONTIG = 0, DS_CHUNK_ROWS = 1, DS_CHUNK_GENERAL = 2, DS_CHUNK_PERM = 3 };
+// DS_CHUNK_MULTI: general, and every tile of it is one contiguous run; same record.
+enum : uint32_t { DS_CHUNK_CONTIG = 0, DS_CHUNK_ROWS = 1, DS_CHUNK_GENERAL = 2, DS_CHUNK_PERM = 3, DS_CHUNK_MULTI = 4 };
+constexpr uint32_t kMultiTiles = 1024;  // tiles a chunk of kind DS_CHUNK_MULTI may hold
 // CONTIG only, bit 8 of `kind`: the tensor side of the chunk is not 16-byte aligned, and the tensor has at least
 // 16 more bytes on either side of it, so the gather may read the 16-byte aligned units that cover the chunk's
 // bytes (one more than the chunk has) without leaving the tensor.
@@ -113,7 +115,8 @@ struct ds_plan {
   std::vector<uint32_t> perm_first;        // perms.size() + 1 entries: a view's first block
   std::vector<uint32_t> rest_ids;          // if there are such views: the chunks that are not of kind DS_CHUNK_PERM ...
   std::vector<DsChunkRec> rest_recs;       // ... and their records, so that a launch has no empty work items
-  uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL and DS_CHUNK_PERM)
+  uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
+  bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
   // device copies (one allocation)
   int device = -1;
   void *dev_blob = nullptr;

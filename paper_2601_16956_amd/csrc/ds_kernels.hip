@@ -9,11 +9,12 @@
 // however fragmented its part of the image is.
 //
 // One kernel, ds_move_kernel, serves a pack (or unpack) call; a work-group takes one chunk down one of
-// two paths:
+// two paths (plans of contiguous shards only, most of whose chunks hold several, have a simpler second one,
+// multi_chunk, and views with runs shorter than 16 bytes are moved by a kernel of their own, ds_perm_kernel):
 //
 // lean path: one pass per chunk, a chunk being exactly threads x unroll
-//   units (16 KiB by default), so a thread issues all its loads, then all its
-//   stores, and is done.  Measured on MI355X a plain copy of this shape runs
+//   units (16 KiB by default; the scatter cuts it into pieces of 8 KiB), so a
+//   thread issues all its loads, then all its stores, and is done.  Measured on MI355X a plain copy of this shape runs
 //   at ~6 TB/s (read+write) against ~5.3 TB/s for work-groups that stream
 //   through 64-256 KiB each: many short-lived work-groups keep the addresses
 //   in flight inside a compact, moving window of HBM.  Everything the path
@@ -43,6 +44,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "ds_internal.h"
 #include "ds_splice.h"
@@ -64,6 +66,8 @@ struct MoveArgs {
   uint64_t total;       // image length
   uint32_t chunk_log2;
   uint32_t n_extra;     // 0..2 chunks cut by img_lo / img_hi: they take the general path whatever their kind
+                        // (pieces of chunks: | log2(pieces per chunk) << 8).  Both
+                        // structures together have 120 bytes: with 128 the 23 MB gather took 0.2 us longer
   uint32_t extra[2];
 };
 
@@ -74,8 +78,8 @@ struct LeanArgs {
   uint64_t img_lo;
   uint32_t chunk_log2;
   uint32_t c_lo;       // record of the first whole chunk inside [img_lo, img_hi)
-  uint32_t n_chunks;   // records of whole chunks inside the range
-  uint32_t xcd_span;   // chunks per XCD (ceil(n_chunks / 8)); 0 = work-group i takes chunk i
+  uint32_t n_pieces;   // work-groups' pieces of the whole chunks inside the range
+  uint32_t xcd_span;   // pieces per XCD (ceil(n_pieces / 8)); 0 = work-group i takes piece i
 };
 
 // ---- 16-byte accesses -------------------------------------------------------
@@ -340,10 +344,42 @@ __device__ __forceinline__ void store_low_bytes(uint8_t *p, u32x4 v, uint32_t n)
   }
   if (n & 1) *(DS_GLOBAL uint8_t *)p = (uint8_t)lo;
 }
+// ... and the n < 16 bytes at p, as one load each of 8, 4, 2 and 1 bytes, zeros behind them
+__device__ __forceinline__ u32x4 load_low_bytes(const uint8_t *p, uint32_t n) {
+  uint32_t f0 = 0, f1 = 0, x = 0, y = 0;
+  if (n & 8) {
+    const uint64_t first = *(const DS_GLOBAL u64_unaligned *)p;
+    f0 = (uint32_t)first;
+    f1 = (uint32_t)(first >> 32);
+  }
+  if (n & 4) x = *(const DS_GLOBAL u32_unaligned *)(p + (n & 8));
+  if (n & 2) y = *(const DS_GLOBAL u16_unaligned *)(p + (n & 12));
+  if (n & 1) {
+    const uint32_t last = *(const DS_GLOBAL uint8_t *)(p + (n & 14));
+    y |= n & 2 ? last << 16 : last;
+  }
+  if (!(n & 4)) {
+    x = y;
+    y = 0;
+  }
+  return n & 8 ? u32x4{f0, f1, x, y} : u32x4{x, y, 0, 0};
+}
 // bytes [0,k) of v go to p0, bytes [k,valid) to p1 (0 < k < 16, k <= valid <= 16); exactly those bytes are written
 __device__ __forceinline__ void store_cut(uint8_t *p0, uint8_t *p1, uint32_t k, u32x4 v, uint32_t valid = 16) {
   store_low_bytes(p0, v, k);
   if (valid > k) store_low_bytes(p1, splice(v, u32x4{0, 0, 0, 0}, k), valid - k);
+}
+
+// Image bytes [cb, ce) of chunk c (WHOLE), or of its piece of BYTES from byte `piece` on, that lie in the launch's range;
+// false if none do.
+template <bool WHOLE, uint32_t BYTES>
+__device__ __forceinline__ bool piece_range(const MoveArgs &a, uint64_t c, uint32_t piece, uint64_t &cb, uint64_t &ce) {
+  const uint64_t c_begin = (c << a.chunk_log2) + (WHOLE ? 0u : piece);
+  uint64_t c_end = WHOLE ? (c + 1) << a.chunk_log2 : c_begin + BYTES;
+  if (c_end > a.total) c_end = a.total;
+  cb = c_begin > a.img_lo ? c_begin : a.img_lo;
+  ce = c_end < a.img_hi ? c_end : a.img_hi;
+  return cb < ce;
 }
 
 // What a batch of up to 64 tiles of a general chunk needs, staged in LDS by the first wavefront.  Everything
@@ -378,16 +414,12 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 // only the rest (runs shorter than 16 bytes, views with several outer dimensions) goes one by one through
 // move_unit afterwards.
 // LIST: a launch of blocks moves the views marked DS_HOT_PERM.
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST>
-__device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t t0, uint32_t t1, GenLds *g) {
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST, bool WHOLE>
+__device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1, GenLds *g) {
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & (kWave - 1);
-  const uint64_t c_begin = c << a.chunk_log2;
-  uint64_t c_end = (c + 1) << a.chunk_log2;
-  if (c_end > a.total) c_end = a.total;
-  const uint64_t cb = c_begin > a.img_lo ? c_begin : a.img_lo;
-  const uint64_t ce = c_end < a.img_hi ? c_end : a.img_hi;
-  if (cb >= ce) return;
+  uint64_t cb, ce;
+  if (!piece_range<WHOLE, NT * UNROLL * 16>(a, c, piece, cb, ce)) return;
   uint8_t *const cimg = a.img + (cb - a.img_lo);  // the chunk's (clipped) start in the image buffer
   // Gather with buffer stores: the resource covers exactly the chunk's part of the image, and a lane that has
   // nothing to store in a phase gives an offset beyond it, which the hardware drops.  The stores of a phase
@@ -422,7 +454,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
       }
       const uint32_t n_outer = meta & 0xFFu;
       const uint32_t units = (uint32_t)((hi - lo) >> 4);
-      const bool big = units >= kBigUnits && n_outer > 1;
+      const bool big = NT * UNROLL >= kBigUnits && units >= kBigUnits && n_outer > 1;
       const uint64_t big_mask = __ballot(big);
       const uint32_t incl = wave_inclusive_scan(big ? 0u : units, lane);
       const uint64_t b0 = lo - tb;  // byte of the tile's own range at which its clipped range starts
@@ -615,7 +647,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
           move_unit<PACK, NTL, NTS>(a.tiles + bt + q, tb, cb + (uint64_t)(ip[i] - cimg), ip[i]);
         }
     }
-    uint64_t big_mask = g->big_mask;
+    uint64_t big_mask = NT * UNROLL >= kBigUnits ? g->big_mask : 0;
     while (big_mask) {
       const uint32_t p = (uint32_t)__builtin_ctzll(big_mask);
       big_mask &= big_mask - 1;
@@ -623,6 +655,103 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
       const uint64_t tb = a.hot[t].img_off, te = a.hot[t + 1].img_off;
       const uint64_t lo2 = tb > cb ? tb : cb, hi2 = te < ce ? te : ce;
       move_tile_direct<PACK, NT, UNROLL, NTL, NTS>(a.tiles + t, tb, lo2, hi2, a.img, a.img_lo);
+    }
+  }
+}
+
+// ---- chunks of several contiguous tiles ---------------------------------------------------------------------
+// One chunk, whole work-group, every tile of it one contiguous run (tables of small tensors, and the chunks between
+// two large ones).  The tiles' ranges follow each other in the image without a gap, so unit u of the chunk IS the
+// 16 bytes at 16u: no scan over unit counts, only a binary search over where the tiles begin, as deep as the chunk
+// has tiles.  And one load per unit serves all kinds: a unit cut by the end of its payload is the tile's last 16
+// bytes, moved down by the bytes that were read before it.
+// Bound by latency (record -> descriptors -> data) and instruction issue: see the measurements at ds_move_kernel.
+struct MultiLds {
+  uint64_t src[kMultiTiles];    // address of the tile's (clipped) start
+  uint32_t begin[kMultiTiles];  // that start, relative to the chunk's clipped start
+  uint32_t rem[kMultiTiles];    // payload bytes from there on (clamped to 2^30) | kWholeBelow16
+};
+constexpr uint32_t kWholeBelow16 = 1u << 31;  // the tile has less than 16 bytes: nothing to read a unit from
+
+template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, bool WHOLE>
+__device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1, MultiLds *g) {
+  const uint32_t tid = threadIdx.x;
+  uint64_t cb, ce;
+  if (!piece_range<WHOLE, 256 * UNROLL * 16>(a, c, piece, cb, ce)) return;
+  uint8_t *const cimg = a.img + (cb - a.img_lo);
+  const uint32_t size = (uint32_t)(ce - cb), n = t1 - t0 + 1;
+  __syncthreads();  // readers of the previous chunk are done
+  for (uint32_t i = tid; i < n; i += 256) {
+    const DsTileHot *h = a.hot + t0 + i;
+    const uint64_t tb = h->img_off, nbytes = h->nbytes;
+    const uint64_t b0 = cb > tb ? cb - tb : 0;  // byte of the tile at which its clipped range starts
+    uint64_t rem = nbytes > b0 ? nbytes - b0 : 0;
+    if (rem > (1ull << 30)) rem = 1ull << 30;
+    g->src[i] = h->src + b0;
+    g->begin[i] = (uint32_t)(tb + b0 - cb);  // beyond the chunk's end for tiles behind the clipped range: never found
+    g->rem[i] = (uint32_t)rem | (nbytes < 16 ? kWholeBelow16 : 0u);
+  }
+  __syncthreads();
+  uint32_t p[UNROLL], d[UNROLL], rem[UNROLL];
+  const uint8_t *sp[UNROLL];
+#pragma unroll
+  for (int i = 0; i < UNROLL; ++i) p[i] = 0;
+  // the last tile that begins at or before the unit
+  for (uint32_t step = 1u << (31 - __builtin_clz(n)); step > 0; step >>= 1) {
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t q = p[i] + step;
+      if (q < n && g->begin[q] <= 16u * (i * 256 + tid)) p[i] = q;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < UNROLL; ++i) {
+    d[i] = 16u * (i * 256 + tid) - g->begin[p[i]];
+    rem[i] = g->rem[p[i]];
+    sp[i] = (const uint8_t *)g->src[p[i]] + d[i];
+  }
+  u32x4 v[UNROLL];
+  if (PACK) {
+    uint32_t s[UNROLL];  // by how much the 16 bytes read lie before the unit; 16 = nothing of it is payload
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t whole = rem[i] & ~kWholeBelow16;
+      s[i] = d[i] + 16u > whole ? d[i] + 16u - whole : 0u;
+      if (s[i] > 16u || (rem[i] & kWholeBelow16)) s[i] = 16u;
+      // lanes with nothing to read load the table's first bytes, so that no load hangs on a condition
+      v[i] = ld16_any<NTL>(s[i] < 16u ? sp[i] - s[i] : (const uint8_t *)(a.hot + t0));
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __amdgpu_buffer_rsrc_t image_rsrc;
+    if (BUFST) image_rsrc = __builtin_amdgcn_make_buffer_rsrc(cimg, 0, (int)size, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      if (__ballot(s[i] != 0)) {
+        const u32x4 cut = splice(v[i], u32x4{0, 0, 0, 0}, s[i] & 15u);
+        if (s[i] != 0) v[i] = s[i] < 16u ? cut : u32x4{0, 0, 0, 0};
+        if ((rem[i] & kWholeBelow16) && d[i] < 16u) v[i] = load_low_bytes(sp[i], rem[i] & 15u);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t off = 16u * (i * 256 + tid);
+      if (BUFST) __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
+      else if (off < size) st16_aligned<NTS>(cimg + off, v[i]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t off = 16u * (i * 256 + tid);
+      v[i] = ld16_aligned<NTL>(cimg + (off < size ? off : size - 16u));
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t whole = rem[i] & ~kWholeBelow16;
+      if (16u * (i * 256 + tid) < size && d[i] < whole) {
+        if (d[i] + 16u <= whole) st16_any<NTS>((uint8_t *)sp[i], v[i]);
+        else store_low_bytes((uint8_t *)sp[i], v[i], whole - d[i]);
+      }
     }
   }
 }
@@ -635,15 +764,16 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
 // the work-group's chunk, so an out-of-range store would be dropped by the hardware.
 
 // Number of lean work items of a launch; item ci takes one lean chunk, whole work-group.
-__device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd_span ? a.xcd_span * 8u : a.n_chunks; }
+__device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd_span ? a.xcd_span * 8u : a.n_pieces; }
 
-// Work item ci of a launch: moves its chunk if the chunk is lean and returns false; for a general chunk it
-// moves nothing, says which chunk and tiles (c, t0, t1) and returns true: the caller sends it down the general
-// path (one call site, so that the general path is in the kernel once).
+// Work item ci of a launch: moves its chunk if the chunk is lean and returns 0; for any other it moves nothing, says
+// which chunk and tiles (c, t0, t1) and returns the chunk's kind: the caller sends it down its path (one call site
+// each, so that these paths are in the kernel once).
 // LIST: the launch's records are not those of all its chunks, and `ids` names the chunk of each.  A template
 // parameter and not a test of the pointer: the test alone made a 23 MB gather 0.9 us slower.
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST>
-__device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint64_t &c_gen, uint32_t &t0, uint32_t &t1) {
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST, bool WHOLE>
+__device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, uint32_t pieces_log2, uint64_t &c_gen,
+                                               uint32_t &piece, uint32_t &t0, uint32_t &t1) {
   const uint32_t tid = threadIdx.x;
   {
     // Work-groups are dealt to the 8 XCDs round-robin (work-group i runs on XCD i mod 8).  Chunk
@@ -653,24 +783,26 @@ __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint6
     uint32_t cm = ci;
     if (a.xcd_span) {
       cm = (ci & 7u) * a.xcd_span + (ci >> 3);
-      if (cm >= a.n_chunks) return false;
+      if (cm >= a.n_pieces) return 0;
     }
-    const DsChunkRec r = a.recs[a.c_lo + cm];
-    const uint32_t c = LIST ? a.ids[a.c_lo + cm] : a.c_lo + cm;
+    if (!WHOLE) piece = (cm & ((1u << pieces_log2) - 1)) * (NT * UNROLL * 16);  // offset inside the chunk
+    const uint32_t rec = a.c_lo + (WHOLE ? cm : cm >> pieces_log2);
+    const DsChunkRec r = a.recs[rec];
+    const uint32_t c = LIST ? a.ids[rec] : rec;
     const uint32_t kind = r.kind & 0xFF;  // bits 8.. hold log2(itemsize)
     if (kind >= DS_CHUNK_GENERAL) {
       // its record names the tiles it holds: one load away from them, and in place among its neighbours
       c_gen = c;
       t0 = r.tile;
       t1 = r.tile + r.col0;
-      return true;
+      return kind;
     }
-    uint8_t *imgp = a.img + (((uint64_t)c << a.chunk_log2) - a.img_lo);
+    uint8_t *imgp = a.img + (((uint64_t)c << a.chunk_log2) - a.img_lo) + (WHOLE ? 0u : piece);
     __amdgpu_buffer_rsrc_t image_rsrc;
     if (PACK && BUFST) image_rsrc = __builtin_amdgcn_make_buffer_rsrc(imgp, 0, NT * UNROLL * 16, 0x00020000);
     u32x4 v[UNROLL];
     if (kind == DS_CHUNK_CONTIG) {
-      uint8_t *s = reinterpret_cast<uint8_t *>(r.addr);
+      uint8_t *s = reinterpret_cast<uint8_t *>(r.addr) + (WHOLE ? 0u : piece);
       // (the scatter keeps "nt" global stores on the tensor side: the write-through buffer stores that serve
       // the image so well cost it 3 % on the Llama ranks and 10 % on the fragmentation set, measured)
       if (PACK && (r.kind & DS_CHUNK_REALIGN)) {
@@ -723,7 +855,7 @@ __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint6
       // One division for the thread's first unit; its other units are NT*16 bytes further on each,
       // and the plan has divided that step by the run length already (r.tile = quotient << 16 | rest).
       const uint32_t step_q = r.tile >> 16, step_r = r.tile & 0xFFFFu;
-      const uint32_t tt0 = r.col0 + 16u * tid;  // < 2^31 + 2^13
+      const uint32_t tt0 = r.col0 + (WHOLE ? 0u : piece) + 16u * tid;  // < 2^31 + 2^15
       uint32_t q = tt0 / r.run;
       uint32_t col = tt0 - q * r.run;
 #pragma unroll
@@ -766,7 +898,7 @@ __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint6
       }
     }
   }
-  return false;
+  return 0;
 }
 
 // Both paths in one launch: work item i takes whole chunk number i of the range (in the XCD-contiguous
@@ -777,61 +909,106 @@ __device__ __forceinline__ bool lean_chunk(const LeanArgs &a, uint32_t ci, uint6
 // against 6.17 now); the general kernel on a side stream beside the lean one gave the fragmentation set
 // 5.30 -> 5.54 TB/s, one launch 5.85 TB/s.
 //
-// At most 4 waves per SIMD (the attribute makes the compiler pad the register allocation): fewer
-// work-groups in flight keep the addresses in a more compact window of HBM.  Measured with the cap at 4
-// against 5: gather +0.8 % on the 7B and 70B ranks, -0.8 % on the fragmentation set, scatter +0.5 to +1 %
-// everywhere; the scatter, whose own registers would allow 8, loses 5 % there; with 3 or fewer both
-// directions lose ~9 %.
-//
-// A lean chunk is exactly 256 threads x UNROLL x 16 bytes; the general path always works in passes of
-// 256 x 4 units.
-//
-// WAVES = 6 is the instantiation for plans in which most chunks are general (tables of thousands of tiny
-// tensors): that path is bound by its chain of dependent loads, not by HBM, and more wavefronts per SIMD hide
-// more of it -- five for the gather, whose registers allow no more, six for the scatter (measured on tables
-// where every chunk is general: +8 to +10 % both ways with five, another +6 to +10 % for the scatter of tiny
-// tensors with six), while the lean path loses 2 to 5 % there.
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, bool LIST>
+// A work-group takes one piece of a chunk, 256 threads x UNROLL units, with at most WAVES wavefronts per SIMD (the
+// attribute makes the compiler pad the register allocation).  What bounds the lean path is the bytes in flight: the
+// record and then the data take about 3 us, which at 3.2 TB/s each way are 40 KB per CU.
+//   gather, UNROLL 4 and WAVES 4: 64 KB in flight, and few work-groups keep the addresses in a compact window of
+//     HBM (five wavefronts -0.8 % on the 7B and 70B ranks, eight -4 %, three or fewer -9 %).  Two units per thread
+//     would need eight wavefronts to gain anything (70B rank 2.36 ms against 2.40, six wavefronts 2.41), which the
+//     general path's 93 registers do not allow; one unit per thread leaves too little in flight (3.30 ms).
+//   gather of plans of mostly general chunks, WAVES 6: that path is bound by its chain of dependent loads and takes
+//     the five wavefronts its registers allow (+8 to +10 % on tables of tiny tensors against four).
+//   scatter, UNROLL 2 and WAVES 6 (a piece of 8 KiB, 48 KB in flight), or as the gather: see scatter_in_pieces.
+// ALL = false is the instantiation for plans of contiguous shards only, most chunks of which hold several of them:
+// no chunk takes the general path, and multi_chunk's registers allow eight wavefronts.  24 000 tensors of 16 bytes to
+// 16 KiB (58 MB): gather 25.1 us against 29.1 through the general path, scatter 24.5 against 26.7; a plain copy of
+// as many bytes takes 22 us.
+template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, bool LIST, bool ALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
                                                                                                      MoveArgs ma) {
-  __shared__ GenLds s_gen;
+  __shared__ typename std::conditional<ALL, GenLds, MultiLds>::type s_tab;
   const uint32_t n_lean = lean_items(la);
-  const uint32_t n_iter = n_lean + ma.n_extra;
+  constexpr bool WHOLE = PACK || UNROLL >= 4;  // the work-group's piece is the chunk
+  const uint32_t pieces_log2 = WHOLE ? 0 : ma.n_extra >> 8;
+  const uint32_t n_iter = n_lean + (WHOLE ? ma.n_extra : (ma.n_extra & 0xFFu) << pieces_log2);
   for (uint32_t wi = blockIdx.x; wi < n_iter; wi += gridDim.x) {
     uint64_t c = 0;
-    uint32_t t0 = 0, t1 = 0;
-    bool general = true;
+    uint32_t piece = 0, t0 = 0, t1 = 0;
+    uint32_t kind = DS_CHUNK_GENERAL;
     if (wi < n_lean) {
-      general = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST, LIST>(la, wi, c, t0, t1);
+      kind = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST, LIST, WHOLE>(la, wi, pieces_log2, c, piece, t0, t1);
     } else {
-      // a chunk cut by the range: the general path clips to the range, whatever the chunk's kind
-      c = ma.extra[wi - n_lean];
+      // (a piece of) a chunk cut by the range, whatever the chunk's kind: these paths clip to the range
+      const uint32_t x = wi - n_lean;
+      c = ma.extra[x >> pieces_log2];
+      piece = (x & ((1u << pieces_log2) - 1)) * (256 * UNROLL * 16);
       uint64_t c_end = (c + 1) << ma.chunk_log2;
       if (c_end > ma.total) c_end = ma.total;
       t0 = ma.first_tile[c];
       t1 = ma.first_tile[c + 1];
       if (ma.hot[t1].img_off >= c_end) --t1;  // that tile starts where this chunk ends
     }
-    if (general) general_chunk<PACK, 256, 4, NTL, NTS, BUFST, LIST>(ma, c, t0, t1, &s_gen);
+    if constexpr (ALL) {
+      if (kind) general_chunk<PACK, 256, WHOLE ? 4 : UNROLL, NTL, NTS, BUFST, LIST, WHOLE>(ma, c, piece, t0, t1, &s_tab);
+    } else {
+      if (kind) multi_chunk<PACK, UNROLL, NTL, NTS, BUFST, WHOLE>(ma, c, piece, t0, t1, &s_tab);
+    }
   }
 }
 
-template <bool PACK, bool NTL, bool NTS, bool BUFST, int WAVES = 4, bool LIST = false>
-int launch_move(uint32_t chunk_log2, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, hipStream_t stream) {
-  uint32_t grid = (la.xcd_span ? la.xcd_span * 8 : la.n_chunks) + ma.n_extra;
+constexpr uint32_t kMaxGrid = 1u << 23;  // work-groups of 256: a launch has less than 2^32 threads
+
+template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, bool LIST, bool ALL>
+int launch_pieces(LeanArgs la, MoveArgs ma, uint32_t grid_limit, hipStream_t stream) {
+  const uint32_t pieces_log2 = la.chunk_log2 - (12 + __builtin_ctz(UNROLL));
+  la.n_pieces <<= pieces_log2;  // chunks so far
+  la.xcd_span = ds_cfg_variant() == 3 ? 0 : (la.n_pieces + 7) / 8;
+  uint64_t grid = (uint64_t)(la.xcd_span ? la.xcd_span * 8 : la.n_pieces) + (ma.n_extra << pieces_log2);
   if (grid == 0) return DS_OK;
+  if (!PACK && UNROLL == 2) ma.n_extra |= pieces_log2 << 8;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
-#define DS_MOVE(UN) \
-  hipLaunchKernelGGL((ds_move_kernel<PACK, UN, NTL, NTS, BUFST, WAVES, LIST>), dim3(grid), dim3(256), 0, stream, la, ma)
-  switch (chunk_log2) {
-    case 13: DS_MOVE(2); break;
-    case 14: DS_MOVE(4); break;
-    case 15: DS_MOVE(8); break;
-    default: return DS_EINVAL;
-  }
-#undef DS_MOVE
+  if (grid > kMaxGrid) grid = kMaxGrid;
+  hipLaunchKernelGGL((ds_move_kernel<PACK, UNROLL, NTL, NTS, BUFST, WAVES, LIST, ALL>), dim3((uint32_t)grid), dim3(256), 0,
+                     stream, la, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
+}
+
+// The gather: a chunk per work-group.  (Pieces in its kernel, though one per chunk, cost the 23 MB gather 0.3 us.)
+template <bool NTL, bool NTS, bool BUFST, int WAVES = 4, bool LIST = false, bool ALL = true>
+int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, hipStream_t stream) {
+  switch (la.chunk_log2) {
+    case 13: return launch_pieces<true, 2, NTL, NTS, BUFST, WAVES, LIST, ALL>(la, ma, grid_limit, stream);
+    case 14: return launch_pieces<true, 4, NTL, NTS, BUFST, WAVES, LIST, ALL>(la, ma, grid_limit, stream);
+    case 15: return launch_pieces<true, 8, NTL, NTS, BUFST, WAVES, LIST, ALL>(la, ma, grid_limit, stream);
+    default: return DS_EINVAL;
+  }
+}
+
+// The scatter.  In a launch of many rounds pieces of 8 KiB at six wavefronts per SIMD are the faster (7B rank 0.490 ms,
+// chunks at four 0.504).  In one of a few rounds it is the last round that counts: a shape's rounds are what its
+// work-groups need of the 256 CUs x WAVES that run at once, and pieces are taken where they need less of the chip's
+// time by more than 5 % (23 MB state, 1.8 of 2 rounds against 1.4 of 2: 10.9 us instead of 11.5; 38 MB, 3.04 of 4
+// against 2.3 of 3: 16.7 instead of 16.4).  Plans of mostly general chunks keep whole chunks, whose tiles are looked
+// up once (15 MB in 711 views and tensors: 10.7 us, in pieces 11.4).
+inline bool scatter_in_pieces(uint64_t chunks) {
+  const uint64_t whole = (chunks + 1023) / 1024 * 1024, pieces = (2 * chunks + 1535) / 1536 * 768;
+  return chunks > 8 * 1024 || pieces * 21 <= whole * 20;
+}
+
+template <bool NTL, bool NTS, bool LIST = false, bool ALL = true>
+int launch_scatter(bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit,
+                   hipStream_t stream) {
+  if (la.chunk_log2 < 14 || !ALL) return launch_pieces<false, 2, NTL, NTS, false, ALL ? 6 : 8, LIST, ALL>(la, ma, grid_limit, stream);
+  if constexpr (ALL) {
+    const bool pieces = !mostly_general && scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14));
+    if (la.chunk_log2 == 15 && (few || !pieces))
+      return launch_pieces<false, 8, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream);
+    if (few || (!pieces && !mostly_general))
+      return launch_pieces<false, 4, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream);
+    if (mostly_general) return launch_pieces<false, 4, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
+  }
+  return launch_pieces<false, 2, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
 }
 
 // ---- views with runs shorter than 16 bytes, in blocks through LDS (ds_perm.h) ---------------------------
@@ -846,7 +1023,7 @@ struct PermArgs {
   const DsPerm *perms;
   const DsPermItem *items;  // the launch's first block
   uint32_t n_items;
-  uint32_t xcd_span;        // blocks per XCD, as in LeanArgs
+  uint32_t xcd_span;        // blocks per XCD; 0 = work-group i takes block i
   uint8_t *img;             // points at image byte img_lo
   uint64_t img_lo, img_hi;
 };
@@ -1206,16 +1383,16 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   la.img_lo = img_lo;
   la.chunk_log2 = lg;
   la.c_lo = (uint32_t)w_lo;
-  la.n_chunks = w_hi > w_lo ? (uint32_t)(w_hi - w_lo) : 0;
-  if (tb.perms && la.n_chunks) {
+  la.n_pieces = w_hi > w_lo ? (uint32_t)(w_hi - w_lo) : 0;
+  if (tb.perms && la.n_pieces) {
     const auto first = std::lower_bound(plan->rest_ids.begin(), plan->rest_ids.end(), (uint32_t)w_lo);
     const auto last = std::lower_bound(first, plan->rest_ids.end(), (uint32_t)w_hi);
     la.recs = tb.rest_recs;
     la.ids = tb.rest_ids;
     la.c_lo = (uint32_t)(first - plan->rest_ids.begin());
-    la.n_chunks = (uint32_t)(last - first);
+    la.n_pieces = (uint32_t)(last - first);
   }
-  la.xcd_span = ds_cfg_variant() == 3 ? 0 : (la.n_chunks + 7) / 8;
+  la.xcd_span = 0;  // launch_pieces makes pieces of the chunks and orders them
   // ... and the one or two chunks cut by the ends of the range, clipped by the general path
   MoveArgs ma;
   ma.tiles = tb.tiles;
@@ -1238,25 +1415,24 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
     if (c_last >= w_hi) ma.extra[ma.n_extra++] = (uint32_t)c_last;
   }
   const uint64_t variant = ds_cfg_variant();
+  const bool few = variant == 5 || grid_limit;
+  const bool mostly_general = plan->n_general * 2 > n_total && variant != 5 && !tb.perms;
   if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
-    return pack ? launch_move<true, true, true, true, 4, true>(lg, la, ma, grid_limit, stream)
-                : launch_move<false, true, true, false, 4, true>(lg, la, ma, grid_limit, stream);
-  if (variant == 1) {  // plain loads and stores
-    return pack ? launch_move<true, false, false, false>(lg, la, ma, grid_limit, stream)
-                : launch_move<false, false, false, false>(lg, la, ma, grid_limit, stream);
-  }
-  if (variant == 2) {  // non-temporal global loads and stores everywhere (no buffer stores)
-    return pack ? launch_move<true, true, true, false>(lg, la, ma, grid_limit, stream)
-                : launch_move<false, true, true, false>(lg, la, ma, grid_limit, stream);
-  }
-  // default: non-temporal accesses, and the lean gather writes the image with "sc0 sc1 nt" buffer stores;
-  // as many wavefronts per SIMD as the registers allow, up to six, instead of four where most of the plan's
-  // chunks take the general path
-  if (plan->n_general * 2 > n_total && variant != 5)
-    return pack ? launch_move<true, true, true, true, 6>(lg, la, ma, grid_limit, stream)
-                : launch_move<false, true, true, false, 6>(lg, la, ma, grid_limit, stream);
-  return pack ? launch_move<true, true, true, true>(lg, la, ma, grid_limit, stream)
-              : launch_move<false, true, true, false>(lg, la, ma, grid_limit, stream);
+    return pack ? launch_gather<true, true, true, 4, true>(la, ma, grid_limit, stream)
+                : launch_scatter<true, true, true>(few, mostly_general, la, ma, grid_limit, stream);
+  if (variant == 1)  // plain loads and stores
+    return pack ? launch_gather<false, false, false>(la, ma, grid_limit, stream)
+                : launch_scatter<false, false>(few, mostly_general, la, ma, grid_limit, stream);
+  if (variant == 2)  // non-temporal global loads and stores everywhere (no buffer stores)
+    return pack ? launch_gather<true, true, false>(la, ma, grid_limit, stream)
+                : launch_scatter<true, true>(few, mostly_general, la, ma, grid_limit, stream);
+  // default: non-temporal accesses, and the lean gather writes the image with "sc0 sc1 nt" buffer stores
+  if (mostly_general && plan->all_contiguous && !grid_limit)
+    return pack ? launch_gather<true, true, true, 8, false, false>(la, ma, grid_limit, stream)
+                : launch_scatter<true, true, false, false>(few, mostly_general, la, ma, grid_limit, stream);
+  if (!pack) return launch_scatter<true, true>(few, mostly_general, la, ma, grid_limit, stream);
+  if (mostly_general) return launch_gather<true, true, true, 6>(la, ma, grid_limit, stream);
+  return launch_gather<true, true, true>(la, ma, grid_limit, stream);
 }
 
 int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *img, uint64_t img_lo, uint64_t img_hi,

@@ -452,6 +452,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
             p->first_tile[c] = (uint32_t)t;
           }
           p->first_tile[n_chunks] = (uint32_t)p->tiles.size();
+          p->all_contiguous = p->n_strided == 0;
           // classify every chunk for the kernel's lean path
           p->recs.resize(n_chunks);
           for (uint64_t c = 0; c < n_chunks; ++c) {
@@ -494,6 +495,10 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
               if (p->tile_off[t1] >= c_end) --t1;  // that tile starts where this chunk ends
               r.col0 = t1 - ti;
               ++p->n_general;
+              bool multi = r.kind == DS_CHUNK_GENERAL && r.col0 < kMultiTiles;
+              for (uint32_t t2 = ti; multi && t2 <= t1; ++t2) multi = p->tiles[t2].n_outer == 0;
+              if (multi) r.kind = DS_CHUNK_MULTI;
+              else p->all_contiguous = false;
             }
             if (!p->perms.empty() && r.kind != DS_CHUNK_PERM) {
               p->rest_ids.push_back((uint32_t)c);
