@@ -117,6 +117,13 @@ struct ds_plan {
   std::vector<DsChunkRec> rest_recs;       // ... and their records, so that a launch has no empty work items
   uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
+  // The tables the kernels read, laid out one behind the other at these offsets (multiples of 128); the tables of
+  // views moved in blocks come last.  `blob` is that layout on the host where it (or the part before the block
+  // tables) fits the static table memory of ds_pack_noalloc: one copy then takes it to the device.
+  struct Layout {
+    size_t hot = 0, first_tile = 0, recs = 0, perms = 0, perm_items = 0, rest_ids = 0, rest_recs = 0, total = 0;
+  } at;
+  std::vector<uint8_t> blob;
   // device copies (one allocation)
   int device = -1;
   void *dev_blob = nullptr;

@@ -145,46 +145,65 @@ DsTile make_tile(const ds_shard_desc &d, uint64_t nbytes) {
   return t;
 }
 
+// Calls put(offset, data, bytes) for every table of the plan; the block tables only if `blocks`.
+template <typename Put>
+int each_table(const ds_plan *p, bool blocks, Put put) {
+  const auto one = [&](size_t offset, const auto &table) {
+    return table.empty() ? DS_OK : put(offset, table.data(), table.size() * sizeof(table[0]));
+  };
+  int rc = one(0, p->tiles);
+  if (rc == DS_OK) rc = one(p->at.hot, p->hot);
+  if (rc == DS_OK) rc = one(p->at.first_tile, p->first_tile);
+  if (rc == DS_OK) rc = one(p->at.recs, p->recs);
+  if (!blocks) return rc;
+  if (rc == DS_OK) rc = one(p->at.perms, p->perms);
+  if (rc == DS_OK) rc = one(p->at.perm_items, p->perm_items);
+  if (rc == DS_OK) rc = one(p->at.rest_ids, p->rest_ids);
+  if (rc == DS_OK) rc = one(p->at.rest_recs, p->rest_recs);
+  return rc;
+}
+
+void lay_out(ds_plan *p) {
+  ds_plan::Layout &at = p->at;
+  at.hot = p->tiles.size() * sizeof(DsTile);
+  at.first_tile = at.hot + round_up(p->hot.size() * sizeof(DsTileHot), 128);
+  at.recs = at.first_tile + round_up(p->first_tile.size() * sizeof(uint32_t), 128);
+  at.perms = at.recs + round_up(p->recs.size() * sizeof(DsChunkRec), 128);
+  at.perm_items = at.perms + round_up(p->perms.size() * sizeof(DsPerm), 128);
+  at.rest_ids = at.perm_items + round_up(p->perm_items.size() * sizeof(DsPermItem), 128);
+  at.rest_recs = at.rest_ids + round_up(p->rest_ids.size() * sizeof(uint32_t), 128);
+  at.total = at.rest_recs + round_up(p->rest_recs.size() * sizeof(DsChunkRec), 128);
+  if (at.perms > DS_PACK_NOALLOC_TABLE_BYTES) return;
+  const bool blocks = at.total <= DS_PACK_NOALLOC_TABLE_BYTES;
+  p->blob.resize(blocks ? at.total : at.perms);
+  (void)each_table(p, blocks, [p](size_t offset, const void *data, size_t bytes) {
+    std::memcpy(p->blob.data() + offset, data, bytes);
+    return DS_OK;
+  });
+}
+
 int upload(ds_plan *p) {
   DS_HIP_TRY(hipGetDevice(&p->device));
-  const size_t b_tiles = p->tiles.size() * sizeof(DsTile);
-  const size_t b_hot = round_up(p->hot.size() * sizeof(DsTileHot), 128);
-  const size_t b_first = round_up(p->first_tile.size() * sizeof(uint32_t), 128);
-  const size_t b_recs = round_up(p->recs.size() * sizeof(DsChunkRec), 128);
-  const size_t b_perms = round_up(p->perms.size() * sizeof(DsPerm), 128);
-  const size_t b_items = round_up(p->perm_items.size() * sizeof(DsPermItem), 128);
-  const size_t b_ids = round_up(p->rest_ids.size() * sizeof(uint32_t), 128);
-  const size_t b_rest = p->rest_recs.size() * sizeof(DsChunkRec);
-  const size_t total = std::max<size_t>(b_tiles + b_hot + b_first + b_recs + b_perms + b_items + b_ids + b_rest, 128);
-  DS_HIP_TRY(hipMalloc(&p->dev_blob, total));
+  DS_HIP_TRY(hipMalloc(&p->dev_blob, std::max<size_t>(p->at.total, 128)));
   uint8_t *base = (uint8_t *)p->dev_blob;
   p->d_tiles = (const DsTile *)base;
-  p->d_hot = (const DsTileHot *)(base + b_tiles);
-  p->d_first_tile = (const uint32_t *)(base + b_tiles + b_hot);
-  if (b_tiles) DS_HIP_TRY(hipMemcpy(base, p->tiles.data(), b_tiles, hipMemcpyHostToDevice));
-  DS_HIP_TRY(hipMemcpy(base + b_tiles, p->hot.data(), p->hot.size() * sizeof(DsTileHot), hipMemcpyHostToDevice));
-  DS_HIP_TRY(hipMemcpy(base + b_tiles + b_hot, p->first_tile.data(), p->first_tile.size() * sizeof(uint32_t),
-                       hipMemcpyHostToDevice));
-  p->d_recs = (const DsChunkRec *)(base + b_tiles + b_hot + b_first);
-  if (!p->recs.empty())
-    DS_HIP_TRY(hipMemcpy(base + b_tiles + b_hot + b_first, p->recs.data(), p->recs.size() * sizeof(DsChunkRec),
-                         hipMemcpyHostToDevice));
+  p->d_hot = (const DsTileHot *)(base + p->at.hot);
+  p->d_first_tile = (const uint32_t *)(base + p->at.first_tile);
+  p->d_recs = (const DsChunkRec *)(base + p->at.recs);
   if (!p->perms.empty()) {
-    uint8_t *at = base + b_tiles + b_hot + b_first + b_recs;
-    p->d_perms = (const DsPerm *)at;
-    p->d_perm_items = (const DsPermItem *)(at + b_perms);
-    DS_HIP_TRY(hipMemcpy(at, p->perms.data(), p->perms.size() * sizeof(DsPerm), hipMemcpyHostToDevice));
-    DS_HIP_TRY(hipMemcpy(at + b_perms, p->perm_items.data(), p->perm_items.size() * sizeof(DsPermItem),
-                         hipMemcpyHostToDevice));
-    if (!p->rest_ids.empty()) {
-      p->d_rest_ids = (const uint32_t *)(at + b_perms + b_items);
-      p->d_rest_recs = (const DsChunkRec *)(at + b_perms + b_items + b_ids);
-      DS_HIP_TRY(hipMemcpy(at + b_perms + b_items, p->rest_ids.data(), p->rest_ids.size() * sizeof(uint32_t),
-                           hipMemcpyHostToDevice));
-      DS_HIP_TRY(hipMemcpy(at + b_perms + b_items + b_ids, p->rest_recs.data(), b_rest, hipMemcpyHostToDevice));
-    }
+    p->d_perms = (const DsPerm *)(base + p->at.perms);
+    p->d_perm_items = (const DsPermItem *)(base + p->at.perm_items);
+    p->d_rest_ids = (const uint32_t *)(base + p->at.rest_ids);
+    p->d_rest_recs = (const DsChunkRec *)(base + p->at.rest_recs);
   }
-  return DS_OK;
+  if (p->blob.size() == p->at.total && p->at.total) {
+    DS_HIP_TRY(hipMemcpy(base, p->blob.data(), p->blob.size(), hipMemcpyHostToDevice));
+    return DS_OK;
+  }
+  return each_table(p, true, [base](size_t offset, const void *data, size_t bytes) {
+    DS_HIP_TRY(hipMemcpy(base + offset, data, bytes, hipMemcpyHostToDevice));
+    return DS_OK;
+  });
 }
 
 }  // namespace
@@ -508,6 +527,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
         }
       }
     }
+    if (rc == DS_OK) lay_out(p);
   } catch (const std::bad_alloc &) {
     rc = DS_ENOMEM;
   }
