@@ -1079,6 +1079,7 @@ __global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
 int launch_perm(bool pack, const PermArgs &a, uint32_t grid_limit, hipStream_t stream) {
   uint32_t grid = a.xcd_span ? a.xcd_span * 8 : a.n_items;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
+  if (grid > kMaxGrid) grid = kMaxGrid;
   if (pack) hipLaunchKernelGGL(ds_perm_kernel<true>, dim3(grid), dim3(256), 0, stream, a);
   else hipLaunchKernelGGL(ds_perm_kernel<false>, dim3(grid), dim3(256), 0, stream, a);
   DS_HIP_TRY(hipGetLastError());
