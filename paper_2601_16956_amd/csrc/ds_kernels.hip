@@ -1516,15 +1516,17 @@ extern "C" int ds_pack_noalloc(const ds_plan *plan, void *dst_dev, uint64_t img_
   // Copy and kernel on the caller's stream: they run behind whatever that stream still has to do with the
   // array (an earlier call's kernel).  Every entry the kernel reads is written here first, so nothing of an
   // earlier call's tables, which stay in the array, needs clearing.  The host tables belong to the plan, which
-  // the caller keeps until the work has run.  One copy: each is a launch of the runtime's copy kernel (two layers
+  // the caller keeps until the work has run.  One copy where the plan holds them so: each is a launch of the runtime's copy kernel (two layers
   // of a small model, 3 MB: 19.0 us with a copy for each of the four tables, 9.4 us with one).
   hipStream_t st = (hipStream_t)stream;
-  DS_HIP_TRY(hipMemcpyAsync(base, plan->blob.data(), plan->blob.size(), hipMemcpyHostToDevice, st));
+  // the block tables where they fit behind the others; where they do not, the general path takes those views
+  const bool blocks = plan->at.total <= kScratchBytes;
+  const int copied = ds_copy_tables(plan, blocks, base, st);
+  if (copied != DS_OK) return copied;
   DeviceTables tb = {(const DsTile *)base, (const DsTileHot *)(base + plan->at.hot),
                      (const uint32_t *)(base + plan->at.first_tile), (const DsChunkRec *)(base + plan->at.recs),
                      nullptr, nullptr, nullptr, nullptr};
-  if (!plan->perms.empty() && plan->blob.size() == plan->at.total) {
-    // the block tables came along; where they do not fit, the general path takes those views
+  if (!plan->perms.empty() && blocks) {
     tb.perms = (const DsPerm *)(base + plan->at.perms);
     tb.perm_items = (const DsPermItem *)(base + plan->at.perm_items);
     tb.rest_ids = (const uint32_t *)(base + plan->at.rest_ids);

@@ -163,7 +163,7 @@ int each_table(const ds_plan *p, bool blocks, Put put) {
   return rc;
 }
 
-void lay_out(ds_plan *p) {
+void lay_out(ds_plan *p, bool host_only) {
   ds_plan::Layout &at = p->at;
   at.hot = p->tiles.size() * sizeof(DsTile);
   at.first_tile = at.hot + round_up(p->hot.size() * sizeof(DsTileHot), 128);
@@ -175,6 +175,7 @@ void lay_out(ds_plan *p) {
   at.total = at.rest_recs + round_up(p->rest_recs.size() * sizeof(DsChunkRec), 128);
   if (at.perms > DS_PACK_NOALLOC_TABLE_BYTES) return;
   const bool blocks = at.total <= DS_PACK_NOALLOC_TABLE_BYTES;
+  if (!host_only && at.total > (256u << 10)) return;
   p->blob.resize(blocks ? at.total : at.perms);
   (void)each_table(p, blocks, [p](size_t offset, const void *data, size_t bytes) {
     std::memcpy(p->blob.data() + offset, data, bytes);
@@ -207,6 +208,18 @@ int upload(ds_plan *p) {
 }
 
 }  // namespace
+
+int ds_copy_tables(const ds_plan *plan, bool blocks, uint8_t *dst_dev, hipStream_t stream) {
+  const size_t bytes = blocks ? plan->at.total : plan->at.perms;
+  if (plan->blob.size() >= bytes && bytes) {
+    DS_HIP_TRY(hipMemcpyAsync(dst_dev, plan->blob.data(), bytes, hipMemcpyHostToDevice, stream));
+    return DS_OK;
+  }
+  return each_table(plan, blocks, [dst_dev, stream](size_t offset, const void *data, size_t n) {
+    DS_HIP_TRY(hipMemcpyAsync(dst_dev + offset, data, n, hipMemcpyHostToDevice, stream));
+    return DS_OK;
+  });
+}
 
 void ds_set_hip_error(hipError_t e) { g_last_hip_error = (int)e; }
 uint64_t ds_cfg_chunk_bytes() { return g_chunk_bytes.load(); }
@@ -527,7 +540,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
         }
       }
     }
-    if (rc == DS_OK) lay_out(p);
+    if (rc == DS_OK) lay_out(p, flags & DS_PLAN_HOST_ONLY);
   } catch (const std::bad_alloc &) {
     rc = DS_ENOMEM;
   }
