@@ -182,7 +182,8 @@ DS_PERM_FN void ds_perm_put(uint8_t *lds, uint32_t at, E v) {
 // Walk along a, the usual block: ds_perm_full_a<E>() steps along a, one granule per run.  Neighbouring threads take
 // neighbours along a, V granules of type E each as one access of type W (V > 1: dense along a, whole groups of V);
 // a thread goes down b at a fixed step, so that its places in LDS are its first one plus constants.  LDS rows have
-// room for whole batches: columns beyond the block are loaded from its last one and never used.
+// room for whole batches: columns beyond the block are loaded from its last one and never used (the plan takes this
+// walk only where a whole batch of columns lies at 32-bit offsets).
 template <typename E, typename W, bool PACK>
 DS_PERM_FN void ds_perm_full(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   constexpr uint32_t S = (uint32_t)sizeof(E), V = (uint32_t)(sizeof(W) / sizeof(E));
@@ -457,6 +458,9 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   // next unit (up to 15 bytes and a run more), and whole 16-byte units to its end.
   const uint32_t word = g == 8 ? 8 : 4;
   bool full = along_a && !flat && run == g && ta == ds_perm_full_a(g);
+  // ds_perm_full steps through whole batches of columns and pulls what lies beyond the block back to its last one:
+  // all of them, in the block or not, must be at 32-bit offsets
+  if (full && (d->sa >= (1ull << 31) / ta || d->sb >= (1ull << 31) / ds_perm_full_b(g))) full = false;
   for (;;) {
     uint32_t cols = tb + (uint32_t)((14 + run) / run);
     if (((image_bits | tb * run) & 15) == 0 || tb == d->eb) cols = tb;
@@ -471,7 +475,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   }
   // inside a block, positions on either side are 32-bit
   while (ta > 1 && (ta * d->da >= (1ull << 31) || ta * d->sa >= (1ull << 31))) ta /= 2, full = false;
-  while (tb > 1 && (uint64_t)(tb + 16) * d->sb >= (1ull << 31)) tb /= 2;
+  while (tb > 1 && (uint64_t)(tb + 16) * d->sb >= (1ull << 31)) tb /= 2, full = false;
   if ((uint64_t)(tb + 16) * d->sb >= (1ull << 31) || d->da >= (1ull << 31)) return 0;
   if (flat && tb != d->eb) return 0;
   if ((uint64_t)(ta < d->ea ? ta : d->ea) * tb * run < kPermMinBytes) return 0;

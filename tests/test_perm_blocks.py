@@ -1,6 +1,7 @@
 """The block route for views with runs shorter than 16 bytes (csrc/ds_perm.h): on the CPU thread by thread with
 every access counted, and on the GPU against the oracle."""
 import ctypes
+import mmap
 import os
 import subprocess
 
@@ -110,6 +111,40 @@ def test_blocks_move_exactly_the_view(host, k):
     rng = np.random.default_rng(k)
     for shift, at in ((0, 0), (1, 16), (3, 4096)):
         assert _check(host, dtype, shape, strides, shift, at, rng) > 0
+
+
+@pytest.mark.parametrize("dtype,shape,strides", [
+    ("bf16", (64, 64), (1, 20000001)), ("bf16", (64, 104), (1, 20000001)), ("u8", (128, 32), (1, 50000001)),
+    ("f32", (64, 20), (1, 18000001)), ("i64", (32, 50), (1, 9000001))])
+def test_columns_far_apart(host, dtype, shape, strides):
+    """Columns so far apart that 32 bits do not hold the distance over the columns of a usual block: nothing but the
+    view is read or written (memory of which only the view's pages exist)."""
+    es = DTYPES[dtype][1]
+    extent, stride, run = _normal(dtype, shape, strides)
+    nbytes, span = int(np.prod(shape)) * es, ((shape[0] - 1) * strides[0] + (shape[1] - 1) * strides[1] + 1) * es
+    idx = np.arange(shape[0]).reshape(-1, 1) * strides[0] + np.arange(shape[1]) * strides[1]
+    byte = (idx.reshape(-1, 1) * es + np.arange(es)).reshape(-1)
+    flags = mmap.MAP_PRIVATE | mmap.MAP_ANONYMOUS | getattr(mmap, "MAP_NORESERVE", 0x4000)
+    arena = np.frombuffer(mmap.mmap(-1, span, flags=flags), dtype=np.uint8)
+    want = np.random.default_rng(3).integers(0, 256, nbytes, dtype=np.uint8)
+    img = np.zeros(nbytes + 16, dtype=np.uint8)
+    img = img[-img.ctypes.data % 16:][:nbytes]
+    for pack in (1, 0):
+        hits = np.frombuffer(mmap.mmap(-1, span, flags=flags), dtype=np.uint8)
+        image_hits = np.zeros(nbytes, dtype=np.uint8)
+        if pack:
+            arena[byte] = want
+        else:
+            arena[byte] = 0
+            img[:] = want
+        n = host(arena.ctypes.data, span, 0, 0, nbytes, run, len(extent), (ctypes.c_uint64 * 6)(*extent),
+                 (ctypes.c_uint64 * 6)(*stride), pack, 0, nbytes, img.ctypes.data, hits.ctypes.data,
+                 image_hits.ctypes.data)
+        assert n > 0
+        assert np.array_equal(img if pack else arena[byte], want)
+        assert hits[byte].all()
+        hits[byte] = 0
+        assert hits.max() == 0, "an access outside the view"
 
 
 def test_random_permuted_views(host):
