@@ -116,6 +116,7 @@ struct ds_plan {
   std::vector<uint32_t> rest_ids;          // if there are such views: the chunks that are not of kind DS_CHUNK_PERM ...
   std::vector<DsChunkRec> rest_recs;       // ... and their records, so that a launch has no empty work items
   uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
+  uint64_t n_perm_chunks = 0;              // of these the ones of kind DS_CHUNK_PERM
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
   // The tables the kernels read, laid out one behind the other at these offsets (multiples of 128); the tables of
   // views moved in blocks come last.  `blob` is that layout on the host for tables of up to 256 KiB and for plans that
@@ -137,6 +138,11 @@ struct ds_plan {
   const uint32_t *d_rest_ids = nullptr;
   const DsChunkRec *d_rest_recs = nullptr;
   uint64_t n_chunks() const { return first_tile.empty() ? 0 : first_tile.size() - 1; }
+  // Are most chunks of a launch general?  With `blocks` the launch leaves the chunks of kind DS_CHUNK_PERM to another.
+  bool mostly_general(bool blocks) const {
+    const uint64_t left_out = blocks ? n_perm_chunks : 0;
+    return (n_general - left_out) * 2 > n_chunks() - left_out;
+  }
 };
 
 // Copies the plan's tables in their layout to dst_dev on `stream`, the block tables if `blocks`.

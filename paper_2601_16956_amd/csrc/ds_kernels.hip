@@ -999,16 +999,18 @@ inline bool scatter_in_pieces(uint64_t chunks) {
 template <bool NTL, bool NTS, bool LIST = false, bool ALL = true>
 int launch_scatter(bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit,
                    hipStream_t stream) {
-  if (la.chunk_log2 < 14 || !ALL) return launch_pieces<false, 2, NTL, NTS, false, ALL ? 6 : 8, LIST, ALL>(la, ma, grid_limit, stream);
-  if constexpr (ALL) {
-    const bool pieces = !mostly_general && scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14));
-    if (la.chunk_log2 == 15 && (few || !pieces))
-      return launch_pieces<false, 8, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream);
-    if (few || (!pieces && !mostly_general))
-      return launch_pieces<false, 4, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream);
-    if (mostly_general) return launch_pieces<false, 4, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
+  if constexpr (!ALL) {
+    return launch_pieces<false, 2, NTL, NTS, false, 8, LIST, ALL>(la, ma, grid_limit, stream);
+  } else {
+    const bool large = la.chunk_log2 == 15;
+    if (la.chunk_log2 > 13 && mostly_general)
+      return large ? launch_pieces<false, 8, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream)
+                   : launch_pieces<false, 4, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
+    if (la.chunk_log2 > 13 && (few || !scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14))))
+      return large ? launch_pieces<false, 8, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream)
+                   : launch_pieces<false, 4, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream);
+    return launch_pieces<false, 2, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
   }
-  return launch_pieces<false, 2, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
 }
 
 // ---- views with runs shorter than 16 bytes, in blocks through LDS (ds_perm.h) ---------------------------
@@ -1417,10 +1419,12 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   }
   const uint64_t variant = ds_cfg_variant();
   const bool few = variant == 5 || grid_limit;
-  const bool mostly_general = plan->n_general * 2 > n_total && variant != 5 && !tb.perms;
-  if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
-    return pack ? launch_gather<true, true, true, 4, true>(la, ma, grid_limit, stream)
-                : launch_scatter<true, true, true>(few, mostly_general, la, ma, grid_limit, stream);
+  const bool mostly_general = plan->mostly_general(tb.perms != nullptr) && variant != 5;
+  if (tb.perms) {  // (variants 1, 2 and 5 are given no block tables)
+    if (!pack) return launch_scatter<true, true, true>(few, mostly_general, la, ma, grid_limit, stream);
+    if (mostly_general) return launch_gather<true, true, true, 6, true>(la, ma, grid_limit, stream);
+    return launch_gather<true, true, true, 4, true>(la, ma, grid_limit, stream);
+  }
   if (variant == 1)  // plain loads and stores
     return pack ? launch_gather<false, false, false>(la, ma, grid_limit, stream)
                 : launch_scatter<false, false>(few, mostly_general, la, ma, grid_limit, stream);

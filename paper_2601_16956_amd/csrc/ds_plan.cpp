@@ -518,6 +518,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
                 r.tile = (uint32_t)(((step / tl.run_bytes) << 16) | (step % tl.run_bytes));
               } else if (p->hot[ti].meta & DS_HOT_PERM) {
                 r.kind = DS_CHUNK_PERM;
+                ++p->n_perm_chunks;
               }
             }
             if ((r.kind & 0xFF) >= DS_CHUNK_GENERAL) {

@@ -1,0 +1,14 @@
+// What a plan holds and which rules its launches follow, read from the library's own plan objects (csrc/ds_internal.h,
+// included unchanged) for the tests of those rules.
+#include "ds_internal.h"
+
+extern "C" void plan_facts(const ds_plan *p, uint64_t *out) {
+  const bool blocks = !p->perms.empty();
+  out[0] = p->n_chunks();
+  out[1] = p->n_general;
+  out[2] = p->n_perm_chunks;
+  out[3] = p->perms.size();
+  out[4] = p->perm_items.size();
+  out[5] = p->rest_recs.size();
+  out[6] = p->mostly_general(blocks);
+}

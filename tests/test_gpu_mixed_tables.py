@@ -1,0 +1,67 @@
+"""Tables of mostly small tensors with views among them, which the general path takes in the launch of mostly general
+chunks: row views, and views of which another launch moves the whole units.  Against the oracle, whole and in ranges."""
+import numpy as np
+import pytest
+
+from oracle import ds_oracle as orc
+from workloads.configs import DTYPES, Shard, Workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(views, rng):
+    """6000 tensors of 1 to 900 bytes, each of the views behind some of them."""
+    shards, at = [], 0
+
+    def add(name, dtype, shape, strides, gap):
+        nonlocal at
+        es = DTYPES[dtype][1]
+        at = -(-at // es) * es + gap * es
+        shards.append(Shard(name, dtype, shape, strides, at, len(shards)))
+        at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    every = 6000 // len(views)
+    for k in range(6000):
+        dtype = ("u8", "bf16", "f32", "i64")[k % 4]
+        n = max(1, int(rng.integers(1, 900)) // DTYPES[dtype][1])
+        add(f"s{k}", dtype, (n,), (1,), int(rng.integers(0, 3)))
+        if k % every == every // 2:
+            add(f"v{k}", *views[k // every], int(rng.integers(0, 3)))
+    return Workload("mixed", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+
+
+ROWS = [("u8", (40 + k, 300 + k), (450 + 3 * k, 1)) for k in range(9)]
+TRANSPOSED = [("bf16", (90 + 30 * k, 70 + 11 * k), (1, 95 + 30 * k)) for k in range(9)]
+
+
+@pytest.mark.parametrize("grid_limit", [0, 40])
+@pytest.mark.parametrize("chunk_bytes", [8192, 16384, 32768])
+@pytest.mark.parametrize("views", ["rows", "transposed"])
+def test_small_tensors_beside_views(views, chunk_bytes, grid_limit):
+    import paper_2601_16956_amd as ds
+    import gpu_util as gu
+    rng = np.random.default_rng(chunk_bytes)
+    w = _table(ROWS if views == "rows" else TRANSPOSED, rng)
+    want, offs, tab = gu.oracle_image(w)
+    old = [(key, ds.ds_config_get(key)) for key in ("chunk_bytes", "grid_limit")]
+    ds.ds_config_set("chunk_bytes", chunk_bytes)
+    ds.ds_config_set("grid_limit", grid_limit)
+    try:
+        dw = gu.DeviceWorkload(w)
+        try:
+            print(f"[case] small tensors beside {views} chunk={chunk_bytes} grid={grid_limit}", flush=True)
+            cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, dw.total // 16, 6)) + [dw.total]
+            ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+            for lo, hi in [(0, dw.total)] + ranges:
+                assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+            w.arena[:] = 0x5A
+            orc.unpack(tab, len(w.shards), want)
+            for parts in ([(0, dw.total)], ranges):
+                dw.arena.fill_(0x5A)
+                for lo, hi in parts:
+                    dw.unpack(want, lo, hi)
+                assert gu.first_mismatch(dw.arena_host(), w.arena) is None, parts
+        finally:
+            dw.close()
+    finally:
+        for key, value in old:
+            ds.ds_config_set(key, value)

@@ -1,0 +1,59 @@
+"""Which route a plan's launches take when it holds views of several kinds: the rules of csrc/ds_plan.cpp, read from
+plans made without a device."""
+import ctypes
+import os
+import subprocess
+from types import SimpleNamespace
+
+import pytest
+
+import paper_2601_16956_amd as ds
+from workloads.configs import DTYPES
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general")
+
+
+@pytest.fixture(scope="module")
+def facts(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("facts") / "plan_facts.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-fPIC", "-shared",
+                    "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c_abi", "plan_facts.cpp"), "-o", so], check=True)
+    fn = ctypes.CDLL(so).plan_facts
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+
+    def of(views, align=64):
+        shards, at = [], 4096
+        for k, (dtype, shape, strides) in enumerate(views):
+            shards.append(SimpleNamespace(dtype=dtype, shape=shape, strides=strides, byte_offset=at, tensor_id=k))
+            at += -(-(sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * DTYPES[dtype][1] // 256) * 256
+        descs = ds.make_descs(shards, 1 << 40)
+        ds.ds_layout_assign(descs, len(shards), align)
+        plan = ds.ds_plan_create(descs, len(shards), align, ds.DS_PLAN_HOST_ONLY)
+        out = (ctypes.c_uint64 * len(FACTS))()
+        fn(plan, out)
+        ds.ds_plan_destroy(plan)
+        return SimpleNamespace(**dict(zip(FACTS, [int(x) for x in out])))
+    return of
+
+
+def _small(n, nbytes=1000):
+    return [("u8", (nbytes,), (1,))] * n
+
+
+def _transposed(n, dtype="bf16"):
+    return (dtype, (n, n), (1, n))
+
+
+def test_the_launch_of_the_other_chunks_is_shaped_by_what_it_carries(facts):
+    """Tables of small tensors keep the launch of mostly general chunks beside views that another launch moves; and
+    such views do not make one of a table of large tensors."""
+    assert facts(_small(4000)).mostly_general
+    f = facts(_small(4000) + [_transposed(256)])
+    assert f.n_perms == 1 and f.n_perm_chunks >= 6 and f.mostly_general
+    f = facts([("bf16", (1 << 22,), (1,)), _transposed(4096)])
+    assert f.n_perms == 1 and f.n_general * 2 > f.n_chunks and not f.mostly_general
+    f = facts([_transposed(512)], 16384)
+    assert f.n_perm_chunks == f.n_chunks and not f.mostly_general
