@@ -113,8 +113,16 @@ struct ds_plan {
   std::vector<DsPerm> perms;               // views moved in blocks, image order
   std::vector<DsPermItem> perm_items;      // their blocks, view by view
   std::vector<uint32_t> perm_first;        // perms.size() + 1 entries: a view's first block
-  std::vector<uint32_t> rest_ids;          // if there are such views: the chunks that are not of kind DS_CHUNK_PERM ...
-  std::vector<DsChunkRec> rest_recs;       // ... and their records, so that a launch has no empty work items
+  // The other chunks and their records, so that a launch of those has no empty work items: in a plan of at most
+  // kListAlways chunks, or where at least one chunk in kListShare is of kind DS_CHUNK_PERM.  In a larger plan with fewer
+  // of them such chunks are work items that end at their record, and the list would be nearly a second copy of the table.
+  // (300 MB rank with 2.8 % such chunks: gather 102.8 to 103.2 us, with a list 102.5; a list of the 7.6 GB rank with one
+  // transposed matrix of 16 KiB: plan in 25 ms on the host, without it in 3.  In short launches the empty items count:
+  // 25 MB with 8 % of them 17.5 us, with a list 16.8.)
+  static constexpr uint64_t kListAlways = 8192, kListShare = 16;
+  bool listed = false;
+  std::vector<uint32_t> rest_ids;
+  std::vector<DsChunkRec> rest_recs;
   uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
   uint64_t n_perm_chunks = 0;              // of these the ones of kind DS_CHUNK_PERM
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run

@@ -55,6 +55,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_unaligned __attribute__((aligned(1)));
 
 constexpr int kWave = 64;
+// Beside a launch of blocks (ds_perm_kernel): the launch of the other chunks takes a list of them, or passes over the
+// few chunks the blocks cover.
+enum : int { kAlone = 0, kBeside = 1, kListed = 2 };
 constexpr uint32_t kBigUnits = 512;       // N-D views: pieces of >= 8 KiB inside a chunk leave the scan
 
 struct MoveArgs {
@@ -73,7 +76,7 @@ struct MoveArgs {
 
 struct LeanArgs {
   const DsChunkRec *recs;
-  const uint32_t *ids; // LIST launches: the chunk a record belongs to
+  const uint32_t *ids; // kListed launches: the chunk a record belongs to
   uint8_t *img;        // points at image byte img_lo
   uint64_t img_lo;
   uint32_t chunk_log2;
@@ -413,8 +416,8 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 // of a 2-D view), padding, and units cut by the end of a run of at least 16 bytes are handled in the phases;
 // only the rest (runs shorter than 16 bytes, views with several outer dimensions) goes one by one through
 // move_unit afterwards.
-// LIST: a launch of blocks moves the views marked DS_HOT_PERM.
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST, bool WHOLE>
+// BLOCKS (not kAlone): a launch of blocks moves the views marked DS_HOT_PERM.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int BLOCKS, bool WHOLE>
 __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1, GenLds *g) {
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & (kWave - 1);
@@ -445,7 +448,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
         meta = h->meta;
         const uint64_t te = h[1].img_off;  // the entry behind the last tile is a sentinel
         lo = tb > cb ? tb : cb;
-        if (LIST && (meta & DS_HOT_PERM)) {  // its whole units are moved in blocks: what is left is the cut unit and padding
+        if (BLOCKS && (meta & DS_HOT_PERM)) {  // its whole units are moved in blocks: what is left is the cut unit and padding
           const uint64_t rest = tb + (nbytes & ~(uint64_t)15);
           lo = rest > lo ? rest : lo;
         }
@@ -769,9 +772,8 @@ __device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd
 // Work item ci of a launch: moves its chunk if the chunk is lean and returns 0; for any other it moves nothing, says
 // which chunk and tiles (c, t0, t1) and returns the chunk's kind: the caller sends it down its path (one call site
 // each, so that these paths are in the kernel once).
-// LIST: the launch's records are not those of all its chunks, and `ids` names the chunk of each.  A template
-// parameter and not a test of the pointer: the test alone made a 23 MB gather 0.9 us slower.
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool LIST, bool WHOLE>
+// BLOCKS is a template parameter and not a test of `ids`: the test alone made a 23 MB gather 0.9 us slower.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int BLOCKS, bool WHOLE>
 __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, uint32_t pieces_log2, uint64_t &c_gen,
                                                uint32_t &piece, uint32_t &t0, uint32_t &t1) {
   const uint32_t tid = threadIdx.x;
@@ -788,8 +790,9 @@ __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, u
     if (!WHOLE) piece = (cm & ((1u << pieces_log2) - 1)) * (NT * UNROLL * 16);  // offset inside the chunk
     const uint32_t rec = a.c_lo + (WHOLE ? cm : cm >> pieces_log2);
     const DsChunkRec r = a.recs[rec];
-    const uint32_t c = LIST ? a.ids[rec] : rec;
+    const uint32_t c = BLOCKS == kListed ? a.ids[rec] : rec;
     const uint32_t kind = r.kind & 0xFF;  // bits 8.. hold log2(itemsize)
+    if (BLOCKS == kBeside && kind == DS_CHUNK_PERM) return 0;
     if (kind >= DS_CHUNK_GENERAL) {
       // its record names the tiles it holds: one load away from them, and in place among its neighbours
       c_gen = c;
@@ -923,7 +926,7 @@ __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, u
 // no chunk takes the general path, and multi_chunk's registers allow eight wavefronts.  24 000 tensors of 16 bytes to
 // 16 KiB (58 MB): gather 25.1 us against 29.1 through the general path, scatter 24.5 against 26.7; a plain copy of
 // as many bytes takes 22 us.
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, bool LIST, bool ALL>
+template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, bool ALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
                                                                                                      MoveArgs ma) {
   __shared__ typename std::conditional<ALL, GenLds, MultiLds>::type s_tab;
@@ -936,7 +939,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES)))
     uint32_t piece = 0, t0 = 0, t1 = 0;
     uint32_t kind = DS_CHUNK_GENERAL;
     if (wi < n_lean) {
-      kind = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST, LIST, WHOLE>(la, wi, pieces_log2, c, piece, t0, t1);
+      kind = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST, BLOCKS, WHOLE>(la, wi, pieces_log2, c, piece, t0, t1);
     } else {
       // (a piece of) a chunk cut by the range, whatever the chunk's kind: these paths clip to the range
       const uint32_t x = wi - n_lean;
@@ -949,7 +952,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES)))
       if (ma.hot[t1].img_off >= c_end) --t1;  // that tile starts where this chunk ends
     }
     if constexpr (ALL) {
-      if (kind) general_chunk<PACK, 256, WHOLE ? 4 : UNROLL, NTL, NTS, BUFST, LIST, WHOLE>(ma, c, piece, t0, t1, &s_tab);
+      if (kind) general_chunk<PACK, 256, WHOLE ? 4 : UNROLL, NTL, NTS, BUFST, BLOCKS, WHOLE>(ma, c, piece, t0, t1, &s_tab);
     } else {
       if (kind) multi_chunk<PACK, UNROLL, NTL, NTS, BUFST, WHOLE>(ma, c, piece, t0, t1, &s_tab);
     }
@@ -958,7 +961,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES)))
 
 constexpr uint32_t kMaxGrid = 1u << 23;  // work-groups of 256: a launch has less than 2^32 threads
 
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, bool LIST, bool ALL>
+template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, bool ALL>
 int launch_pieces(LeanArgs la, MoveArgs ma, uint32_t grid_limit, hipStream_t stream) {
   const uint32_t pieces_log2 = la.chunk_log2 - (12 + __builtin_ctz(UNROLL));
   la.n_pieces <<= pieces_log2;  // chunks so far
@@ -968,19 +971,19 @@ int launch_pieces(LeanArgs la, MoveArgs ma, uint32_t grid_limit, hipStream_t str
   if (!PACK && UNROLL == 2) ma.n_extra |= pieces_log2 << 8;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
   if (grid > kMaxGrid) grid = kMaxGrid;
-  hipLaunchKernelGGL((ds_move_kernel<PACK, UNROLL, NTL, NTS, BUFST, WAVES, LIST, ALL>), dim3((uint32_t)grid), dim3(256), 0,
+  hipLaunchKernelGGL((ds_move_kernel<PACK, UNROLL, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>), dim3((uint32_t)grid), dim3(256), 0,
                      stream, la, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
 
 // The gather: a chunk per work-group.  (Pieces in its kernel, though one per chunk, cost the 23 MB gather 0.3 us.)
-template <bool NTL, bool NTS, bool BUFST, int WAVES = 4, bool LIST = false, bool ALL = true>
+template <bool NTL, bool NTS, bool BUFST, int WAVES = 4, int BLOCKS = kAlone, bool ALL = true>
 int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, hipStream_t stream) {
   switch (la.chunk_log2) {
-    case 13: return launch_pieces<true, 2, NTL, NTS, BUFST, WAVES, LIST, ALL>(la, ma, grid_limit, stream);
-    case 14: return launch_pieces<true, 4, NTL, NTS, BUFST, WAVES, LIST, ALL>(la, ma, grid_limit, stream);
-    case 15: return launch_pieces<true, 8, NTL, NTS, BUFST, WAVES, LIST, ALL>(la, ma, grid_limit, stream);
+    case 13: return launch_pieces<true, 2, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>(la, ma, grid_limit, stream);
+    case 14: return launch_pieces<true, 4, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>(la, ma, grid_limit, stream);
+    case 15: return launch_pieces<true, 8, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>(la, ma, grid_limit, stream);
     default: return DS_EINVAL;
   }
 }
@@ -996,21 +999,30 @@ inline bool scatter_in_pieces(uint64_t chunks) {
   return chunks > 8 * 1024 || pieces * 21 <= whole * 20;
 }
 
-template <bool NTL, bool NTS, bool LIST = false, bool ALL = true>
+template <bool NTL, bool NTS, int BLOCKS = kAlone, bool ALL = true>
 int launch_scatter(bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit,
                    hipStream_t stream) {
   if constexpr (!ALL) {
-    return launch_pieces<false, 2, NTL, NTS, false, 8, LIST, ALL>(la, ma, grid_limit, stream);
+    return launch_pieces<false, 2, NTL, NTS, false, 8, BLOCKS, ALL>(la, ma, grid_limit, stream);
   } else {
     const bool large = la.chunk_log2 == 15;
     if (la.chunk_log2 > 13 && mostly_general)
-      return large ? launch_pieces<false, 8, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream)
-                   : launch_pieces<false, 4, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
+      return large ? launch_pieces<false, 8, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream)
+                   : launch_pieces<false, 4, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream);
     if (la.chunk_log2 > 13 && (few || !scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14))))
-      return large ? launch_pieces<false, 8, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream)
-                   : launch_pieces<false, 4, NTL, NTS, false, 4, LIST, ALL>(la, ma, grid_limit, stream);
-    return launch_pieces<false, 2, NTL, NTS, false, 6, LIST, ALL>(la, ma, grid_limit, stream);
+      return large ? launch_pieces<false, 8, NTL, NTS, false, 4, BLOCKS, ALL>(la, ma, grid_limit, stream)
+                   : launch_pieces<false, 4, NTL, NTS, false, 4, BLOCKS, ALL>(la, ma, grid_limit, stream);
+    return launch_pieces<false, 2, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream);
   }
+}
+
+// The chunks of a plan whose views with short runs another launch moves in blocks.
+template <int BLOCKS>
+int launch_beside_blocks(bool pack, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma,
+                         uint32_t grid_limit, hipStream_t stream) {
+  if (!pack) return launch_scatter<true, true, BLOCKS>(few, mostly_general, la, ma, grid_limit, stream);
+  if (mostly_general) return launch_gather<true, true, true, 6, BLOCKS>(la, ma, grid_limit, stream);
+  return launch_gather<true, true, true, 4, BLOCKS>(la, ma, grid_limit, stream);
 }
 
 // ---- views with runs shorter than 16 bytes, in blocks through LDS (ds_perm.h) ---------------------------
@@ -1364,7 +1376,7 @@ struct DeviceTables {
   const DsChunkRec *recs;
   const DsPerm *perms;             // null: no block tables, the general path takes those views
   const DsPermItem *perm_items;
-  const uint32_t *rest_ids;        // the chunks left beside them
+  const uint32_t *rest_ids;        // plan->listed: the chunks left beside them
   const DsChunkRec *rest_recs;
 };
 
@@ -1387,7 +1399,7 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   la.chunk_log2 = lg;
   la.c_lo = (uint32_t)w_lo;
   la.n_pieces = w_hi > w_lo ? (uint32_t)(w_hi - w_lo) : 0;
-  if (tb.perms && la.n_pieces) {
+  if (tb.perms && plan->listed && la.n_pieces) {
     const auto first = std::lower_bound(plan->rest_ids.begin(), plan->rest_ids.end(), (uint32_t)w_lo);
     const auto last = std::lower_bound(first, plan->rest_ids.end(), (uint32_t)w_hi);
     la.recs = tb.rest_recs;
@@ -1420,11 +1432,9 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   const uint64_t variant = ds_cfg_variant();
   const bool few = variant == 5 || grid_limit;
   const bool mostly_general = plan->mostly_general(tb.perms != nullptr) && variant != 5;
-  if (tb.perms) {  // (variants 1, 2 and 5 are given no block tables)
-    if (!pack) return launch_scatter<true, true, true>(few, mostly_general, la, ma, grid_limit, stream);
-    if (mostly_general) return launch_gather<true, true, true, 6, true>(la, ma, grid_limit, stream);
-    return launch_gather<true, true, true, 4, true>(la, ma, grid_limit, stream);
-  }
+  if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
+    return plan->listed ? launch_beside_blocks<kListed>(pack, few, mostly_general, la, ma, grid_limit, stream)
+                        : launch_beside_blocks<kBeside>(pack, few, mostly_general, la, ma, grid_limit, stream);
   if (variant == 1)  // plain loads and stores
     return pack ? launch_gather<false, false, false>(la, ma, grid_limit, stream)
                 : launch_scatter<false, false>(few, mostly_general, la, ma, grid_limit, stream);
@@ -1433,8 +1443,8 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
                 : launch_scatter<true, true>(few, mostly_general, la, ma, grid_limit, stream);
   // default: non-temporal accesses, and the lean gather writes the image with "sc0 sc1 nt" buffer stores
   if (mostly_general && plan->all_contiguous && !grid_limit)
-    return pack ? launch_gather<true, true, true, 8, false, false>(la, ma, grid_limit, stream)
-                : launch_scatter<true, true, false, false>(few, mostly_general, la, ma, grid_limit, stream);
+    return pack ? launch_gather<true, true, true, 8, kAlone, false>(la, ma, grid_limit, stream)
+                : launch_scatter<true, true, kAlone, false>(few, mostly_general, la, ma, grid_limit, stream);
   if (!pack) return launch_scatter<true, true>(few, mostly_general, la, ma, grid_limit, stream);
   if (mostly_general) return launch_gather<true, true, true, 6>(la, ma, grid_limit, stream);
   return launch_gather<true, true, true>(la, ma, grid_limit, stream);

@@ -533,10 +533,16 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
               if (multi) r.kind = DS_CHUNK_MULTI;
               else p->all_contiguous = false;
             }
-            if (!p->perms.empty() && r.kind != DS_CHUNK_PERM) {
-              p->rest_ids.push_back((uint32_t)c);
-              p->rest_recs.push_back(r);
-            }
+          }
+          p->listed = p->n_perm_chunks && (n_chunks <= ds_plan::kListAlways || p->n_perm_chunks * ds_plan::kListShare >= n_chunks);
+          if (p->listed) {
+            p->rest_ids.reserve(n_chunks - p->n_perm_chunks);
+            p->rest_recs.reserve(n_chunks - p->n_perm_chunks);
+            for (uint64_t c = 0; c < n_chunks; ++c)
+              if (p->recs[c].kind != DS_CHUNK_PERM) {
+                p->rest_ids.push_back((uint32_t)c);
+                p->rest_recs.push_back(p->recs[c]);
+              }
           }
         }
       }

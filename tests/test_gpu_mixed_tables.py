@@ -29,18 +29,33 @@ def _table(views, rng):
     return Workload("mixed", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
 
 
-ROWS = [("u8", (40 + k, 300 + k), (450 + 3 * k, 1)) for k in range(9)]
-TRANSPOSED = [("bf16", (90 + 30 * k, 70 + 11 * k), (1, 95 + 30 * k)) for k in range(9)]
+VIEWS = {"rows": [("u8", (40 + k, 300 + k), (450 + 3 * k, 1)) for k in range(9)],
+         "transposed": [("bf16", (90 + 30 * k, 70 + 11 * k), (1, 95 + 30 * k)) for k in range(9)],
+         "small transposed": [("bf16", (24 + k, 23 + k), (1, 30 + k)) for k in range(9)]}
 
 
 @pytest.mark.parametrize("grid_limit", [0, 40])
 @pytest.mark.parametrize("chunk_bytes", [8192, 16384, 32768])
-@pytest.mark.parametrize("views", ["rows", "transposed"])
+@pytest.mark.parametrize("views", VIEWS)
 def test_small_tensors_beside_views(views, chunk_bytes, grid_limit):
+    rng = np.random.default_rng(chunk_bytes)
+    _check(_table(VIEWS[views], rng), chunk_bytes, grid_limit, f"small tensors beside {views}", rng)
+
+
+@pytest.mark.parametrize("chunk_bytes", [8192, 16384])
+def test_a_large_table_with_one_transposed_view(chunk_bytes):
+    """More chunks than a plan always lists, a few of which the blocks cover."""
+    rng = np.random.default_rng(chunk_bytes)
+    n = 4097 * chunk_bytes + 48
+    shards = [Shard("a", "u8", (n,), (1,), 16, 0), Shard("t", "bf16", (301, 203), (1, 303), n + 64, 1),
+              Shard("b", "u8", (n,), (1,), n + 64 + 2 * 303 * 203, 2)]
+    _check(Workload("large", 64, 0, rng.integers(0, 256, size=2 * n + 200000, dtype=np.uint8), shards), chunk_bytes, 0,
+           "one transposed view", rng)
+
+
+def _check(w, chunk_bytes, grid_limit, what, rng):
     import paper_2601_16956_amd as ds
     import gpu_util as gu
-    rng = np.random.default_rng(chunk_bytes)
-    w = _table(ROWS if views == "rows" else TRANSPOSED, rng)
     want, offs, tab = gu.oracle_image(w)
     old = [(key, ds.ds_config_get(key)) for key in ("chunk_bytes", "grid_limit")]
     ds.ds_config_set("chunk_bytes", chunk_bytes)
@@ -48,7 +63,7 @@ def test_small_tensors_beside_views(views, chunk_bytes, grid_limit):
     try:
         dw = gu.DeviceWorkload(w)
         try:
-            print(f"[case] small tensors beside {views} chunk={chunk_bytes} grid={grid_limit}", flush=True)
+            print(f"[case] {what} chunk={chunk_bytes} grid={grid_limit}", flush=True)
             cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, dw.total // 16, 6)) + [dw.total]
             ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
             for lo, hi in [(0, dw.total)] + ranges:

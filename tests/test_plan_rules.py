@@ -57,3 +57,17 @@ def test_the_launch_of_the_other_chunks_is_shaped_by_what_it_carries(facts):
     assert f.n_perms == 1 and f.n_general * 2 > f.n_chunks and not f.mostly_general
     f = facts([_transposed(512)], 16384)
     assert f.n_perm_chunks == f.n_chunks and not f.mostly_general
+
+
+def test_the_other_chunks_are_listed_where_it_pays(facts):
+    """No second copy of a large table for the sake of one view; a compact list in small plans and where one chunk in
+    sixteen is left out."""
+    f = facts([("bf16", (1 << 22,), (1,)), _transposed(128)])
+    assert (f.n_chunks, f.n_perm_chunks, f.n_listed) == (514, 2, 512)
+    rest = [("bf16", (1 << 26,), (1,))]                         # 8192 chunks
+    f = facts(rest + [_transposed(128)])
+    assert (f.n_chunks, f.n_perm_chunks, f.n_listed) == (8194, 2, 0)
+    f = facts(rest + [("bf16", (4096, 1096), (1, 4096))])      # 548 of 8740: one in 15.9
+    assert (f.n_chunks, f.n_perm_chunks, f.n_listed) == (8740, 548, 8192)
+    f = facts(rest + [("bf16", (4096, 1088), (1, 4096))])      # 544 of 8736: one in 16.1
+    assert (f.n_chunks, f.n_perm_chunks, f.n_listed) == (8736, 544, 0)
