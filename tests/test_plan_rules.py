@@ -71,3 +71,18 @@ def test_the_other_chunks_are_listed_where_it_pays(facts):
     assert (f.n_chunks, f.n_perm_chunks, f.n_listed) == (8740, 548, 8192)
     f = facts(rest + [("bf16", (4096, 1088), (1, 4096))])      # 544 of 8736: one in 16.1
     assert (f.n_chunks, f.n_perm_chunks, f.n_listed) == (8736, 544, 0)
+
+
+def test_a_few_KiB_of_short_runs_are_not_worth_a_launch(facts):
+    """Views that could be moved in blocks stay with the general path where the other chunks hide them."""
+    def blocks(rest, *views):
+        f = facts(rest + list(views))
+        assert (f.n_perms > 0) == (f.n_blocks > 0)
+        return f.n_perms
+    long, short = [("bf16", (1600 * 8192,), (1,))], [("bf16", (1500 * 8192,), (1,))]     # 1600 and 1500 chunks
+    assert blocks(long, _transposed(24)) == 0 and blocks(short, _transposed(24)) == 1
+    assert blocks(long, _transposed(64)) == 0 and blocks(long, _transposed(65)) == 1     # 8192 and 8450 bytes
+    assert blocks(long, *[_transposed(32)] * 4) == 0 and blocks(long, *[_transposed(32)] * 5) == 5   # 2048 bytes each
+    rows = ("u8", (60, 8), (13, 1))                                                      # 480 bytes, runs of 8
+    assert blocks(short + [rows], _transposed(45)) == 0 and blocks(short + [rows], _transposed(46)) == 1
+    assert blocks([], _transposed(24)) == 1
