@@ -439,7 +439,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
     tb = (uint32_t)((16384 / ta) / run);
     if (tb == 0) tb = 1;
     if (tb > d->eb) tb = d->eb;
-    else if ((image_bits & 15) && tb * run >= 128) tb -= (uint32_t)(16 / g);
+    else if ((image_bits & 15) && tb * run >= 128) tb -= (uint32_t)((15 + run) / run);
   } else {
     tb = (uint32_t)(4096 / run);
     if (tb > d->eb) tb = d->eb;

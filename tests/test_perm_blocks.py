@@ -27,6 +27,10 @@ VIEWS = [
     ("u8", (90, 40, 5), (5, 460, 1)), ("f32", (33, 70, 2), (2, 66, 1)), ("u8", (40, 100, 1), (1, 41, 1)),
     ("bf16", (700, 2), (2, 3)), ("bf16", (64, 3, 2, 32), (1, 64, 192, 384)),
     ("bf16", (70, 8, 301), (1, 70, 560)),
+    # runs of several granules at odd addresses, in rows that are not whole units
+    ("u8", (200, 101, 8), (9, 1800, 1)), ("u8", (64, 300, 15), (15, 961, 1)), ("u8", (128, 101, 8), (8, 1025, 1)),
+    ("u8", (130, 131, 12), (13, 1701, 1)), ("bf16", (70, 107, 7), (7, 491, 1)), ("bf16", (70, 203, 3), (3, 211, 1)),
+    ("f32", (66, 203, 3), (3, 199, 1)), ("u8", (140, 301, 2), (3, 421, 1)),
 ]
 
 
