@@ -1456,15 +1456,20 @@ int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *i
   if (variant == 1 || variant == 2 || variant == 5) tb.perms = nullptr;
   const int rc = launch_chunks(plan, tb, pack, img, img_lo, img_hi, grid_limit, stream);
   if (rc != DS_OK || !tb.perms) return rc;
-  // the views that are moved in blocks and have a whole unit in the range
-  size_t v0 = 0, v1 = plan->perms.size();
-  while (v0 < v1 && plan->perms[v0].end16 <= img_lo) ++v0;
-  while (v1 > v0 && plan->perms[v1 - 1].img >= img_hi) --v1;
+  // the views that are moved in blocks and have a whole unit in the range; of the first and the last the blocks in it
+  const auto v0 = std::upper_bound(plan->perms.begin(), plan->perms.end(), img_lo,
+                                   [](uint64_t at, const DsPerm &d) { return at < d.end16; });
+  const auto v1 = std::lower_bound(v0, plan->perms.end(), img_hi, [](const DsPerm &d, uint64_t at) { return d.img < at; });
   if (v0 == v1) return DS_OK;
+  uint64_t first, last, other;
+  ds_perm_range(*v0, img_lo, img_hi, &first, &other);
+  ds_perm_range(*(v1 - 1), img_lo, img_hi, &other, &last);
+  first += plan->perm_first[v0 - plan->perms.begin()];
+  last += plan->perm_first[v1 - 1 - plan->perms.begin()];
   PermArgs a;
   a.perms = tb.perms;
-  a.items = tb.perm_items + plan->perm_first[v0];
-  a.n_items = plan->perm_first[v1] - plan->perm_first[v0];
+  a.items = tb.perm_items + first;
+  a.n_items = (uint32_t)(last - first);
   a.xcd_span = variant == 3 ? 0 : (a.n_items + 7) / 8;
   a.img = img;
   a.img_lo = img_lo;

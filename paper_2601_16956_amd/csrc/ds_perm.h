@@ -64,7 +64,7 @@ struct DsPerm {
   uint32_t lanes_log2;        // threads that share a row on the image side
   uint32_t flags;             // log2(granule) | kPermAlongA (tensor side walked along a) | kPermFlat | kPermFull (the
                               // usual block) | kPermLines (rows are whole 128-byte lines of the image)
-  uint32_t pad_[1];
+  uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
 static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
 
@@ -419,6 +419,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
       d->bimg[d->n_batch] = image_stride[j];
       image_bits |= image_stride[j];
       ++d->n_batch;
+      if (j < a) ++d->n_slower;
       batches *= extent[j];
     }
   // Rows of less than 512 bytes that are neighbours in the image are taken as one piece, unless they are whole
@@ -489,4 +490,35 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
              (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u);
   const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
   return tiles < (1u << 31) ? (uint64_t)tiles : 0;
+}
+
+// A launch takes the blocks in image order: by the dimensions slower than a, along a, by the dimensions between a and b,
+// along b.  The number of the i-th (ds_perm_block counts along a behind all other dimensions).
+static inline uint32_t ds_perm_in_image_order(const DsPerm &d, uint32_t i) {
+  if (d.n_slower == d.n_batch) return i;
+  uint32_t between = 1;
+  for (uint32_t j = d.n_slower; j < d.n_batch; ++j) between *= d.bext[j];
+  const uint32_t tb = i % d.tiles_b, x = i / d.tiles_b % between, ta = i / d.tiles_b / between % d.tiles_a;
+  const uint32_t slower = i / d.tiles_b / between / d.tiles_a;
+  return ((slower * between + x) * d.tiles_a + ta) * d.tiles_b + tb;
+}
+
+// The blocks [first, last), in that order, that can hold image bytes of [img_lo, img_hi), which holds some of the view's:
+// in a launch of a part of the image every block outside it would be a work-group that ends at once, and an image moved
+// in n parts would launch n times its blocks (1 GiB of bf16 transposed, 32768 x 16384: gather in 64 parts 7.1 ms, now
+// 0.86; whole 0.53).
+static inline void ds_perm_range(const DsPerm &d, uint64_t img_lo, uint64_t img_hi, uint64_t *first, uint64_t *last) {
+  uint64_t group = d.tiles_b;  // blocks that share their rows along a
+  for (uint32_t j = d.n_slower; j < d.n_batch; ++j) group *= d.bext[j];
+  const uint64_t lo = img_lo > d.img ? img_lo - d.img : 0, hi = (img_hi < d.end16 ? img_hi : d.end16) - 1 - d.img;
+  const uint64_t row_lo = lo / d.da, row_hi = hi / d.da;  // steps along a, counted through the dimensions slower than it
+  const uint64_t at_lo = row_lo / d.ea * d.tiles_a + row_lo % d.ea / d.ta;
+  const uint64_t at_hi = row_hi / d.ea * d.tiles_a + row_hi % d.ea / d.ta;
+  *first = at_lo * group;
+  *last = (at_hi + 1) * group;
+  if (row_lo == row_hi && group == d.tiles_b) {  // inside one row: a block's units can reach 15 bytes into the next block
+    const uint64_t bytes = (uint64_t)d.tb * d.run, from = lo - row_lo * d.da;
+    *first += (from < 15 ? 0 : from - 15) / bytes;
+    *last = at_hi * group + (hi - row_hi * d.da) / bytes + 1;
+  }
 }

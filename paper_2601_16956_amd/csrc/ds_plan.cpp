@@ -495,7 +495,8 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
           for (uint32_t t : in_blocks) p->hot[t].meta |= DS_HOT_PERM;
           if (!p->perms.empty()) p->perm_items.reserve(p->perm_first.back());
           for (uint32_t v = 0; v < p->perms.size(); ++v)
-            for (uint32_t b = 0; b < p->perm_first[v + 1] - p->perm_first[v]; ++b) p->perm_items.push_back({v, b});
+            for (uint32_t b = 0; b < p->perm_first[v + 1] - p->perm_first[v]; ++b)
+              p->perm_items.push_back({v, ds_perm_in_image_order(p->perms[v], b)});
         } else {
           p->perms.clear();
           p->perm_first.clear();

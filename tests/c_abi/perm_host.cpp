@@ -43,7 +43,10 @@ static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigne
 }
 
 // Moves image bytes [lo, hi) of one view at image offset `at`; `img` holds byte lo.  Returns the number of blocks
-// (0: not this route's), or -1 if an access was out of bounds or not aligned.
+// (0: not this route's), or -1 if an access was out of bounds or not aligned.  Runs the blocks that a launch for the
+// range would have, which perm_host_launched counts.
+static uint64_t g_launched;
+extern "C" uint64_t perm_host_launched() { return g_launched; }
 extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_t offset, uint64_t at, uint64_t nbytes,
                                uint64_t run, uint32_t n_outer, const uint64_t *extent, const uint64_t *stride, int pack,
                                uint64_t lo, uint64_t hi, unsigned char *img, unsigned char *arena_hits,
@@ -58,9 +61,13 @@ extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_
   alignas(16) static uint8_t lds[kPermLdsBytes];
   DsPerm d;
   const uint64_t n = ds_perm_make(g_arena + offset, at, nbytes, run, n_outer, extent, stride, &d);
-  for (uint64_t t = 0; t < n; ++t) {
+  uint64_t first = 0, last = n;
+  if (n) ds_perm_range(d, lo, hi, &first, &last);
+  if (last > n) ++g_bad;
+  g_launched += last - first;
+  for (uint64_t t = first; t < last; ++t) {
     DsPermBlock k;
-    if (!ds_perm_block(d, (uint32_t)t, lo, hi, pack, k)) continue;
+    if (!ds_perm_block(d, ds_perm_in_image_order(d, (uint32_t)t), lo, hi, pack, k)) continue;
     switch (d.flags & 0xFFu) {
       case 0: move_block<uint8_t, uint32_t>(d, k, pack, img, lo, lds); break;
       case 1: move_block<uint16_t, uint32_t>(d, k, pack, img, lo, lds); break;

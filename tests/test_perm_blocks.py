@@ -56,10 +56,13 @@ def host(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
                     os.path.join(ROOT, "tests", "c_abi", "perm_host.cpp"), "-o", so], check=True)
-    fn = ctypes.CDLL(so).perm_host_move
+    lib = ctypes.CDLL(so)
+    fn, launched = lib.perm_host_move, lib.perm_host_launched
     u64, vp = ctypes.c_uint64, ctypes.c_void_p
     fn.restype = ctypes.c_long
     fn.argtypes = [vp, u64, u64, u64, u64, u64, ctypes.c_uint32, vp, vp, ctypes.c_int, u64, u64, vp, vp, vp]
+    launched.restype = u64
+    fn.launched = launched
     return fn
 
 
@@ -149,6 +152,40 @@ def test_columns_far_apart(host, dtype, shape, strides):
         assert hits[byte].all()
         hits[byte] = 0
         assert hits.max() == 0, "an access outside the view"
+
+
+@pytest.mark.parametrize("dtype,shape,strides", [
+    ("bf16", (1200, 1501), (1, 1203)), ("f32", (60, 70, 3, 3), (630, 1, 210, 70)), ("u8", (700001,), (2,)),
+    ("bf16", (600, 4, 301), (1, 600, 2400)), ("f32", (300, 900), (2000, 2)), ("u8", (5, 60, 16, 100), (16, 80, 1, 4801))])
+def test_blocks_follow_the_range(host, dtype, shape, strides):
+    """An image moved in parts has few more blocks than one moved whole, and all its bytes are moved."""
+    es = DTYPES[dtype][1]
+    extent, stride, run = _normal(dtype, shape, strides)
+    nbytes = int(np.prod(shape)) * es
+    idx = sum((np.arange(e) * s).reshape([-1 if i == j else 1 for i in range(len(shape))])
+              for j, (e, s) in enumerate(zip(shape, strides)))
+    byte = (idx.reshape(-1, 1) * es + np.arange(es)).reshape(-1)
+    rng = np.random.default_rng(len(shape))
+    arena = rng.integers(0, 256, int(byte.max()) + 17, dtype=np.uint8)
+    arena = arena[-arena.ctypes.data % 16:][:int(byte.max()) + 1]
+    whole, at = nbytes & ~15, 48
+    img = np.zeros(nbytes + 64, dtype=np.uint8)
+    img = img[-img.ctypes.data % 16:]
+    ah, ih = np.zeros(arena.size, dtype=np.uint8), np.zeros(nbytes + 64, dtype=np.uint8)
+
+    def move(lo, hi):
+        before = host.launched()
+        n = host(arena.ctypes.data, arena.size, 0, at, nbytes, run, len(extent), (ctypes.c_uint64 * 6)(*extent),
+                 (ctypes.c_uint64 * 6)(*stride), 1, lo, hi, img.ctypes.data + lo - at, ah.ctypes.data, ih.ctypes.data)
+        assert n > 0
+        return n, host.launched() - before
+    n, all_of_them = move(at, at + whole)
+    assert all_of_them == n
+    img[:] = 0
+    cuts = [at] + sorted({at + 16 * int(x) for x in rng.integers(1, whole // 16, 11)}) + [at + whole]
+    total = sum(move(lo, hi)[1] for lo, hi in zip(cuts, cuts[1:]))
+    assert np.array_equal(img[:whole], arena[byte[:whole]])
+    assert total <= 3 * n, (total, n)
 
 
 def test_random_permuted_views(host):
