@@ -457,7 +457,8 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
       }
       const uint32_t n_outer = meta & 0xFFu;
       const uint32_t units = (uint32_t)((hi - lo) >> 4);
-      const bool big = NT * UNROLL >= kBigUnits && units >= kBigUnits && n_outer > 1;
+      // (of a view that is moved in blocks only padding can be large: that is what the scan's units write fastest)
+      const bool big = NT * UNROLL >= kBigUnits && units >= kBigUnits && n_outer > 1 && !(BLOCKS && (meta & DS_HOT_PERM));
       const uint64_t big_mask = __ballot(big);
       const uint32_t incl = wave_inclusive_scan(big ? 0u : units, lane);
       const uint64_t b0 = lo - tb;  // byte of the tile's own range at which its clipped range starts

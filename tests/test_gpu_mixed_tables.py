@@ -53,6 +53,15 @@ def test_a_large_table_with_one_transposed_view(chunk_bytes):
            "one transposed view", rng)
 
 
+@pytest.mark.parametrize("chunk_bytes", [8192, 16384, 32768])
+def test_much_padding_behind_views_of_several_dimensions(chunk_bytes):
+    """What is left of a view that is moved in blocks: its cut unit and more than 8 KiB of padding."""
+    rng = np.random.default_rng(chunk_bytes)
+    shards = [Shard(f"p{k}", "u8", (5 + k % 3, 65 + k, 17), (1400, 1, 80), 10000 * k + k, k) for k in range(9)]
+    _check(Workload("padded", 32768, 0, rng.integers(0, 256, size=90000, dtype=np.uint8), shards), chunk_bytes, 0,
+           "padding", rng)
+
+
 def _check(w, chunk_bytes, grid_limit, what, rng):
     import paper_2601_16956_amd as ds
     import gpu_util as gu
