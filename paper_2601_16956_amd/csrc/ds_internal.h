@@ -125,6 +125,8 @@ struct ds_plan {
   std::vector<DsChunkRec> rest_recs;
   uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
   uint64_t n_perm_chunks = 0;              // of these the ones of kind DS_CHUNK_PERM
+  uint64_t n_one_by_one = 0;               // ... and those with (parts of) views of several outer dimensions
+  uint64_t n_short_rows = 0;               // chunks of rows of at most 512 bytes
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
   // The tables the kernels read, laid out one behind the other at these offsets (multiples of 128); the tables of
   // views moved in blocks come last.  `blob` is that layout on the host for tables of up to 256 KiB and for plans that
@@ -150,6 +152,24 @@ struct ds_plan {
   bool mostly_general(bool blocks) const {
     const uint64_t left_out = blocks ? n_perm_chunks : 0;
     return (n_general - left_out) * 2 > n_chunks() - left_out;
+  }
+  // Is a scatter of `chunks` whole chunks of 16 KiB launched in pieces of 8 KiB, six wavefronts per SIMD instead of
+  // four?  Measured over tables of one kind, pieces / whole, us.  Many rounds: pieces (7B rank 490 / 504).  Fewer chunks
+  // than give each CU two work-groups: pieces (383 chunks of rows of 1000 bytes 6.2 / 7.2, one tensor 4.3 / 4.3).
+  // Between them, by what the chunks hold:
+  //   one in sixteen or more views of several outer dimensions, whose units move one by one: pieces at any size (443
+  //     chunks 7.4 / 9.3, 1082 13.0 / 15.6, 4889 33.7 / 36.2);
+  //   one in five or more rows of at most 512 bytes: whole while all chunks run at once (926 chunks 8.8 / 7.9, 700
+  //     6.7 / 6.0), and beyond that pieces where their last round is the fuller one (1405 chunks, 1.4 rounds of 1024
+  //     against 1.8 of 1536: 10.9 / 11.3);
+  //   anything else: whole up to two rounds (700 chunks of tensors of 300 KB 7.1 / 6.6, 900 of rows of 3000 bytes 9.4 /
+  //     8.0, 1200 of one tensor 8.8 / 8.3, 1800 of rows 15.2 / 14.0), then by the rounds too (2200 chunks 15.1 / 15.2,
+  //     3072 19.2 / 19.5, 2402 16.2 / 15.7).
+  bool scatter_in_pieces(uint64_t chunks) const {
+    if (chunks <= 384 || chunks > 8 * 1024 || n_one_by_one * 16 >= n_chunks()) return true;
+    if (chunks <= (n_short_rows * 5 >= n_chunks() ? 1024u : 2048u)) return false;
+    const uint64_t whole = (chunks + 1023) / 1024 * 1024, pieces = (2 * chunks + 1535) / 1536 * 768;
+    return pieces * 21 <= whole * 20;
   }
 };
 

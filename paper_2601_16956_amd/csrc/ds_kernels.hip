@@ -922,7 +922,7 @@ __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, u
 //     general path's 93 registers do not allow; one unit per thread leaves too little in flight (3.30 ms).
 //   gather of plans of mostly general chunks, WAVES 6: that path is bound by its chain of dependent loads and takes
 //     the five wavefronts its registers allow (+8 to +10 % on tables of tiny tensors against four).
-//   scatter, UNROLL 2 and WAVES 6 (a piece of 8 KiB, 48 KB in flight), or as the gather: see scatter_in_pieces.
+//   scatter, UNROLL 2 and WAVES 6 (a piece of 8 KiB, 48 KB in flight), or as the gather: see launch_scatter.
 // ALL = false is the instantiation for plans of contiguous shards only, most chunks of which hold several of them:
 // no chunk takes the general path, and multi_chunk's registers allow eight wavefronts.  24 000 tensors of 16 bytes to
 // 16 KiB (58 MB): gather 25.1 us against 29.1 through the general path, scatter 24.5 against 26.7; a plain copy of
@@ -989,19 +989,11 @@ int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, h
   }
 }
 
-// The scatter.  In a launch of many rounds pieces of 8 KiB at six wavefronts per SIMD are the faster (7B rank 0.490 ms,
-// chunks at four 0.504).  In one of a few rounds it is the last round that counts: a shape's rounds are what its
-// work-groups need of the 256 CUs x WAVES that run at once, and pieces are taken where they need less of the chip's
-// time by more than 5 % (23 MB state, 1.8 of 2 rounds against 1.4 of 2: 10.9 us instead of 11.5; 38 MB, 3.04 of 4
-// against 2.3 of 3: 16.7 instead of 16.4).  Plans of mostly general chunks keep whole chunks, whose tiles are looked
-// up once (15 MB in 711 views and tensors: 10.7 us, in pieces 11.4).
-inline bool scatter_in_pieces(uint64_t chunks) {
-  const uint64_t whole = (chunks + 1023) / 1024 * 1024, pieces = (2 * chunks + 1535) / 1536 * 768;
-  return chunks > 8 * 1024 || pieces * 21 <= whole * 20;
-}
-
+// The scatter, in whole chunks at four wavefronts per SIMD or in pieces of 8 KiB at six (ds_plan::scatter_in_pieces).
+// Plans of mostly general chunks keep whole chunks, whose tiles are looked up once, at six (15 MB in 711 views and
+// tensors: 10.7 us, in pieces 11.4).
 template <bool NTL, bool NTS, int BLOCKS = kAlone, bool ALL = true>
-int launch_scatter(bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit,
+int launch_scatter(const ds_plan *plan, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit,
                    hipStream_t stream) {
   if constexpr (!ALL) {
     return launch_pieces<false, 2, NTL, NTS, false, 8, BLOCKS, ALL>(la, ma, grid_limit, stream);
@@ -1010,7 +1002,7 @@ int launch_scatter(bool few, bool mostly_general, const LeanArgs &la, const Move
     if (la.chunk_log2 > 13 && mostly_general)
       return large ? launch_pieces<false, 8, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream)
                    : launch_pieces<false, 4, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream);
-    if (la.chunk_log2 > 13 && (few || !scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14))))
+    if (la.chunk_log2 > 13 && (few || !plan->scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14))))
       return large ? launch_pieces<false, 8, NTL, NTS, false, 4, BLOCKS, ALL>(la, ma, grid_limit, stream)
                    : launch_pieces<false, 4, NTL, NTS, false, 4, BLOCKS, ALL>(la, ma, grid_limit, stream);
     return launch_pieces<false, 2, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream);
@@ -1019,9 +1011,9 @@ int launch_scatter(bool few, bool mostly_general, const LeanArgs &la, const Move
 
 // The chunks of a plan whose views with short runs another launch moves in blocks.
 template <int BLOCKS>
-int launch_beside_blocks(bool pack, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma,
-                         uint32_t grid_limit, hipStream_t stream) {
-  if (!pack) return launch_scatter<true, true, BLOCKS>(few, mostly_general, la, ma, grid_limit, stream);
+int launch_beside_blocks(const ds_plan *plan, bool pack, bool few, bool mostly_general, const LeanArgs &la,
+                         const MoveArgs &ma, uint32_t grid_limit, hipStream_t stream) {
+  if (!pack) return launch_scatter<true, true, BLOCKS>(plan, few, mostly_general, la, ma, grid_limit, stream);
   if (mostly_general) return launch_gather<true, true, true, 6, BLOCKS>(la, ma, grid_limit, stream);
   return launch_gather<true, true, true, 4, BLOCKS>(la, ma, grid_limit, stream);
 }
@@ -1434,19 +1426,19 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   const bool few = variant == 5 || grid_limit;
   const bool mostly_general = plan->mostly_general(tb.perms != nullptr) && variant != 5;
   if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
-    return plan->listed ? launch_beside_blocks<kListed>(pack, few, mostly_general, la, ma, grid_limit, stream)
-                        : launch_beside_blocks<kBeside>(pack, few, mostly_general, la, ma, grid_limit, stream);
+    return plan->listed ? launch_beside_blocks<kListed>(plan, pack, few, mostly_general, la, ma, grid_limit, stream)
+                        : launch_beside_blocks<kBeside>(plan, pack, few, mostly_general, la, ma, grid_limit, stream);
   if (variant == 1)  // plain loads and stores
     return pack ? launch_gather<false, false, false>(la, ma, grid_limit, stream)
-                : launch_scatter<false, false>(few, mostly_general, la, ma, grid_limit, stream);
+                : launch_scatter<false, false>(plan, few, mostly_general, la, ma, grid_limit, stream);
   if (variant == 2)  // non-temporal global loads and stores everywhere (no buffer stores)
     return pack ? launch_gather<true, true, false>(la, ma, grid_limit, stream)
-                : launch_scatter<true, true>(few, mostly_general, la, ma, grid_limit, stream);
+                : launch_scatter<true, true>(plan, few, mostly_general, la, ma, grid_limit, stream);
   // default: non-temporal accesses, and the lean gather writes the image with "sc0 sc1 nt" buffer stores
   if (mostly_general && plan->all_contiguous && !grid_limit)
     return pack ? launch_gather<true, true, true, 8, kAlone, false>(la, ma, grid_limit, stream)
-                : launch_scatter<true, true, kAlone, false>(few, mostly_general, la, ma, grid_limit, stream);
-  if (!pack) return launch_scatter<true, true>(few, mostly_general, la, ma, grid_limit, stream);
+                : launch_scatter<true, true, kAlone, false>(plan, few, mostly_general, la, ma, grid_limit, stream);
+  if (!pack) return launch_scatter<true, true>(plan, few, mostly_general, la, ma, grid_limit, stream);
   if (mostly_general) return launch_gather<true, true, true, 6>(la, ma, grid_limit, stream);
   return launch_gather<true, true, true>(la, ma, grid_limit, stream);
 }

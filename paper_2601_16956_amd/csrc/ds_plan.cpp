@@ -539,6 +539,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
                 r.pitch = tl.stride[0];
                 r.col0 = (uint32_t)(b0 - row0 * tl.run_bytes);
                 r.run = (uint32_t)tl.run_bytes;
+                if (r.run <= 512) ++p->n_short_rows;
                 // a thread's units are 256 threads x 16 bytes apart: that step, divided by the run
                 // length once here instead of once per unit in the kernel
                 const uint64_t step = 4096;
@@ -557,8 +558,15 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
               ++p->n_general;
               bool multi = r.kind == DS_CHUNK_GENERAL && r.col0 < kMultiTiles;
               for (uint32_t t2 = ti; multi && t2 <= t1; ++t2) multi = p->tiles[t2].n_outer == 0;
-              if (multi) r.kind = DS_CHUNK_MULTI;
-              else p->all_contiguous = false;
+              if (multi) {
+                r.kind = DS_CHUNK_MULTI;
+              } else {
+                p->all_contiguous = false;
+                bool one_by_one = false;
+                for (uint32_t t2 = ti; r.kind == DS_CHUNK_GENERAL && t2 <= t1 && !one_by_one; ++t2)
+                  one_by_one = (p->hot[t2].meta & 0xFF) > 1 && !(p->hot[t2].meta & DS_HOT_PERM);
+                p->n_one_by_one += one_by_one;
+              }
             }
           }
           p->listed = p->n_perm_chunks && (n_chunks <= ds_plan::kListAlways || p->n_perm_chunks * ds_plan::kListShare >= n_chunks);

@@ -11,4 +11,5 @@ extern "C" void plan_facts(const ds_plan *p, uint64_t *out) {
   out[4] = p->perm_items.size();
   out[5] = p->rest_recs.size();
   out[6] = p->mostly_general(blocks);
+  out[7] = p->scatter_in_pieces(p->n_chunks());
 }

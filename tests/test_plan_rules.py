@@ -11,7 +11,8 @@ import paper_2601_16956_amd as ds
 from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general")
+FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
+         "in_pieces")
 
 
 @pytest.fixture(scope="module")
@@ -86,3 +87,19 @@ def test_a_few_KiB_of_short_runs_are_not_worth_a_launch(facts):
     rows = ("u8", (60, 8), (13, 1))                                                      # 480 bytes, runs of 8
     assert blocks(short + [rows], _transposed(45)) == 0 and blocks(short + [rows], _transposed(46)) == 1
     assert blocks([], _transposed(24)) == 1
+
+
+@pytest.mark.parametrize("kind,pieces", [
+    ("tensor", {100: 1, 384: 1, 450: 0, 700: 0, 1000: 0, 1200: 0, 1536: 0, 1800: 0, 2200: 1, 2500: 0, 3200: 1, 9000: 1}),
+    ("rows of 3000", {380: 1, 700: 0, 900: 0, 1100: 0, 1400: 0, 1800: 0, 2200: 1, 9000: 1}),
+    ("rows of 256", {380: 1, 700: 0, 900: 0, 1100: 1, 1400: 1, 1800: 0, 2200: 1}),
+    ("several dimensions", {380: 1, 450: 1, 700: 1, 1000: 1, 1700: 1, 2500: 1})])
+def test_which_scatters_are_cut_into_pieces(facts, kind, pieces):
+    """The table of sizes at which one work-group per 8 KiB measured faster than one per 16 KiB, by what is in the
+    chunks.  450 to 768 and 1025 to 1536 chunks of one tensor or of long rows were cut, and 2 to 16 % slower for it."""
+    for chunks, want in pieces.items():
+        n = chunks * 16384
+        view = {"tensor": ("u8", (n,), (1,)), "rows of 3000": ("u8", (n // 3000, 3000), (4000, 1)),
+                "rows of 256": ("u8", (n // 256, 256), (512, 1)),
+                "several dimensions": ("u8", (n // 1280, 5, 256), (2600, 512, 1))}[kind]
+        assert facts([view]).in_pieces == want, chunks
