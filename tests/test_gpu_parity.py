@@ -653,9 +653,10 @@ def test_contiguous_tensors_at_every_byte_alignment():
 
 
 def test_plans_of_mostly_general_chunks():
-    """A table of thousands of tiny tensors (every 16 KiB chunk holds tile boundaries): such a plan is launched
-    with five wavefronts per SIMD instead of four (variant 5 keeps four).  Both launches against the oracle,
-    gather and scatter, whole image and whole arena."""
+    """A table of thousands of tiny contiguous tensors (every 16 KiB chunk holds tile boundaries): such a plan has
+    the path without the scan; variant 5 sends it down the general path with four wavefronts per SIMD (the general
+    path with more of them: test_gpu_mixed_tables.py).  Both launches against the oracle, gather and scatter, whole
+    image and whole arena."""
     ds, orc, gu = _mods()
     rng = np.random.default_rng(555)
     arena = rng.integers(0, 256, size=48 << 20, dtype=np.uint8)

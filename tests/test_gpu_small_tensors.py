@@ -37,6 +37,7 @@ def test_small_contiguous_tensors(chunk_bytes, align, sizes, holes):
     shards, offsets, span = _table([int(x) for x in size], align, rng, holes)
     w = Workload("small", align, 0, rng.integers(0, 256, size=span + 64, dtype=np.uint8), shards)
     want, offs, tab = gu.oracle_image(w, offsets=offsets)
+    old = ds.ds_config_get("chunk_bytes")
     ds.ds_config_set("chunk_bytes", chunk_bytes)
     try:
         dw = gu.DeviceWorkload(w, offsets=offsets)
@@ -59,4 +60,4 @@ def test_small_contiguous_tensors(chunk_bytes, align, sizes, holes):
         finally:
             dw.close()
     finally:
-        ds.ds_config_set("chunk_bytes", 16384)
+        ds.ds_config_set("chunk_bytes", old)

@@ -253,3 +253,35 @@ def test_gather_and_scatter_of_permuted_views(chunk_bytes):
             dw.close()
     finally:
         ds.ds_config_set("chunk_bytes", old)
+
+
+@pytest.mark.gpu
+def test_allocation_free_gather_without_room_for_the_block_tables():
+    """Tables that fit the static array only without those of the blocks: the general path moves the views then."""
+    import paper_2601_16956_amd as ds
+    import gpu_util as gu
+    import torch
+    rng = np.random.default_rng(9)
+    shards, at = [], 0
+    for k in range(20000):
+        n = 24 if k % 5000 else 190                          # four of them hold whole chunks
+        shards.append(Shard(f"p{k}", "bf16", (n, n), (1, n + k % 3), at, k))
+        at += 2 * n * (n + 2)
+    w = Workload("many views", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print("[case] noalloc without block tables", flush=True)
+        base = 168 * dw.info["n_tiles"] + 36 * dw.info["n_chunks"] + 512
+        assert base <= 4 << 20 < base + 176 * len(shards)
+        plan = ds.ds_plan_create(dw.descs, dw.n, w.align, ds.DS_PLAN_HOST_ONLY)
+        out = torch.full((2, dw.total), 0xFF, dtype=torch.uint8, device="cuda")
+        stream = torch.cuda.current_stream().cuda_stream
+        ds.ds_pack_noalloc(plan, out[0].data_ptr(), 0, dw.total, stream)
+        ds.ds_pack_noalloc(dw.plan, out[1].data_ptr(), 0, dw.total, stream)
+        for image in out.cpu().numpy():
+            assert gu.first_mismatch(image, want) is None
+        ds.ds_plan_destroy(plan)
+        assert gu.first_mismatch(dw.pack(), want) is None
+    finally:
+        dw.close()
