@@ -237,7 +237,7 @@ int ds_unpack(const ds_plan *plan, const void *src_dev, uint64_t img_lo, uint64_
  * an image of about 1.7 GB with few shards does, DS_ETOOBIG otherwise
  * (returned before anything is enqueued).  Views with runs shorter than
  * 16 bytes are moved in blocks if the tables of those (176 bytes per such view,
- * 8 per block, 36 per other chunk) fit behind the rest, unit by unit if not.
+ * 8 per block, up to 36 per other chunk) fit behind the rest, unit by unit if not.
  * All calls on one GPU share the one array and it keeps the last call's tables:
  * calls on the same stream are ordered by it, calls that may overlap on one GPU
  * (different streams, or different threads) race and are the caller's to

@@ -13,7 +13,7 @@
 // multi_chunk, and views with runs shorter than 16 bytes are moved by a kernel of their own, ds_perm_kernel):
 //
 // lean path: one pass per chunk, a chunk being exactly threads x unroll
-//   units (16 KiB by default; the scatter cuts it into pieces of 8 KiB), so a
+//   units (16 KiB by default; the scatter may cut it into pieces of 8 KiB), so a
 //   thread issues all its loads, then all its stores, and is done.  Measured on MI355X a plain copy of this shape runs
 //   at ~6 TB/s (read+write) against ~5.3 TB/s for work-groups that stream
 //   through 64-256 KiB each: many short-lived work-groups keep the addresses
@@ -418,7 +418,8 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 // move_unit afterwards.
 // BLOCKS (not kAlone): a launch of blocks moves the views marked DS_HOT_PERM.
 template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int BLOCKS, bool WHOLE>
-__device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1, GenLds *g) {
+__device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1,
+                                              GenLds *g) {
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & (kWave - 1);
   uint64_t cb, ce;
@@ -448,7 +449,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
         meta = h->meta;
         const uint64_t te = h[1].img_off;  // the entry behind the last tile is a sentinel
         lo = tb > cb ? tb : cb;
-        if (BLOCKS && (meta & DS_HOT_PERM)) {  // its whole units are moved in blocks: what is left is the cut unit and padding
+        if (BLOCKS && (meta & DS_HOT_PERM)) {  // its whole units are moved in blocks: the cut unit and padding are left
           const uint64_t rest = tb + (nbytes & ~(uint64_t)15);
           lo = rest > lo ? rest : lo;
         }
@@ -678,7 +679,8 @@ struct MultiLds {
 constexpr uint32_t kWholeBelow16 = 1u << 31;  // the tile has less than 16 bytes: nothing to read a unit from
 
 template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, bool WHOLE>
-__device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1, MultiLds *g) {
+__device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1,
+                                            MultiLds *g) {
   const uint32_t tid = threadIdx.x;
   uint64_t cb, ce;
   if (!piece_range<WHOLE, 256 * UNROLL * 16>(a, c, piece, cb, ce)) return;
@@ -924,9 +926,9 @@ __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, u
 //     the five wavefronts its registers allow (+8 to +10 % on tables of tiny tensors against four).
 //   scatter, UNROLL 2 and WAVES 6 (a piece of 8 KiB, 48 KB in flight), or as the gather: see launch_scatter.
 // ALL = false is the instantiation for plans of contiguous shards only, most chunks of which hold several of them:
-// no chunk takes the general path, and multi_chunk's registers allow eight wavefronts.  24 000 tensors of 16 bytes to
-// 16 KiB (58 MB): gather 25.1 us against 29.1 through the general path, scatter 24.5 against 26.7; a plain copy of
-// as many bytes takes 22 us.
+// no chunk takes the general path, and multi_chunk's registers (gather 78, scatter 40) allow six and eight wavefronts.
+// 24 000 tensors of 16 bytes to 16 KiB (58 MB): gather 25.2 us against 29.1 through the general path, scatter 24.2
+// against 26.6.
 template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, bool ALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
                                                                                                      MoveArgs ma) {
@@ -993,8 +995,8 @@ int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, h
 // Plans of mostly general chunks keep whole chunks, whose tiles are looked up once, at six (15 MB in 711 views and
 // tensors: 10.7 us, in pieces 11.4).
 template <bool NTL, bool NTS, int BLOCKS = kAlone, bool ALL = true>
-int launch_scatter(const ds_plan *plan, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit,
-                   hipStream_t stream) {
+int launch_scatter(const ds_plan *plan, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma,
+                   uint32_t grid_limit, hipStream_t stream) {
   if constexpr (!ALL) {
     return launch_pieces<false, 2, NTL, NTS, false, 8, BLOCKS, ALL>(la, ma, grid_limit, stream);
   } else {
@@ -1528,8 +1530,8 @@ extern "C" int ds_pack_noalloc(const ds_plan *plan, void *dst_dev, uint64_t img_
   // Copy and kernel on the caller's stream: they run behind whatever that stream still has to do with the
   // array (an earlier call's kernel).  Every entry the kernel reads is written here first, so nothing of an
   // earlier call's tables, which stay in the array, needs clearing.  The host tables belong to the plan, which
-  // the caller keeps until the work has run.  One copy where the plan holds them so: each is a launch of the runtime's copy kernel (two layers
-  // of a small model, 3 MB: 19.0 us with a copy for each of the four tables, 9.4 us with one).
+  // the caller keeps until the work has run.  One copy where the plan holds them so: each is a launch of the runtime's
+  // copy kernel (two layers of a small model, 3 MB: 19.0 us with a copy for each of the four tables, 9.4 us with one).
   hipStream_t st = (hipStream_t)stream;
   // the block tables where they fit behind the others; where they do not, the general path takes those views
   const bool blocks = plan->at.total <= kScratchBytes;

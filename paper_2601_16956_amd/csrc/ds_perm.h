@@ -63,7 +63,8 @@ struct DsPerm {
   uint32_t pitch;             // LDS bytes between rows of the block
   uint32_t lanes_log2;        // threads that share a row on the image side
   uint32_t flags;             // log2(granule) | kPermAlongA (tensor side walked along a) | kPermFlat | kPermFull (the
-                              // usual block) | kPermLines (rows are whole 128-byte lines of the image)
+                              // usual block) | kPermLines (rows are whole 128-byte lines of the image, or the block
+                              // is one piece of it, of which only the two ends are parts of lines)
   uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
 static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
@@ -304,7 +305,8 @@ DS_PERM_FN void ds_perm_tensor_side(const DsPerm &d, const DsPermBlock &k, uint8
 // The bytes of the row a work-group writes (gather), relative to the start of the 16-byte unit that holds the
 // row's first byte.  Inside a row, blocks meet at unit boundaries, so a unit is written whole by one block;
 // only where a row starts or ends inside a unit are its two parts written by two rows.
-DS_PERM_FN void ds_perm_window(const DsPerm &d, const DsPermBlock &k, uint32_t unit, uint32_t skew, uint32_t &w0, uint32_t &w1) {
+DS_PERM_FN void ds_perm_window(const DsPerm &d, const DsPermBlock &k, uint32_t unit, uint32_t skew, uint32_t &w0,
+                               uint32_t &w1) {
   if (d.flags & kPermFlat) {
     w0 = skew;
     w1 = skew + k.na * k.da;

@@ -569,7 +569,8 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
               }
             }
           }
-          p->listed = p->n_perm_chunks && (n_chunks <= ds_plan::kListAlways || p->n_perm_chunks * ds_plan::kListShare >= n_chunks);
+          p->listed = p->n_perm_chunks && (n_chunks <= ds_plan::kListAlways ||
+                                           p->n_perm_chunks * ds_plan::kListShare >= n_chunks);
           if (p->listed) {
             p->rest_ids.reserve(n_chunks - p->n_perm_chunks);
             p->rest_recs.reserve(n_chunks - p->n_perm_chunks);
