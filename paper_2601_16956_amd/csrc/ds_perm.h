@@ -495,14 +495,16 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
 }
 
 // A launch takes the blocks in image order: by the dimensions slower than a, along a, by the dimensions between a and b,
-// along b.  The number of the i-th (ds_perm_block counts along a behind all other dimensions).
-static inline uint32_t ds_perm_in_image_order(const DsPerm &d, uint32_t i) {
-  if (d.n_slower == d.n_batch) return i;
+// along b (ds_perm_block counts along a behind all other dimensions).  Writes the items of a view of n blocks.
+static inline void ds_perm_items(const DsPerm &d, uint32_t perm, uint32_t n, DsPermItem *out) {
   uint32_t between = 1;
   for (uint32_t j = d.n_slower; j < d.n_batch; ++j) between *= d.bext[j];
-  const uint32_t tb = i % d.tiles_b, x = i / d.tiles_b % between, ta = i / d.tiles_b / between % d.tiles_a;
-  const uint32_t slower = i / d.tiles_b / between / d.tiles_a;
-  return ((slower * between + x) * d.tiles_a + ta) * d.tiles_b + tb;
+  const uint32_t n_slower = n / (between * d.tiles_a * d.tiles_b);
+  for (uint32_t slower = 0; slower < n_slower; ++slower)
+    for (uint32_t ta = 0; ta < d.tiles_a; ++ta)
+      for (uint32_t x = 0; x < between; ++x)
+        for (uint32_t tb = 0; tb < d.tiles_b; ++tb)
+          *out++ = {perm, ((slower * between + x) * d.tiles_a + ta) * d.tiles_b + tb};
 }
 
 // The blocks [first, last), in that order, that can hold image bytes of [img_lo, img_hi), which holds some of the view's:

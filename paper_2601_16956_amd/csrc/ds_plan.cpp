@@ -493,10 +493,9 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
         }
         if (blocks_are_worth_a_launch(block_bytes, n_chunks, one_by_one)) {
           for (uint32_t t : in_blocks) p->hot[t].meta |= DS_HOT_PERM;
-          if (!p->perms.empty()) p->perm_items.reserve(p->perm_first.back());
+          if (!p->perms.empty()) p->perm_items.resize(p->perm_first.back());
           for (uint32_t v = 0; v < p->perms.size(); ++v)
-            for (uint32_t b = 0; b < p->perm_first[v + 1] - p->perm_first[v]; ++b)
-              p->perm_items.push_back({v, ds_perm_in_image_order(p->perms[v], b)});
+            ds_perm_items(p->perms[v], v, p->perm_first[v + 1] - p->perm_first[v], p->perm_items.data() + p->perm_first[v]);
         } else {
           p->perms.clear();
           p->perm_first.clear();

@@ -3,6 +3,8 @@
 // exactly the bytes of the view and of the image range are read and written, and that LDS is not left.
 #include <stdint.h>
 
+#include <vector>
+
 static unsigned char *g_arena_hits, *g_image_hits;  // accesses per byte
 static uint64_t g_arena, g_arena_len, g_image, g_image_len;
 static long g_bad;
@@ -64,10 +66,12 @@ extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_
   uint64_t first = 0, last = n;
   if (n) ds_perm_range(d, lo, hi, &first, &last);
   if (last > n) ++g_bad;
+  std::vector<DsPermItem> items(n);
+  if (n) ds_perm_items(d, 0, (uint32_t)n, items.data());
   g_launched += last - first;
   for (uint64_t t = first; t < last; ++t) {
     DsPermBlock k;
-    if (!ds_perm_block(d, ds_perm_in_image_order(d, (uint32_t)t), lo, hi, pack, k)) continue;
+    if (!ds_perm_block(d, items[t].tile, lo, hi, pack, k)) continue;
     switch (d.flags & 0xFFu) {
       case 0: move_block<uint8_t, uint32_t>(d, k, pack, img, lo, lds); break;
       case 1: move_block<uint16_t, uint32_t>(d, k, pack, img, lo, lds); break;
