@@ -8,16 +8,16 @@
 // shards look like, and every work-group moves the same number of bytes
 // however fragmented its part of the image is.
 //
-// One kernel, ds_move_kernel, serves a pack (or unpack) call; a work-group takes one chunk down one of
-// two paths (plans of contiguous shards only, most of whose chunks hold several, have a simpler second one,
-// multi_chunk, and views with runs shorter than 16 bytes are moved by a kernel of their own, ds_perm_kernel):
+// One kernel serves a pack (or unpack) call; a work-group takes (a piece of) one chunk down one of two paths:
+// ds_unit_kernel, one unit per thread, in a default call; ds_move_kernel, several units per thread, in plans of
+// contiguous shards only, most of whose chunks hold several (they have a simpler second path, multi_chunk), and with
+// the options for comparison (other chunk sizes, a grid limit, the variants).  Views with runs shorter than 16 bytes
+// are moved by a kernel of their own, ds_perm_kernel.
 //
-// lean path: one pass per chunk, a chunk being exactly threads x unroll
-//   units (16 KiB by default; the scatter may cut it into pieces of 8 KiB), so a
-//   thread issues all its loads, then all its stores, and is done.  Measured on MI355X a plain copy of this shape runs
-//   at ~6 TB/s (read+write) against ~5.3 TB/s for work-groups that stream
-//   through 64-256 KiB each: many short-lived work-groups keep the addresses
-//   in flight inside a compact, moving window of HBM.  Everything the path
+// lean path: a thread issues all its loads, then all its stores, and is done.  Many short-lived work-groups keep the
+//   addresses in flight inside a compact, moving window of HBM: measured on MI355X a plain copy of one unit per thread
+//   and eight wavefronts per SIMD runs at 6.75 TB/s (read+write), of four units and four wavefronts at 6.3, and one
+//   whose work-groups stream through 64-256 KiB each at 5.3.  Everything the path
 //   needs for a chunk is one 32-byte record prepared by the plan (DsChunkRec),
 //   so the only dependent load before the data is that record.  It handles the
 //   chunks that are whole units of one tile (contiguous, or rows of a 2-D view
@@ -28,7 +28,7 @@
 //   64 at a time: the first wavefront reads one tile's compact descriptor
 //   (DsTileHot, 40 bytes) per lane, a wavefront inclusive scan over the unit
 //   counts turns the 64 tiles into one dense index space, and the threads of
-//   the work-group share that space evenly, four units each per pass, in three
+//   the work-group share that space evenly, one unit each per pass (ds_move_kernel: up to four), in three
 //   phases: (1) registers and LDS only: find the tile of each unit by binary
 //   search over the scan and classify it; (2) all loads, nothing between
 //   them; (3) all stores.  Large pieces of views with several outer dimensions
@@ -39,7 +39,7 @@
 // is one (possibly unaligned) dwordx4 access; a unit that is cut by the end of
 // a run or of the payload is assembled from 16-byte loads that lie inside the
 // runs (gather), stored in pieces that cover exactly its bytes (scatter), or,
-// for runs shorter than 16 bytes, moved element by element, so no byte outside
+// for runs shorter than 16 bytes, moved piece by piece, so no byte outside
 // the described views is ever read or written.
 
 #include <algorithm>
@@ -58,6 +58,12 @@ constexpr int kWave = 64;
 // Beside a launch of blocks (ds_perm_kernel): the launch of the other chunks takes a list of them, or passes over the
 // few chunks the blocks cover.
 enum : int { kAlone = 0, kBeside = 1, kListed = 2 };
+constexpr uint32_t kUnitPieces = 4;       // work-groups of ds_unit_kernel per chunk
+// Images of at most so many bytes are moved with ordinary loads, larger ones with non-temporal ones, which leave nothing
+// in the 256 MB last-level cache.  Copies of one unit per thread, three pairs of buffers in turn, ordinary / non-
+// temporal: 23 MB 7.4 / 8.4 us, 40 MB 11.9 / 14.5, 58 MB 16.6 / 20.6, 70 MB 19.7 / 23.2, 85 MB 27.1 / 27.7, 110 MB (nothing
+// is found again) 36.8 / 34.6, 1.5 GB 476 / 453.
+constexpr uint64_t kCachedBytes = 64ull << 20;
 constexpr uint32_t kBigUnits = 512;       // N-D views: pieces of >= 8 KiB inside a chunk leave the scan
 
 struct MoveArgs {
@@ -139,168 +145,6 @@ __device__ __forceinline__ uint64_t run_address(const DsTile *t, uint64_t row) {
   return a + row * t->stride[0];
 }
 
-// ---- element-wise move of (part of) one unit, exact bounds -------------------
-template <int ES> struct ElemType;
-template <> struct ElemType<1> { typedef uint8_t type; };
-template <> struct ElemType<2> { typedef uint16_t type; };
-template <> struct ElemType<4> { typedef uint32_t type; };
-template <> struct ElemType<8> { typedef uint64_t type; };
-
-union Unit {
-  u32x4 q;
-  uint8_t b[16];
-  uint16_t h[8];
-  uint32_t w[4];
-  uint64_t d[2];
-};
-
-template <int ES> __device__ __forceinline__ typename ElemType<ES>::type unit_get(const Unit &u, int e);
-template <> __device__ __forceinline__ uint8_t unit_get<1>(const Unit &u, int e) { return u.b[e]; }
-template <> __device__ __forceinline__ uint16_t unit_get<2>(const Unit &u, int e) { return u.h[e]; }
-template <> __device__ __forceinline__ uint32_t unit_get<4>(const Unit &u, int e) { return u.w[e]; }
-template <> __device__ __forceinline__ uint64_t unit_get<8>(const Unit &u, int e) { return u.d[e]; }
-template <int ES> __device__ __forceinline__ void unit_set(Unit &u, int e, typename ElemType<ES>::type x);
-template <> __device__ __forceinline__ void unit_set<1>(Unit &u, int e, uint8_t x) { u.b[e] = x; }
-template <> __device__ __forceinline__ void unit_set<2>(Unit &u, int e, uint16_t x) { u.h[e] = x; }
-template <> __device__ __forceinline__ void unit_set<4>(Unit &u, int e, uint32_t x) { u.w[e] = x; }
-template <> __device__ __forceinline__ void unit_set<8>(Unit &u, int e, uint64_t x) { u.d[e] = x; }
-
-// Moves the first `valid` bytes (a multiple of ES, <= 16) of a unit whose first
-// byte is byte `col` of run `row`.  PACK: tensor -> val (rest stays 0);
-// else val -> tensor.
-template <int ES, bool PACK>
-__device__ __forceinline__ void move_elements(const DsTile *t, uint64_t row, uint64_t col, uint32_t valid, Unit &val) {
-  typedef typename ElemType<ES>::type E;
-  const uint64_t L = t->run_bytes;
-  uint64_t ra = run_address(t, row);
-#pragma unroll
-  for (int e = 0; e < 16 / ES; ++e) {
-    if ((uint32_t)(e * ES) < valid) {
-      if (col >= L) {  // the run ended exactly here: go on in the next one
-        col = 0;
-        ++row;
-        ra = run_address(t, row);
-      }
-      E *p = reinterpret_cast<E *>(ra + col);
-      if (PACK) unit_set<ES>(val, e, *p);
-      else *p = unit_get<ES>(val, e);
-      col += ES;
-    }
-  }
-}
-
-// Kept out of line: it is the rare path, and inlining its four instantiations
-// at every call site multiplies code size and build time.
-// The unit travels by value (in registers), not through the stack.
-template <bool PACK>
-__device__ __noinline__ u32x4 move_elements_any(const DsTile *t, uint64_t row, uint64_t col, uint32_t valid, u32x4 in) {
-  Unit val;
-  val.q = in;
-  switch (t->es_log2) {
-    case 0: move_elements<1, PACK>(t, row, col, valid, val); break;
-    case 1: move_elements<2, PACK>(t, row, col, valid, val); break;
-    case 2: move_elements<4, PACK>(t, row, col, valid, val); break;
-    default: move_elements<8, PACK>(t, row, col, valid, val); break;
-  }
-  return val.q;
-}
-
-// ---- one unit, any tile, any position (the general routine) ------------------
-// x: image offset of the unit (multiple of 16) inside tile t's range; imgp: its
-// address in the image buffer.
-template <bool PACK, bool NTL, bool NTS>
-__device__ __forceinline__ void move_unit(const DsTile *t, uint64_t tile_begin, uint64_t x, uint8_t *imgp) {
-  const uint64_t nbytes = t->nbytes;
-  const uint64_t b = x - tile_begin;
-  if (b >= nbytes) {  // padding
-    if (PACK) st16_aligned<NTS>(imgp, u32x4{0, 0, 0, 0});
-    return;
-  }
-  const uint64_t left = nbytes - b;
-  const uint32_t valid = left < 16 ? (uint32_t)left : 16u;
-  const uint64_t L = t->run_bytes;
-  uint64_t row = 0, col = b;
-  if (t->n_outer) divmod(b, L, row, col);
-  if (valid == 16 && col + 16 <= L) {
-    uint8_t *p = reinterpret_cast<uint8_t *>(run_address(t, row) + col);
-    if (PACK) st16_aligned<NTS>(imgp, ld16_any<NTL>(p));
-    else st16_any<NTS>(p, ld16_aligned<NTL>(imgp));
-    return;
-  }
-  if (PACK) st16_aligned<NTS>(imgp, move_elements_any<true>(t, row, col, valid, u32x4{0, 0, 0, 0}));
-  else (void)move_elements_any<false>(t, row, col, valid, ld16_aligned<NTL>(imgp));
-}
-
-// ---- direct path: one tile range, whole work-group ---------------------------
-// [lo, hi): image range of the tile clipped to the chunk, multiples of 16.
-template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS>
-__device__ __forceinline__ void move_tile_direct(const DsTile *t, uint64_t tile_begin, uint64_t lo, uint64_t hi,
-                                                 uint8_t *img, uint64_t img_lo) {
-  const uint32_t tid = threadIdx.x;
-  const uint64_t nbytes = t->nbytes;
-  const uint64_t full_end = tile_begin + (nbytes & ~(uint64_t)15);  // image offset where whole payload units end
-  const uint32_t n_all = (uint32_t)((hi - lo) >> 4);
-  uint32_t n_full = 0;
-  if (full_end > lo) n_full = (uint32_t)(((full_end < hi ? full_end : hi) - lo) >> 4);
-  uint8_t *imgp = img + (lo - img_lo);
-  const uint64_t b0 = lo - tile_begin;
-  const uint32_t m = t->n_outer;
-
-  if (m == 0) {
-    uint8_t *s = reinterpret_cast<uint8_t *>(t->src + b0);
-    for (uint32_t base = 0; base < n_full; base += NT * UNROLL) {
-      u32x4 v[UNROLL];
-#pragma unroll
-      for (int i = 0; i < UNROLL; ++i) {
-        const uint32_t u = base + i * NT + tid;
-        if (u < n_full) v[i] = PACK ? ld16_any<NTL>(s + 16ull * u) : ld16_aligned<NTL>(imgp + 16ull * u);
-      }
-#pragma unroll
-      for (int i = 0; i < UNROLL; ++i) {
-        const uint32_t u = base + i * NT + tid;
-        if (u < n_full) {
-          if (PACK) st16_aligned<NTS>(imgp + 16ull * u, v[i]);
-          else st16_any<NTS>(s + 16ull * u, v[i]);
-        }
-      }
-    }
-  } else {
-    const uint64_t L = t->run_bytes;
-    uint64_t row0, col0;
-    divmod(b0, L, row0, col0);
-    if (L < (1ull << 31)) {
-      const uint32_t L32 = (uint32_t)L, c32 = (uint32_t)col0;
-      for (uint32_t base = 0; base < n_full; base += NT * UNROLL) {
-#pragma unroll
-        for (int i = 0; i < UNROLL; ++i) {
-          const uint32_t u = base + i * NT + tid;
-          if (u < n_full) {
-            const uint32_t tt = c32 + 16u * u;        // < 2^31 + 2^22
-            const uint32_t q = tt / L32;
-            const uint32_t col = tt - q * L32;
-            const uint64_t row = row0 + q;
-            uint8_t *ip = imgp + 16ull * u;
-            if (col + 16u <= L32) {
-              uint8_t *p = reinterpret_cast<uint8_t *>(run_address(t, row) + col);
-              if (PACK) st16_aligned<NTS>(ip, ld16_any<NTL>(p));
-              else st16_any<NTS>(p, ld16_aligned<NTL>(ip));
-            } else {
-              if (PACK) st16_aligned<NTS>(ip, move_elements_any<true>(t, row, col, 16, u32x4{0, 0, 0, 0}));
-              else (void)move_elements_any<false>(t, row, col, 16, ld16_aligned<NTL>(ip));
-            }
-          }
-        }
-      }
-    } else {
-      for (uint32_t u = tid; u < n_full; u += NT)
-        move_unit<PACK, NTL, NTS>(t, tile_begin, lo + 16ull * u, imgp + 16ull * u);
-    }
-  }
-  // the unit cut by the end of the payload, then padding
-  for (uint32_t u = n_full + tid; u < n_all; u += NT)
-    move_unit<PACK, NTL, NTS>(t, tile_begin, lo + 16ull * u, imgp + 16ull * u);
-}
-
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, uint32_t lane) {
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
@@ -371,6 +215,127 @@ __device__ __forceinline__ u32x4 load_low_bytes(const uint8_t *p, uint32_t n) {
 __device__ __forceinline__ void store_cut(uint8_t *p0, uint8_t *p1, uint32_t k, u32x4 v, uint32_t valid = 16) {
   store_low_bytes(p0, v, k);
   if (valid > k) store_low_bytes(p1, splice(v, u32x4{0, 0, 0, 0}, k), valid - k);
+}
+
+// A unit of a view with outer dimensions that lies in several runs, piece by piece: its first `valid` bytes, of which
+// the first k (all that is left of run `row`, or 16) are at p.  PACK: tensor -> the unit (its rest stays 0), else the
+// unit v -> tensor.  A loop over pieces and not over elements in registers: that took 86 registers and kept every
+// kernel with this routine below six wavefronts per SIMD.
+template <bool PACK>
+__device__ __forceinline__ u32x4 move_runs(const DsTile *t, uint64_t row, uint8_t *p, uint32_t k, uint32_t valid, u32x4 v) {
+  const uint32_t run = t->run_bytes < 16 ? (uint32_t)t->run_bytes : 16u;
+  uint32_t at = 0;
+#pragma unroll 1
+  while (true) {
+    const uint32_t n = k < valid - at ? k : valid - at;
+    if (PACK) {
+      const u32x4 x = load_low_bytes(p, n);
+      v |= at ? splice(u32x4{0, 0, 0, 0}, x, 16u - at) : x;
+    } else {
+      store_low_bytes(p, at ? splice(v, u32x4{0, 0, 0, 0}, at) : v, n);
+    }
+    at += n;
+    if (at >= valid) return v;
+    p = reinterpret_cast<uint8_t *>(run_address(t, ++row));
+    k = run;
+  }
+}
+
+// ---- one unit, any tile, any position (the general routine) ------------------
+// x: image offset of the unit (multiple of 16) inside tile t's range; imgp: its
+// address in the image buffer.
+template <bool PACK, bool NTL, bool NTS>
+__device__ __forceinline__ void move_unit(const DsTile *t, uint64_t tile_begin, uint64_t x, uint8_t *imgp) {
+  const uint64_t nbytes = t->nbytes;
+  const uint64_t b = x - tile_begin;
+  if (b >= nbytes) {  // padding
+    if (PACK) st16_aligned<NTS>(imgp, u32x4{0, 0, 0, 0});
+    return;
+  }
+  const uint64_t left = nbytes - b;
+  const uint32_t valid = left < 16 ? (uint32_t)left : 16u;
+  const uint64_t L = t->run_bytes;
+  uint64_t row = 0, col = b;
+  if (t->n_outer) divmod(b, L, row, col);
+  uint8_t *const p = reinterpret_cast<uint8_t *>(run_address(t, row) + col);
+  if (valid == 16 && col + 16 <= L) {
+    if (PACK) st16_aligned<NTS>(imgp, ld16_any<NTL>(p));
+    else st16_any<NTS>(p, ld16_aligned<NTL>(imgp));
+    return;
+  }
+  const uint32_t k = L - col < 16 ? (uint32_t)(L - col) : 16u;
+  if (PACK) st16_aligned<NTS>(imgp, move_runs<true>(t, row, p, k, valid, u32x4{0, 0, 0, 0}));
+  else (void)move_runs<false>(t, row, p, k, valid, ld16_aligned<NTL>(imgp));
+}
+
+// ---- direct path: one tile range, whole work-group ---------------------------
+// [lo, hi): image range of the tile clipped to the chunk, multiples of 16.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS>
+__device__ __forceinline__ void move_tile_direct(const DsTile *t, uint64_t tile_begin, uint64_t lo, uint64_t hi,
+                                                 uint8_t *img, uint64_t img_lo) {
+  const uint32_t tid = threadIdx.x;
+  const uint64_t nbytes = t->nbytes;
+  const uint64_t full_end = tile_begin + (nbytes & ~(uint64_t)15);  // image offset where whole payload units end
+  const uint32_t n_all = (uint32_t)((hi - lo) >> 4);
+  uint32_t n_full = 0;
+  if (full_end > lo) n_full = (uint32_t)(((full_end < hi ? full_end : hi) - lo) >> 4);
+  uint8_t *imgp = img + (lo - img_lo);
+  const uint64_t b0 = lo - tile_begin;
+  const uint32_t m = t->n_outer;
+
+  if (m == 0) {
+    uint8_t *s = reinterpret_cast<uint8_t *>(t->src + b0);
+    for (uint32_t base = 0; base < n_full; base += NT * UNROLL) {
+      u32x4 v[UNROLL];
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i) {
+        const uint32_t u = base + i * NT + tid;
+        if (u < n_full) v[i] = PACK ? ld16_any<NTL>(s + 16ull * u) : ld16_aligned<NTL>(imgp + 16ull * u);
+      }
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i) {
+        const uint32_t u = base + i * NT + tid;
+        if (u < n_full) {
+          if (PACK) st16_aligned<NTS>(imgp + 16ull * u, v[i]);
+          else st16_any<NTS>(s + 16ull * u, v[i]);
+        }
+      }
+    }
+  } else {
+    const uint64_t L = t->run_bytes;
+    uint64_t row0, col0;
+    divmod(b0, L, row0, col0);
+    if (L < (1ull << 31)) {
+      const uint32_t L32 = (uint32_t)L, c32 = (uint32_t)col0;
+      for (uint32_t base = 0; base < n_full; base += NT * UNROLL) {
+#pragma unroll
+        for (int i = 0; i < UNROLL; ++i) {
+          const uint32_t u = base + i * NT + tid;
+          if (u < n_full) {
+            const uint32_t tt = c32 + 16u * u;        // < 2^31 + 2^22
+            const uint32_t q = tt / L32;
+            const uint32_t col = tt - q * L32;
+            const uint64_t row = row0 + q;
+            uint8_t *ip = imgp + 16ull * u;
+            uint8_t *const p = reinterpret_cast<uint8_t *>(run_address(t, row) + col);
+            if (col + 16u <= L32) {
+              if (PACK) st16_aligned<NTS>(ip, ld16_any<NTL>(p));
+              else st16_any<NTS>(p, ld16_aligned<NTL>(ip));
+            } else {
+              if (PACK) st16_aligned<NTS>(ip, move_runs<true>(t, row, p, L32 - col, 16, u32x4{0, 0, 0, 0}));
+              else (void)move_runs<false>(t, row, p, L32 - col, 16, ld16_aligned<NTL>(ip));
+            }
+          }
+        }
+      }
+    } else {
+      for (uint32_t u = tid; u < n_full; u += NT)
+        move_unit<PACK, NTL, NTS>(t, tile_begin, lo + 16ull * u, imgp + 16ull * u);
+    }
+  }
+  // the unit cut by the end of the payload, then padding
+  for (uint32_t u = n_full + tid; u < n_all; u += NT)
+    move_unit<PACK, NTL, NTS>(t, tile_begin, lo + 16ull * u, imgp + 16ull * u);
 }
 
 // Image bytes [cb, ce) of chunk c (WHOLE), or of its piece of BYTES from byte `piece` on, that lie in the launch's range;
@@ -459,7 +424,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
       const uint32_t n_outer = meta & 0xFFu;
       const uint32_t units = (uint32_t)((hi - lo) >> 4);
       // (of a view that is moved in blocks only padding can be large: that is what the scan's units write fastest)
-      const bool big = NT * UNROLL >= kBigUnits && units >= kBigUnits && n_outer > 1 && !(BLOCKS && (meta & DS_HOT_PERM));
+      const bool big = UNROLL > 1 && NT * UNROLL >= kBigUnits && units >= kBigUnits && n_outer > 1 && !(BLOCKS && (meta & DS_HOT_PERM));
       const uint64_t big_mask = __ballot(big);
       const uint32_t incl = wave_inclusive_scan(big ? 0u : units, lane);
       const uint64_t b0 = lo - tb;  // byte of the tile's own range at which its clipped range starts
@@ -493,7 +458,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
     for (uint32_t base = 0; base < n_units; base += NT * UNROLL) {
       // how[i]: kind | k << 8 | last << 16 | tile << 24 (k: bytes of a cut unit that end its run; last: the
       // payload ends with that run; tile: 0..63 inside the batch)
-      enum : uint32_t { kNone = 0, kFast = 1, kZero = 2, kCut = 3, kSlow = 4, kCutHeld = 5, kKind = 0xFFu, kLast = 1u << 16 };
+      enum : uint32_t { kNone = 0, kFast = 1, kZero = 2, kCut = 3, kSlow = 4, kCutHeld = 5, kTiny = 6, kKind = 0xFFu, kLast = 1u << 16 };
       uint32_t j[UNROLL], p[UNROLL], how[UNROLL];
       uint8_t *ip[UNROLL];   // the unit in the image buffer
       uint8_t *sp[UNROLL];   // kFast, kCut: where the unit starts in the tensor
@@ -529,6 +494,10 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
             how[i] = kZero;
           } else if ((meta & 0xFFu) > 1 || !(meta & kRunGe16)) {
             how[i] = kSlow | (q << 24);
+            if (!(meta & 0xFFu)) {
+              how[i] = kTiny | (rem << 8);
+              sp[i] = reinterpret_cast<uint8_t *>(g->src0[q]);
+            }
           } else {
             // the run the unit starts in: what is left of the payload, or one row of a 2-D view
             uint64_t run0 = g->src0[q];
@@ -580,8 +549,9 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
         const uint32_t kind = how[i] & kKind;
         if (PACK) {
           if (kind == kFast) v[i] = ld16_any<NTL>(sp[i]);
+          if (kind == kTiny) v[i] = load_low_bytes(sp[i], how[i] >> 8);
         } else {
-          if (kind == kFast || kind == kCut) v[i] = ld16_aligned<NTL>(ip[i]);
+          if (kind == kFast || kind == kCut || kind == kTiny) v[i] = ld16_aligned<NTL>(ip[i]);
         }
       }
       if (PACK && cut_held) {
@@ -608,7 +578,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
 #pragma unroll
         for (int i = 0; i < UNROLL; ++i) {
           const uint32_t kind = how[i] & kKind;
-          const bool stores = kind == kFast || kind == kZero || kind == kCutHeld;
+          const bool stores = kind == kFast || kind == kZero || kind == kCutHeld || kind == kTiny;
           if (BUFST)
             __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)(stores ? (uint32_t)(ip[i] - cimg) : kNoStore), 0,
                                                    kStorePolicySc0Sc1Nt);
@@ -626,13 +596,15 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
             const uint32_t k = (how[i] >> 8) & 0xFFu, q = how[i] >> 24;
             const bool last = how[i] & kLast;
             store_cut(sp[i], sp[i] + k + (g->pitch[q] - g->run[q]), k, v[i], last ? k : 16u);
+          } else if (kind == kTiny) {
+            store_low_bytes(sp[i], v[i], how[i] >> 8);
           }
         }
       }
       // Gather: a thread's further cut units, one after the other: the first k bytes end their run, the rest
       // start the next one or are padding when the payload ends there; both parts come from 16-byte loads
       // that lie wholly inside their runs.
-      if (PACK) {
+      if (PACK && UNROLL > 1) {
 #pragma unroll
         for (int i = 0; i < UNROLL; ++i)
           if ((how[i] & kKind) == kCut) {
@@ -652,7 +624,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
           move_unit<PACK, NTL, NTS>(a.tiles + bt + q, tb, cb + (uint64_t)(ip[i] - cimg), ip[i]);
         }
     }
-    uint64_t big_mask = NT * UNROLL >= kBigUnits ? g->big_mask : 0;
+    uint64_t big_mask = UNROLL > 1 && NT * UNROLL >= kBigUnits ? g->big_mask : 0;
     while (big_mask) {
       const uint32_t p = (uint32_t)__builtin_ctzll(big_mask);
       big_mask &= big_mask - 1;
@@ -678,16 +650,16 @@ struct MultiLds {
 };
 constexpr uint32_t kWholeBelow16 = 1u << 31;  // the tile has less than 16 bytes: nothing to read a unit from
 
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, bool WHOLE>
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, bool WHOLE>
 __device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1,
                                             MultiLds *g) {
   const uint32_t tid = threadIdx.x;
   uint64_t cb, ce;
-  if (!piece_range<WHOLE, 256 * UNROLL * 16>(a, c, piece, cb, ce)) return;
+  if (!piece_range<WHOLE, NT * UNROLL * 16>(a, c, piece, cb, ce)) return;
   uint8_t *const cimg = a.img + (cb - a.img_lo);
   const uint32_t size = (uint32_t)(ce - cb), n = t1 - t0 + 1;
   __syncthreads();  // readers of the previous chunk are done
-  for (uint32_t i = tid; i < n; i += 256) {
+  for (uint32_t i = tid; i < n; i += NT) {
     const DsTileHot *h = a.hot + t0 + i;
     const uint64_t tb = h->img_off, nbytes = h->nbytes;
     const uint64_t b0 = cb > tb ? cb - tb : 0;  // byte of the tile at which its clipped range starts
@@ -707,12 +679,12 @@ __device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint3
 #pragma unroll
     for (int i = 0; i < UNROLL; ++i) {
       const uint32_t q = p[i] + step;
-      if (q < n && g->begin[q] <= 16u * (i * 256 + tid)) p[i] = q;
+      if (q < n && g->begin[q] <= 16u * (i * NT + tid)) p[i] = q;
     }
   }
 #pragma unroll
   for (int i = 0; i < UNROLL; ++i) {
-    d[i] = 16u * (i * 256 + tid) - g->begin[p[i]];
+    d[i] = 16u * (i * NT + tid) - g->begin[p[i]];
     rem[i] = g->rem[p[i]];
     sp[i] = (const uint8_t *)g->src[p[i]] + d[i];
   }
@@ -740,21 +712,21 @@ __device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint3
     }
 #pragma unroll
     for (int i = 0; i < UNROLL; ++i) {
-      const uint32_t off = 16u * (i * 256 + tid);
+      const uint32_t off = 16u * (i * NT + tid);
       if (BUFST) __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
       else if (off < size) st16_aligned<NTS>(cimg + off, v[i]);
     }
   } else {
 #pragma unroll
     for (int i = 0; i < UNROLL; ++i) {
-      const uint32_t off = 16u * (i * 256 + tid);
+      const uint32_t off = 16u * (i * NT + tid);
       v[i] = ld16_aligned<NTL>(cimg + (off < size ? off : size - 16u));
     }
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
 #pragma unroll
     for (int i = 0; i < UNROLL; ++i) {
       const uint32_t whole = rem[i] & ~kWholeBelow16;
-      if (16u * (i * 256 + tid) < size && d[i] < whole) {
+      if (16u * (i * NT + tid) < size && d[i] < whole) {
         if (d[i] + 16u <= whole) st16_any<NTS>((uint8_t *)sp[i], v[i]);
         else store_low_bytes((uint8_t *)sp[i], v[i], whole - d[i]);
       }
@@ -769,6 +741,122 @@ __device__ __forceinline__ void multi_chunk(const MoveArgs &a, uint64_t c, uint3
 // intrinsic with a cache-policy operand for it (and none for global stores); the resource covers exactly
 // the work-group's chunk, so an out-of-range store would be dropped by the hardware.
 
+// A record, in one scalar load: the table is constant while the kernel runs.  Through an ordinary pointer the compiler
+// reads it in two vector loads, the second behind the first's answer.
+__device__ __forceinline__ DsChunkRec load_rec(const DsChunkRec *recs, uint64_t i) {
+  typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+  const u32x8 w = *(const __attribute__((address_space(4))) u32x8 *)(uintptr_t)(recs + i);
+  return DsChunkRec{w[0] | (uint64_t)w[1] << 32, w[2] | (uint64_t)w[3] << 32, w[4], w[5], w[6], w[7]};
+}
+__device__ __forceinline__ uint32_t load_id(const uint32_t *ids, uint64_t i) {
+  return *(const __attribute__((address_space(4))) uint32_t *)(uintptr_t)(ids + i);
+}
+
+// Moves a lean chunk, or its piece of NT * UNROLL units from byte `piece` on, which is at imgp in the image buffer.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST>
+__device__ __forceinline__ void lean_move(const DsChunkRec &r, uint8_t *imgp, uint32_t piece) {
+  const uint32_t tid = threadIdx.x;
+  __amdgpu_buffer_rsrc_t image_rsrc;
+  if (PACK && BUFST) image_rsrc = __builtin_amdgcn_make_buffer_rsrc(imgp, 0, NT * UNROLL * 16, 0x00020000);
+  u32x4 v[UNROLL];
+  if ((r.kind & 0xFFu) == DS_CHUNK_CONTIG) {
+    uint8_t *s = reinterpret_cast<uint8_t *>(r.addr) + piece;
+    // (the scatter keeps "nt" global stores on the tensor side: the write-through buffer stores that serve
+    // the image so well cost it 3 % on the Llama ranks and 10 % on the fragmentation set, measured)
+    if (PACK && (r.kind & DS_CHUNK_REALIGN)) {
+      // The tensor side is at an odd address: a 16-byte load there costs about twice an aligned one.  Every
+      // lane loads the ALIGNED unit that holds the first byte of its image unit and takes the rest from
+      // the unit of the lane above it (of the same wavefront: the last lane loads that unit itself); the
+      // plan sets the flag only where those units lie inside the tensor.
+      const uint32_t m = (uint32_t)r.addr & 15u;
+      uint8_t *base = s - m;
+      const bool last_lane = (tid & (kWave - 1)) == kWave - 1;
+      u32x4 a[UNROLL], e[UNROLL];
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i) a[i] = ld16_aligned<NTL>(base + 16u * (i * NT + tid));
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i) {
+        e[i] = u32x4{0, 0, 0, 0};
+        if (last_lane) e[i] = ld16_aligned<NTL>(base + 16u * (i * NT + tid) + 16u);
+      }
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i) {
+        u32x4 up = u32x4{lane_above(a[i].x), lane_above(a[i].y), lane_above(a[i].z), lane_above(a[i].w)};
+        if (last_lane) up = e[i];
+        v[i] = splice(a[i], up, m);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i) {
+        const uint32_t off = 16u * (i * NT + tid);
+        v[i] = PACK ? ld16_any<NTL>(s + off) : ld16_aligned<NTL>(imgp + off);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t off = 16u * (i * NT + tid);
+      if (PACK && BUFST) __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
+      else if (PACK) st16_aligned<NTS>(imgp + off, v[i]);
+      else st16_any<NTS>(s + off, v[i]);
+    }
+  } else {
+    // DS_CHUNK_ROWS: runs of r.run >= 16 bytes, r.pitch apart.  A unit that lies in one
+    // run is one access.  A unit cut by the end of a run takes its first k bytes from
+    // the end of that run and the other 16-k from the start of the next one; on the
+    // gather side both come from 16-byte loads that lie wholly inside their runs
+    // (the last 16 bytes of the one, the first 16 of the other), so nothing outside
+    // the view is read; on the scatter side each part is stored as at most four pieces
+    // of 8, 4, 2 and 1 bytes, exactly the bytes of the view.
+    uint8_t *p[UNROLL];
+    uint32_t cut[UNROLL];  // k, or 0 if the unit is not cut
+    u32x4 w[UNROLL];       // gather: the first 16 bytes of the next run, for cut units
+    // One division for the thread's first unit; its other units are NT*16 bytes further on each,
+    // and the plan has divided that step by the run length already (r.tile = quotient << 16 | rest).
+    const uint32_t step_q = r.tile >> 16, step_r = r.tile & 0xFFFFu;
+    const uint32_t tt0 = r.col0 + piece + 16u * tid;  // < 2^31 + 2^15
+    uint32_t q = tt0 / r.run;
+    uint32_t col = tt0 - q * r.run;
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t off = 16u * (i * NT + tid);
+      uint8_t *row = reinterpret_cast<uint8_t *>(r.addr + (uint64_t)q * r.pitch);
+      p[i] = row + col;
+      cut[i] = col + 16u > r.run ? r.run - col : 0u;
+      if (PACK) {
+        // all loads are issued before any of them is used: no wait inside this loop
+        v[i] = ld16_any<NTL>(cut[i] ? row + r.run - 16u : p[i]);
+        if (cut[i]) w[i] = ld16_any<NTL>(row + r.pitch);
+      } else {
+        v[i] = ld16_aligned<NTL>(imgp + off);
+      }
+      q += step_q;
+      col += step_r;
+      if (col >= r.run) {
+        col -= r.run;
+        ++q;
+      }
+    }
+    if (PACK) {
+#pragma unroll
+      for (int i = 0; i < UNROLL; ++i)
+        if (cut[i]) v[i] = splice(v[i], w[i], 16u - cut[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < UNROLL; ++i) {
+      const uint32_t off = 16u * (i * NT + tid);
+      if (PACK && BUFST) {
+        __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
+      } else if (PACK) {
+        st16_aligned<NTS>(imgp + off, v[i]);
+      } else if (cut[i] == 0) {
+        st16_any<NTS>(p[i], v[i]);
+      } else {
+        store_cut(p[i], p[i] + cut[i] + (r.pitch - r.run), cut[i], v[i]);
+      }
+    }
+  }
+}
+
 // Number of lean work items of a launch; item ci takes one lean chunk, whole work-group.
 __device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd_span ? a.xcd_span * 8u : a.n_pieces; }
 
@@ -779,132 +867,40 @@ __device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd
 template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int BLOCKS, bool WHOLE>
 __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, uint32_t pieces_log2, uint64_t &c_gen,
                                                uint32_t &piece, uint32_t &t0, uint32_t &t1) {
-  const uint32_t tid = threadIdx.x;
-  {
-    // Work-groups are dealt to the 8 XCDs round-robin (work-group i runs on XCD i mod 8).  Chunk
-    // numbers are permuted so that each XCD walks ONE contiguous eighth of the range instead of every
-    // eighth chunk: measured +1.5 % (7B rank) to +5 % (fragmentation set) on the gather and +4 to +8 %
-    // on the scatter.
-    uint32_t cm = ci;
-    if (a.xcd_span) {
-      cm = (ci & 7u) * a.xcd_span + (ci >> 3);
-      if (cm >= a.n_pieces) return 0;
-    }
-    if (!WHOLE) piece = (cm & ((1u << pieces_log2) - 1)) * (NT * UNROLL * 16);  // offset inside the chunk
-    const uint32_t rec = a.c_lo + (WHOLE ? cm : cm >> pieces_log2);
-    const DsChunkRec r = a.recs[rec];
-    const uint32_t c = BLOCKS == kListed ? a.ids[rec] : rec;
-    const uint32_t kind = r.kind & 0xFF;  // bits 8.. hold log2(itemsize)
-    if (BLOCKS == kBeside && kind == DS_CHUNK_PERM) return 0;
-    if (kind >= DS_CHUNK_GENERAL) {
-      // its record names the tiles it holds: one load away from them, and in place among its neighbours
-      c_gen = c;
-      t0 = r.tile;
-      t1 = r.tile + r.col0;
-      return kind;
-    }
-    uint8_t *imgp = a.img + (((uint64_t)c << a.chunk_log2) - a.img_lo) + (WHOLE ? 0u : piece);
-    __amdgpu_buffer_rsrc_t image_rsrc;
-    if (PACK && BUFST) image_rsrc = __builtin_amdgcn_make_buffer_rsrc(imgp, 0, NT * UNROLL * 16, 0x00020000);
-    u32x4 v[UNROLL];
-    if (kind == DS_CHUNK_CONTIG) {
-      uint8_t *s = reinterpret_cast<uint8_t *>(r.addr) + (WHOLE ? 0u : piece);
-      // (the scatter keeps "nt" global stores on the tensor side: the write-through buffer stores that serve
-      // the image so well cost it 3 % on the Llama ranks and 10 % on the fragmentation set, measured)
-      if (PACK && (r.kind & DS_CHUNK_REALIGN)) {
-        // The tensor side is at an odd address: a 16-byte load there costs about twice an aligned one.  Every
-        // lane loads the ALIGNED unit that holds the first byte of its image unit and takes the rest from
-        // the unit of the lane above it (of the same wavefront: the last lane loads that unit itself); the
-        // plan sets the flag only where those units lie inside the tensor.
-        const uint32_t m = (uint32_t)r.addr & 15u;
-        uint8_t *base = s - m;
-        const bool last_lane = (tid & (kWave - 1)) == kWave - 1;
-        u32x4 a[UNROLL], e[UNROLL];
-#pragma unroll
-        for (int i = 0; i < UNROLL; ++i) a[i] = ld16_aligned<NTL>(base + 16u * (i * NT + tid));
-#pragma unroll
-        for (int i = 0; i < UNROLL; ++i) {
-          e[i] = u32x4{0, 0, 0, 0};
-          if (last_lane) e[i] = ld16_aligned<NTL>(base + 16u * (i * NT + tid) + 16u);
-        }
-#pragma unroll
-        for (int i = 0; i < UNROLL; ++i) {
-          u32x4 up = u32x4{lane_above(a[i].x), lane_above(a[i].y), lane_above(a[i].z), lane_above(a[i].w)};
-          if (last_lane) up = e[i];
-          v[i] = splice(a[i], up, m);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < UNROLL; ++i) {
-          const uint32_t off = 16u * (i * NT + tid);
-          v[i] = PACK ? ld16_any<NTL>(s + off) : ld16_aligned<NTL>(imgp + off);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < UNROLL; ++i) {
-        const uint32_t off = 16u * (i * NT + tid);
-        if (PACK && BUFST) __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
-        else if (PACK) st16_aligned<NTS>(imgp + off, v[i]);
-        else st16_any<NTS>(s + off, v[i]);
-      }
-    } else {
-      // DS_CHUNK_ROWS: runs of r.run >= 16 bytes, r.pitch apart.  A unit that lies in one
-      // run is one access.  A unit cut by the end of a run takes its first k bytes from
-      // the end of that run and the other 16-k from the start of the next one; on the
-      // gather side both come from 16-byte loads that lie wholly inside their runs
-      // (the last 16 bytes of the one, the first 16 of the other), so nothing outside
-      // the view is read; on the scatter side each part is stored as at most four pieces
-      // of 8, 4, 2 and 1 bytes, exactly the bytes of the view.
-      uint8_t *p[UNROLL];
-      uint32_t cut[UNROLL];  // k, or 0 if the unit is not cut
-      u32x4 w[UNROLL];       // gather: the first 16 bytes of the next run, for cut units
-      // One division for the thread's first unit; its other units are NT*16 bytes further on each,
-      // and the plan has divided that step by the run length already (r.tile = quotient << 16 | rest).
-      const uint32_t step_q = r.tile >> 16, step_r = r.tile & 0xFFFFu;
-      const uint32_t tt0 = r.col0 + (WHOLE ? 0u : piece) + 16u * tid;  // < 2^31 + 2^15
-      uint32_t q = tt0 / r.run;
-      uint32_t col = tt0 - q * r.run;
-#pragma unroll
-      for (int i = 0; i < UNROLL; ++i) {
-        const uint32_t off = 16u * (i * NT + tid);
-        uint8_t *row = reinterpret_cast<uint8_t *>(r.addr + (uint64_t)q * r.pitch);
-        p[i] = row + col;
-        cut[i] = col + 16u > r.run ? r.run - col : 0u;
-        if (PACK) {
-          // all loads are issued before any of them is used: no wait inside this loop
-          v[i] = ld16_any<NTL>(cut[i] ? row + r.run - 16u : p[i]);
-          if (cut[i]) w[i] = ld16_any<NTL>(row + r.pitch);
-        } else {
-          v[i] = ld16_aligned<NTL>(imgp + off);
-        }
-        q += step_q;
-        col += step_r;
-        if (col >= r.run) {
-          col -= r.run;
-          ++q;
-        }
-      }
-      if (PACK) {
-#pragma unroll
-        for (int i = 0; i < UNROLL; ++i)
-          if (cut[i]) v[i] = splice(v[i], w[i], 16u - cut[i]);
-      }
-#pragma unroll
-      for (int i = 0; i < UNROLL; ++i) {
-        const uint32_t off = 16u * (i * NT + tid);
-        if (PACK && BUFST) {
-          __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
-        } else if (PACK) {
-          st16_aligned<NTS>(imgp + off, v[i]);
-        } else if (cut[i] == 0) {
-          st16_any<NTS>(p[i], v[i]);
-        } else {
-          store_cut(p[i], p[i] + cut[i] + (r.pitch - r.run), cut[i], v[i]);
-        }
-      }
-    }
+  // Work-groups are dealt to the 8 XCDs round-robin (work-group i runs on XCD i mod 8).  Chunk
+  // numbers are permuted so that each XCD walks ONE contiguous eighth of the range instead of every
+  // eighth chunk: measured +1.5 % (7B rank) to +5 % (fragmentation set) on the gather and +4 to +8 %
+  // on the scatter.
+  uint32_t cm = ci;
+  if (a.xcd_span) {
+    cm = (ci & 7u) * a.xcd_span + (ci >> 3);
+    if (cm >= a.n_pieces) return 0;
   }
+  if (!WHOLE) piece = (cm & ((1u << pieces_log2) - 1)) * (NT * UNROLL * 16);  // offset inside the chunk
+  const uint32_t rec = a.c_lo + (WHOLE ? cm : cm >> pieces_log2);
+  const DsChunkRec r = load_rec(a.recs, rec);
+  const uint32_t c = BLOCKS == kListed ? load_id(a.ids, rec) : rec;
+  const uint32_t kind = r.kind & 0xFF;  // bits 8.. hold log2(itemsize)
+  if (BLOCKS == kBeside && kind == DS_CHUNK_PERM) return 0;
+  if (kind >= DS_CHUNK_GENERAL) {
+    // its record names the tiles it holds: one load away from them, and in place among its neighbours
+    c_gen = c;
+    t0 = r.tile;
+    t1 = r.tile + r.col0;
+    return kind;
+  }
+  const uint32_t from = WHOLE ? 0u : piece;
+  lean_move<PACK, NT, UNROLL, NTL, NTS, BUFST>(r, a.img + (((uint64_t)c << a.chunk_log2) - a.img_lo) + from, from);
   return 0;
+}
+
+// The tiles t0 .. t1 of a chunk that is cut by the range.
+__device__ __forceinline__ void cut_chunk_tiles(const MoveArgs &a, uint64_t c, uint32_t &t0, uint32_t &t1) {
+  uint64_t c_end = (c + 1) << a.chunk_log2;
+  if (c_end > a.total) c_end = a.total;
+  t0 = a.first_tile[c];
+  t1 = a.first_tile[c + 1];
+  if (a.hot[t1].img_off >= c_end) --t1;  // that tile starts where this chunk ends
 }
 
 // Both paths in one launch: work item i takes whole chunk number i of the range (in the XCD-contiguous
@@ -916,25 +912,25 @@ __device__ __forceinline__ uint32_t lean_chunk(const LeanArgs &a, uint32_t ci, u
 // 5.30 -> 5.54 TB/s, one launch 5.85 TB/s.
 //
 // A work-group takes one piece of a chunk, 256 threads x UNROLL units, with at most WAVES wavefronts per SIMD (the
-// attribute makes the compiler pad the register allocation).  What bounds the lean path is the bytes in flight: the
-// record and then the data take about 3 us, which at 3.2 TB/s each way are 40 KB per CU.
+// attribute makes the compiler pad the register allocation).
 //   gather, UNROLL 4 and WAVES 4: 64 KB in flight, and few work-groups keep the addresses in a compact window of
-//     HBM (five wavefronts -0.8 % on the 7B and 70B ranks, eight -4 %, three or fewer -9 %).  Two units per thread
-//     would need eight wavefronts to gain anything (70B rank 2.36 ms against 2.40, six wavefronts 2.41), which the
-//     general path's 93 registers do not allow; one unit per thread leaves too little in flight (3.30 ms).
-//   gather of plans of mostly general chunks, WAVES 6: that path is bound by its chain of dependent loads and takes
-//     the five wavefronts its registers allow (+8 to +10 % on tables of tiny tensors against four).
+//     HBM (five wavefronts -0.8 % on the 7B and 70B ranks, eight -4 %, three or fewer -9 %).
+//   gather of plans of mostly general chunks, WAVES 6: that path is bound by its chain of dependent loads (+8 to +10 %
+//     on tables of tiny tensors against four).
 //   scatter, UNROLL 2 and WAVES 6 (a piece of 8 KiB, 48 KB in flight), or as the gather: see launch_scatter.
-// ALL = false is the instantiation for plans of contiguous shards only, most chunks of which hold several of them:
-// no chunk takes the general path, and multi_chunk's registers (gather 78, scatter 40) allow six and eight wavefronts.
+// PATH kMulti is the instantiation for plans of contiguous shards only, most chunks of which hold several of them:
+// no chunk takes the general path, and multi_chunk's registers (gather 78, scatter 32) allow six and eight wavefronts.
 // 24 000 tensors of 16 bytes to 16 KiB (58 MB): gather 25.2 us against 29.1 through the general path, scatter 24.2
 // against 26.6.
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, bool ALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
+enum : int { kEvery = 0, kMulti = 1 };
+// Does a work-group of so many units take whole chunks (else pieces of them)?
+constexpr bool takes_whole_chunks(bool pack, int units) { return units >= (pack ? 512 : 1024); }
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, int PATH>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
                                                                                                      MoveArgs ma) {
-  __shared__ typename std::conditional<ALL, GenLds, MultiLds>::type s_tab;
+  __shared__ typename std::conditional<PATH == kMulti, MultiLds, GenLds>::type s_tab;
   const uint32_t n_lean = lean_items(la);
-  constexpr bool WHOLE = PACK || UNROLL >= 4;  // the work-group's piece is the chunk
+  constexpr bool WHOLE = takes_whole_chunks(PACK, NT * UNROLL);
   const uint32_t pieces_log2 = WHOLE ? 0 : ma.n_extra >> 8;
   const uint32_t n_iter = n_lean + (WHOLE ? ma.n_extra : (ma.n_extra & 0xFFu) << pieces_log2);
   for (uint32_t wi = blockIdx.x; wi < n_iter; wi += gridDim.x) {
@@ -942,51 +938,107 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WAVES)))
     uint32_t piece = 0, t0 = 0, t1 = 0;
     uint32_t kind = DS_CHUNK_GENERAL;
     if (wi < n_lean) {
-      kind = lean_chunk<PACK, 256, UNROLL, NTL, NTS, BUFST, BLOCKS, WHOLE>(la, wi, pieces_log2, c, piece, t0, t1);
+      kind = lean_chunk<PACK, NT, UNROLL, NTL, NTS, BUFST, BLOCKS, WHOLE>(la, wi, pieces_log2, c, piece, t0, t1);
     } else {
       // (a piece of) a chunk cut by the range, whatever the chunk's kind: these paths clip to the range
       const uint32_t x = wi - n_lean;
       c = ma.extra[x >> pieces_log2];
-      piece = (x & ((1u << pieces_log2) - 1)) * (256 * UNROLL * 16);
-      uint64_t c_end = (c + 1) << ma.chunk_log2;
-      if (c_end > ma.total) c_end = ma.total;
-      t0 = ma.first_tile[c];
-      t1 = ma.first_tile[c + 1];
-      if (ma.hot[t1].img_off >= c_end) --t1;  // that tile starts where this chunk ends
+      piece = (x & ((1u << pieces_log2) - 1)) * (NT * UNROLL * 16);
+      cut_chunk_tiles(ma, c, t0, t1);
     }
-    if constexpr (ALL) {
-      if (kind) general_chunk<PACK, 256, WHOLE ? 4 : UNROLL, NTL, NTS, BUFST, BLOCKS, WHOLE>(ma, c, piece, t0, t1, &s_tab);
+    if constexpr (PATH == kMulti) {
+      if (kind) multi_chunk<PACK, NT, UNROLL, NTL, NTS, BUFST, WHOLE>(ma, c, piece, t0, t1, &s_tab);
     } else {
-      if (kind) multi_chunk<PACK, UNROLL, NTL, NTS, BUFST, WHOLE>(ma, c, piece, t0, t1, &s_tab);
+      constexpr int PASS = PATH == kEvery && WHOLE ? 4 : UNROLL;
+      if (kind)
+        general_chunk<PACK, NT, PASS, NTL, NTS, BUFST, BLOCKS, WHOLE>(ma, c, piece, t0, t1, &s_tab);
     }
   }
 }
 
+// The same, one unit per thread and one piece of 4 KiB per work-group, for plans of 16 KiB chunks: what a default call
+// launches unless most chunks hold several contiguous tensors (multi_chunk).  With one load and one store per wavefront
+// the lean path is bound by HBM as long as eight wavefronts per SIMD fit (64 registers: hence no loop over work items,
+// whose constants the compiler keeps in registers, and move_runs) and a wavefront has done its work in the 700 cycles
+// that its 1 KiB takes its SIMD's share of HBM: the record in one scalar load, nothing else in front of the data.  (With
+// the record in two vector loads, one behind the other, the 7.6 GB gather took 3137 us.)  Measured, four units per thread
+// and four wavefronts (scatter: two and six) before / now: gather of a 70B rank (7.6 GB) 2392 / 2280 us, scatter of a 7B
+// rank (1.5 GB) 490 / 473, 20 000 fragments (7.5 GB) 2488 / 2356, a 23 MB state 10.9 / 9.1 and scatter 11.4 / 8.9 (with the
+// ordinary loads of small images; non-temporal 10.0 and 10.6), 475 fragments with many rows (1 MB) 8.0 / 6.3.
+// Work-groups of 512 and 1024 threads measure the same on large tensors and 3 to 5 % slower on fragments.
+template <bool PACK, bool NTL, int BLOCKS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_unit_kernel(
+    const DsChunkRec *recs, const uint32_t *ids, uint8_t *img0, uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
+  __shared__ GenLds s_tab;
+  const uint32_t wi = blockIdx.x, cm = (wi & 7u) * span + (wi >> 3);
+  uint64_t c;
+  uint32_t piece, t0, t1;
+  if (wi < span * 8u) {
+    if (cm >= n) return;
+    const uint32_t rec = c_lo + cm / kUnitPieces;
+    piece = cm % kUnitPieces * 4096;
+    const DsChunkRec r = load_rec(recs, rec);
+    c = BLOCKS == kListed ? load_id(ids, rec) : rec;
+    const uint32_t kind = r.kind & 0xFFu;
+    if (kind < DS_CHUNK_GENERAL) {
+      lean_move<PACK, 256, 1, NTL, true, PACK>(r, img0 + (c << 14) + piece, piece);
+      return;
+    }
+    if (BLOCKS == kBeside && kind == DS_CHUNK_PERM) return;
+    t0 = r.tile;
+    t1 = r.tile + r.col0;
+  } else {
+    const uint32_t x = wi - span * 8u;
+    c = ma.extra[x / kUnitPieces];
+    piece = x % kUnitPieces * 4096;
+    cut_chunk_tiles(ma, c, t0, t1);
+  }
+  general_chunk<PACK, 256, 1, NTL, true, PACK, BLOCKS, false>(ma, c, piece, t0, t1, &s_tab);
+}
+
+template <bool PACK, bool NTL, int BLOCKS>
+int launch_units(const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  const uint32_t n = la.n_pieces * kUnitPieces, span = (n + 7) / 8, grid = span * 8 + ma.n_extra * kUnitPieces;
+  if (grid == 0) return DS_OK;
+  hipLaunchKernelGGL((ds_unit_kernel<PACK, NTL, BLOCKS>), dim3(grid), dim3(256), 0, stream, la.recs, la.ids,
+                     la.img - la.img_lo, n, span, la.c_lo, ma);
+  DS_HIP_TRY(hipGetLastError());
+  return DS_OK;
+}
+
+template <int BLOCKS>
+int launch_units(const ds_plan *plan, bool pack, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  if (plan->total_bytes <= kCachedBytes)
+    return pack ? launch_units<true, false, BLOCKS>(la, ma, stream) : launch_units<false, false, BLOCKS>(la, ma, stream);
+  return pack ? launch_units<true, true, BLOCKS>(la, ma, stream) : launch_units<false, true, BLOCKS>(la, ma, stream);
+}
+
 constexpr uint32_t kMaxGrid = 1u << 23;  // work-groups of 256: a launch has less than 2^32 threads
 
-template <bool PACK, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, bool ALL>
+template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, int PATH>
 int launch_pieces(LeanArgs la, MoveArgs ma, uint32_t grid_limit, hipStream_t stream) {
-  const uint32_t pieces_log2 = la.chunk_log2 - (12 + __builtin_ctz(UNROLL));
+  const uint32_t pieces_log2 = la.chunk_log2 - (4 + __builtin_ctz(NT * UNROLL));
   la.n_pieces <<= pieces_log2;  // chunks so far
   la.xcd_span = ds_cfg_variant() == 3 ? 0 : (la.n_pieces + 7) / 8;
   uint64_t grid = (uint64_t)(la.xcd_span ? la.xcd_span * 8 : la.n_pieces) + (ma.n_extra << pieces_log2);
   if (grid == 0) return DS_OK;
-  if (!PACK && UNROLL == 2) ma.n_extra |= pieces_log2 << 8;
+  if (!takes_whole_chunks(PACK, NT * UNROLL)) ma.n_extra |= pieces_log2 << 8;
+  else if (pieces_log2) return DS_EINVAL;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
-  if (grid > kMaxGrid) grid = kMaxGrid;
-  hipLaunchKernelGGL((ds_move_kernel<PACK, UNROLL, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>), dim3((uint32_t)grid), dim3(256), 0,
-                     stream, la, ma);
+  if (grid > kMaxGrid * 256 / NT) grid = kMaxGrid * 256 / NT;
+  hipLaunchKernelGGL((ds_move_kernel<PACK, NT, UNROLL, NTL, NTS, BUFST, WAVES, BLOCKS, PATH>), dim3((uint32_t)grid),
+                     dim3(NT), 0, stream, la, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
 
 // The gather: a chunk per work-group.  (Pieces in its kernel, though one per chunk, cost the 23 MB gather 0.3 us.)
-template <bool NTL, bool NTS, bool BUFST, int WAVES = 4, int BLOCKS = kAlone, bool ALL = true>
+template <bool NTL, bool NTS, bool BUFST, int WAVES = 4, int BLOCKS = kAlone, int PATH = kEvery>
 int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, hipStream_t stream) {
   switch (la.chunk_log2) {
-    case 13: return launch_pieces<true, 2, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>(la, ma, grid_limit, stream);
-    case 14: return launch_pieces<true, 4, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>(la, ma, grid_limit, stream);
-    case 15: return launch_pieces<true, 8, NTL, NTS, BUFST, WAVES, BLOCKS, ALL>(la, ma, grid_limit, stream);
+    case 13: return launch_pieces<true, 256, 2, NTL, NTS, BUFST, WAVES, BLOCKS, PATH>(la, ma, grid_limit, stream);
+    case 14: return launch_pieces<true, 256, 4, NTL, NTS, BUFST, WAVES, BLOCKS, PATH>(la, ma, grid_limit, stream);
+    case 15: return launch_pieces<true, 256, 8, NTL, NTS, BUFST, WAVES, BLOCKS, PATH>(la, ma, grid_limit, stream);
     default: return DS_EINVAL;
   }
 }
@@ -994,20 +1046,20 @@ int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, h
 // The scatter, in whole chunks at four wavefronts per SIMD or in pieces of 8 KiB at six (ds_plan::scatter_in_pieces).
 // Plans of mostly general chunks keep whole chunks, whose tiles are looked up once, at six (15 MB in 711 views and
 // tensors: 10.7 us, in pieces 11.4).
-template <bool NTL, bool NTS, int BLOCKS = kAlone, bool ALL = true>
+template <bool NTL, bool NTS, int BLOCKS = kAlone, int PATH = kEvery>
 int launch_scatter(const ds_plan *plan, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma,
                    uint32_t grid_limit, hipStream_t stream) {
-  if constexpr (!ALL) {
-    return launch_pieces<false, 2, NTL, NTS, false, 8, BLOCKS, ALL>(la, ma, grid_limit, stream);
+  if constexpr (PATH == kMulti) {
+    return launch_pieces<false, 256, 2, NTL, NTS, false, 8, BLOCKS, PATH>(la, ma, grid_limit, stream);
   } else {
     const bool large = la.chunk_log2 == 15;
     if (la.chunk_log2 > 13 && mostly_general)
-      return large ? launch_pieces<false, 8, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream)
-                   : launch_pieces<false, 4, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream);
+      return large ? launch_pieces<false, 256, 8, NTL, NTS, false, 6, BLOCKS, PATH>(la, ma, grid_limit, stream)
+                   : launch_pieces<false, 256, 4, NTL, NTS, false, 6, BLOCKS, PATH>(la, ma, grid_limit, stream);
     if (la.chunk_log2 > 13 && (few || !plan->scatter_in_pieces((uint64_t)la.n_pieces << (la.chunk_log2 - 14))))
-      return large ? launch_pieces<false, 8, NTL, NTS, false, 4, BLOCKS, ALL>(la, ma, grid_limit, stream)
-                   : launch_pieces<false, 4, NTL, NTS, false, 4, BLOCKS, ALL>(la, ma, grid_limit, stream);
-    return launch_pieces<false, 2, NTL, NTS, false, 6, BLOCKS, ALL>(la, ma, grid_limit, stream);
+      return large ? launch_pieces<false, 256, 8, NTL, NTS, false, 4, BLOCKS, PATH>(la, ma, grid_limit, stream)
+                   : launch_pieces<false, 256, 4, NTL, NTS, false, 4, BLOCKS, PATH>(la, ma, grid_limit, stream);
+    return launch_pieces<false, 256, 2, NTL, NTS, false, 6, BLOCKS, PATH>(la, ma, grid_limit, stream);
   }
 }
 
@@ -1427,6 +1479,13 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   const uint64_t variant = ds_cfg_variant();
   const bool few = variant == 5 || grid_limit;
   const bool mostly_general = plan->mostly_general(tb.perms != nullptr) && variant != 5;
+  // the default, up to images of 64 GiB (a launch has less than 2^32 threads)
+  if ((variant == 0 || variant == 4) && !grid_limit && lg == 14 && la.n_pieces < (1u << 22) - 16 &&
+      !(mostly_general && plan->all_contiguous)) {
+    if (!tb.perms) return launch_units<kAlone>(plan, pack, la, ma, stream);
+    return plan->listed ? launch_units<kListed>(plan, pack, la, ma, stream)
+                        : launch_units<kBeside>(plan, pack, la, ma, stream);
+  }
   if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
     return plan->listed ? launch_beside_blocks<kListed>(plan, pack, few, mostly_general, la, ma, grid_limit, stream)
                         : launch_beside_blocks<kBeside>(plan, pack, few, mostly_general, la, ma, grid_limit, stream);
@@ -1438,8 +1497,8 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
                 : launch_scatter<true, true>(plan, few, mostly_general, la, ma, grid_limit, stream);
   // default: non-temporal accesses, and the lean gather writes the image with "sc0 sc1 nt" buffer stores
   if (mostly_general && plan->all_contiguous && !grid_limit)
-    return pack ? launch_gather<true, true, true, 8, kAlone, false>(la, ma, grid_limit, stream)
-                : launch_scatter<true, true, kAlone, false>(plan, few, mostly_general, la, ma, grid_limit, stream);
+    return pack ? launch_gather<true, true, true, 8, kAlone, kMulti>(la, ma, grid_limit, stream)
+                : launch_scatter<true, true, kAlone, kMulti>(plan, few, mostly_general, la, ma, grid_limit, stream);
   if (!pack) return launch_scatter<true, true>(plan, few, mostly_general, la, ma, grid_limit, stream);
   if (mostly_general) return launch_gather<true, true, true, 6>(la, ma, grid_limit, stream);
   return launch_gather<true, true, true>(la, ma, grid_limit, stream);
