@@ -1073,13 +1073,13 @@ int launch_beside_blocks(const ds_plan *plan, bool pack, bool few, bool mostly_g
 }
 
 // ---- views with runs shorter than 16 bytes, in blocks through LDS (ds_perm.h) ---------------------------
-// Bound by the memory system's handling of 128-byte pieces: a block reads (scatter: writes) 128 bytes at a time
-// along a, one row of the tensor after the other, and 256 bytes and more along b.  Measured, gather / scatter
-// (two thirds of the working set in the last-level cache, launch included): bf16 4096 x 4120 transposed 18.0 / 16.8
-// us = 3.8 / 4.0 TB/s, odd extents 28 / 25 us, four transposed 4096 x 1024 experts 16.2 / 16.4 us, every second
-// fp32 column 10.9 / 14.4 us; unit by unit the table of such views of perf/cases.py took 460 / 524 us, now
-// 103 / 109.  Blocks are numbered along b first: along a first costs 15 % of the gather.  Five wavefronts per
-// SIMD hold the 16 loads of a thread without scratch; four and six measure 3 to 8 % slower.
+// Bound by HBM as far as both sides have whole lines (wide blocks, ds_perm.h: 4.7 TB/s on large transpositions), else by
+// the memory system's handling of parts of lines: every second column, six of every sixteen columns, whose lines the
+// scatter writes in part.  A block's descriptor is read as constant memory: read through ordinary pointers, again after
+// every store that might have changed it, the table of such views of perf/cases.py took 93.4 us instead of 79.3 (gather).
+// That table: unit by unit 460 / 524 us, in narrow blocks 100 / 108, now 79 / 98; channels-last 14.1 / 14.5, now 10.8 /
+// 13.1; every second fp32 column 10.9 / 14.4, now 10.1 / 12.8.  Blocks are numbered along b first: along a first costs
+// 15 % of the gather.  LDS has room for five work-groups per CU.
 struct PermArgs {
   const DsPerm *perms;
   const DsPermItem *items;  // the launch's first block
@@ -1090,15 +1090,17 @@ struct PermArgs {
 };
 
 template <typename E, typename W, bool PACK>
-__device__ __forceinline__ void move_perm_block(const DsPerm &d, const DsPermBlock &k, const PermArgs &a, uint8_t *lds) {
-  const uint32_t tid = threadIdx.x;
+__device__ __forceinline__ void move_perm_block(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, const PermArgs &a, uint8_t *lds) {
+  // opaque, so that nothing made of it is kept in registers (beyond 96: in scratch) across the loop over the blocks
+  uint32_t tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   if (PACK) {
     ds_perm_tensor_side<E, W, true>(d, k, lds, tid);
     __syncthreads();
     // rows that end inside a line leave its rest to another block: the line is better kept in the L2 until then
     // (bytes transposed into rows of 112: 16.1 us streaming, 12.1 us cached; rows of whole lines 16.2 and 17.7)
     // (Two loops: one loop with both stores is compiled to one store, the cached one.)
-    if (d.flags & kPermLines)
+    if (d.flags & (kPermLines | kPermWide))
       ds_perm_image_store<E>(d, k, lds, a.img, a.img_lo, tid, [](uint64_t p, const DsPermUnit &v) {
         st16_aligned<true>((uint8_t *)p, u32x4{v.w[0], v.w[1], v.w[2], v.w[3]});
       });
@@ -1123,8 +1125,8 @@ __global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
   for (uint32_t wi = blockIdx.x; wi < n; wi += gridDim.x) {
     const uint32_t i = a.xcd_span ? (wi & 7u) * a.xcd_span + (wi >> 3) : wi;
     if (i >= a.n_items) continue;
-    const DsPermItem item = a.items[i];
-    const DsPerm &d = a.perms[item.perm];
+    const DS_PERM_TABLE DsPermItem &item = ((const DS_PERM_TABLE DsPermItem *)(uintptr_t)a.items)[i];
+    const DS_PERM_TABLE DsPerm &d = ((const DS_PERM_TABLE DsPerm *)(uintptr_t)a.perms)[item.perm];
     DsPermBlock k;
     if (!ds_perm_block(d, item.tile, a.img_lo, a.img_hi, PACK, k)) continue;
     switch (d.flags & 0xFFu) {

@@ -17,22 +17,29 @@
 #include <stdint.h>
 #include <string.h>
 
+#include "ds_splice.h"
+
 #if defined(__HIPCC__)
 #define DS_PERM_FN __host__ __device__ __forceinline__
 #else
 #define DS_PERM_FN static inline
 #endif
+// The plan's tables do not change while a kernel runs: as constant memory they are read into scalar registers, once.
+// (Through ordinary pointers, which the stores of a block might change, the compiler reads a field again at every use.)
 #if defined(__HIP_DEVICE_COMPILE__)
 #define DS_PERM_GLOBAL __attribute__((address_space(1)))
+#define DS_PERM_TABLE __attribute__((address_space(4)))
 #else
 #define DS_PERM_GLOBAL
+#define DS_PERM_TABLE
 #endif
 #ifndef DS_PERM_TOUCH  // the CPU test's hook: (kind, address or LDS offset, bytes, alignment)
 #define DS_PERM_TOUCH(kind, at, n, align)
 #endif
 
 constexpr uint32_t kPermThreads = 256;
-constexpr uint32_t kPermLdsBytes = 21504;
+constexpr uint32_t kPermLdsBytes = 32000;  // five work-groups per CU
+constexpr uint32_t kPermNarrowBytes = 21504;  // of which the blocks that are not wide use so many
 constexpr uint32_t kPermMaxBatch = 4;      // dimensions beside a and b (DS_MAX_DIMS - 2)
 // Smaller views, and views whose blocks would hold less, stay with the general path, which takes 64 tiles at a time.
 // Gather of 20 000 square bf16 views, blocks / general path: of 512 bytes 62 / 40 us, of 1152 bytes 69 / 81, of 2048
@@ -40,7 +47,19 @@ constexpr uint32_t kPermMaxBatch = 4;      // dimensions beside a and b (DS_MAX_
 constexpr uint64_t kPermMinBytes = 1024;
 constexpr int kPermUnroll = 8;             // granules a thread has in flight
 
-enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11 };
+enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11,
+                  kPermWide = 1u << 12, kPermStream = 1u << 13 };
+
+// Wide blocks: views dense along a (16-byte loads of neighbours along a, transposed in registers), kPermWideA steps along a;
+// of each row 384 bytes where rows start at lines of the image, else up to 368, and a block writes the lines that start in
+// its part of a row.  LDS rows hold 496 bytes: 368 and the 127 up to the end of the last line.
+// What bounds a transposition is how much of a line one store has: a plain one of 8192 x 8256 16-bit elements with whole
+// lines and streaming stores takes 53 us, with 128 bytes that straddle two lines 69 (cached) or 115 (streaming).  Reading
+// up to 127 bytes of a row twice costs less (55 to 57 us).  Gather / scatter, the blocks of before (128 bytes by 256,
+// elements one by one through LDS) and these, us: bf16 8192 x 8216 68.5 / 73.9, now 56.1 / 57.8; 8208 x 8232 82.2 / 93.6,
+// now 63.6 / 85.6; bytes 48.2 / 54.0, now 28.5 / 47.2; 4096 x 4120 17.6 / 16.4, now 13.5 / 12.5; four transposed 4096 x
+// 1024 15.9 / 16.2, now 13.6 / 13.1.  Blocks of 64 x 880 bytes in 64 KB of LDS measure the same.
+constexpr uint32_t kPermWideA = 64, kPermWidePitch = 496, kPermWideRow = 368, kPermWideLines = 384, kPermLine = 128;
 
 // Steps along a of the usual block, by granule: at least a 128-byte line of the tensor.
 // Its columns are what LDS has room for: a thread's 16 granules (words of up to 4 bytes), all in flight at once.
@@ -64,7 +83,10 @@ struct DsPerm {
   uint32_t lanes_log2;        // threads that share a row on the image side
   uint32_t flags;             // log2(granule) | kPermAlongA (tensor side walked along a) | kPermFlat | kPermFull (the
                               // usual block) | kPermLines (rows are whole 128-byte lines of the image, or the block
-                              // is one piece of it, of which only the two ends are parts of lines)
+                              // is one piece of it, of which only the two ends are parts of lines) | kPermWide |
+                              // kPermStream (wide, and the columns of the tensor start at multiples of 64 bytes: the
+                              // scatter's stores stream.  Streaming / cached, us: fp32 4096 x 4099 21.2 / 29.3, bytes
+                              // 8192 x 8216 24.5 / 40.0; columns at multiples of 32 bytes 25.5 / 16.6, 109 / 86)
   uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
 static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
@@ -83,7 +105,8 @@ struct DsPermBlock {
   uint32_t lo, hi;     // image offsets to move (the call's range, cut to the view's whole units): multiples of 16
   uint32_t da, sa, sb; // distances as in DsPerm
   uint32_t na, nb;     // elements of the block
-  uint32_t nbx;        // gather: columns read, up to 15 bytes more than nb where the next block starts inside a unit
+  uint32_t nbx;        // gather: columns read, up to 15 bytes (wide blocks: 127) more than nb where the next block starts
+                       // inside a unit (a line)
   bool first_b, last_b;  // does the block hold the first / the last column of its rows?
   bool inside;         // do all its bytes lie in [lo, hi)?
 };
@@ -101,7 +124,7 @@ DS_PERM_FN uint32_t ds_perm_offset(uint64_t x, uint64_t from) {  // x - from, cu
 }
 
 // Block t of the view; false if none of it lies in image bytes [img_lo, img_hi).
-DS_PERM_FN bool ds_perm_block(const DsPerm &d, uint32_t t, uint64_t img_lo, uint64_t img_hi, bool pack, DsPermBlock &k) {
+DS_PERM_FN bool ds_perm_block(const DS_PERM_TABLE DsPerm &d, uint32_t t, uint64_t img_lo, uint64_t img_hi, bool pack, DsPermBlock &k) {
   const uint32_t rest = t / d.tiles_b, tb = t - rest * d.tiles_b;
   uint32_t batch = rest / d.tiles_a;
   const uint32_t ta = rest - batch * d.tiles_a;
@@ -126,6 +149,8 @@ DS_PERM_FN bool ds_perm_block(const DsPerm &d, uint32_t t, uint64_t img_lo, uint
   k.last_b = b0 + k.nb == d.eb;
   const bool units = ((k.skew | k.da | k.nb * d.run) & 15u) == 0;  // every row is whole 16-byte units
   k.nbx = pack && !k.last_b && !units ? ds_perm_min(k.nb + (14 + d.run) / d.run, d.eb - b0) : k.nb;
+  if (pack && (d.flags & (kPermWide | kPermLines)) == kPermWide)
+    k.nbx = ds_perm_min(k.nb + (kPermLine - 1) / d.run, d.eb - b0);
   k.lo = ds_perm_offset(img_lo > d.img ? img_lo : d.img, k.unit0);
   k.hi = ds_perm_offset(img_hi < d.end16 ? img_hi : d.end16, k.unit0);
   const uint32_t end = k.skew + (k.na - 1) * k.da + k.nbx * d.run;
@@ -136,9 +161,12 @@ DS_PERM_FN bool ds_perm_block(const DsPerm &d, uint32_t t, uint64_t img_lo, uint
 // Where row a of the block starts in the image, and in LDS: a row lies in LDS at the same position inside a
 // 16-byte unit as in the image.
 DS_PERM_FN uint32_t ds_perm_row_image(const DsPermBlock &k, uint32_t a) { return k.skew + a * k.da; }
-DS_PERM_FN uint32_t ds_perm_row_lds(const DsPerm &d, const DsPermBlock &k, uint32_t a) {
+DS_PERM_FN uint32_t ds_perm_row_start(const DS_PERM_TABLE DsPerm &d, uint32_t a) {
+  return a * d.pitch + (d.flags & kPermWide ? a / 4 * 16 : 0u);
+}
+DS_PERM_FN uint32_t ds_perm_row_lds(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint32_t a) {
   if (d.flags & kPermFlat) return ds_perm_row_image(k, a);
-  return a * d.pitch + (ds_perm_row_image(k, a) & 15u);
+  return ds_perm_row_start(d, a) + (ds_perm_row_image(k, a) & 15u);
 }
 
 // ---- tensor side: granules of type E -------------------------------------------------------------------
@@ -158,12 +186,13 @@ DS_PERM_FN T ds_perm_load(uint64_t base, uint32_t off, uint32_t align) {
   (void)align;
   return v;
 }
-template <typename T>
+template <typename T, bool NT = false>
 DS_PERM_FN void ds_perm_store(uint64_t base, uint32_t off, T v, uint32_t align) {
   DS_PERM_TOUCH('w', base + off, sizeof(T), align);
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef T any __attribute__((aligned(1)));
-  *(DS_PERM_GLOBAL any *)(base + off) = v;
+  if (NT) __builtin_nontemporal_store(v, (DS_PERM_GLOBAL any *)(base + off));
+  else *(DS_PERM_GLOBAL any *)(base + off) = v;
 #else
   memcpy((void *)(uintptr_t)(base + off), &v, sizeof(T));
 #endif
@@ -186,7 +215,7 @@ DS_PERM_FN void ds_perm_put(uint8_t *lds, uint32_t at, E v) {
 // room for whole batches: columns beyond the block are loaded from its last one and never used (the plan takes this
 // walk only where a whole batch of columns lies at 32-bit offsets).
 template <typename E, typename W, bool PACK>
-DS_PERM_FN void ds_perm_full(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+DS_PERM_FN void ds_perm_full(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   constexpr uint32_t S = (uint32_t)sizeof(E), V = (uint32_t)(sizeof(W) / sizeof(E));
   constexpr uint32_t lanes = ds_perm_full_a(S) / V, step = kPermThreads / lanes;
   constexpr int U = ds_perm_full_b(S) / step < 16 ? ds_perm_full_b(S) / step : 16;
@@ -226,7 +255,7 @@ DS_PERM_FN void ds_perm_full(const DsPerm &d, const DsPermBlock &k, uint8_t *lds
 
 // Walk along a, any block (d.ta is a power of two).
 template <typename E, bool PACK>
-DS_PERM_FN void ds_perm_along_a(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+DS_PERM_FN void ds_perm_along_a(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   const uint32_t n_cols = PACK ? k.nbx : k.nb;
   const uint32_t step = kPermThreads / d.ta, a = tid & (d.ta - 1), ac = ds_perm_min(a, k.na - 1);
   const uint32_t first = ac * k.sa, row = ds_perm_row_lds(d, k, ac);
@@ -260,7 +289,7 @@ DS_PERM_FN void ds_perm_along_a(const DsPerm &d, const DsPermBlock &k, uint8_t *
 
 // Walk along b: granule i of the block, rows one behind the other.
 template <typename E, bool PACK>
-DS_PERM_FN void ds_perm_along_b(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+DS_PERM_FN void ds_perm_along_b(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   const uint32_t K = d.run / (uint32_t)sizeof(E);
   const uint32_t per_row = (PACK ? k.nbx : k.nb) * K, total = k.na * per_row;
   const uint32_t m_row = ds_perm_magic(per_row > 1 ? per_row : 2), m_run = ds_perm_magic(K > 1 ? K : 2);
@@ -292,10 +321,143 @@ DS_PERM_FN void ds_perm_along_b(const DsPerm &d, const DsPermBlock &k, uint8_t *
   }
 }
 
+// ---- wide blocks, tensor side ----
+// A thread takes 8 columns of 16 bytes along a and transposes them in registers: its loads, its stores and its accesses
+// of LDS are 16 bytes each (bytes: LDS 8).  In LDS row a starts at ds_perm_row_start: an odd number of 16-byte words
+// apart, one more after every fourth, which puts the words that 16 neighbouring lanes write into different banks.
+typedef uint32_t DsPermQuad __attribute__((vector_size(16)));
+
+// LDS accesses of type T at ALIGN bytes
+template <typename T, uint32_t ALIGN>
+DS_PERM_FN T ds_perm_lds_load(const uint8_t *lds, uint32_t at) {
+  DS_PERM_TOUCH('l', at, sizeof(T), ALIGN);
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef T aligned_so __attribute__((aligned(ALIGN)));
+  return *(const aligned_so *)(lds + at);
+#else
+  T v;
+  memcpy(&v, lds + at, sizeof(T));
+  return v;
+#endif
+}
+template <typename T>
+DS_PERM_FN void ds_perm_lds_store(uint8_t *lds, uint32_t at, T v) {
+  DS_PERM_TOUCH('l', at, sizeof(T), sizeof(T));
+#if defined(__HIP_DEVICE_COMPILE__)
+  *(T *)(lds + at) = v;
+#else
+  memcpy(lds + at, &v, sizeof(T));
+#endif
+}
+
+// bytes of hi || lo (lo: bytes 0..3), picked by the four bytes of sel
+DS_PERM_FN uint32_t ds_perm_pick(uint32_t hi, uint32_t lo, uint32_t sel) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_perm(hi, lo, sel);
+#else
+  const uint64_t both = (uint64_t)hi << 32 | lo;
+  uint32_t r = 0;
+  for (int i = 0; i < 4; ++i) r |= (uint32_t)(both >> (8 * (sel >> (8 * i) & 7u)) & 0xFFu) << (8 * i);
+  return r;
+#endif
+}
+
+// Word w of row x of the transposed of `in`, rows of W words with elements of S bytes.
+template <uint32_t S, int W>
+DS_PERM_FN uint32_t ds_perm_word(const uint32_t (*in)[W], int x, int w) {
+  if (S == 8) return in[w / 2][2 * x + (w & 1)];
+  if (S == 4) return in[w][x];
+  if (S == 2) return ds_perm_pick(in[2 * w + 1][x / 2], in[2 * w][x / 2], x & 1 ? 0x07060302u : 0x05040100u);
+  const int c = x / 4;
+  const uint32_t pair = x & 2 ? 0x07030602u : 0x05010400u;  // two bytes of two rows
+  const uint32_t p = ds_perm_pick(in[4 * w + 1][c], in[4 * w][c], pair);
+  const uint32_t q = ds_perm_pick(in[4 * w + 3][c], in[4 * w + 2][c], pair);
+  return ds_perm_pick(q, p, x & 1 ? 0x07060302u : 0x05040100u);
+}
+
+// N words from any byte of LDS (S = 4, 8: any word)
+template <uint32_t S, int N>
+DS_PERM_FN void ds_perm_lds_words(const uint8_t *lds, uint32_t at, uint32_t *out) {
+  static_assert(N == 2 || N % 4 == 0, "whole quads, or two words");
+  const uint32_t from = at & ~3u;
+  uint32_t v[N + 1];
+  if (N == 2) {
+    v[0] = ds_perm_lds_load<uint32_t, 4>(lds, from);
+    v[1] = ds_perm_lds_load<uint32_t, 4>(lds, from + 4);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+      const DsPermQuad q = ds_perm_lds_load<DsPermQuad, 4>(lds, from + 16 * i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[4 * i + j] = q[j];
+    }
+  }
+  if (S >= 4) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = v[i];
+    return;
+  }
+  v[N] = ds_perm_lds_load<uint32_t, 4>(lds, from + 4 * N);
+#pragma unroll
+  for (int i = 0; i < N; ++i) out[i] = ds_align_bytes(v[i + 1], v[i], at & 3u);
+}
+
+// (two loops, each behind an opaque offset: else the compiler makes one of them, with cached stores)
+template <uint32_t S, bool NT>
+DS_PERM_FN void ds_perm_wide_columns(const uint32_t (*in)[2 * S], const DsPermBlock &k, uint32_t off, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (NT) asm volatile("" : "+v"(off));
+#endif
+#pragma unroll
+  for (int j = 0; j < 8; ++j, off += k.sb)
+    if (c + j < k.nb)
+      ds_perm_store<DsPermQuad, NT>(k.src0, off, DsPermQuad{ds_perm_word<S>(in, j, 0), ds_perm_word<S>(in, j, 1),
+                                                            ds_perm_word<S>(in, j, 2), ds_perm_word<S>(in, j, 3)}, S);
+}
+
+template <typename E, bool PACK>
+DS_PERM_FN void ds_perm_wide(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  constexpr uint32_t S = (uint32_t)sizeof(E), G = 16 / S, lanes = kPermWideA / G;
+  constexpr int W = 2 * S;  // words of 8 elements
+  const uint32_t a = tid % lanes * G, c = tid / lanes * 8, n_cols = PACK ? k.nbx : k.nb;
+  if (a >= k.na || c >= n_cols) return;
+  const uint32_t first = a * S + c * k.sb, last = a * S + (n_cols - 1) * k.sb;
+  if (PACK) {
+    uint32_t in[8][4], off = first;
+#pragma unroll
+    for (int j = 0; j < 8; ++j, off += k.sb) {  // columns beyond the block: its last one again
+      const DsPermQuad q = ds_perm_load<DsPermQuad>(k.src0, ds_perm_min(off, last), S);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) in[j][w] = q[w];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < G; ++i) {
+      const uint32_t at = ds_perm_row_start(d, a + i) + c * S;
+      if (S == 1) {
+        ds_perm_lds_store(lds, at, ds_perm_word<S>(in, i, 0) | (uint64_t)ds_perm_word<S>(in, i, 1) << 32);
+      } else {
+#pragma unroll
+        for (int u = 0; u < W; u += 4) {
+          if (u && c + u * 4 / S >= n_cols) break;
+          ds_perm_lds_store(lds, at + 4 * u, DsPermQuad{ds_perm_word<S>(in, i, u), ds_perm_word<S>(in, i, u + 1),
+                                                        ds_perm_word<S>(in, i, u + 2), ds_perm_word<S>(in, i, u + 3)});
+        }
+      }
+    }
+  } else {
+    uint32_t in[G][W];
+#pragma unroll
+    for (uint32_t i = 0; i < G; ++i) ds_perm_lds_words<S, W>(lds, ds_perm_row_lds(d, k, a + i) + c * S, in[i]);
+    if (d.flags & kPermStream) ds_perm_wide_columns<S, true>(in, k, first, c);
+    else ds_perm_wide_columns<S, false>(in, k, first, c);
+  }
+}
+
 template <typename E, typename W, bool PACK>
-DS_PERM_FN void ds_perm_tensor_side(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+DS_PERM_FN void ds_perm_tensor_side(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   constexpr uint32_t V = (uint32_t)(sizeof(W) / sizeof(E));
-  if (!(d.flags & kPermAlongA)) ds_perm_along_b<E, PACK>(d, k, lds, tid);
+  if ((d.flags & kPermWide) && (PACK || k.inside)) ds_perm_wide<E, PACK>(d, k, lds, tid);
+  else if (!(d.flags & kPermAlongA)) ds_perm_along_b<E, PACK>(d, k, lds, tid);
   else if (!(d.flags & kPermFull)) ds_perm_along_a<E, PACK>(d, k, lds, tid);
   else if (V > 1 && d.sa == sizeof(E) && k.na % V == 0 && (PACK || k.inside)) ds_perm_full<E, W, PACK>(d, k, lds, tid);
   else ds_perm_full<E, E, PACK>(d, k, lds, tid);
@@ -305,11 +467,17 @@ DS_PERM_FN void ds_perm_tensor_side(const DsPerm &d, const DsPermBlock &k, uint8
 // The bytes of the row a work-group writes (gather), relative to the start of the 16-byte unit that holds the
 // row's first byte.  Inside a row, blocks meet at unit boundaries, so a unit is written whole by one block;
 // only where a row starts or ends inside a unit are its two parts written by two rows.
-DS_PERM_FN void ds_perm_window(const DsPerm &d, const DsPermBlock &k, uint32_t unit, uint32_t skew, uint32_t &w0,
+DS_PERM_FN void ds_perm_window(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint32_t unit, uint32_t skew, uint32_t &w0,
                                uint32_t &w1) {
   if (d.flags & kPermFlat) {
     w0 = skew;
     w1 = skew + k.na * k.da;
+  } else if (d.flags & kPermWide) {
+    // ... at line boundaries of the image
+    const uint32_t read_end = skew + k.nbx * d.run, line = (uint32_t)(k.unit0 + unit) & (kPermLine - 1);
+    w0 = k.first_b ? skew : ds_perm_min(((line + skew + kPermLine - 1) & ~(kPermLine - 1)) - line, read_end);
+    w1 = k.last_b ? read_end
+                  : ds_perm_min(((line + skew + k.nb * d.run + kPermLine - 1) & ~(kPermLine - 1)) - line, read_end);
   } else {
     const uint32_t read_end = skew + k.nbx * d.run;
     w0 = k.first_b ? skew : ds_perm_min((skew + 15u) & ~15u, read_end);
@@ -325,11 +493,40 @@ struct DsPermUnit {
 };
 
 // Gather: LDS -> image, `img` pointing at image byte img_lo.
+// Wide blocks: 32 threads have room for a row's window, which is at most 31 units.
 template <typename E, typename StoreUnit>
-DS_PERM_FN void ds_perm_image_store(const DsPerm &d, const DsPermBlock &k, const uint8_t *lds, uint8_t *img, uint64_t img_lo,
+DS_PERM_FN void ds_perm_wide_store(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, const uint8_t *lds, uint64_t base, uint32_t tid,
+                                   StoreUnit store_unit) {
+  constexpr uint32_t S = (uint32_t)sizeof(E);
+#pragma unroll 2
+  for (uint32_t i = 0; i < kPermWideA / 8; ++i) {
+    const uint32_t a = tid / 32 + 8 * i;
+    if (a >= k.na) return;
+    const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = ds_perm_row_start(d, a);
+    uint32_t w0, w1;
+    ds_perm_window(d, k, unit, skew, w0, w1);
+    const uint32_t x = (w0 & ~15u) + 16u * (tid & 31u);
+    if (x >= w0 && x + 16u <= w1) {
+      DsPermUnit v;
+      ds_perm_lds_words<S, 4>(lds, row + x - skew, v.w);
+      DS_PERM_TOUCH('i', base + (unit + x), 16, 16);
+      store_unit(base + (unit + x), v);
+    } else {
+      const uint32_t x1 = ds_perm_min(w1, x + 16u);
+      for (uint32_t y = w0 > x ? w0 : x; y < x1; y += S) {
+        DS_PERM_TOUCH('i', base + (unit + y), S, S);
+        *(DS_PERM_GLOBAL E *)(base + (unit + y)) = ds_perm_get<E>(lds, row + y - skew);
+      }
+    }
+  }
+}
+
+template <typename E, typename StoreUnit>
+DS_PERM_FN void ds_perm_image_store(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, const uint8_t *lds, uint8_t *img, uint64_t img_lo,
                                     uint32_t tid, StoreUnit store_unit) {
   const uint32_t lanes = 1u << d.lanes_log2, rows = d.flags & kPermFlat ? 1u : k.na;
   const uint64_t base = (uint64_t)(uintptr_t)img + (k.unit0 - img_lo);
+  if (d.flags & kPermWide) return ds_perm_wide_store<E>(d, k, lds, base, tid, store_unit);
 #pragma unroll 1
   for (uint32_t a = tid >> d.lanes_log2; a < rows; a += kPermThreads >> d.lanes_log2) {
     const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = a * d.pitch;
@@ -356,13 +553,33 @@ DS_PERM_FN void ds_perm_image_store(const DsPerm &d, const DsPermBlock &k, const
 
 // Scatter: image -> LDS, every unit of the range that holds bytes of the block's rows.
 template <typename LoadUnit>
-DS_PERM_FN void ds_perm_image_load(const DsPerm &d, const DsPermBlock &k, uint8_t *lds, const uint8_t *img, uint64_t img_lo,
+DS_PERM_FN void ds_perm_image_load(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, const uint8_t *img, uint64_t img_lo,
                                    uint32_t tid, LoadUnit load_unit) {
   const uint32_t lanes = 1u << d.lanes_log2, flat = d.flags & kPermFlat, rows = flat ? 1u : k.na;
   const uint64_t base = (uint64_t)(uintptr_t)img + (k.unit0 - img_lo);
+  if ((d.flags & kPermWide) && k.inside) {  // a thread's units of all its rows at once
+    DsPermUnit v[kPermWideA / 8];
+#pragma unroll
+    for (uint32_t i = 0; i < kPermWideA / 8; ++i) {
+      const uint32_t a = ds_perm_min(tid / 32 + 8 * i, k.na - 1);
+      const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, x = 16u * (tid & 31u);
+      if (x < skew + k.nb * d.run) {
+        DS_PERM_TOUCH('j', base + (at - skew + x), 16, 16);
+        v[i] = load_unit(base + (at - skew + x));
+      }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kPermWideA / 8; ++i) {
+      const uint32_t a = ds_perm_min(tid / 32 + 8 * i, k.na - 1);
+      const uint32_t skew = ds_perm_row_image(k, a) & 15u, x = 16u * (tid & 31u);
+      if (x < skew + k.nb * d.run)
+        ds_perm_lds_store(lds, ds_perm_row_start(d, a) + x, DsPermQuad{v[i].w[0], v[i].w[1], v[i].w[2], v[i].w[3]});
+    }
+    return;
+  }
 #pragma unroll 1
   for (uint32_t a = tid >> d.lanes_log2; a < rows; a += kPermThreads >> d.lanes_log2) {
-    const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = a * d.pitch;
+    const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = ds_perm_row_start(d, a);
     const uint32_t end = skew + (flat ? k.na * k.da : k.nb * d.run);
     for (uint32_t x = 16u * (tid & (lanes - 1)); x < end; x += 16u * lanes) {
       if (unit + x < k.lo || unit + x >= k.hi) continue;
@@ -383,10 +600,11 @@ DS_PERM_FN void ds_perm_image_load(const DsPerm &d, const DsPermBlock &k, uint8_
 static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes, uint64_t run, uint32_t n_outer,
                                     const uint64_t *extent, const uint64_t *stride, DsPerm *d) {
   if (n_outer == 0 || run >= 16 || nbytes < kPermMinBytes) return 0;
-  uint64_t bits = src | run;
+  uint64_t bits = src | run, columns = src;  // `columns`: where those of a view dense along a can start
   for (uint32_t j = 0; j < n_outer; ++j) {
     if (extent[j] >= (1ull << 31)) return 0;
     bits |= stride[j];
+    if (stride[j] != run) columns |= stride[j];
   }
   memset(d, 0, sizeof(*d));
   d->src = src;
@@ -471,7 +689,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
     if (full) cols = ds_perm_full_b(g);
     d->pitch = (uint32_t)(cols * run + 30 + word - 1) / word * word;
     if (!(d->pitch / word & 1)) d->pitch += word;
-    if (flat || ta * d->pitch <= kPermLdsBytes) break;
+    if (flat || ta * d->pitch <= kPermNarrowBytes) break;
     if (full) full = false;
     else if (ta > 1) ta /= 2;
     else return 0;
@@ -481,15 +699,30 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   while (tb > 1 && (uint64_t)(tb + 16) * d->sb >= (1ull << 31)) tb /= 2, full = false;
   if ((uint64_t)(tb + 16) * d->sb >= (1ull << 31) || d->da >= (1ull << 31)) return 0;
   if (flat && tb != d->eb) return 0;
+  // Wide blocks, where they have whole 16 bytes along a, and rows of at least four lines
+  const bool lines = (image_bits & (kPermLine - 1)) == 0;
+  bool wide = along_a && !flat && run == g && d->sa == g && d->ea >= kPermWideA && d->ea % (16 / g) == 0 && row_bytes >= 512;
+  if (wide) {
+    const uint32_t most = (lines ? kPermWideLines : kPermWideRow) / g, n = (d->eb + most - 1) / most;
+    const uint32_t cols = lines ? most : (d->eb + n - 1) / n;
+    wide = (cols + kPermLine) * d->sb < (1ull << 31) && kPermWideA * d->da < (1ull << 31);
+    if (wide) {
+      ta = kPermWideA;
+      tb = cols;
+      full = false;
+      d->pitch = kPermWidePitch;
+    }
+  }
   if ((uint64_t)(ta < d->ea ? ta : d->ea) * tb * run < kPermMinBytes) return 0;
   d->ta = ta;
   d->tb = tb;
   d->tiles_a = (d->ea + ta - 1) / ta;
   d->tiles_b = (d->eb + tb - 1) / tb;
   const uint32_t units = (uint32_t)((flat ? kPermThreads * 16 : tb * run) / 16);
-  while (d->lanes_log2 < 8 && (2u << d->lanes_log2) <= units) ++d->lanes_log2;
+  while (d->lanes_log2 < 8 && (2u << d->lanes_log2) <= units) ++d->lanes_log2;  // (not used by wide blocks inside the range)
   d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
-             (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u);
+             (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
+             (wide && (columns & 63) == 0 ? kPermStream : 0u);
   const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
   return tiles < (1u << 31) ? (uint64_t)tiles : 0;
 }
@@ -520,9 +753,9 @@ static inline void ds_perm_range(const DsPerm &d, uint64_t img_lo, uint64_t img_
   const uint64_t at_hi = row_hi / d.ea * d.tiles_a + row_hi % d.ea / d.ta;
   *first = at_lo * group;
   *last = (at_hi + 1) * group;
-  if (row_lo == row_hi && group == d.tiles_b) {  // inside one row: a block's units can reach 15 bytes into the next block
-    const uint64_t bytes = (uint64_t)d.tb * d.run, from = lo - row_lo * d.da;
-    *first += (from < 15 ? 0 : from - 15) / bytes;
+  if (row_lo == row_hi && group == d.tiles_b) {  // inside one row: a block's units (lines) can reach into the next block
+    const uint64_t bytes = (uint64_t)d.tb * d.run, from = lo - row_lo * d.da, reach = d.flags & kPermWide ? kPermLine - 1 : 15;
+    *first += (from < reach ? 0 : from - reach) / bytes;
     *last = at_hi * group + (hi - row_hi * d.da) / bytes + 1;
   }
 }

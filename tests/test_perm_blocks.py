@@ -120,6 +120,25 @@ def test_blocks_move_exactly_the_view(host, k):
         assert _check(host, dtype, shape, strides, shift, at, rng) > 0
 
 
+# views in wide blocks: the smallest, rows that are whole lines of the image and rows that are not, the last block of a row
+# and of the steps along a nearly empty or full, rows at every place in a unit, batches on either side of a
+WIDE = [
+    ("bf16", (64, 256), (1, 64)), ("bf16", (72, 257), (1, 72)), ("bf16", (136, 1031), (1, 140)), ("bf16", (64, 384), (1, 64)),
+    ("bf16", (120, 577), (1, 121)), ("u8", (64, 512), (1, 64)), ("u8", (80, 1031), (1, 81)), ("u8", (144, 737), (1, 144)),
+    ("f32", (64, 128), (1, 64)), ("f32", (68, 129), (1, 68)), ("f32", (132, 277), (1, 133)), ("i64", (64, 64), (1, 64)),
+    ("i64", (66, 65), (1, 67)), ("i64", (130, 187), (1, 130)), ("bf16", (3, 64, 300), (64 * 300, 1, 64)),
+    ("f32", (70, 3, 192), (576, 1, 3)), ("f32", (72, 3, 192), (1, 72, 216)), ("u8", (2, 64, 3, 514), (99000, 1, 32896, 64)),
+]
+
+
+@pytest.mark.parametrize("k", range(len(WIDE)))
+def test_wide_blocks_move_exactly_the_view(host, k):
+    dtype, shape, strides = WIDE[k]
+    rng = np.random.default_rng(k)
+    for shift, at in ((0, 0), (1, 16), (3, 4096), (0, 80)):
+        assert _check(host, dtype, shape, strides, shift, at, rng) > 0
+
+
 @pytest.mark.parametrize("dtype,shape,strides", [
     ("bf16", (64, 64), (1, 20000001)), ("bf16", (64, 104), (1, 20000001)), ("u8", (128, 32), (1, 50000001)),
     ("f32", (64, 20), (1, 18000001)), ("i64", (32, 50), (1, 9000001))])
@@ -253,6 +272,42 @@ def test_gather_and_scatter_of_permuted_views(chunk_bytes):
             dw.close()
     finally:
         ds.ds_config_set("chunk_bytes", old)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gather_and_scatter_in_wide_blocks(shift):
+    """Views in wide blocks with columns at multiples of 64 bytes (shift 0: the scatter's stores stream) and at odd
+    elements, whole and in ranges that cut blocks."""
+    import paper_2601_16956_amd as ds
+    import gpu_util as gu
+    rng = np.random.default_rng(6)
+    big = [("bf16", (1024, 1531), (1, 1024)), ("f32", (512, 1111), (1, 512)), ("u8", (704, 1901), (1, 704)),
+           ("i64", (130, 513), (1, 136)), ("bf16", (2, 512, 768), (512 * 768, 1, 512))]
+    shards, at = [], 0
+    for k, (dtype, shape, strides) in enumerate(WIDE + big):
+        es = DTYPES[dtype][1]
+        start = -(-at // 256) * 256 + es * shift
+        shards.append(Shard(f"w{k}", dtype, shape, strides, start, k))
+        at = start + (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    w = Workload("wide", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print(f"[case] wide blocks shift={shift} image={dw.total}", flush=True)
+        cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, dw.total // 16, 9)) + [dw.total]
+        ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+        for lo, hi in [(0, dw.total)] + ranges:
+            assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        for parts in ([(0, dw.total)], ranges):
+            dw.arena.fill_(0x5A)
+            for lo, hi in parts:
+                dw.unpack(want, lo, hi)
+            assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+    finally:
+        dw.close()
 
 
 @pytest.mark.gpu
