@@ -920,8 +920,9 @@ __device__ __forceinline__ void cut_chunk_tiles(const MoveArgs &a, uint64_t c, u
 //   scatter, UNROLL 2 and WAVES 6 (a piece of 8 KiB, 48 KB in flight), or as the gather: see launch_scatter.
 // PATH kMulti is the instantiation for plans of contiguous shards only, most chunks of which hold several of them:
 // no chunk takes the general path, and multi_chunk's registers (gather 78, scatter 32) allow six and eight wavefronts.
-// 24 000 tensors of 16 bytes to 16 KiB (58 MB): gather 25.2 us against 29.1 through the general path, scatter 24.2
-// against 26.6.
+// 24 000 tensors of 16 bytes to 16 KiB (58 MB), with non-temporal loads: gather 24.7 us against 29.1 through the general
+// path, scatter 23.9 against 26.6; with ordinary loads (kCachedBytes) 19.1 and 18.8, a plain copy of it takes 16.6.  One
+// unit per thread 19.8 and 21.0 (147 MB: 56.4 and 55.2, as it is 54.0 and 55.4), ordinary stores 26.6 and 26.9.
 enum : int { kEvery = 0, kMulti = 1 };
 // Does a work-group of so many units take whole chunks (else pieces of them)?
 constexpr bool takes_whole_chunks(bool pack, int units) { return units >= (pack ? 512 : 1024); }
@@ -1498,9 +1499,13 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
     return pack ? launch_gather<true, true, false>(la, ma, grid_limit, stream)
                 : launch_scatter<true, true>(plan, few, mostly_general, la, ma, grid_limit, stream);
   // default: non-temporal accesses, and the lean gather writes the image with "sc0 sc1 nt" buffer stores
-  if (mostly_general && plan->all_contiguous && !grid_limit)
+  if (mostly_general && plan->all_contiguous && !grid_limit) {
+    if (plan->total_bytes <= kCachedBytes)
+      return pack ? launch_gather<false, true, true, 8, kAlone, kMulti>(la, ma, grid_limit, stream)
+                  : launch_scatter<false, true, kAlone, kMulti>(plan, few, mostly_general, la, ma, grid_limit, stream);
     return pack ? launch_gather<true, true, true, 8, kAlone, kMulti>(la, ma, grid_limit, stream)
                 : launch_scatter<true, true, kAlone, kMulti>(plan, few, mostly_general, la, ma, grid_limit, stream);
+  }
   if (!pack) return launch_scatter<true, true>(plan, few, mostly_general, la, ma, grid_limit, stream);
   if (mostly_general) return launch_gather<true, true, true, 6>(la, ma, grid_limit, stream);
   return launch_gather<true, true, true>(la, ma, grid_limit, stream);

@@ -61,3 +61,24 @@ def test_small_contiguous_tensors(chunk_bytes, align, sizes, holes):
             dw.close()
     finally:
         ds.ds_config_set("chunk_bytes", old)
+
+
+def test_images_beyond_the_size_moved_with_ordinary_loads():
+    """The same path in an image of more than 64 MiB, up to which the loads are ordinary ones."""
+    import gpu_util as gu
+    rng = np.random.default_rng(8)
+    shards, offsets, span = _table([int(x) for x in rng.integers(7000, 9500, 8400)], 16, rng, False)
+    w = Workload("small", 16, 0, rng.integers(0, 256, size=span + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w, offsets=offsets)
+    dw = gu.DeviceWorkload(w, offsets=offsets)
+    try:
+        print(f"[case] small tensors, image of {dw.total}", flush=True)
+        assert dw.total > 64 << 20 and dw.info["n_general_chunks"] * 2 > dw.info["n_chunks"]
+        assert gu.first_mismatch(dw.pack(), want) is None
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        dw.arena.fill_(0x5A)
+        dw.unpack(want, 0, dw.total)
+        assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+    finally:
+        dw.close()
