@@ -1119,6 +1119,21 @@ __device__ __forceinline__ void move_perm_block(const DS_PERM_TABLE DsPerm &d, c
   }
 }
 
+// Item i of a launch: one block.
+template <bool PACK>
+__device__ __forceinline__ void move_perm_item(const PermArgs &a, uint32_t i, uint8_t *lds) {
+  const DS_PERM_TABLE DsPermItem &item = ((const DS_PERM_TABLE DsPermItem *)(uintptr_t)a.items)[i];
+  const DS_PERM_TABLE DsPerm &d = ((const DS_PERM_TABLE DsPerm *)(uintptr_t)a.perms)[item.perm];
+  DsPermBlock k;
+  if (!ds_perm_block(d, item.tile, a.img_lo, a.img_hi, PACK, k)) return;
+  switch (d.flags & 0xFFu) {
+    case 0: move_perm_block<uint8_t, uint32_t, PACK>(d, k, a, lds); break;
+    case 1: move_perm_block<uint16_t, uint32_t, PACK>(d, k, a, lds); break;
+    case 2: move_perm_block<uint32_t, uint32_t, PACK>(d, k, a, lds); break;
+    default: move_perm_block<uint64_t, uint64_t, PACK>(d, k, a, lds); break;
+  }
+}
+
 template <bool PACK>
 __global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t s_block[kPermLdsBytes];
@@ -1126,18 +1141,60 @@ __global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
   for (uint32_t wi = blockIdx.x; wi < n; wi += gridDim.x) {
     const uint32_t i = a.xcd_span ? (wi & 7u) * a.xcd_span + (wi >> 3) : wi;
     if (i >= a.n_items) continue;
-    const DS_PERM_TABLE DsPermItem &item = ((const DS_PERM_TABLE DsPermItem *)(uintptr_t)a.items)[i];
-    const DS_PERM_TABLE DsPerm &d = ((const DS_PERM_TABLE DsPerm *)(uintptr_t)a.perms)[item.perm];
-    DsPermBlock k;
-    if (!ds_perm_block(d, item.tile, a.img_lo, a.img_hi, PACK, k)) continue;
-    switch (d.flags & 0xFFu) {
-      case 0: move_perm_block<uint8_t, uint32_t, PACK>(d, k, a, s_block); break;
-      case 1: move_perm_block<uint16_t, uint32_t, PACK>(d, k, a, s_block); break;
-      case 2: move_perm_block<uint32_t, uint32_t, PACK>(d, k, a, s_block); break;
-      default: move_perm_block<uint64_t, uint64_t, PACK>(d, k, a, s_block); break;
-    }
+    move_perm_item<PACK>(a, i, s_block);
     __syncthreads();  // the block in LDS has been used
   }
+}
+
+constexpr uint32_t kMixedChunks = 4096;  // other chunks up to which blocks and chunks share a launch
+
+// Blocks and the plan's other chunks in one launch: first the blocks, then the chunks, 16 KiB per work-group, which fill
+// the chip while the last blocks end.  A second launch costs 3 us and the ramps between the two; in exchange the chunks move at
+// five wavefronts per SIMD, four units per thread.  One launch / two, us, gather and scatter: the views of perf/cases.py
+// (157 MB, 2048 chunks beside the blocks) 75.3 / 79.4 and 97.0 / 98.5, the same at a quarter of the columns 9.0 / 11.8 and
+// 9.7 / 13.7, at a sixteenth 6.9 / 9.9; one transposed matrix of 32 KB to 8 MB beside 32 MB 14.5 to 16.7 / 16.3 to 18.9;
+// beside 100 MB (6400 chunks) 40.9 / 41.5 and 40.3 / 39.3; 32 MB beside 400 MB 153.8 / 142.8 and 152.8 / 145.7.
+template <bool PACK, bool NTL>
+__global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsChunkRec *recs, const uint32_t *ids,
+                                                          uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
+  __shared__ union {
+    __attribute__((aligned(16))) uint8_t block[kPermLdsBytes];
+    GenLds tab;
+  } s;
+  uint32_t wi = blockIdx.x;
+  if (wi < a.xcd_span * 8u) {
+    const uint32_t i = (wi & 7u) * a.xcd_span + (wi >> 3);
+    if (i < a.n_items) move_perm_item<PACK>(a, i, s.block);
+    return;
+  }
+  wi -= a.xcd_span * 8u;
+  uint64_t c;
+  uint32_t t0, t1;
+  if (wi < span * 8u) {
+    const uint32_t cm = (wi & 7u) * span + (wi >> 3);
+    if (cm >= n) return;
+    const DsChunkRec r = load_rec(recs, c_lo + cm);
+    c = load_id(ids, c_lo + cm);
+    if ((r.kind & 0xFFu) < DS_CHUNK_GENERAL) {
+      lean_move<PACK, 256, 4, NTL, true, PACK>(r, a.img + ((c << 14) - a.img_lo), 0);
+      return;
+    }
+    t0 = r.tile;
+    t1 = r.tile + r.col0;
+  } else {
+    c = ma.extra[wi - span * 8u];
+    cut_chunk_tiles(ma, c, t0, t1);
+  }
+  general_chunk<PACK, 256, 1, NTL, true, PACK, kListed, true>(ma, c, 0, t0, t1, &s.tab);
+}
+
+template <bool PACK, bool NTL>
+int launch_mixed(const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  const uint32_t span = (la.n_pieces + 7) / 8;
+  hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL>), dim3(a.xcd_span * 8 + span * 8 + ma.n_extra), dim3(256), 0, stream, a,
+                     la.recs, la.ids, la.n_pieces, span, la.c_lo, ma);
+  DS_HIP_TRY(hipGetLastError());
+  return DS_OK;
 }
 
 int launch_perm(bool pack, const PermArgs &a, uint32_t grid_limit, hipStream_t stream) {
@@ -1430,18 +1487,16 @@ struct DeviceTables {
   const DsChunkRec *rest_recs;
 };
 
-// The chunks of the range, lean and general, in one launch.
-int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_t *img, uint64_t img_lo,
-                     uint64_t img_hi, uint32_t grid_limit, hipStream_t stream) {
+// What the launch of the range's chunks, lean and general, takes.
+void chunk_args(const ds_plan *plan, const DeviceTables &tb, uint8_t *img, uint64_t img_lo, uint64_t img_hi, LeanArgs &la,
+                MoveArgs &ma) {
   const uint32_t lg = plan->chunk_log2;
   const uint64_t C = (uint64_t)1 << lg;
   const uint64_t n_total = plan->n_chunks();
-  if (img_hi > plan->total_bytes || img_lo >= img_hi) return DS_ERANGE;
   // whole chunks inside the range: one work item each, lean or general by their record ...
   uint64_t w_lo = (img_lo + C - 1) >> lg;
   uint64_t w_hi = img_hi >> lg;
   if (img_hi == plan->total_bytes) w_hi = n_total;  // the last chunk may be short; its record says 'general' then
-  LeanArgs la;
   la.recs = tb.recs;
   la.ids = nullptr;
   la.img = img;
@@ -1459,7 +1514,6 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
   }
   la.xcd_span = 0;  // launch_pieces makes pieces of the chunks and orders them
   // ... and the one or two chunks cut by the ends of the range, clipped by the general path
-  MoveArgs ma;
   ma.tiles = tb.tiles;
   ma.hot = tb.hot;
   ma.first_tile = tb.first_tile;
@@ -1479,6 +1533,12 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, uint8_
     if (c_first < w_lo) ma.extra[ma.n_extra++] = (uint32_t)c_first;
     if (c_last >= w_hi) ma.extra[ma.n_extra++] = (uint32_t)c_last;
   }
+}
+
+// The chunks of the range in one launch.
+int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, const LeanArgs &la, const MoveArgs &ma,
+                  uint32_t grid_limit, hipStream_t stream) {
+  const uint32_t lg = plan->chunk_log2;
   const uint64_t variant = ds_cfg_variant();
   const bool few = variant == 5 || grid_limit;
   const bool mostly_general = plan->mostly_general(tb.perms != nullptr) && variant != 5;
@@ -1515,26 +1575,38 @@ int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *i
                      uint32_t grid_limit, hipStream_t stream) {
   const uint64_t variant = ds_cfg_variant();
   if (variant == 1 || variant == 2 || variant == 5) tb.perms = nullptr;
-  const int rc = launch_chunks(plan, tb, pack, img, img_lo, img_hi, grid_limit, stream);
-  if (rc != DS_OK || !tb.perms) return rc;
+  if (img_hi > plan->total_bytes || img_lo >= img_hi) return DS_ERANGE;
+  LeanArgs la;
+  MoveArgs ma;
+  chunk_args(plan, tb, img, img_lo, img_hi, la, ma);
+  if (!tb.perms) return launch_chunks(plan, tb, pack, la, ma, grid_limit, stream);
   // the views that are moved in blocks and have a whole unit in the range; of the first and the last the blocks in it
   const auto v0 = std::upper_bound(plan->perms.begin(), plan->perms.end(), img_lo,
                                    [](uint64_t at, const DsPerm &d) { return at < d.end16; });
   const auto v1 = std::lower_bound(v0, plan->perms.end(), img_hi, [](const DsPerm &d, uint64_t at) { return d.img < at; });
-  if (v0 == v1) return DS_OK;
-  uint64_t first, last, other;
-  ds_perm_range(*v0, img_lo, img_hi, &first, &other);
-  ds_perm_range(*(v1 - 1), img_lo, img_hi, &other, &last);
-  first += plan->perm_first[v0 - plan->perms.begin()];
-  last += plan->perm_first[v1 - 1 - plan->perms.begin()];
-  PermArgs a;
-  a.perms = tb.perms;
-  a.items = tb.perm_items + first;
-  a.n_items = (uint32_t)(last - first);
-  a.xcd_span = variant == 3 ? 0 : (a.n_items + 7) / 8;
-  a.img = img;
-  a.img_lo = img_lo;
-  a.img_hi = img_hi;
+  PermArgs a = {};
+  if (v0 != v1) {
+    uint64_t first, last, other;
+    ds_perm_range(*v0, img_lo, img_hi, &first, &other);
+    ds_perm_range(*(v1 - 1), img_lo, img_hi, &other, &last);
+    first += plan->perm_first[v0 - plan->perms.begin()];
+    last += plan->perm_first[v1 - 1 - plan->perms.begin()];
+    a.perms = tb.perms;
+    a.items = tb.perm_items + first;
+    a.n_items = (uint32_t)(last - first);
+    a.xcd_span = variant == 3 ? 0 : (a.n_items + 7) / 8;
+    a.img = img;
+    a.img_lo = img_lo;
+    a.img_hi = img_hi;
+    if (plan->listed && (variant == 0 || variant == 4) && !grid_limit && plan->chunk_log2 == 14 &&
+        la.n_pieces <= kMixedChunks && a.n_items < kMaxGrid / 2) {
+      if (plan->total_bytes <= kCachedBytes)
+        return pack ? launch_mixed<true, false>(a, la, ma, stream) : launch_mixed<false, false>(a, la, ma, stream);
+      return pack ? launch_mixed<true, true>(a, la, ma, stream) : launch_mixed<false, true>(a, la, ma, stream);
+    }
+  }
+  const int rc = launch_chunks(plan, tb, pack, la, ma, grid_limit, stream);
+  if (rc != DS_OK || v0 == v1) return rc;
   return launch_perm(pack, a, grid_limit, stream);
 }
 

@@ -311,6 +311,43 @@ def test_gather_and_scatter_in_wide_blocks(shift):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("beside", [1 << 20, 62 << 20, 70 << 20])
+def test_blocks_beside_other_chunks(beside):
+    """Blocks and the other chunks in one launch (up to 4096 such chunks; images on both sides of the size read with
+    ordinary loads) and in two: tensor ends, rows, padding and views of several dimensions among the other chunks."""
+    import gpu_util as gu
+    rng = np.random.default_rng(beside >> 20)
+    views = [("bf16", (1024, 1531), (1, 1024)), ("u8", (300, 33), (1, 301)), ("u8", (41, 513), (700, 1)),
+             ("u8", (beside // 3 + 7,), (1,)), ("f32", (333, 111), (222, 2)), ("i64", (3, 4, 5, 9), (900, 200, 20, 1)),
+             ("bf16", (beside // 6 // 1000, 1000), (1012, 1)), ("f32", (512, 4099), (1, 512)), ("bf16", (3,), (1,)),
+             ("u8", (beside // 3 + 5,), (1,)), ("u8", (80, 1031), (1, 81)), ("bf16", (11, 7), (1, 13))]
+    shards, at = [], 0
+    for k, (dtype, shape, strides) in enumerate(views):
+        es = DTYPES[dtype][1]
+        at = -(-at // 64) * 64 + es * int(rng.integers(0, 3))
+        shards.append(Shard(f"b{k}", dtype, shape, strides, at, k))
+        at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    w = Workload("beside", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print(f"[case] blocks beside {beside} bytes, image={dw.total}", flush=True)
+        cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, dw.total // 16, 5)) + [dw.total]
+        ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+        for lo, hi in [(0, dw.total)] + ranges:
+            assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        for parts in ([(0, dw.total)], ranges):
+            dw.arena.fill_(0x5A)
+            for lo, hi in parts:
+                dw.unpack(want, lo, hi)
+            assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+    finally:
+        dw.close()
+
+
+@pytest.mark.gpu
 def test_allocation_free_gather_without_room_for_the_block_tables():
     """Tables that fit the static array only without those of the blocks: the general path moves the views then."""
     import paper_2601_16956_amd as ds
