@@ -229,7 +229,9 @@ int ds_unpack(const ds_plan *plan, const void *src_dev, uint64_t img_lo, uint64_
  * plan's tables.  ds_pack reads them from the device allocation ds_plan_create
  * made; this call copies them (on `stream`, ahead of the kernel) into a static
  * device array of DS_PACK_NOALLOC_TABLE_BYTES that the library holds on every
- * GPU it runs on until the process ends, and calls neither hipMalloc nor
+ * GPU it runs on until the process ends (plans of up to 64 contiguous shards at
+ * multiples of 16 bytes hand it to the kernel in its arguments instead, and use
+ * no array), and calls neither hipMalloc nor
  * hipFree nor anything else that allocates.  `plan` may therefore be a
  * DS_PLAN_HOST_ONLY plan, whose creation touches no device either.
  * Limit: the tables (168 bytes per non-empty shard, 36 bytes per work-group
@@ -673,9 +675,8 @@ int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_t block_byt
  *                   under it do not mark chunks for the gather's aligned-load route (tensors at
  *                   addresses that are not multiples of 16 are then read with unaligned loads),
  *                   5 = every launch is of work-groups of 16 KiB at four wavefronts per SIMD that know all
- *                   kinds of chunks (by default the scatter's take 8 KiB at six, a plan of mostly general
- *                   chunks gets five for the gather, and plans of contiguous shards and views with runs
- *                   shorter than 16 bytes have kernels of their own)
+ *                   kinds of chunks (by default work-groups take 4 KiB at eight, and plans of small
+ *                   contiguous shards and views with runs shorter than 16 bytes have kernels of their own)
  *   "grid_limit"    work-groups per launch of ds_pack / ds_unpack (each then walks several chunks);
  *                   0 = one per chunk or part of one (default).  Engines have their own pack_grid_limit
  *   "drop_pinned_cache"   (set only) a non-zero value frees the pinned ring and the device staging the

@@ -153,9 +153,10 @@ struct ds_plan {
     const uint64_t left_out = blocks ? n_perm_chunks : 0;
     return (n_general - left_out) * 2 > n_chunks() - left_out;
   }
-  // Is a scatter of `chunks` whole chunks of 16 KiB launched in pieces of 8 KiB, six wavefronts per SIMD instead of
-  // four?  Measured over tables of one kind, pieces / whole, us.  Many rounds: pieces (7B rank 490 / 504).  Fewer chunks
-  // than give each CU two work-groups: pieces (383 chunks of rows of 1000 bytes 6.2 / 7.2, one tensor 4.3 / 4.3).
+  // Is a scatter of `chunks` whole chunks of 16 KiB by ds_move_kernel launched in pieces of 8 KiB, six wavefronts per
+  // SIMD instead of four?  (Images of 64 GiB and more, and the options for comparison: every other default call
+  // launches ds_unit_kernel, which takes 4 KiB at eight.)  Measured over tables of one kind, pieces / whole, us.
+  // Many rounds: pieces (7B rank 490 / 504).  Fewer chunks than give each CU two work-groups: pieces (383 chunks of rows of 1000 bytes 6.2 / 7.2, one tensor 4.3 / 4.3).
   // Between them, by what the chunks hold:
   //   one in sixteen or more views of several outer dimensions, whose units move one by one: pieces at any size (443
   //     chunks 7.4 / 9.3, 1082 13.0 / 15.6, 4889 33.7 / 36.2);
