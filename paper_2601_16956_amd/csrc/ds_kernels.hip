@@ -1368,35 +1368,50 @@ __global__ __launch_bounds__(kScanThreads) void ds_exclusive_scan_kernel(const u
   if (tid == 0) pos[n] = carry;
 }
 
-// Kept blocks go to their slots in `packed`, one behind the other.  One work-group takes 1024 units (16 KiB), which
-// lie in one block (the block size is a power of two of at least 16 KiB).
-constexpr uint32_t kStripeLog2 = 6;  // work-groups
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void ds_pack_kept_blocks_kernel(
+// Kept blocks go to their slots in `packed`, one behind the other.  One work-group takes 256 x UNROLL units (4 or 16
+// KiB), which lie in one block (the block size is a power of two of at least 16 KiB).
+// Bound by HBM.  One unit per thread at eight wavefronts per SIMD, as in ds_unit_kernel (1 GiB of which 30 % is constant,
+// all of ds_image_compress: 305.6 us with four units at four wavefronts, now 299.3); launches of that shape have room for
+// images of up to 64 GiB, larger ones take four units per thread.
+constexpr uint32_t kStripeUnitsLog2 = 16;
+template <int UNROLL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_pack_kept_blocks_kernel(
     const u32x4 *__restrict__ img, uint64_t n_units, uint32_t units_per_block_log2, const uint32_t *__restrict__ keep,
     const uint32_t *__restrict__ pos, u32x4 *__restrict__ packed) {
-  const uint32_t n_groups = (uint32_t)((n_units + 1023) / 1024);
+  constexpr uint32_t kUnits = 256 * UNROLL, kGroupsLog2 = kStripeUnitsLog2 - __builtin_ctz(kUnits);
   // an XCD takes every eighth stripe of 1 MiB: neighbours share an L2, and runs of constant blocks, which leave
-  // nothing to do, are dealt evenly (241 us; one contiguous eighth per XCD 271 us)
+  // nothing to do, are dealt evenly (four units per thread 241 us; one contiguous eighth per XCD 271 us)
   const uint32_t i8 = blockIdx.x >> 3;
-  const uint32_t g = ((i8 >> kStripeLog2) * 8 + (blockIdx.x & 7u)) << kStripeLog2 | (i8 & ((1u << kStripeLog2) - 1));
-  if (g >= n_groups) return;
-  const uint64_t first = (uint64_t)g * 1024;
+  const uint32_t g = ((i8 >> kGroupsLog2) * 8 + (blockIdx.x & 7u)) << kGroupsLog2 | (i8 & ((1u << kGroupsLog2) - 1));
+  const uint64_t first = (uint64_t)g * kUnits;
+  if (first >= n_units) return;
   const uint64_t left = n_units - first;
-  const uint32_t mine = left < 1024 ? (uint32_t)left : 1024u;
+  const uint32_t mine = left < kUnits ? (uint32_t)left : kUnits;
   const uint64_t block = first >> units_per_block_log2;
   const uint64_t in_block = first - (block << units_per_block_log2);
   const uint32_t slot = pos[block];
   if (!keep[block]) return;
-  u32x4 x[4];
+  u32x4 x[UNROLL];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < UNROLL; ++i)
     if (threadIdx.x + 256u * i < mine) x[i] = __builtin_nontemporal_load(img + first + threadIdx.x + 256 * i);
   __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(packed + ((uint64_t)slot << units_per_block_log2) + in_block,
                                                                  0, (int)(mine * 16u), 0x00020000);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < UNROLL; ++i)
     if (threadIdx.x + 256u * i < mine)
       __builtin_amdgcn_raw_buffer_store_b128(x[i], out, (int)(16u * (threadIdx.x + 256u * i)), 0, kStorePolicySc0Sc1Nt);
+}
+
+template <int UNROLL>
+int launch_pack_kept(const u32x4 *img, uint64_t n_units, uint32_t upb_log2, const uint32_t *keep, const uint32_t *pos,
+                     u32x4 *packed, hipStream_t stream) {
+  const uint64_t stripes = ((n_units + (1u << kStripeUnitsLog2) - 1) >> kStripeUnitsLog2);
+  const uint32_t grid = (uint32_t)((stripes + 7) / 8 * 8 << (kStripeUnitsLog2 - __builtin_ctz(256 * UNROLL)));
+  hipLaunchKernelGGL(ds_pack_kept_blocks_kernel<UNROLL>, dim3(grid), dim3(256), 0, stream, img, n_units, upb_log2, keep, pos,
+                     packed);
+  DS_HIP_TRY(hipGetLastError());
+  return DS_OK;
 }
 
 }  // namespace
@@ -1419,7 +1434,6 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   const uint32_t ups_log2 = upb_log2 < kSegmentUnitsLog2 ? upb_log2 : kSegmentUnitsLog2;
   const uint64_t segments = (n_units + (1ull << ups_log2) - 1) >> ups_log2;
   const dim3 seg_grid((uint32_t)segments);
-  const uint64_t stripes = (((groups + (1u << kStripeLog2) - 1) >> kStripeLog2) + 7) / 8 * 8;
   if (ups_log2 == upb_log2) {
     hipLaunchKernelGGL(ds_constant_segments_kernel<true>, seg_grid, dim3(256), 0, st, (const u32x4 *)image_dev, n_units,
                        upb_log2, ups_log2, keep_dev, (u32x4 *)patterns_dev);
@@ -1432,10 +1446,10 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   DS_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(ds_exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, keep_dev, pos_dev, n_blocks);
   DS_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(ds_pack_kept_blocks_kernel, dim3((uint32_t)(stripes << kStripeLog2)), dim3(256), 0, st,
-                     (const u32x4 *)image_dev, n_units, upb_log2, keep_dev, pos_dev, (u32x4 *)packed_dev);
-  DS_HIP_TRY(hipGetLastError());
-  return DS_OK;
+  // (launches have less than 2^32 threads, and are rounded up to 8 MiB of image)
+  return n_units <= (1ull << 32) - (16u << kStripeUnitsLog2)
+             ? launch_pack_kept<1>((const u32x4 *)image_dev, n_units, upb_log2, keep_dev, pos_dev, (u32x4 *)packed_dev, st)
+             : launch_pack_kept<4>((const u32x4 *)image_dev, n_units, upb_log2, keep_dev, pos_dev, (u32x4 *)packed_dev, st);
 }
 
 extern "C" int ds_image_diff(const void *image_a_dev, const void *image_b_dev, uint64_t nbytes, uint64_t block_bytes,

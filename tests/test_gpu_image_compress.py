@@ -58,3 +58,31 @@ def test_more_blocks_than_one_step_of_the_scan(n_blocks):
     assert np.array_equal(keep, want) and np.array_equal(pos, np.concatenate([[0], np.cumsum(want)])) and not pats.any()
     last = packed[:int(want.sum()) * block].view(np.int32).reshape(-1, block // 4)
     assert np.array_equal(last[:, -1], np.flatnonzero(want) + 1) and not last[:, :-1].any()
+
+
+@pytest.mark.parametrize("beyond", [0, 16])
+def test_the_largest_image_with_one_unit_per_thread_and_the_next(beyond):
+    """Images of up to 64 GiB - 16 MiB are packed one unit per thread, larger ones four."""
+    import paper_2601_16956_amd as ds
+    import torch
+    block, nbytes = 1 << 21, (64 << 30) - (16 << 20) + beyond
+    n_blocks = -(-nbytes // block)
+    img = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    kept = sorted({0, 1, n_blocks // 2, nbytes // block - 1, n_blocks - 1})
+    if beyond:
+        kept.remove(n_blocks - 1)  # one unit: constant whatever it holds
+    rng = torch.Generator(device="cuda").manual_seed(1)
+    for k in kept:
+        img[k * block:(k + 1) * block] = torch.randint(0, 256, (block,), dtype=torch.uint8, device="cuda", generator=rng)
+    keep = torch.full((n_blocks,), 9, dtype=torch.int32, device="cuda")
+    pos = torch.full((n_blocks + 1,), 9, dtype=torch.int32, device="cuda")
+    pats = torch.full((n_blocks, 16), 0xCC, dtype=torch.uint8, device="cuda")
+    packed = torch.full(((len(kept) + 1) * block,), 0xCC, dtype=torch.uint8, device="cuda")
+    print(f"[case] compress {nbytes} bytes", flush=True)
+    ds.ds_image_compress(img.data_ptr(), nbytes, block, keep.data_ptr(), pos.data_ptr(), pats.data_ptr(),
+                         packed.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.nonzero(keep).flatten().tolist() == kept and int(pos[-1]) == len(kept)
+    for i, k in enumerate(kept):
+        assert torch.equal(packed[i * block:(i + 1) * block], img[k * block:(k + 1) * block])
+    assert bool((packed[len(kept) * block:] == 0xCC).all())
