@@ -280,7 +280,7 @@ def timed_region(c: Ctx, L: Loaded, cfg, steps, warmup, extras=True):
         "value": round(L.payload * steps / elapsed / 1e9, 3), "steps": steps, "warmup": warmup,
         "ms_per_step": round(elapsed * 1e3 / steps, 3),
         "roofline": {
-            "bound": "hbm", "kernel": "ds_move_kernel<pack>", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+            "bound": "hbm", "kernel": "ds_unit_kernel<pack>", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic, "traffic_source": traffic_src,
             "launches": launches, "avg_launch_ms": round(pack_ms / max(launches, 1), 4),
             "algorithmic_bytes_per_launch": L.algo_bytes * steps // max(launches, 1)},
