@@ -615,14 +615,27 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
             st16_aligned<NTS>(ip[i], splice(va, vb, 16u - k));
           }
       }
-      // the rare rest (runs shorter than 16 bytes, views with several outer dimensions), one by one
+      // the rare rest (runs shorter than 16 bytes, views with several outer dimensions), one by one: a loop over those the
+      // thread has, so that move_unit is in the kernel once (inlined for each of four units it takes 102 registers in the
+      // scatter, which is launched for six wavefronts per SIMD: 20 MB of tensors of 1 KiB beside a view, 2048
+      // work-groups, 15.7 us instead of 11.4)
+      uint32_t slow = 0;
 #pragma unroll
-      for (int i = 0; i < UNROLL; ++i)
-        if ((how[i] & kKind) == kSlow) {
-          const uint32_t q = how[i] >> 24;
-          const uint64_t tb = a.hot[bt + q].img_off;
-          move_unit<PACK, NTL, NTS>(a.tiles + bt + q, tb, cb + (uint64_t)(ip[i] - cimg), ip[i]);
-        }
+      for (int i = 0; i < UNROLL; ++i) slow |= (how[i] & kKind) == kSlow ? 1u << i : 0u;
+#pragma unroll 1
+      for (; slow; slow &= slow - 1) {
+        const int s = __builtin_ctz(slow);
+        uint32_t q = how[0] >> 24;
+        uint8_t *at = ip[0];
+#pragma unroll
+        for (int i = 1; i < UNROLL; ++i)
+          if (i == s) {
+            q = how[i] >> 24;
+            at = ip[i];
+          }
+        const uint64_t tb = a.hot[bt + q].img_off;
+        move_unit<PACK, NTL, NTS>(a.tiles + bt + q, tb, cb + (uint64_t)(at - cimg), at);
+      }
     }
     uint64_t big_mask = UNROLL > 1 && NT * UNROLL >= kBigUnits ? g->big_mask : 0;
     while (big_mask) {
