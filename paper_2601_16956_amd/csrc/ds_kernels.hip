@@ -146,9 +146,10 @@ __device__ __forceinline__ uint64_t run_address(const DsTile *t, uint64_t row) {
 }
 
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, uint32_t lane) {
+  asm volatile("" : "+v"(lane));  // else the six lanes read from are kept in registers across a loop over scans
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, kWave);
+    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane - (uint32_t)d) * 4), (int)x);
     if (lane >= (uint32_t)d) x += y;
   }
   return x;

@@ -87,3 +87,11 @@ def test_the_scatter_has_the_wavefronts_it_is_launched_for():
     assert any(a[2] == "4" and a[6] == "6" for a, _ in scatters) and any(a[2] == "8" for a, _ in scatters)
     for args, k in scatters:
         assert _waves(k) >= int(args[6]), (args, k[".vgpr_count"])
+
+
+def test_one_unit_per_thread_runs_at_eight_wavefronts():
+    """With one load per thread under way the default kernel is bound by HBM only if eight wavefronts per SIMD fit."""
+    units = _kernels()["ds_unit_kernel"]
+    assert len(units) >= 8
+    for args, k in units:
+        assert _waves(k) == 8, (args, k[".vgpr_count"])
