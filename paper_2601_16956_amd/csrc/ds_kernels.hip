@@ -269,6 +269,87 @@ __device__ __forceinline__ void move_unit(const DsTile *t, uint64_t tile_begin, 
   else (void)move_runs<false>(t, row, p, k, valid, ld16_aligned<NTL>(imgp));
 }
 
+// ---- units of views with runs shorter than 16 bytes, an element per lane ----------------------------------
+// For DS_HOT_LANES: the few units that such views leave to the general path while everything else is under way.  Bound by
+// latency: move_unit has one piece of a unit after the other, up to 16, each behind the tile's descriptor again, and a
+// launch that holds one such unit ends with it.  Here the elements of a wavefront's units are dealt to its lanes, and the
+// descriptor is read once.  Piece by piece / by lanes, us: a state of 20 MB with one view of 400 transposed bytes, gather
+// 23.5 / 15.4, scatter 23.2 / 15.0; of 40 MB with a transposed matrix of 2 KB 24.7 / 21.6 and 23.7 / 23.3.
+// `units`: a mask of the wavefront's lanes that hold one, of tile bt + q, `off` bytes behind cb in the image, which is at
+// cimg.  They are taken tile by tile, so that the descriptor is in scalar registers.
+#define DS_CONSTANT __attribute__((address_space(4)))
+template <typename E, bool PACK>
+__device__ __forceinline__ void move_elements_by_lanes(const DS_CONSTANT DsTile *t, uint32_t before_cb, uint8_t *cimg,
+                                                       uint32_t lane, uint32_t n, uint32_t list) {
+  constexpr uint32_t kPerUnit = 16 / sizeof(E), kStep = kWave / kPerUnit;
+  constexpr int kAhead = PACK ? 2 : 3;  // loads a lane has under way: more take registers that six wavefronts of ds_move_kernel do not have
+  const uint32_t in_unit = lane % kPerUnit * (uint32_t)sizeof(E), run = (uint32_t)t->run_bytes;
+#pragma unroll 1
+  for (uint32_t base = 0; base < n; base += kAhead * kStep) {
+    uint64_t p[kAhead];   // the element's address; 0: padding, or no unit
+    uint32_t at[kAhead];  // its place in the image, from cimg; ~0: no unit
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const uint32_t k = base + i * kStep + lane / kPerUnit;
+      const uint32_t unit = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(k * 4), (int)list);  // (of lane k mod 64)
+      p[i] = 0;
+      at[i] = ~0u;
+      if (k < n) {
+        at[i] = unit + in_unit;
+        const uint32_t b = before_cb + at[i];
+        if (b < (uint32_t)t->nbytes) {
+          uint32_t row = b / run;
+          uint64_t x = t->src + (b - row * run);
+#pragma unroll 1
+          for (uint32_t j = t->n_outer - 1; j > 0; --j) {
+            const uint32_t extent = (uint32_t)t->extent[j], rows = row / extent;
+            x += (row - rows * extent) * t->stride[j];
+            row = rows;
+          }
+          p[i] = x + row * t->stride[0];
+        }
+      }
+    }
+    E v[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      v[i] = 0;
+      if (p[i]) v[i] = PACK ? *(const DS_GLOBAL E *)p[i] : *(const DS_GLOBAL E *)(cimg + at[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      if (PACK && at[i] != ~0u) *(DS_GLOBAL E *)(cimg + at[i]) = v[i];
+      if (!PACK && p[i]) *(DS_GLOBAL E *)p[i] = v[i];
+    }
+  }
+}
+template <bool PACK>
+__device__ __forceinline__ void move_by_lanes(const MoveArgs &a, uint32_t bt, uint64_t cb, uint8_t *cimg, uint64_t units,
+                                              uint32_t q, uint32_t off) {
+  uint32_t lane = threadIdx.x & (kWave - 1);
+  asm volatile("" : "+v"(lane));  // nothing made of it is kept in registers while the other units are moved
+#pragma unroll 1
+  while (units) {
+    const uint32_t q0 = (uint32_t)__builtin_amdgcn_readlane((int)q, __builtin_ctzll(units));
+    const uint64_t here = units & __ballot(q == q0);
+    units &= ~here;
+    const uint32_t n = (uint32_t)__builtin_popcountll(here);
+    // lane r gets the r-th unit: its owner sends it there, and the others send to the lanes behind
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0));
+    const uint32_t to = here >> lane & 1 ? before : n + lane - before;
+    const uint32_t list = (uint32_t)__builtin_amdgcn_ds_permute((int)(to * 4), (int)off);
+    const DS_CONSTANT DsTile *t = (const DS_CONSTANT DsTile *)(uintptr_t)(a.tiles + bt) + q0;
+    // (a view of less than 4 GiB: 32 bits hold the distance modulo 2^32, and what it is added to brings it into the view)
+    const uint32_t before_cb = (uint32_t)(cb - ((const DS_CONSTANT DsTileHot *)(uintptr_t)(a.hot + bt) + q0)->img_off);
+    switch (t->es_log2) {
+      case 0: move_elements_by_lanes<uint8_t, PACK>(t, before_cb, cimg, lane, n, list); break;
+      case 1: move_elements_by_lanes<uint16_t, PACK>(t, before_cb, cimg, lane, n, list); break;
+      case 2: move_elements_by_lanes<uint32_t, PACK>(t, before_cb, cimg, lane, n, list); break;
+      default: move_elements_by_lanes<uint64_t, PACK>(t, before_cb, cimg, lane, n, list); break;
+    }
+  }
+}
+
 // ---- direct path: one tile range, whole work-group ---------------------------
 // [lo, hi): image range of the tile clipped to the chunk, multiples of 16.
 template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS>
@@ -360,7 +441,7 @@ struct GenLds {
   uint32_t rem[kWave];    // payload bytes from there on (clamped to 2^31; 0 = padding only)
   uint32_t run[kWave];    // views with one outer dimension: run length
   uint32_t col0[kWave];   // ... and the position of the clipped start inside its run
-  uint32_t meta[kWave];   // n_outer | log2(itemsize) << 8 | kRunGe16 if the runs are at least 16 bytes long
+  uint32_t meta[kWave];   // n_outer | log2(itemsize) << 8 | kRunGe16 if the runs are at least 16 bytes long | DS_HOT_*
   uint64_t src0[kWave];   // address of the clipped start (one run), or of the start of the run that holds it
   uint64_t pitch[kWave];  // views with one outer dimension: distance between runs
   uint64_t big_mask;      // tiles taken out of the scan (large pieces of views with several outer dimensions)
@@ -629,26 +710,38 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
             st16_aligned<NTS>(ip[i], splice(va, vb, 16u - k));
           }
       }
-      // the rare rest (runs shorter than 16 bytes, views with several outer dimensions), one by one: a loop over those the
-      // thread has, so that move_unit is in the kernel once (inlined for each of four units it takes 102 registers in the
+      // the rare rest (runs shorter than 16 bytes, views with several outer dimensions): a loop over a wavefront's units
+      // that has each routine in the kernel once (move_unit, inlined for each of four units, takes 102 registers in the
       // scatter, which is launched for six wavefronts per SIMD: 20 MB of tensors of 1 KiB beside a view, 2048
       // work-groups, 15.7 us instead of 11.4)
       uint32_t slow = 0;
 #pragma unroll
-      for (int i = 0; i < UNROLL; ++i) slow |= (how[i] & kKind) == kSlow ? 1u << i : 0u;
+      for (int i = 0; i < UNROLL; ++i) slow |= __ballot((how[i] & kKind) == kSlow) ? 1u << i : 0u;
+      const auto rest = [&](uint32_t what, uint32_t off) {  // off: the unit's place behind cb
+        const uint32_t q = what >> 24;
+        const uint32_t meta = (what & kKind) == kSlow ? g->meta[q] : 0u;
+        const uint64_t by_lanes = __ballot(meta & DS_HOT_LANES);
+        if (by_lanes)
+          move_by_lanes<PACK>(a, bt, cb, cimg, by_lanes, q, off);
+        if ((what & kKind) == kSlow && !(meta & DS_HOT_LANES))
+          move_unit<PACK, NTL, NTS>(a.tiles + bt + q, a.hot[bt + q].img_off, cb + off, cimg + off);
+      };
+      if (UNROLL == 1) {
+        if (slow) rest(how[0], (uint32_t)(ip[0] - cimg));
+        continue;
+      }
 #pragma unroll 1
       for (; slow; slow &= slow - 1) {
         const int s = __builtin_ctz(slow);
-        uint32_t q = how[0] >> 24;
-        uint8_t *at = ip[0];
+        uint32_t what = how[0];
+        uint32_t off = (uint32_t)(ip[0] - cimg);
 #pragma unroll
         for (int i = 1; i < UNROLL; ++i)
           if (i == s) {
-            q = how[i] >> 24;
-            at = ip[i];
+            what = how[i];
+            off = (uint32_t)(ip[i] - cimg);
           }
-        const uint64_t tb = a.hot[bt + q].img_off;
-        move_unit<PACK, NTL, NTS>(a.tiles + bt + q, tb, cb + (uint64_t)(at - cimg), at);
+        rest(what, off);
       }
     }
     uint64_t big_mask = UNROLL > 1 && NT * UNROLL >= kBigUnits ? g->big_mask : 0;

@@ -500,6 +500,18 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
           p->perms.clear();
           p->perm_first.clear();
         }
+        // what the general path is left with of views with short runs
+        uint64_t one_element = 0;
+        for (size_t t = 0; t < p->tiles.size(); ++t) {
+          const DsTile &tl = p->tiles[t];
+          if (tl.n_outer && tl.run_bytes == 1ull << tl.es_log2 && !(p->hot[t].meta & DS_HOT_PERM)) one_element += tl.nbytes;
+        }
+        for (size_t t = 0; t < p->tiles.size(); ++t) {
+          const DsTile &tl = p->tiles[t];
+          if (!tl.n_outer || tl.run_bytes >= 16 || tl.nbytes >> 32) continue;
+          if ((p->hot[t].meta & DS_HOT_PERM) || (tl.run_bytes == 1ull << tl.es_log2 && one_element <= kLanesBytes))
+            p->hot[t].meta |= DS_HOT_LANES;
+        }
         if (n_chunks >= 0x7FFFFFFFull || p->tiles.size() >= 0x7FFFFFFFull) rc = DS_EINVAL;
         if (rc == DS_OK) {
           p->first_tile.resize(n_chunks + 1);

@@ -89,3 +89,26 @@ def _check(w, chunk_bytes, grid_limit, what, rng):
     finally:
         for key, value in old:
             ds.ds_config_set(key, value)
+
+
+BY_LANES = [("u8", (20, 20), (1, 20)), ("u8", (3, 7), (9, 2)), ("bf16", (5, 7, 9), (1, 50, 5)), ("bf16", (31, 2), (2, 64)),
+            ("f32", (10, 20), (40, 2)), ("f32", (3, 3, 3, 3), (200, 1, 31, 5)), ("i64", (7, 5), (1, 8)), ("i64", (2,), (3,)),
+            ("u8", (1, 1), (1, 1)), ("bf16", (29, 17), (1, 31))]
+
+
+@pytest.mark.parametrize("grid_limit", [0, 7])
+@pytest.mark.parametrize("chunk_bytes", [8192, 16384, 32768])
+def test_units_moved_an_element_per_lane(chunk_bytes, grid_limit):
+    """Few views with runs of one element, of every itemsize: many in a wavefront's units and one by itself, with last
+    units of every length, and what is left of views that are moved in blocks."""
+    rng = np.random.default_rng(chunk_bytes + grid_limit)
+    shards, at = [], 0
+    views = [BY_LANES[k % len(BY_LANES)] for k in range(150)] + [("u8", (50000,), (1,)), BY_LANES[0], ("u8", (90000,), (1,)),
+             ("bf16", (91, 91), (1, 91)), ("u8", (121, 121), (1, 121)), ("f32", (75, 75), (1, 75)), BY_LANES[4]]
+    for k, (dtype, shape, strides) in enumerate(views):
+        es = DTYPES[dtype][1]
+        at = -(-at // es) * es + es * int(rng.integers(0, 3))
+        shards.append(Shard(f"l{k}", dtype, shape, strides, at, k))
+        at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    _check(Workload("lanes", 16, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards), chunk_bytes, grid_limit,
+           "an element per lane", rng)

@@ -89,6 +89,12 @@ def test_the_scatter_has_the_wavefronts_it_is_launched_for():
         assert _waves(k) >= int(args[6]), (args, k[".vgpr_count"])
 
 
+def test_the_gather_of_mostly_general_chunks_has_six_wavefronts():
+    for args, k in _kernels()["ds_move_kernel"]:
+        if args[0] == "true" and args[2] in ("2", "4") and args[6] == "6":
+            assert _waves(k) >= 6, (args, k[".vgpr_count"])
+
+
 def test_one_unit_per_thread_runs_at_eight_wavefronts():
     """With one load per thread under way the default kernel is bound by HBM only if eight wavefronts per SIMD fit."""
     units = _kernels()["ds_unit_kernel"]

@@ -12,7 +12,7 @@ from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
-         "in_pieces")
+         "in_pieces", "n_lanes")
 
 
 @pytest.fixture(scope="module")
