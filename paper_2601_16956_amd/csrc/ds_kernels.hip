@@ -145,13 +145,20 @@ __device__ __forceinline__ uint64_t run_address(const DsTile *t, uint64_t row) {
   return a + row * t->stride[0];
 }
 
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, uint32_t lane) {
-  asm volatile("" : "+v"(lane));  // else the six lanes read from are kept in registers across a loop over scans
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane - (uint32_t)d) * 4), (int)x);
-    if (lane >= (uint32_t)d) x += y;
-  }
+// Inclusive scan over the wavefront, by data-parallel moves: inside each row of 16 lanes, then the last lane of rows 0 and
+// 2 to the row behind, then that of the first half to the second.  (Through LDS, by __shfl_up, the lanes read from stay in
+// registers across the loops around it: 66 in the gather beside blocks, which is launched for eight wavefronts per SIMD.)
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+  const auto add = [&](auto ctrl, auto rows) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+  };
+  constexpr std::integral_constant<int, 0xF> all;
+  add(std::integral_constant<int, 0x111>(), all);  // row_shr 1, 2, 4, 8
+  add(std::integral_constant<int, 0x112>(), all);
+  add(std::integral_constant<int, 0x114>(), all);
+  add(std::integral_constant<int, 0x118>(), all);
+  add(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xA>());  // row_bcast 15
+  add(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xC>());  // row_bcast 31
   return x;
 }
 
@@ -508,7 +515,7 @@ __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uin
       // (of a view that is moved in blocks only padding can be large: that is what the scan's units write fastest)
       const bool big = UNROLL > 1 && NT * UNROLL >= kBigUnits && units >= kBigUnits && n_outer > 1 && !(BLOCKS && (meta & DS_HOT_PERM));
       const uint64_t big_mask = __ballot(big);
-      const uint32_t incl = wave_inclusive_scan(big ? 0u : units, lane);
+      const uint32_t incl = wave_inclusive_scan(big ? 0u : units);
       const uint64_t b0 = lo - tb;  // byte of the tile's own range at which its clipped range starts
       uint64_t rem = b0 < nbytes ? nbytes - b0 : 0;
       if (rem > (1ull << 31)) rem = 1ull << 31;
@@ -1471,14 +1478,14 @@ __global__ __launch_bounds__(kScanThreads) void ds_exclusive_scan_kernel(const u
 #pragma unroll
     for (uint32_t j = 0; j < kScanQuads; ++j) {
       const uint32_t mine = x[j].x + x[j].y + x[j].z + x[j].w;
-      const uint32_t incl = wave_inclusive_scan(mine, lane);
+      const uint32_t incl = wave_inclusive_scan(mine);
       before[j] = sum + incl - mine;
       sum += __shfl(incl, kWave - 1, kWave);
     }
     if (lane == 0) wave_sum[wv] = sum;
     __syncthreads();
     const uint32_t other = lane < kScanThreads / kWave ? wave_sum[lane] : 0u;
-    const uint32_t waves = wave_inclusive_scan(other, lane);
+    const uint32_t waves = wave_inclusive_scan(other);
     const uint32_t start = carry + __shfl(waves - other, wv, kWave);
     carry += __shfl(waves, kWave - 1, kWave);
 #pragma unroll
