@@ -40,11 +40,12 @@ enum : uint32_t {
   DS_HOT_PERM = 1u << 17,  // the view's whole units are moved in blocks (ds_perm.h)
   DS_HOT_LANES = 1u << 18  // a view of less than 4 GiB with runs shorter than 16 bytes, of which the general path moves so
                            // little that it does so an element per lane: what is left of a view moved in blocks, and views
-                           // with runs of one element of which the plan has at most kLanesBytes
+                           // with runs of one element of 1 or 2 bytes, of which the plan has at most kLanesBytes
 };
 // Where such views keep the chip busy, the pieces of a unit one after the other are the faster way: 20 000 views of 512
 // bytes (bf16, transposed) 26.5 / 32.0 us, of 400 bytes 40.0 / 45.2; 300 of them 9.2 / 7.1 and 15.9 / 11.5.  Runs of several
-// elements have fewer pieces (300 views with rows of 9 bytes 5.5 / 6.7).
+// elements, and elements of 4 bytes and more, have fewer pieces (300 views with rows of 9 bytes 5.5 / 6.7, every second of
+// 20 floats 5.7 / 6.1).
 constexpr uint64_t kLanesBytes = 256 << 10;
 static_assert(sizeof(DsTileHot) == 40, "five 8-byte words");
 

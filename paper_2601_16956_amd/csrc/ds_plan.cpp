@@ -504,12 +504,14 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
         uint64_t one_element = 0;
         for (size_t t = 0; t < p->tiles.size(); ++t) {
           const DsTile &tl = p->tiles[t];
-          if (tl.n_outer && tl.run_bytes == 1ull << tl.es_log2 && !(p->hot[t].meta & DS_HOT_PERM)) one_element += tl.nbytes;
+          if (tl.n_outer && tl.run_bytes <= 2 && tl.run_bytes == 1ull << tl.es_log2 && !(p->hot[t].meta & DS_HOT_PERM))
+            one_element += tl.nbytes;
         }
         for (size_t t = 0; t < p->tiles.size(); ++t) {
           const DsTile &tl = p->tiles[t];
           if (!tl.n_outer || tl.run_bytes >= 16 || tl.nbytes >> 32) continue;
-          if ((p->hot[t].meta & DS_HOT_PERM) || (tl.run_bytes == 1ull << tl.es_log2 && one_element <= kLanesBytes))
+          if ((p->hot[t].meta & DS_HOT_PERM) ||
+              (tl.run_bytes <= 2 && tl.run_bytes == 1ull << tl.es_log2 && one_element <= kLanesBytes))
             p->hot[t].meta |= DS_HOT_LANES;
         }
         if (n_chunks >= 0x7FFFFFFFull || p->tiles.size() >= 0x7FFFFFFFull) rc = DS_EINVAL;

@@ -104,7 +104,8 @@ def test_units_moved_an_element_per_lane(chunk_bytes, grid_limit):
     rng = np.random.default_rng(chunk_bytes + grid_limit)
     shards, at = [], 0
     views = [BY_LANES[k % len(BY_LANES)] for k in range(150)] + [("u8", (50000,), (1,)), BY_LANES[0], ("u8", (90000,), (1,)),
-             ("bf16", (91, 91), (1, 91)), ("u8", (121, 121), (1, 121)), ("f32", (75, 75), (1, 75)), BY_LANES[4]]
+             ("bf16", (91, 91), (1, 91)), ("u8", (121, 121), (1, 121)), ("f32", (75, 75), (1, 75)),
+             ("i64", (33, 41), (1, 33)), ("u8", (11, 300, 3), (3, 40, 1)), BY_LANES[4]]
     for k, (dtype, shape, strides) in enumerate(views):
         es = DTYPES[dtype][1]
         at = -(-at // es) * es + es * int(rng.integers(0, 3))

@@ -103,3 +103,16 @@ def test_which_scatters_are_cut_into_pieces(facts, kind, pieces):
                 "rows of 256": ("u8", (n // 256, 256), (512, 1)),
                 "several dimensions": ("u8", (n // 1280, 5, 256), (2600, 512, 1))}[kind]
         assert facts([view]).in_pieces == want, chunks
+
+
+def test_few_units_of_views_with_short_runs_are_moved_by_lanes(facts):
+    """What is left of a view that is moved in blocks, and views with runs of one element of 1 or 2 bytes, of which
+    there are at most 256 KiB; not where those keep the chip busy, nor runs that are few pieces of a unit."""
+    assert facts([("u8", (1 << 24,), (1,)), _transposed(20, "u8")]).n_lanes == 1
+    f = facts([("u8", (1 << 24,), (1,)), _transposed(91)])                 # 16 562 bytes, moved in blocks
+    assert (f.n_perms, f.n_lanes) == (1, 1)
+    assert facts([_transposed(16)] * 512).n_lanes == 512                  # 256 KiB
+    assert facts([_transposed(16)] * 513).n_lanes == 0
+    assert facts([("u8", (40, 9), (13, 1))] * 9).n_lanes == 0
+    assert facts([("f32", (10, 9), (40, 2))] * 9).n_lanes == 0
+    assert facts([("u8", (40, 16), (23, 1)), ("u8", (1000,), (1,))]).n_lanes == 0
