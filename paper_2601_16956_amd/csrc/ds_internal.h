@@ -56,7 +56,12 @@ static_assert(sizeof(DsTileHot) == 40, "five 8-byte words");
 // record names the tiles they hold (tile, col0).  DS_CHUNK_PERM: the whole chunk is whole units of one view that is
 // moved in blocks (ds_perm.h); its record is that of a general chunk, for launches without the block tables.
 // DS_CHUNK_MULTI: general, and every tile of it is one contiguous run; same record.
-enum : uint32_t { DS_CHUNK_CONTIG = 0, DS_CHUNK_ROWS = 1, DS_CHUNK_GENERAL = 2, DS_CHUNK_PERM = 3, DS_CHUNK_MULTI = 4 };
+// DS_CHUNK_DIMS: the whole chunk is whole units of one view with several outer dimensions, fewer than 2^32 runs of 16 bytes
+// and more; the record of a general chunk, with addr = number of the run that holds the chunk's first byte, pitch = that
+// byte's position in it, run.
+enum : uint32_t {
+  DS_CHUNK_CONTIG = 0, DS_CHUNK_ROWS = 1, DS_CHUNK_GENERAL = 2, DS_CHUNK_PERM = 3, DS_CHUNK_MULTI = 4, DS_CHUNK_DIMS = 5
+};
 constexpr uint32_t kMultiTiles = 1024;  // tiles a chunk of kind DS_CHUNK_MULTI may hold
 // CONTIG only, bit 8 of `kind`: the tensor side of the chunk is not 16-byte aligned, and the tensor has at least
 // 16 more bytes on either side of it, so the gather may read the 16-byte aligned units that cover the chunk's
@@ -135,6 +140,7 @@ struct ds_plan {
   std::vector<DsChunkRec> rest_recs;
   uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
   uint64_t n_perm_chunks = 0;              // of these the ones of kind DS_CHUNK_PERM
+  uint64_t n_dims = 0;                     // ... of kind DS_CHUNK_DIMS
   uint64_t n_one_by_one = 0;               // ... and those with (parts of) views of several outer dimensions
   uint64_t n_short_rows = 0;               // chunks of rows of at most 512 bytes
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run

@@ -984,6 +984,61 @@ __device__ __forceinline__ void lean_move(const DsChunkRec &r, uint8_t *imgp, ui
   }
 }
 
+// Moves a chunk of kind DS_CHUNK_DIMS, or its piece of NT * UNROLL units from byte `piece` on, which is at imgp in the image
+// buffer.  As lean_move does with rows, but for the address of a run, which takes a division per outer dimension; the tile's
+// extents and strides are in scalar registers.  Through the general path (LDS, the tile's descriptor per lane, one unit after
+// the other) a view of three dimensions was slower with one unit per thread than with four.  64 MB in runs of 256 bytes,
+// gather / scatter, four units and one through the general path 63.5 / 53.8 and 60.1 / 60.2 us, now 26.5 / 29.3; 5 GB of
+// runs of 2 KiB 4095 / 3622, 4149 / 3943, now 1606 / 1704.
+template <bool PACK, int NT, int UNROLL, bool NTL, bool BUFST>
+__device__ __forceinline__ void dims_move(const DsChunkRec &r, const DsTile *tiles, uint8_t *imgp, uint32_t piece) {
+  const uint32_t tid = threadIdx.x;
+  const DS_CONSTANT DsTile *t = (const DS_CONSTANT DsTile *)(uintptr_t)(tiles + r.tile);
+  const auto run_at = [&](uint32_t row) {
+    uint64_t x = t->src;
+#pragma unroll 1
+    for (uint32_t j = t->n_outer - 1; j > 0; --j) {
+      const uint32_t extent = (uint32_t)t->extent[j], rows = row / extent;
+      x += (row - rows * extent) * t->stride[j];
+      row = rows;
+    }
+    return reinterpret_cast<uint8_t *>(x + row * t->stride[0]);
+  };
+  __amdgpu_buffer_rsrc_t image_rsrc;
+  if (PACK && BUFST) image_rsrc = __builtin_amdgcn_make_buffer_rsrc(imgp, 0, NT * UNROLL * 16, 0x00020000);
+  uint8_t *p[UNROLL], *next[UNROLL];  // the unit; the run behind its own, if it goes on there
+  uint32_t cut[UNROLL];               // how much of it is in its own run, or 0 if all is
+  u32x4 v[UNROLL], w[UNROLL];
+#pragma unroll
+  for (int i = 0; i < UNROLL; ++i) {
+    const uint32_t off = 16u * (i * NT + tid), at = (uint32_t)r.pitch + piece + off;  // < 2^31 + 2^14
+    const uint32_t rows = at / r.run, col = at - rows * r.run, row = (uint32_t)r.addr + rows;
+    uint8_t *const run = run_at(row);
+    p[i] = run + col;
+    cut[i] = col + 16u > r.run ? r.run - col : 0u;
+    if (cut[i]) next[i] = run_at(row + 1);
+    if (PACK) {
+      v[i] = ld16_any<NTL>(cut[i] ? run + r.run - 16u : p[i]);
+      if (cut[i]) w[i] = ld16_any<NTL>(next[i]);
+    } else {
+      v[i] = ld16_aligned<NTL>(imgp + off);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < UNROLL; ++i) {
+    const uint32_t off = 16u * (i * NT + tid);
+    if (PACK) {
+      if (cut[i]) v[i] = splice(v[i], w[i], 16u - cut[i]);
+      if (BUFST) __builtin_amdgcn_raw_buffer_store_b128(v[i], image_rsrc, (int)off, 0, kStorePolicySc0Sc1Nt);
+      else st16_aligned<true>(imgp + off, v[i]);
+    } else if (cut[i]) {
+      store_cut(p[i], next[i], cut[i], v[i]);
+    } else {
+      st16_any<true>(p[i], v[i]);
+    }
+  }
+}
+
 // Number of lean work items of a launch; item ci takes one lean chunk, whole work-group.
 __device__ __forceinline__ uint32_t lean_items(const LeanArgs &a) { return a.xcd_span ? a.xcd_span * 8u : a.n_pieces; }
 
@@ -1098,8 +1153,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, WAVES))) 
 // rank (1.5 GB) 490 / 473, 20 000 fragments (7.5 GB) 2488 / 2356, a 23 MB state 10.9 / 9.1 and scatter 11.4 / 8.9 (with the
 // ordinary loads of small images; non-temporal 10.0 and 10.6), 475 fragments with many rows (1 MB) 8.0 / 6.3.
 // Work-groups of 512 and 1024 threads measure the same on large tensors and 3 to 5 % slower on fragments.
-template <bool PACK, bool NTL, int BLOCKS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_unit_kernel(
+// (DIMS: the plan has chunks of that kind.  The test alone makes the compiler move scalar registers to and fro in front of
+// every chunk: a 210 MB rank 65.9 us instead of 64.7.)
+template <bool PACK, bool NTL, int BLOCKS, bool DIMS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void ds_unit_kernel(
     const DsChunkRec *recs, const uint32_t *ids, uint8_t *img0, uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
   __shared__ GenLds s_tab;
   const uint32_t wi = blockIdx.x, cm = (wi & 7u) * span + (wi >> 3);
@@ -1116,6 +1173,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
       lean_move<PACK, 256, 1, NTL, true, PACK>(r, img0 + (c << 14) + piece, piece);
       return;
     }
+    if (DIMS && kind == DS_CHUNK_DIMS) {
+      dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, img0 + (c << 14) + piece, piece);
+      return;
+    }
     if (BLOCKS == kBeside && kind == DS_CHUNK_PERM) return;
     t0 = r.tile;
     t1 = r.tile + r.col0;
@@ -1128,21 +1189,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
   general_chunk<PACK, 256, 1, NTL, true, PACK, BLOCKS, false>(ma, c, piece, t0, t1, &s_tab);
 }
 
-template <bool PACK, bool NTL, int BLOCKS>
+template <bool PACK, bool NTL, int BLOCKS, bool DIMS>
 int launch_units(const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
   const uint32_t n = la.n_pieces * kUnitPieces, span = (n + 7) / 8, grid = span * 8 + ma.n_extra * kUnitPieces;
   if (grid == 0) return DS_OK;
-  hipLaunchKernelGGL((ds_unit_kernel<PACK, NTL, BLOCKS>), dim3(grid), dim3(256), 0, stream, la.recs, la.ids,
+  hipLaunchKernelGGL((ds_unit_kernel<PACK, NTL, BLOCKS, DIMS>), dim3(grid), dim3(256), 0, stream, la.recs, la.ids,
                      la.img - la.img_lo, n, span, la.c_lo, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
 
-template <int BLOCKS>
-int launch_units(const ds_plan *plan, bool pack, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+template <bool PACK, int BLOCKS>
+int launch_units(const ds_plan *plan, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  const bool dims = plan->n_dims != 0;
   if (plan->total_bytes <= kCachedBytes)
-    return pack ? launch_units<true, false, BLOCKS>(la, ma, stream) : launch_units<false, false, BLOCKS>(la, ma, stream);
-  return pack ? launch_units<true, true, BLOCKS>(la, ma, stream) : launch_units<false, true, BLOCKS>(la, ma, stream);
+    return dims ? launch_units<PACK, false, BLOCKS, true>(la, ma, stream) : launch_units<PACK, false, BLOCKS, false>(la, ma, stream);
+  return dims ? launch_units<PACK, true, BLOCKS, true>(la, ma, stream) : launch_units<PACK, true, BLOCKS, false>(la, ma, stream);
 }
 
 constexpr uint32_t kMaxGrid = 1u << 23;  // work-groups of 256: a launch has less than 2^32 threads
@@ -1315,6 +1377,12 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsCh
     c = load_id(ids, c_lo + cm);
     if ((r.kind & 0xFFu) < DS_CHUNK_GENERAL) {
       lean_move<PACK, 256, 4, NTL, true, PACK>(r, a.img + ((c << 14) - a.img_lo), 0);
+      return;
+    }
+    if ((r.kind & 0xFFu) == DS_CHUNK_DIMS) {
+#pragma unroll 1
+      for (uint32_t piece = 0; piece < 16384; piece += 4096)
+        dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, a.img + ((c << 14) - a.img_lo) + piece, piece);
       return;
     }
     t0 = r.tile;
@@ -1697,9 +1765,14 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, const 
   // the default, up to images of 64 GiB (a launch has less than 2^32 threads)
   if ((variant == 0 || variant == 4) && !grid_limit && lg == 14 && la.n_pieces < (1u << 22) - 16 &&
       !(mostly_general && plan->all_contiguous)) {
-    if (!tb.perms) return launch_units<kAlone>(plan, pack, la, ma, stream);
-    return plan->listed ? launch_units<kListed>(plan, pack, la, ma, stream)
-                        : launch_units<kBeside>(plan, pack, la, ma, stream);
+    const int blocks = !tb.perms ? kAlone : plan->listed ? kListed : kBeside;
+    if (pack)
+      return blocks == kAlone    ? launch_units<true, kAlone>(plan, la, ma, stream)
+             : blocks == kListed ? launch_units<true, kListed>(plan, la, ma, stream)
+                                 : launch_units<true, kBeside>(plan, la, ma, stream);
+    return blocks == kAlone    ? launch_units<false, kAlone>(plan, la, ma, stream)
+           : blocks == kListed ? launch_units<false, kListed>(plan, la, ma, stream)
+                               : launch_units<false, kBeside>(plan, la, ma, stream);
   }
   if (tb.perms)  // (variants 1, 2 and 5 are given no block tables)
     return plan->listed ? launch_beside_blocks<kListed>(plan, pack, few, mostly_general, la, ma, grid_limit, stream)

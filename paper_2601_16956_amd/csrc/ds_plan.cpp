@@ -579,6 +579,14 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
                 for (uint32_t t2 = ti; r.kind == DS_CHUNK_GENERAL && t2 <= t1 && !one_by_one; ++t2)
                   one_by_one = (p->hot[t2].meta & 0xFF) > 1 && !(p->hot[t2].meta & DS_HOT_PERM);
                 p->n_one_by_one += one_by_one;
+                if (one_by_one && ce <= p->total_bytes && ce <= tb + (tl.nbytes & ~(uint64_t)15) && tl.n_outer > 1 &&
+                    tl.run_bytes >= 16 && tl.run_bytes < ((uint64_t)1 << 31) && tl.nbytes / tl.run_bytes >> 32 == 0) {
+                  r.kind = DS_CHUNK_DIMS;
+                  ++p->n_dims;
+                  r.addr = (cb - tb) / tl.run_bytes;
+                  r.pitch = (cb - tb) % tl.run_bytes;
+                  r.run = (uint32_t)tl.run_bytes;
+                }
               }
             }
           }

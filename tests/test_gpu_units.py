@@ -54,3 +54,47 @@ def test_every_kind_of_chunk(total, align):
             assert gu.first_mismatch(dw.arena_host(), w.arena) is None, parts
     finally:
         dw.close()
+
+
+DIMS = [("u8", (40, 30, 1000), (31 * 1500, 1500, 1)), ("u8", (90, 33, 17), (33 * 23 + 5, 23, 1)),
+        ("bf16", (6, 7, 9, 260), (40000, 5000, 512, 1)), ("f32", (5, 4, 3, 2, 4099), (300000, 70000, 20000, 9000, 1)),
+        ("i64", (50, 20, 6), (200, 8, 1)), ("u8", (3, 70000, 16), (2000000, 24, 1)), ("bf16", (3, 2, 40001), (200000, 50000, 1)),
+        ("f32", (20, 300, 4), (300 * 8 + 4, 8, 1))]
+
+
+@pytest.mark.parametrize("blocks", [0, 1, 2])
+@pytest.mark.parametrize("large", [0, CACHED])
+def test_views_of_several_outer_dimensions(large, blocks):
+    """Chunks inside such views (runs of 16 bytes to more than a chunk, units cut by a run's end at every place), alone,
+    beside views moved in blocks in the same launch, and in a launch of their own."""
+    import gpu_util as gu
+    rng = np.random.default_rng(blocks)
+    views = DIMS + ([("bf16", (301, 203), (1, 303))] if blocks else [])
+    if blocks == 2:
+        views = views + [("u8", (70 << 20,), (1,))]     # more chunks than share a launch
+    if large:
+        views = views + [("u8", (large,), (1,))]
+    shards, at = [], 0
+    for k, (dtype, shape, strides) in enumerate(views):
+        es = DTYPES[dtype][1]
+        at = -(-at // es) * es + es * int(rng.integers(0, 4))
+        shards.append(Shard(f"d{k}", dtype, shape, strides, at, k))
+        at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    w = Workload("dims", 16, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print(f"[case] several dimensions, blocks={blocks} image={dw.total}", flush=True)
+        cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, min(dw.total, 8 << 20) // 16, 9)) + [dw.total]
+        ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+        for lo, hi in [(0, dw.total)] + ranges:
+            assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        for parts in ([(0, dw.total)], ranges):
+            dw.arena.fill_(0x5A)
+            for lo, hi in parts:
+                dw.unpack(want, lo, hi)
+            assert gu.first_mismatch(dw.arena_host(), w.arena) is None, parts
+    finally:
+        dw.close()

@@ -65,8 +65,9 @@ def _kernels():
 
 
 def _waves(k):
-    """Wavefronts per SIMD that registers and LDS leave room for (512 registers in steps of 8, 160 KiB per CU)."""
-    by_registers = 512 // (-(-k[".vgpr_count"] // 8) * 8)
+    """Wavefronts per SIMD that registers and LDS leave room for (512 vector registers in steps of 8, 800 scalar ones in
+    steps of 16, 160 KiB per CU)."""
+    by_registers = min(512 // (-(-k[".vgpr_count"] // 8) * 8), 800 // (-(-k[".sgpr_count"] // 16) * 16))
     lds = k[".group_segment_fixed_size"]
     groups = (160 * 1024) // lds if lds else 99
     per_group = -(-k[".max_flat_workgroup_size"] // 256)  # wavefronts per SIMD of one work-group

@@ -12,7 +12,7 @@ from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
-         "in_pieces", "n_lanes")
+         "in_pieces", "n_lanes", "n_dims")
 
 
 @pytest.fixture(scope="module")
@@ -116,3 +116,14 @@ def test_few_units_of_views_with_short_runs_are_moved_by_lanes(facts):
     assert facts([("u8", (40, 9), (13, 1))] * 9).n_lanes == 0
     assert facts([("f32", (10, 9), (40, 2))] * 9).n_lanes == 0
     assert facts([("u8", (40, 16), (23, 1)), ("u8", (1000,), (1,))]).n_lanes == 0
+
+
+def test_chunks_inside_views_of_several_dimensions_have_records(facts):
+    """Whole chunks of a view with several outer dimensions and runs of at least 16 bytes; not those of shorter runs, nor
+    the last one with the end of the payload, nor rows that merge into one dimension."""
+    view = ("u8", (40, 10, 1000), (20000, 1500, 1))                       # 400 000 bytes = 24 chunks and a part
+    assert facts([view]).n_dims == 24
+    assert facts([("u8", (5000,), (1,)), view]).n_dims == 23
+    assert facts([("u8", (40, 10, 1000), (15000, 1500, 1))]).n_dims == 0  # one outer dimension
+    assert facts([("f32", (50, 40, 30, 3), (20000, 400, 10, 1))], 64).n_dims == 0
+    assert facts([("f32", (50, 40, 30, 4), (20000, 400, 10, 1))], 64).n_dims == 58
