@@ -140,6 +140,7 @@ struct ds_plan {
   std::vector<DsChunkRec> rest_recs;
   uint64_t n_general = 0;                  // chunks that are not lean (kinds DS_CHUNK_GENERAL, _PERM and _MULTI)
   uint64_t n_perm_chunks = 0;              // of these the ones of kind DS_CHUNK_PERM
+  uint64_t n_multi = 0;                    // ... of kind DS_CHUNK_MULTI
   uint64_t n_dims = 0;                     // ... of kind DS_CHUNK_DIMS
   uint64_t n_one_by_one = 0;               // ... and those with (parts of) views of several outer dimensions
   uint64_t n_short_rows = 0;               // chunks of rows of at most 512 bytes
@@ -168,6 +169,17 @@ struct ds_plan {
   bool mostly_general(bool blocks) const {
     const uint64_t left_out = blocks ? n_perm_chunks : 0;
     return (n_general - left_out) * 2 > n_chunks() - left_out;
+  }
+  // Do most chunks of a launch hold several contiguous tensors, in a plan that has views too and an image of more than
+  // 16 MiB?  They then take the general path with four units per thread, whose chain of dependent loads (record,
+  // descriptors, data) one unit per thread, with a quarter of the bytes in flight, pays four times.  Four units / one, us,
+  // gather and scatter, tensors of one size beside a small view: 100 MB of 4 KiB 42.3 / 48.4 and 41.4 / 46.1, 48 MB of
+  // 20 KB, out of the last-level cache, 21.8 / 24.3 and 22.4 / 24.5, in it 16.6 / 17.8 and 17.5 / 18.5, 36 MB of 300 bytes
+  // 15.9 / 17.7 and 16.4 / 16.7; 16 MB 9.0 / 9.1 and 9.0 / 9.1; 4 MB of 4 KiB 5.1 / 3.8 and 6.4 / 4.1.  Not where the chunks hold views: 20
+  // MB of 60 000 fragments, a third of them rows, 27.4 / 26.2 and 25.8 / 23.4, of rows only 37.1 / 31.5 and 34.0 / 28.5.
+  bool mostly_several(bool blocks) const {
+    const uint64_t left_out = blocks ? n_perm_chunks : 0;
+    return !all_contiguous && total_bytes > (16ull << 20) && n_multi * 2 > n_chunks() - left_out;
   }
   // Is a scatter of `chunks` whole chunks of 16 KiB by ds_move_kernel launched in pieces of 8 KiB, six wavefronts per
   // SIMD instead of four?  (Images of 64 GiB and more, and the options for comparison: every other default call

@@ -1273,6 +1273,18 @@ int launch_beside_blocks(const ds_plan *plan, bool pack, bool few, bool mostly_g
   return launch_gather<true, true, true, 4, BLOCKS>(la, ma, grid_limit, stream);
 }
 
+// Plans of views and mostly chunks of several contiguous tensors (ds_plan::mostly_several), chunks of 16 KiB.
+template <bool NTL, int BLOCKS>
+int launch_several(bool pack, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  if (pack) return launch_pieces<true, 256, 4, NTL, true, true, 6, BLOCKS, kEvery>(la, ma, 0, stream);
+  return launch_pieces<false, 256, 4, NTL, true, false, 6, BLOCKS, kEvery>(la, ma, 0, stream);
+}
+template <int BLOCKS>
+int launch_several(const ds_plan *plan, bool pack, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  return plan->total_bytes <= kCachedBytes ? launch_several<false, BLOCKS>(pack, la, ma, stream)
+                                           : launch_several<true, BLOCKS>(pack, la, ma, stream);
+}
+
 // ---- views with runs shorter than 16 bytes, in blocks through LDS (ds_perm.h) ---------------------------
 // Bound by HBM as far as both sides have whole lines (wide blocks, ds_perm.h: 4.7 TB/s on large transpositions), else by
 // the memory system's handling of parts of lines: every second column, six of every sixteen columns, whose lines the
@@ -1766,6 +1778,10 @@ int launch_chunks(const ds_plan *plan, const DeviceTables &tb, bool pack, const 
   if ((variant == 0 || variant == 4) && !grid_limit && lg == 14 && la.n_pieces < (1u << 22) - 16 &&
       !(mostly_general && plan->all_contiguous)) {
     const int blocks = !tb.perms ? kAlone : plan->listed ? kListed : kBeside;
+    if (variant == 0 && plan->mostly_several(blocks != kAlone))
+      return blocks == kAlone    ? launch_several<kAlone>(plan, pack, la, ma, stream)
+             : blocks == kListed ? launch_several<kListed>(plan, pack, la, ma, stream)
+                                 : launch_several<kBeside>(plan, pack, la, ma, stream);
     if (pack)
       return blocks == kAlone    ? launch_units<true, kAlone>(plan, la, ma, stream)
              : blocks == kListed ? launch_units<true, kListed>(plan, la, ma, stream)

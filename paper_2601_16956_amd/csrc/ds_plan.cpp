@@ -573,6 +573,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
               for (uint32_t t2 = ti; multi && t2 <= t1; ++t2) multi = p->tiles[t2].n_outer == 0;
               if (multi) {
                 r.kind = DS_CHUNK_MULTI;
+                ++p->n_multi;
               } else {
                 p->all_contiguous = false;
                 bool one_by_one = false;

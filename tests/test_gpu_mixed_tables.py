@@ -113,3 +113,23 @@ def test_units_moved_an_element_per_lane(chunk_bytes, grid_limit):
         at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
     _check(Workload("lanes", 16, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards), chunk_bytes, grid_limit,
            "an element per lane", rng)
+
+
+@pytest.mark.parametrize("nbytes,n,view", [
+    (4000, 4500, ("u8", (41, 513), (700, 1))), (4000, 4500, ("bf16", (301, 203), (1, 303))), (9000, 7600, ("f32", (75, 25), (31, 1))),
+    (16100, 4700, ("bf16", (31, 25), (1, 33)))])
+def test_many_small_tensors_beside_a_view_in_larger_images(nbytes, n, view):
+    """The launch of four units per thread: images on both sides of the size read with ordinary loads, in the list beside
+    blocks and alone, with tensors below 16 bytes among the others."""
+    rng = np.random.default_rng(n)
+    shards, at = [], 3
+    for k in range(n):
+        size = nbytes + k % 61 if k % 100 else 1 + k // 100 % 15
+        shards.append(Shard(f"t{k}", "u8", (size,), (1,), at, len(shards)))
+        at += size + k % 5
+        if k == n // 2:
+            dtype, shape, strides = view
+            at = -(-at // 8) * 8
+            shards.append(Shard("view", dtype, shape, strides, at, len(shards)))
+            at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * DTYPES[dtype][1]
+    _check(Workload("several", 16, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards), 16384, 0, "several", rng)

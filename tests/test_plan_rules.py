@@ -12,7 +12,7 @@ from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
-         "in_pieces", "n_lanes", "n_dims")
+         "in_pieces", "n_lanes", "n_dims", "mostly_several")
 
 
 @pytest.fixture(scope="module")
@@ -127,3 +127,14 @@ def test_chunks_inside_views_of_several_dimensions_have_records(facts):
     assert facts([("u8", (40, 10, 1000), (15000, 1500, 1))]).n_dims == 0  # one outer dimension
     assert facts([("f32", (50, 40, 30, 3), (20000, 400, 10, 1))], 64).n_dims == 0
     assert facts([("f32", (50, 40, 30, 4), (20000, 400, 10, 1))], 64).n_dims == 58
+
+
+def test_which_plans_of_small_tensors_and_views_keep_four_units_per_thread(facts):
+    """Where most chunks hold several contiguous tensors, beside a view, in an image of more than 16 MiB."""
+    rows, small = ("u8", (60, 100), (140, 1)), 4096
+    assert facts(_small(4200, small) + [rows]).mostly_several
+    assert not facts(_small(4000, small) + [rows]).mostly_several                       # 15.6 MiB
+    assert not facts(_small(4200, small)).mostly_several                                # contiguous tensors only
+    assert facts(_small(4200, small) + [_transposed(512)]).mostly_several               # beside blocks
+    assert not facts(([("u8", (small,), (1,))] * 2 + [rows]) * 2500).mostly_several      # chunks that hold views
+    assert not facts([("u8", (1 << 25,), (1,)), rows] + _small(100, small)).mostly_several
