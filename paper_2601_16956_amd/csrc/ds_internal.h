@@ -144,6 +144,7 @@ struct ds_plan {
   uint64_t n_dims = 0;                     // ... of kind DS_CHUNK_DIMS
   uint64_t n_one_by_one = 0;               // ... and those with (parts of) views of several outer dimensions
   uint64_t n_short_rows = 0;               // chunks of rows of at most 512 bytes
+  bool any_wide = false;                   // does a view of `perms` move in wide blocks (ds_perm.h)?
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
   // The tables the kernels read, laid out one behind the other at these offsets (multiples of 128); the tables of
   // views moved in blocks come last.  `blob` is that layout on the host for tables of up to 256 KiB and for plans that

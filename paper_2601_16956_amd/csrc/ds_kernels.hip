@@ -1292,7 +1292,9 @@ int launch_several(const ds_plan *plan, bool pack, const LeanArgs &la, const Mov
 // every store that might have changed it, the table of such views of perf/cases.py took 93.4 us instead of 79.3 (gather).
 // That table: unit by unit 460 / 524 us, in narrow blocks 100 / 108, now 79 / 98; channels-last 14.1 / 14.5, now 10.8 /
 // 13.1; every second fp32 column 10.9 / 14.4, now 10.1 / 12.8.  Blocks are numbered along b first: along a first costs
-// 15 % of the gather.  LDS has room for five work-groups per CU.
+// 15 % of the gather.  LDS has room for five work-groups per CU, in launches without wide blocks (WIDE = false) for seven:
+// 8000 squares of 24 bf16, gather / scatter, 30.4 / 32.0 with five, 27.1 / 28.8 with seven; a channels-last convolution of 46 MB
+// 24.0 / 28.5 and 21.7 / 26.1; three of every eight bytes 34.1 / 42.9 and 32.9 / 43.0.
 struct PermArgs {
   const DsPerm *perms;
   const DsPermItem *items;  // the launch's first block
@@ -1346,9 +1348,9 @@ __device__ __forceinline__ void move_perm_item(const PermArgs &a, uint32_t i, ui
   }
 }
 
-template <bool PACK>
+template <bool PACK, bool WIDE>
 __global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
-  __shared__ __attribute__((aligned(16))) uint8_t s_block[kPermLdsBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t s_block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
   const uint32_t n = a.xcd_span ? a.xcd_span * 8u : a.n_items;
   for (uint32_t wi = blockIdx.x; wi < n; wi += gridDim.x) {
     const uint32_t i = a.xcd_span ? (wi & 7u) * a.xcd_span + (wi >> 3) : wi;
@@ -1366,11 +1368,11 @@ constexpr uint32_t kMixedChunks = 4096;  // other chunks up to which blocks and 
 // (157 MB, 2048 chunks beside the blocks) 75.3 / 79.4 and 97.0 / 98.5, the same at a quarter of the columns 9.0 / 11.8 and
 // 9.7 / 13.7, at a sixteenth 6.9 / 9.9; one transposed matrix of 32 KB to 8 MB beside 32 MB 14.5 to 16.7 / 16.3 to 18.9;
 // beside 100 MB (6400 chunks) 40.9 / 41.5 and 40.3 / 39.3; 32 MB beside 400 MB 153.8 / 142.8 and 152.8 / 145.7.
-template <bool PACK, bool NTL>
+template <bool PACK, bool NTL, bool WIDE>
 __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsChunkRec *recs, const uint32_t *ids,
                                                           uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
   __shared__ union {
-    __attribute__((aligned(16))) uint8_t block[kPermLdsBytes];
+    __attribute__((aligned(16))) uint8_t block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
     GenLds tab;
   } s;
   uint32_t wi = blockIdx.x;
@@ -1407,20 +1409,30 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsCh
 }
 
 template <bool PACK, bool NTL>
-int launch_mixed(const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
   const uint32_t span = (la.n_pieces + 7) / 8;
-  hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL>), dim3(a.xcd_span * 8 + span * 8 + ma.n_extra), dim3(256), 0, stream, a,
-                     la.recs, la.ids, la.n_pieces, span, la.c_lo, ma);
+  const dim3 grid(a.xcd_span * 8 + span * 8 + ma.n_extra);
+  if (plan->any_wide)
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, true>), grid, dim3(256), 0, stream, a, la.recs, la.ids, la.n_pieces, span,
+                       la.c_lo, ma);
+  else
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, false>), grid, dim3(256), 0, stream, a, la.recs, la.ids, la.n_pieces, span,
+                       la.c_lo, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
 
-int launch_perm(bool pack, const PermArgs &a, uint32_t grid_limit, hipStream_t stream) {
+int launch_perm(const ds_plan *plan, bool pack, const PermArgs &a, uint32_t grid_limit, hipStream_t stream) {
   uint32_t grid = a.xcd_span ? a.xcd_span * 8 : a.n_items;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
   if (grid > kMaxGrid) grid = kMaxGrid;
-  if (pack) hipLaunchKernelGGL(ds_perm_kernel<true>, dim3(grid), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(ds_perm_kernel<false>, dim3(grid), dim3(256), 0, stream, a);
+  if (plan->any_wide) {
+    if (pack) hipLaunchKernelGGL((ds_perm_kernel<true, true>), dim3(grid), dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((ds_perm_kernel<false, true>), dim3(grid), dim3(256), 0, stream, a);
+  } else {
+    if (pack) hipLaunchKernelGGL((ds_perm_kernel<true, false>), dim3(grid), dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((ds_perm_kernel<false, false>), dim3(grid), dim3(256), 0, stream, a);
+  }
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
@@ -1842,13 +1854,13 @@ int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *i
     if (plan->listed && (variant == 0 || variant == 4) && !grid_limit && plan->chunk_log2 == 14 &&
         la.n_pieces <= kMixedChunks && a.n_items < kMaxGrid / 2) {
       if (plan->total_bytes <= kCachedBytes)
-        return pack ? launch_mixed<true, false>(a, la, ma, stream) : launch_mixed<false, false>(a, la, ma, stream);
-      return pack ? launch_mixed<true, true>(a, la, ma, stream) : launch_mixed<false, true>(a, la, ma, stream);
+        return pack ? launch_mixed<true, false>(plan, a, la, ma, stream) : launch_mixed<false, false>(plan, a, la, ma, stream);
+      return pack ? launch_mixed<true, true>(plan, a, la, ma, stream) : launch_mixed<false, true>(plan, a, la, ma, stream);
     }
   }
   const int rc = launch_chunks(plan, tb, pack, la, ma, grid_limit, stream);
   if (rc != DS_OK || v0 == v1) return rc;
-  return launch_perm(pack, a, grid_limit, stream);
+  return launch_perm(plan, pack, a, grid_limit, stream);
 }
 
 }  // namespace

@@ -485,6 +485,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
             if (p->perms.empty()) p->perm_first.push_back(0);
             p->perm_first.push_back((uint32_t)(before + blocks));
             p->perms.push_back(perm);
+            p->any_wide |= (perm.flags & kPermWide) != 0;
             in_blocks.push_back((uint32_t)t);
             block_bytes += tl.nbytes;
           } else if (n_outer > 1 || (n_outer && tl.run_bytes < 16)) {

@@ -102,3 +102,10 @@ def test_one_unit_per_thread_runs_at_eight_wavefronts():
     assert len(units) >= 8
     for args, k in units:
         assert _waves(k) == 8, (args, k[".vgpr_count"])
+
+
+def test_blocks_that_are_not_wide_have_seven_work_groups_per_CU():
+    """Wide blocks need LDS that leaves room for five; launches without them do not pay for it."""
+    for name in ("ds_perm_kernel", "ds_mixed_kernel"):
+        for args, k in _kernels()[name]:
+            assert _waves(k) >= (5 if args[-1] == "true" else 6 if args[0] == "true" else 7), (name, args, k[".vgpr_count"])
