@@ -31,8 +31,10 @@
 //   the work-group share that space evenly, one unit each per pass (ds_move_kernel: up to four), in three
 //   phases: (1) registers and LDS only: find the tile of each unit by binary
 //   search over the scan and classify it; (2) all loads, nothing between
-//   them; (3) all stores.  Large pieces of views with several outer dimensions
-//   are taken out of the scan and walked by the whole work-group ("direct").
+//   them; (3) all stores.  Chunks inside a view with several outer dimensions
+//   and runs of 16 bytes and more need none of that: ds_unit_kernel moves them
+//   by their record (dims_move); ds_move_kernel takes large pieces of such views
+//   out of the scan and walks them with the whole work-group ("direct").
 //
 // Tensor-side addresses are only element-aligned.  gfx950 runs with unaligned
 // global access enabled, so a 16-byte unit that lies inside one contiguous run
@@ -62,7 +64,11 @@ constexpr uint32_t kUnitPieces = 4;       // work-groups of ds_unit_kernel per c
 // Images of at most so many bytes are moved with ordinary loads, larger ones with non-temporal ones, which leave nothing
 // in the 256 MB last-level cache.  Copies of one unit per thread, three pairs of buffers in turn, ordinary / non-
 // temporal: 23 MB 7.4 / 8.4 us, 40 MB 11.9 / 14.5, 58 MB 16.6 / 20.6, 70 MB 19.7 / 23.2, 85 MB 27.1 / 27.7, 110 MB (nothing
-// is found again) 36.8 / 34.6, 1.5 GB 476 / 453.
+// is found again) 36.8 / 34.6, 1.5 GB 476 / 453.  What that gains is the second pass over the same bytes: it is a property of
+// that rotation as much as of the cache.  On bytes that no cache holds (the gather and the scatter over tables, images
+// and tensors of 700 MB in rotation) ordinary loads cost 3 to 26 %: one tensor of 5 MB 4.05 / 3.78 and 3.80 / 3.02, of 23 MB
+// 11.6 / 10.5 and 11.4 / 9.8, of 60 MB 24.1 / 22.0 and 24.3 / 22.0, a 27 MB training state 12.8 / 11.6 and 12.2 / 10.7; and a
+// plain copy behind a pass that reads and writes its source 5 MB 3.1 / 3.1, 23 MB 12.7 / 10.5, 40 MB 11.4 / 15.5, 60 MB 17.6 / 20.7.
 constexpr uint64_t kCachedBytes = 64ull << 20;
 constexpr uint32_t kBigUnits = 512;       // N-D views: pieces of >= 8 KiB inside a chunk leave the scan
 
@@ -468,8 +474,9 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 // all stores.  So a chunk costs three dependent trips to memory (record -> descriptors -> data) however many
 // tiles it holds.  Units that are one 16-byte access (inside the payload of a contiguous tile or inside a row
 // of a 2-D view), padding, and units cut by the end of a run of at least 16 bytes are handled in the phases;
-// only the rest (runs shorter than 16 bytes, views with several outer dimensions) goes one by one through
-// move_unit afterwards.
+// only the rest (runs shorter than 16 bytes, views with several outer dimensions) goes afterwards, an element per lane
+// where the plan has little of it (DS_HOT_LANES), else one by one through
+// move_unit.
 // BLOCKS (not kAlone): a launch of blocks moves the views marked DS_HOT_PERM.
 template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int BLOCKS, bool WHOLE>
 __device__ __forceinline__ void general_chunk(const MoveArgs &a, uint64_t c, uint32_t piece, uint32_t t0, uint32_t t1,
@@ -1146,7 +1153,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, WAVES))) 
 // The same, one unit per thread and one piece of 4 KiB per work-group, for plans of 16 KiB chunks: what a default call
 // launches unless most chunks hold several contiguous tensors (multi_chunk).  With one load and one store per wavefront
 // the lean path is bound by HBM as long as eight wavefronts per SIMD fit (64 registers: hence no loop over work items,
-// whose constants the compiler keeps in registers, and move_runs) and a wavefront has done its work in the 700 cycles
+// whose constants the compiler keeps in registers, move_runs, and a scan without LDS) and a wavefront has done its work in the 700 cycles
 // that its 1 KiB takes its SIMD's share of HBM: the record in one scalar load, nothing else in front of the data.  (With
 // the record in two vector loads, one behind the other, the 7.6 GB gather took 3137 us.)  Measured, four units per thread
 // and four wavefronts (scatter: two and six) before / now: gather of a 70B rank (7.6 GB) 2392 / 2280 us, scatter of a 7B
@@ -1245,8 +1252,8 @@ int launch_gather(const LeanArgs &la, const MoveArgs &ma, uint32_t grid_limit, h
 }
 
 // The scatter, in whole chunks at four wavefronts per SIMD or in pieces of 8 KiB at six (ds_plan::scatter_in_pieces).
-// Plans of mostly general chunks keep whole chunks, whose tiles are looked up once, at six (15 MB in 711 views and
-// tensors: 10.7 us, in pieces 11.4).
+// Plans of mostly general chunks keep whole chunks, whose tiles are looked up once, at six (20 MB of tensors of 1 KiB
+// beside a view, 2048 work-groups: 11.3 us, at four 15.7).
 template <bool NTL, bool NTS, int BLOCKS = kAlone, int PATH = kEvery>
 int launch_scatter(const ds_plan *plan, bool few, bool mostly_general, const LeanArgs &la, const MoveArgs &ma,
                    uint32_t grid_limit, hipStream_t stream) {
@@ -1437,9 +1444,11 @@ int launch_perm(const ds_plan *plan, bool pack, const PermArgs &a, uint32_t grid
   return DS_OK;
 }
 
-// A plain contiguous copy in the lean path's shape (256 threads x 4 units per
-// work-group, non-temporal 16-byte accesses): the measured ceiling the gather
-// is compared with, and the known-size kernel the HBM counters are scaled by.
+// A plain contiguous copy in ds_move_kernel's shape (256 threads x 4 units per
+// work-group, four wavefronts per SIMD, non-temporal 16-byte accesses): the rate
+// the gather is compared with, and the known-size kernel the HBM counters are
+// scaled by.  No ceiling: one unit per thread at eight wavefronts, as in
+// ds_unit_kernel, copies at 6.75 TB/s, this one at 6.34 to 6.48.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void ds_copy_probe_kernel(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst,
                                                             uint64_t n_units) {
   // the same XCD-contiguous order of work-groups as the lean path

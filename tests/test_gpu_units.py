@@ -98,3 +98,44 @@ def test_views_of_several_outer_dimensions(large, blocks):
             assert gu.first_mismatch(dw.arena_host(), w.arena) is None, parts
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("chunks", [(1 << 22) - 17, (1 << 22) - 16])
+def test_the_largest_image_with_one_unit_per_thread_and_the_next(chunks):
+    """A launch has less than 2^32 threads: images of up to 2^22 - 17 chunks are moved one unit per thread, larger ones
+    several.  One tensor whose last unit is cut, at an odd address, behind a small one."""
+    import paper_2601_16956_amd as ds
+    import torch
+    n = chunks * 16384 - 64 - 5
+    arena = torch.empty((n + 4096) // 8 + 8, dtype=torch.int64, device="cuda").random_()
+    raw = arena.view(torch.uint8)
+    shards = [Shard("a", "u8", (61,), (1,), 3, 0), Shard("b", "u8", (n,), (1,), 129, 1)]
+    descs = ds.make_descs(shards, arena.data_ptr())
+    total = ds.ds_layout_assign(descs, 2, 64)
+    assert -(-total // 16384) == chunks
+    plan = ds.ds_plan_create(descs, 2, 64, ds.DS_PLAN_CHECK_MEMORY)
+    image = torch.full((total // 8,), -1, dtype=torch.int64, device="cuda")
+    img, stream, step = image.view(torch.uint8), torch.cuda.current_stream().cuda_stream, 1 << 30
+
+    def same():
+        return (torch.equal(img[:61], raw[3:64]) and not img[61:64].any() and not img[64 + n:].any() and
+                all(torch.equal(img[64 + at:64 + min(at + step, n)], raw[129 + at:129 + min(at + step, n)])
+                    for at in range(0, n, step)))
+    try:
+        print(f"[case] {chunks} chunks", flush=True)
+        ds.ds_pack(plan, image.data_ptr(), 0, total, stream)
+        torch.cuda.synchronize()
+        assert same()
+        raw[:3].zero_()
+        raw[64:129].fill_(7)
+        raw[129 + n:].fill_(9)
+        kept = [raw[:3].clone(), raw[64:129].clone(), raw[129 + n:].clone()]
+        raw[3:64].zero_()
+        raw[129:129 + n].zero_()
+        ds.ds_unpack(plan, image.data_ptr(), 0, total, stream)
+        torch.cuda.synchronize()
+        assert same()
+        assert all(torch.equal(a, b) for a, b in zip(kept, (raw[:3], raw[64:129], raw[129 + n:])))
+    finally:
+        torch.cuda.synchronize()
+        ds.ds_plan_destroy(plan)

@@ -141,7 +141,9 @@ def test_wide_blocks_move_exactly_the_view(host, k):
 
 @pytest.mark.parametrize("dtype,shape,strides", [
     ("bf16", (64, 64), (1, 20000001)), ("bf16", (64, 104), (1, 20000001)), ("u8", (128, 32), (1, 50000001)),
-    ("f32", (64, 20), (1, 18000001)), ("i64", (32, 50), (1, 9000001))])
+    ("f32", (64, 20), (1, 18000001)), ("i64", (32, 50), (1, 9000001)),
+    # on both sides of the distance up to which wide blocks are taken: (129 + 128) columns in 2^31 bytes
+    ("bf16", (64, 257), (1, 4177983)), ("bf16", (64, 257), (1, 4177984))])
 def test_columns_far_apart(host, dtype, shape, strides):
     """Columns so far apart that 32 bits do not hold the distance over the columns of a usual block: nothing but the
     view is read or written (memory of which only the view's pages exist)."""

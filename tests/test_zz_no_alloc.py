@@ -87,10 +87,13 @@ def test_no_alloc_gather_refuses_tables_beyond_its_static_memory():
     del arena
 
 
-@pytest.mark.parametrize("n,align,large", [(1, 16, 0), (63, 16, 0), (64, 64, 0), (65, 64, 0), (64, 16, 70 << 20)])
-def test_no_alloc_gather_with_its_table_in_the_arguments(n, align, large):
+@pytest.mark.parametrize("n,align,large,hole", [
+    (1, 16, 0, 0), (1, 16, 0, 1), (63, 16, 0, 1), (64, 64, 0, 0), (64, 64, 0, 1), (65, 64, 0, 0), (64, 16, 70 << 20, 0),
+    (63, 16, 70 << 20, 1), (64, 16, 70 << 20, 1)])
+def test_no_alloc_gather_with_its_table_in_the_arguments(n, align, large, hole):
     """Up to 64 contiguous tensors at multiples of 16 bytes: tails of every length, several tensors in 1 KiB, holes, an
-    image beyond the size read with ordinary loads; one tensor more, or one at an odd address, takes the copied tables."""
+    image beyond the size read with ordinary loads; one tensor more (a hole in front of the image counts as one), or one
+    at an odd address, takes the copied tables."""
     import torch
     import paper_2601_16956_amd as ds
     import gpu_util as gu
@@ -104,14 +107,16 @@ def test_no_alloc_gather_with_its_table_in_the_arguments(n, align, large):
             start = -(-at // 16) * 16 + (odd if k == n - 1 else 0)
             shards.append(Shard(f"t{k}", "u8", (size,), (1,), start, k))
             at = start + size
-            img += align * int(rng.integers(0, 70)) if k % 7 == 0 else 0       # (the image begins with a hole, or not)
+            if k % 7 == 0:
+                img += align * int(rng.integers(1, 70)) if k or hole else 0
             offsets.append(img)
             img = -(-(img + size) // align) * align
         w = Workload("arguments", align, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
         want, offs, _ = gu.oracle_image(w, offsets=offsets)
         dw = gu.DeviceWorkload(w, offsets=offsets)
         try:
-            print(f"[case] table in the arguments n={n} align={align} odd={odd} image={dw.total}", flush=True)
+            assert dw.info["n_tiles"] == n + hole and dw.total > large      # 64 of them fit the arguments
+            print(f"[case] table in the arguments n={n} hole={hole} align={align} odd={odd} image={dw.total}", flush=True)
             whole = _image(ds, torch, ds.ds_pack_noalloc, dw.plan, 0, dw.total)
             assert gu.first_mismatch(whole, want) is None, gu.first_mismatch(whole, want)
             cuts = [0] + sorted(16 * int(x) for x in rng.integers(0, dw.total // 16 + 1, 6)) + [dw.total]
