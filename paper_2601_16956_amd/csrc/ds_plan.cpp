@@ -145,14 +145,15 @@ DsTile make_tile(const ds_shard_desc &d, uint64_t nbytes) {
   return t;
 }
 
-// Views moved in blocks need a launch of their own, which adds about 4 us to a call.  The general path moves a few KiB
-// of them while the other chunks of the plan are under way, where there is enough under way, or enough that takes
-// it as long: one that holds one of 1 to 8 KiB takes 5 to 12 us.  Averages over places in the table, general path /
-// blocks, gather: 45 MB state (2781 chunks) with one of 2 KiB 27.5 / 30.7 us, of 8 KiB 28.4 / 31.3, of 16 KiB 36.7 /
-// 32.3; 24 000 small tensors (3551) 30.5 / 33.0, 33.5 / 33.7, 41.1 / 34.6; 292 MB rank 95.6 / 99.1, 98.5 / 99.8, 104.8 /
-// 100.6; but 23 MB state (1406, not one and a half rounds of 1024) 15.0 / 14.8, 19.9 / 15.1, 26.4 / 16.4; and 2000
-// fragments among which are rows of 2 to 15 bytes (669) with one of 2 KiB 12.8 / 14.9, of 4 KiB 14.9 / 15.1, of
-// 8 KiB 16.5 / 15.8.
+// Views moved in blocks need a launch of their own in plans of more than 4096 other chunks or without a list of them, which
+// adds 1 to 3 us to a call, and in others work-groups that hold more LDS.  The general path moves a few KiB of them, an
+// element per lane, while the other chunks of the plan are under way, where there is enough under way.  General path /
+// blocks, gather and scatter, us: 150 MB in two tensors (9600 chunks) with one of 2 KiB 52.8 / 53.9 and 53.0 / 53.6, of 8 KiB
+// 52.8 / 55.0 and 53.7 / 53.5; 40 MB of them (2560) 21.4 / 22.2 and 23.1 / 22.2, 21.3 / 22.5 and 24.1 / 22.4; 2000 tensors of 20
+// KB (2500) 18.7 / 21.6 and 20.9 / 22.6, 21.1 / 22.1 and 25.5 / 23.4; 24 000 small tensors (3551) 26.9 / 30.4 and 29.3 / 32.6,
+// but with one of 8 KiB 38.1 / 30.8 and 36.8 / 33.1.  With an earlier state of both, which the limits below are of: of 16 KiB
+// 36.7 / 32.3, 41.1 / 34.6; 23 MB state (1406, not one and a half rounds of 1024) with one of 2 KiB 15.0 / 14.8, of 8 KiB 19.9 /
+// 15.1; 2000 fragments among which are rows of 2 to 15 bytes (669) with one of 2 KiB 12.8 / 14.9, of 8 KiB 16.5 / 15.8.
 bool blocks_are_worth_a_launch(uint64_t block_bytes, uint64_t n_chunks, bool one_by_one) {
   return block_bytes > 8192 || (n_chunks <= 1536 && !(one_by_one && block_bytes <= 4096));
 }
