@@ -1298,26 +1298,34 @@ int launch_several(const ds_plan *plan, bool pack, const LeanArgs &la, const Mov
 // scatter writes in part.  A block's descriptor is read as constant memory: read through ordinary pointers, again after
 // every store that might have changed it, the table of such views of perf/cases.py took 93.4 us instead of 79.3 (gather).
 // That table: unit by unit 460 / 524 us, in narrow blocks 100 / 108, now 79 / 98; channels-last 14.1 / 14.5, now 10.8 /
-// 13.1; every second fp32 column 10.9 / 14.4, now 10.1 / 12.8.  Blocks are numbered along b first: along a first costs
-// 15 % of the gather.  LDS has room for five work-groups per CU, in launches without wide blocks (WIDE = false) for seven:
+// 13.1; every second fp32 column 10.9 / 14.4, now 10.1 / 12.8; with the blocks in stripes over the XCDs (ds_perm_order) and
+// streaming loads (STREAM: images that no cache holds until the next pass) 63.2 / 68.8.  Streaming loads alone are worth, us:
+// gather, where no line of the tensor is another block's too (kPermOnce), bf16 4096 x 4096 62.4 / 59.5 (five of them), every
+// second column 86.5 / 80.6 (ten), channels-last 75.8 / 72.1; where lines are shared they cost (bytes 4096 x 4120 68 / 81);
+// the scatter's loads 62.4 / 57.9, but not beside wide blocks whose stores stay in the caches to meet their lines' other
+// parts (1000 x 1007 75.4 / 82.1).  Images that the last-level cache holds lose (one of 33 MB 13.1 / 16.5).
+// Blocks are numbered along b first: along a first costs 15 % of the gather.  LDS has room for five work-groups per CU, in launches without wide blocks (WIDE = false) for seven:
 // 8000 squares of 24 bf16, gather / scatter, 30.4 / 32.0 with five, 27.1 / 28.8 with seven; a channels-last convolution of 46 MB
 // 24.0 / 28.5 and 21.7 / 26.1; three of every eight bytes 34.1 / 42.9 and 32.9 / 43.0.
 struct PermArgs {
   const DsPerm *perms;
   const DsPermItem *items;  // the launch's first block
   uint32_t n_items;
-  uint32_t xcd_span;        // blocks per XCD; 0 = work-group i takes block i
+  uint32_t xcd_span;        // work-groups per XCD; 0 = work-group i takes block i
+  uint32_t stripe, magic;   // the order of the blocks (DsPermOrder)
+};
+struct ImageArgs {
   uint8_t *img;             // points at image byte img_lo
   uint64_t img_lo, img_hi;
 };
 
-template <typename E, typename W, bool PACK>
-__device__ __forceinline__ void move_perm_block(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, const PermArgs &a, uint8_t *lds) {
+template <typename E, typename W, bool PACK, bool STREAM>
+__device__ __forceinline__ void move_perm_block(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, const ImageArgs &a, uint8_t *lds) {
   // opaque, so that nothing made of it is kept in registers (beyond 96: in scratch) across the loop over the blocks
   uint32_t tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   if (PACK) {
-    ds_perm_tensor_side<E, W, true>(d, k, lds, tid);
+    ds_perm_tensor_side<E, W, true, STREAM>(d, k, lds, tid);
     __syncthreads();
     // rows that end inside a line leave its rest to another block: the line is better kept in the L2 until then
     // (bytes transposed into rows of 112: 16.1 us streaming, 12.1 us cached; rows of whole lines 16.2 and 17.7)
@@ -1331,38 +1339,44 @@ __device__ __forceinline__ void move_perm_block(const DS_PERM_TABLE DsPerm &d, c
         st16_aligned<false>((uint8_t *)p, u32x4{v.w[0], v.w[1], v.w[2], v.w[3]});
       });
   } else {
-    ds_perm_image_load(d, k, lds, a.img, a.img_lo, tid, [](uint64_t p) {
-      const u32x4 v = ld16_aligned<false>((const uint8_t *)p);
-      return DsPermUnit{{v.x, v.y, v.z, v.w}};
-    });
+    if (STREAM && (d.flags & (kPermWide | kPermStream)) != kPermWide)
+      ds_perm_image_load(d, k, lds, a.img, a.img_lo, ds_perm_apart<true>(tid), [](uint64_t p) {
+        const u32x4 v = ld16_aligned<true>((const uint8_t *)p);
+        return DsPermUnit{{v.x, v.y, v.z, v.w}};
+      });
+    else
+      ds_perm_image_load(d, k, lds, a.img, a.img_lo, tid, [](uint64_t p) {
+        const u32x4 v = ld16_aligned<false>((const uint8_t *)p);
+        return DsPermUnit{{v.x, v.y, v.z, v.w}};
+      });
     __syncthreads();
-    ds_perm_tensor_side<E, W, false>(d, k, lds, tid);
+    ds_perm_tensor_side<E, W, false, STREAM>(d, k, lds, tid);
   }
 }
 
 // Item i of a launch: one block.
-template <bool PACK>
-__device__ __forceinline__ void move_perm_item(const PermArgs &a, uint32_t i, uint8_t *lds) {
-  const DS_PERM_TABLE DsPermItem &item = ((const DS_PERM_TABLE DsPermItem *)(uintptr_t)a.items)[i];
-  const DS_PERM_TABLE DsPerm &d = ((const DS_PERM_TABLE DsPerm *)(uintptr_t)a.perms)[item.perm];
+template <bool PACK, bool STREAM>
+__device__ __forceinline__ void move_perm_item(const PermArgs &p, const ImageArgs &a, uint32_t i, uint8_t *lds) {
+  const DS_PERM_TABLE DsPermItem &item = ((const DS_PERM_TABLE DsPermItem *)(uintptr_t)p.items)[i];
+  const DS_PERM_TABLE DsPerm &d = ((const DS_PERM_TABLE DsPerm *)(uintptr_t)p.perms)[item.perm];
   DsPermBlock k;
   if (!ds_perm_block(d, item.tile, a.img_lo, a.img_hi, PACK, k)) return;
   switch (d.flags & 0xFFu) {
-    case 0: move_perm_block<uint8_t, uint32_t, PACK>(d, k, a, lds); break;
-    case 1: move_perm_block<uint16_t, uint32_t, PACK>(d, k, a, lds); break;
-    case 2: move_perm_block<uint32_t, uint32_t, PACK>(d, k, a, lds); break;
-    default: move_perm_block<uint64_t, uint64_t, PACK>(d, k, a, lds); break;
+    case 0: move_perm_block<uint8_t, uint32_t, PACK, STREAM>(d, k, a, lds); break;
+    case 1: move_perm_block<uint16_t, uint32_t, PACK, STREAM>(d, k, a, lds); break;
+    case 2: move_perm_block<uint32_t, uint32_t, PACK, STREAM>(d, k, a, lds); break;
+    default: move_perm_block<uint64_t, uint64_t, PACK, STREAM>(d, k, a, lds); break;
   }
 }
 
-template <bool PACK, bool WIDE>
-__global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a) {
+template <bool PACK, bool STREAM, bool WIDE>
+__global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a, ImageArgs image) {
   __shared__ __attribute__((aligned(16))) uint8_t s_block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
   const uint32_t n = a.xcd_span ? a.xcd_span * 8u : a.n_items;
   for (uint32_t wi = blockIdx.x; wi < n; wi += gridDim.x) {
-    const uint32_t i = a.xcd_span ? (wi & 7u) * a.xcd_span + (wi >> 3) : wi;
+    const uint32_t i = a.xcd_span ? ds_perm_ordered(wi, a.stripe, a.magic) : wi;
     if (i >= a.n_items) continue;
-    move_perm_item<PACK>(a, i, s_block);
+    move_perm_item<PACK, STREAM>(a, image, i, s_block);
     __syncthreads();  // the block in LDS has been used
   }
 }
@@ -1384,8 +1398,8 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsCh
   } s;
   uint32_t wi = blockIdx.x;
   if (wi < a.xcd_span * 8u) {
-    const uint32_t i = (wi & 7u) * a.xcd_span + (wi >> 3);
-    if (i < a.n_items) move_perm_item<PACK>(a, i, s.block);
+    const uint32_t i = ds_perm_ordered(wi, a.stripe, a.magic);
+    if (i < a.n_items) move_perm_item<PACK, NTL>(a, ImageArgs{ma.img, ma.img_lo, ma.img_hi}, i, s.block);
     return;
   }
   wi -= a.xcd_span * 8u;
@@ -1397,13 +1411,13 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsCh
     const DsChunkRec r = load_rec(recs, c_lo + cm);
     c = load_id(ids, c_lo + cm);
     if ((r.kind & 0xFFu) < DS_CHUNK_GENERAL) {
-      lean_move<PACK, 256, 4, NTL, true, PACK>(r, a.img + ((c << 14) - a.img_lo), 0);
+      lean_move<PACK, 256, 4, NTL, true, PACK>(r, ma.img + ((c << 14) - ma.img_lo), 0);
       return;
     }
     if ((r.kind & 0xFFu) == DS_CHUNK_DIMS) {
 #pragma unroll 1
       for (uint32_t piece = 0; piece < 16384; piece += 4096)
-        dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, a.img + ((c << 14) - a.img_lo) + piece, piece);
+        dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, ma.img + ((c << 14) - ma.img_lo) + piece, piece);
       return;
     }
     t0 = r.tile;
@@ -1429,17 +1443,13 @@ int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, con
   return DS_OK;
 }
 
-int launch_perm(const ds_plan *plan, bool pack, const PermArgs &a, uint32_t grid_limit, hipStream_t stream) {
+template <bool PACK, bool STREAM>
+int launch_perm(const ds_plan *plan, const PermArgs &a, const ImageArgs &image, uint32_t grid_limit, hipStream_t stream) {
   uint32_t grid = a.xcd_span ? a.xcd_span * 8 : a.n_items;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
   if (grid > kMaxGrid) grid = kMaxGrid;
-  if (plan->any_wide) {
-    if (pack) hipLaunchKernelGGL((ds_perm_kernel<true, true>), dim3(grid), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((ds_perm_kernel<false, true>), dim3(grid), dim3(256), 0, stream, a);
-  } else {
-    if (pack) hipLaunchKernelGGL((ds_perm_kernel<true, false>), dim3(grid), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((ds_perm_kernel<false, false>), dim3(grid), dim3(256), 0, stream, a);
-  }
+  if (plan->any_wide) hipLaunchKernelGGL((ds_perm_kernel<PACK, STREAM, true>), dim3(grid), dim3(256), 0, stream, a, image);
+  else hipLaunchKernelGGL((ds_perm_kernel<PACK, STREAM, false>), dim3(grid), dim3(256), 0, stream, a, image);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
@@ -1856,10 +1866,12 @@ int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *i
     a.perms = tb.perms;
     a.items = tb.perm_items + first;
     a.n_items = (uint32_t)(last - first);
-    a.xcd_span = variant == 3 ? 0 : (a.n_items + 7) / 8;
-    a.img = img;
-    a.img_lo = img_lo;
-    a.img_hi = img_hi;
+    if (variant != 3 && a.n_items < kPermOrdered) {
+      const DsPermOrder order = ds_perm_order(a.n_items, pack);
+      a.xcd_span = order.span;
+      a.stripe = order.stripe;
+      a.magic = order.magic;
+    }
     if (plan->listed && (variant == 0 || variant == 4) && !grid_limit && plan->chunk_log2 == 14 &&
         la.n_pieces <= kMixedChunks && a.n_items < kMaxGrid / 2) {
       if (plan->total_bytes <= kCachedBytes)
@@ -1869,7 +1881,10 @@ int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *i
   }
   const int rc = launch_chunks(plan, tb, pack, la, ma, grid_limit, stream);
   if (rc != DS_OK || v0 == v1) return rc;
-  return launch_perm(plan, pack, a, grid_limit, stream);
+  const ImageArgs image = {img, img_lo, img_hi};
+  if (plan->total_bytes <= kCachedBytes)
+    return pack ? launch_perm<true, false>(plan, a, image, grid_limit, stream) : launch_perm<false, false>(plan, a, image, grid_limit, stream);
+  return pack ? launch_perm<true, true>(plan, a, image, grid_limit, stream) : launch_perm<false, true>(plan, a, image, grid_limit, stream);
 }
 
 }  // namespace

@@ -48,7 +48,7 @@ constexpr uint64_t kPermMinBytes = 1024;
 constexpr int kPermUnroll = 8;             // granules a thread has in flight
 
 enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11,
-                  kPermWide = 1u << 12, kPermStream = 1u << 13 };
+                  kPermWide = 1u << 12, kPermStream = 1u << 13, kPermOnce = 1u << 14 };
 
 // Wide blocks: views dense along a (16-byte loads of neighbours along a, transposed in registers), kPermWideA steps along a;
 // of each row 384 bytes where rows start at lines of the image, else up to 368, and a block writes the lines that start in
@@ -86,7 +86,9 @@ struct DsPerm {
                               // is one piece of it, of which only the two ends are parts of lines) | kPermWide |
                               // kPermStream (wide, and the columns of the tensor start at multiples of 64 bytes: the
                               // scatter's stores stream.  Streaming / cached, us: fp32 4096 x 4099 21.2 / 29.3, bytes
-                              // 8192 x 8216 24.5 / 40.0; columns at multiples of 32 bytes 25.5 / 16.6, 109 / 86)
+                              // 8192 x 8216 24.5 / 40.0; columns at multiples of 32 bytes 25.5 / 16.6, 109 / 86) |
+                              // kPermOnce (a block's lines of the tensor are all its own, or nearly: the gather's loads
+                              // of them may stream)
   uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
 static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
@@ -173,13 +175,14 @@ DS_PERM_FN uint32_t ds_perm_row_lds(const DS_PERM_TABLE DsPerm &d, const DsPermB
 // Addresses are the block's (one for the work-group) plus a 32-bit offset.  Gather: every load of a batch is
 // issued before the first is used; indices beyond the block are pulled back to its last element, which is then
 // moved twice, so that no load hangs on a condition.  Scatter: only what lies in [lo, hi) is stored.
-template <typename T>
+template <typename T, bool NT = false>
 DS_PERM_FN T ds_perm_load(uint64_t base, uint32_t off, uint32_t align) {
   DS_PERM_TOUCH('r', base + off, sizeof(T), align);
   T v;
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef T any __attribute__((aligned(1)));
-  v = *(const DS_PERM_GLOBAL any *)(base + off);
+  if (NT) v = __builtin_nontemporal_load((const DS_PERM_GLOBAL any *)(base + off));
+  else v = *(const DS_PERM_GLOBAL any *)(base + off);
 #else
   memcpy(&v, (const void *)(uintptr_t)(base + off), sizeof(T));
 #endif
@@ -197,6 +200,21 @@ DS_PERM_FN void ds_perm_store(uint64_t base, uint32_t off, T v, uint32_t align) 
   memcpy((void *)(uintptr_t)(base + off), &v, sizeof(T));
 #endif
   (void)align;
+}
+// Around streaming accesses: an opaque offset in front, a mark behind loads.  (Of two loops that differ in the cache policy
+// alone the compiler makes one, with cached accesses.)
+template <bool NT>
+DS_PERM_FN uint32_t ds_perm_apart(uint32_t off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (NT) asm volatile("" : "+v"(off));
+#endif
+  return off;
+}
+template <bool NT>
+DS_PERM_FN void ds_perm_loaded() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (NT) asm volatile("; streamed");
+#endif
 }
 template <typename E>
 DS_PERM_FN E ds_perm_get(const uint8_t *lds, uint32_t at) {
@@ -254,11 +272,11 @@ DS_PERM_FN void ds_perm_full(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k
 }
 
 // Walk along a, any block (d.ta is a power of two).
-template <typename E, bool PACK>
+template <typename E, bool PACK, bool NT>
 DS_PERM_FN void ds_perm_along_a(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   const uint32_t n_cols = PACK ? k.nbx : k.nb;
   const uint32_t step = kPermThreads / d.ta, a = tid & (d.ta - 1), ac = ds_perm_min(a, k.na - 1);
-  const uint32_t first = ac * k.sa, row = ds_perm_row_lds(d, k, ac);
+  const uint32_t first = ds_perm_apart<NT>(ac * k.sa), row = ds_perm_row_lds(d, k, ac);
   const uint32_t image = ds_perm_row_image(k, ac);
 #pragma unroll 1
   for (uint32_t b = tid / d.ta; b < n_cols; b += kPermUnroll * step)
@@ -269,8 +287,9 @@ DS_PERM_FN void ds_perm_along_a(const DS_PERM_TABLE DsPerm &d, const DsPermBlock
 #pragma unroll
         for (int j = 0; j < kPermUnroll; ++j) {
           const uint32_t c = ds_perm_min(b + (uint32_t)j * step, n_cols - 1);
-          v[j] = ds_perm_load<E>(k.src0, first + c * k.sb + in_run, sizeof(E));
+          v[j] = ds_perm_load<E, NT>(k.src0, first + c * k.sb + in_run, sizeof(E));
         }
+        ds_perm_loaded<NT>();
 #pragma unroll
         for (int j = 0; j < kPermUnroll; ++j) {
           const uint32_t c = ds_perm_min(b + (uint32_t)j * step, n_cols - 1);
@@ -288,7 +307,7 @@ DS_PERM_FN void ds_perm_along_a(const DS_PERM_TABLE DsPerm &d, const DsPermBlock
 }
 
 // Walk along b: granule i of the block, rows one behind the other.
-template <typename E, bool PACK>
+template <typename E, bool PACK, bool NT>
 DS_PERM_FN void ds_perm_along_b(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   const uint32_t K = d.run / (uint32_t)sizeof(E);
   const uint32_t per_row = (PACK ? k.nbx : k.nb) * K, total = k.na * per_row;
@@ -309,7 +328,7 @@ DS_PERM_FN void ds_perm_along_b(const DS_PERM_TABLE DsPerm &d, const DsPermBlock
     if (PACK) {
       E v[kPermUnroll];
 #pragma unroll
-      for (int j = 0; j < kPermUnroll; ++j) v[j] = ds_perm_load<E>(k.src0, from[j], sizeof(E));
+      for (int j = 0; j < kPermUnroll; ++j) v[j] = ds_perm_load<E, NT>(k.src0, ds_perm_apart<NT>(from[j]), sizeof(E));
 #pragma unroll
       for (int j = 0; j < kPermUnroll; ++j) ds_perm_put<E>(lds, at[j], v[j]);
     } else {
@@ -402,12 +421,9 @@ DS_PERM_FN void ds_perm_lds_words(const uint8_t *lds, uint32_t at, uint32_t *out
   for (int i = 0; i < N; ++i) out[i] = ds_align_bytes(v[i + 1], v[i], at & 3u);
 }
 
-// (two loops, each behind an opaque offset: else the compiler makes one of them, with cached stores)
 template <uint32_t S, bool NT>
 DS_PERM_FN void ds_perm_wide_columns(const uint32_t (*in)[2 * S], const DsPermBlock &k, uint32_t off, uint32_t c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  if (NT) asm volatile("" : "+v"(off));
-#endif
+  off = ds_perm_apart<NT>(off);
 #pragma unroll
   for (int j = 0; j < 8; ++j, off += k.sb)
     if (c + j < k.nb)
@@ -415,7 +431,7 @@ DS_PERM_FN void ds_perm_wide_columns(const uint32_t (*in)[2 * S], const DsPermBl
                                                             ds_perm_word<S>(in, j, 2), ds_perm_word<S>(in, j, 3)}, S);
 }
 
-template <typename E, bool PACK>
+template <typename E, bool PACK, bool NT>
 DS_PERM_FN void ds_perm_wide(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   constexpr uint32_t S = (uint32_t)sizeof(E), G = 16 / S, lanes = kPermWideA / G;
   constexpr int W = 2 * S;  // words of 8 elements
@@ -423,13 +439,14 @@ DS_PERM_FN void ds_perm_wide(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k
   if (a >= k.na || c >= n_cols) return;
   const uint32_t first = a * S + c * k.sb, last = a * S + (n_cols - 1) * k.sb;
   if (PACK) {
-    uint32_t in[8][4], off = first;
+    uint32_t in[8][4], off = ds_perm_apart<NT>(first);
 #pragma unroll
     for (int j = 0; j < 8; ++j, off += k.sb) {  // columns beyond the block: its last one again
-      const DsPermQuad q = ds_perm_load<DsPermQuad>(k.src0, ds_perm_min(off, last), S);
+      const DsPermQuad q = ds_perm_load<DsPermQuad, NT>(k.src0, ds_perm_min(off, last), S);
 #pragma unroll
       for (int w = 0; w < 4; ++w) in[j][w] = q[w];
     }
+    ds_perm_loaded<NT>();
 #pragma unroll
     for (uint32_t i = 0; i < G; ++i) {
       const uint32_t at = ds_perm_row_start(d, a + i) + c * S;
@@ -453,14 +470,26 @@ DS_PERM_FN void ds_perm_wide(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k
   }
 }
 
-template <typename E, typename W, bool PACK>
+// STREAM: the image is one of those that no cache holds until the next pass (kCachedBytes); the gather's loads then stream
+// where no line of the tensor is another block's too.
+template <typename E, typename W, bool PACK, bool STREAM = false>
 DS_PERM_FN void ds_perm_tensor_side(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   constexpr uint32_t V = (uint32_t)(sizeof(W) / sizeof(E));
-  if ((d.flags & kPermWide) && (PACK || k.inside)) ds_perm_wide<E, PACK>(d, k, lds, tid);
-  else if (!(d.flags & kPermAlongA)) ds_perm_along_b<E, PACK>(d, k, lds, tid);
-  else if (!(d.flags & kPermFull)) ds_perm_along_a<E, PACK>(d, k, lds, tid);
-  else if (V > 1 && d.sa == sizeof(E) && k.na % V == 0 && (PACK || k.inside)) ds_perm_full<E, W, PACK>(d, k, lds, tid);
-  else ds_perm_full<E, E, PACK>(d, k, lds, tid);
+  constexpr bool NT = PACK && STREAM;
+  const bool once = NT && (d.flags & kPermOnce);
+  if ((d.flags & kPermWide) && (PACK || k.inside)) {
+    if (once) ds_perm_wide<E, PACK, NT>(d, k, lds, tid);
+    else ds_perm_wide<E, PACK, false>(d, k, lds, tid);
+  } else if (!(d.flags & kPermAlongA)) {
+    ds_perm_along_b<E, PACK, NT>(d, k, lds, tid);
+  } else if (!(d.flags & kPermFull)) {
+    if (once) ds_perm_along_a<E, PACK, NT>(d, k, lds, tid);
+    else ds_perm_along_a<E, PACK, false>(d, k, lds, tid);
+  } else if (V > 1 && d.sa == sizeof(E) && k.na % V == 0 && (PACK || k.inside)) {
+    ds_perm_full<E, W, PACK>(d, k, lds, tid);
+  } else {
+    ds_perm_full<E, E, PACK>(d, k, lds, tid);
+  }
 }
 
 // ---- image side ---------------------------------------------------------------------------------------------
@@ -758,7 +787,8 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   while (d->lanes_log2 < 8 && (2u << d->lanes_log2) <= units) ++d->lanes_log2;  // (not used by wide blocks inside the range)
   d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
              (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
-             (wide && (columns & 63) == 0 ? kPermStream : 0u);
+             (wide && (columns & 63) == 0 ? kPermStream : 0u) |
+             ((wide ? lines && g > 1 && (columns & (kPermLine - 1)) == 0 : ta * d->sa >= 4 * kPermLine) ? kPermOnce : 0u);
   const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
   return tiles < (1u << 31) ? (uint64_t)tiles : 0;
 }
@@ -774,6 +804,34 @@ static inline void ds_perm_items(const DsPerm &d, uint32_t perm, uint32_t n, DsP
       for (uint32_t x = 0; x < between; ++x)
         for (uint32_t tb = 0; tb < d.tiles_b; ++tb)
           *out++ = {perm, ((slower * between + x) * d.tiles_a + ta) * d.tiles_b + tb};
+}
+
+// How a launch's blocks are dealt to the work-groups, of which number w runs on XCD w mod 8: in stripes of neighbouring
+// blocks, stripe by stripe over the XCDs, as many for each.  What runs at a time then lies in one part of the tensors and
+// of the image, which the DRAM takes better than eight parts far apart, while the lines that neighbouring blocks share
+// stay in one L2.  Measured, us, gather / scatter: bf16 4096 x 4120, five of them, one stripe per XCD 64.7 / 64.7, stripes
+// of 256 blocks 65.5 / 65.3, 128 63.2 / 62.8, 64 62.4 / 61.5, 32 62.1 / 60.9, single blocks 64.1 / 62.6; bytes of that shape
+// 72.8 / 83.2, with stripes of 64 68.3 / 73.6, with single blocks 93.0 / 72.9; the views of perf/cases.py 76.7 / 96.9, with
+// stripes 67.5 / 81.6 (kinds of views that take unequal time are dealt evenly too).
+// Gathers of less than 1536 blocks, all but a fifth of which run at once, have one stripe per XCD (1100 blocks of views of
+// bytes 15.7, in two 16.6; the scatter 20.3 and 17.0).
+struct DsPermOrder {
+  uint32_t span;    // work-groups per XCD
+  uint32_t stripe;  // blocks of a stripe, at least 2
+  uint32_t magic;   // ds_perm_magic of it
+};
+constexpr uint32_t kPermOrdered = 1u << 27;
+static inline DsPermOrder ds_perm_order(uint32_t n, bool pack) {  // 0 < n < kPermOrdered
+  const uint32_t blocks = 8 * (pack ? 64 : 48);
+  const uint32_t rounds = n < (pack ? 1536 : blocks) ? 1 : (n + blocks / 2) / blocks;
+  uint32_t stripe = (n + rounds * 8 - 1) / (rounds * 8);
+  if (stripe < 2) stripe = 2;
+  return {rounds * stripe, stripe, ds_perm_magic(stripe)};
+}
+// The block that work-group w < 8 * span takes; n and more: none.  (w / 8 * stripe < 2^32: the quotient is exact.)
+DS_PERM_FN uint32_t ds_perm_ordered(uint32_t w, uint32_t stripe, uint32_t magic) {
+  const uint32_t i = w >> 3, round = (uint32_t)(((uint64_t)i * magic) >> 32);
+  return (round * 7u + (w & 7u)) * stripe + i;  // stripe 8 round + XCD, block i - round * stripe of it
 }
 
 // The blocks [first, last), in that order, that can hold image bytes of [img_lo, img_hi), which holds some of the view's:

@@ -1,0 +1,68 @@
+"""The order in which the blocks of views with short runs are dealt to the XCDs, and the streaming loads of such blocks in
+images of more than 64 MiB."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import ds_oracle as orc
+from workloads.configs import DTYPES, Shard, Workload
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.parametrize("pack", [0, 1])
+def test_every_block_is_taken_once(tmp_path, pack):
+    so = str(tmp_path / "order_host.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-fPIC", "-shared", "-I",
+                    os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c_abi", "order_host.cpp"), "-o", so], check=True)
+    deal = ctypes.CDLL(so).order_host_deal
+    deal.restype, deal.argtypes = ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_int, ctypes.c_void_p]
+    for n in [*range(1, 40), 383, 384, 385, 1535, 1536, 1537, *range(4096, 4110), 100003, (1 << 22) - 1, (1 << 27) - 1]:
+        hits = np.zeros(n, dtype=np.uint8)
+        launched = deal(n, pack, hits.ctypes.data)
+        assert hits.min() == hits.max() == 1
+        # at most one block per XCD and stripe too many (a launch of a few blocks has two per XCD)
+        assert launched <= max(16, n + 8 * (n // (8 * 48) + 1) + 8)
+
+
+# lines of the tensor that are one block's own and lines that two blocks share, in each way to walk a block
+STREAMED = [("bf16", (1024, 1536), (1, 1024)), ("bf16", (1024, 1531), (1, 1024)), ("f32", (512, 1111), (1, 516)),
+            ("u8", (704, 1901), (1, 704)), ("i64", (130, 513), (1, 136)), ("bf16", (2, 512, 768), (512 * 768, 1, 512)),
+            ("f32", (300, 300, 9), (2700, 1, 300)), ("f32", (61, 70, 9), (630, 1, 70)), ("f32", (333, 1111), (2222, 2)),
+            ("bf16", (700, 64, 6), (1024, 16, 1)), ("u8", (131, 259), (1, 133)), ("bf16", (70, 300), (800, 2))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("beside", [60 << 20, 70 << 20])
+def test_blocks_of_images_that_no_cache_holds(beside):
+    """One launch with the other chunks (60 MB) and two (70 MB), whole and in ranges that cut blocks."""
+    import gpu_util as gu
+    rng = np.random.default_rng(beside >> 20)
+    shards, at = [], 0
+    for k, (dtype, shape, strides) in enumerate(STREAMED + [("u8", (beside,), (1,))]):
+        at = -(-at // 256) * 256 + (0 if k % 3 else DTYPES[dtype][1] * int(rng.integers(0, 3)))
+        shards.append(Shard(f"s{k}", dtype, shape, strides, at, k))
+        at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * DTYPES[dtype][1]
+    w = Workload("streamed", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print(f"[case] streamed blocks beside {beside} bytes, image={dw.total}", flush=True)
+        assert dw.total > 64 << 20
+        cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, (dw.total - beside) // 16, 5)) + [dw.total]
+        ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+        for lo, hi in [(0, dw.total)] + ranges:
+            assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        for parts in ([(0, dw.total)], ranges):
+            dw.arena.fill_(0x5A)
+            for lo, hi in parts:
+                dw.unpack(want, lo, hi)
+            assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+    finally:
+        dw.close()
