@@ -1519,7 +1519,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
 // usually shows it in its first 4 KiB, so the flags cost little more than the constant blocks' bytes and the image
 // is read once in all, not twice.  1 GiB of which 30 % is constant, in blocks of 64 KiB: flags, scan and dense
 // copy together 603 us with every byte read by both passes (275 + 280 us) and a scan of 256 entries at a time
-// (46 us).
+// (46 us).  Small images are bound by the launches: see ds_count_and_pack_kernel.
 //
 // One work-group looks at one segment: a whole block of up to 64 KiB, or 64 KiB of a larger one (WHOLE = false; the
 // flags are cleared before).  keep[k] = 1 if some 16-byte unit of block k differs from the block's first unit.
@@ -1561,6 +1561,46 @@ __global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *
     if (WHOLE) keep[block] = any ? 1u : 0u;
     else if (any) atomicOr(keep + block, 1u);
     if (first == block_first) patterns[block] = ref;
+  }
+}
+
+// The same for blocks of more than 64 KiB in images of up to 16 MiB: one work-group looks at a block, so that no flags have
+// to be cleared by a launch of their own.  Behind the block's first 16 KiB it takes 256 KiB at a time.  Bound by the latency
+// of those steps where blocks are constant; a constant block of 1 MiB takes 10 us, which is where the line for the block
+// size lies.  Images of 64 MB are a few us faster in segments (40 MB in blocks of 1 MiB 26.5 / 25.2 us, of 3 MB in blocks of
+// 128 KiB 7.9 / 10.2).
+constexpr uint32_t kBlockThreads = 1024, kBlockUnroll = 16;
+constexpr uint64_t kWholeBlocksBytes = 16ull << 20;
+constexpr uint32_t kWholeBlockUnitsLog2 = 16;
+__global__ __launch_bounds__(kBlockThreads) void ds_constant_blocks_kernel(const u32x4 *__restrict__ img, uint64_t n_units,
+                                                                           uint32_t units_per_block_log2,
+                                                                           uint32_t *__restrict__ keep,
+                                                                           u32x4 *__restrict__ patterns) {
+  const uint32_t tid = threadIdx.x;
+  const uint64_t first = (uint64_t)blockIdx.x << units_per_block_log2, left = n_units - first;
+  const uint32_t n = left < (1ull << units_per_block_log2) ? (uint32_t)left : 1u << units_per_block_log2;
+  const u32x4 *const block = img + first;
+  const u32x4 ref = block[0];
+  u32x4 d = block[tid < n ? tid : 0] ^ ref;
+  int any = __syncthreads_or((d.x | d.y | d.z | d.w) != 0);
+  for (uint32_t base = kBlockThreads; base < n && !any; base += kBlockUnroll * kBlockThreads) {
+    u32x4 y[kBlockUnroll];
+#pragma unroll
+    for (uint32_t i = 0; i < kBlockUnroll; ++i) {
+      const uint32_t u = base + kBlockThreads * i + tid;
+      y[i] = block[u < n ? u : n - 1];
+    }
+    uint32_t diff = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kBlockUnroll; ++i) {
+      d = y[i] ^ ref;
+      diff |= d.x | d.y | d.z | d.w;
+    }
+    any = __syncthreads_or(diff != 0);
+  }
+  if (tid == 0) {
+    keep[blockIdx.x] = any ? 1u : 0u;
+    patterns[blockIdx.x] = ref;
   }
 }
 
@@ -1663,6 +1703,58 @@ int launch_pack_kept(const u32x4 *img, uint64_t n_units, uint32_t upb_log2, cons
   return DS_OK;
 }
 
+// The scan and the pack in one launch, for images of up to 64 MiB in up to 2048 blocks: a work-group counts the kept blocks
+// in front of its own, whose flags are at most 8 KiB in the L2, and the first of each block leaves the count in pos.
+// Small images are bound by the launches, each about 4 us of the caller's time, then by the chain flags -> count -> stores
+// behind the loads; from 8 MiB on by the caches and HBM, where four units per thread and ordinary loads are ahead.  All of
+// ds_image_compress with the scan of its own / so, us: 16 KB 10.2 / 6.0, 1 MB 10.1 / 6.1, 8 MB in blocks of 1 MiB 13.3 / 6.3 (no
+// clearing launch either), 17 MB of which 30 % is constant 16.7 / 13.2 (one unit per thread 13.8), 34 MB in 2048 blocks 18.5 /
+// 14.1, 64 MB 27.7 / 25.8, none of it constant 32.9 / 21.9 (streaming loads 27.7).  Beyond: 134 MB in 2048 blocks 45.1 / 42.2,
+// none constant 49.5 / 51.7; 256 MB 78.3 / 82.5; 1 GiB in 1024 blocks 307 / 331.
+constexpr uint64_t kCountedBlocks = 2048, kOneUnitBytes = 8ull << 20;
+template <int UNROLL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_count_and_pack_kernel(
+    const u32x4 *__restrict__ img, uint32_t n_units, uint32_t units_per_block_log2, const uint32_t *__restrict__ keep,
+    uint32_t *__restrict__ pos, uint32_t n_blocks, u32x4 *__restrict__ packed) {
+  __shared__ uint32_t wave_sum[256 / kWave];
+  constexpr uint32_t kUnits = 256 * UNROLL;  // in one block (of a power of two of at least 16 KiB)
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+  const uint32_t first = blockIdx.x * kUnits, left = n_units - first, mine = left < kUnits ? left : kUnits;
+  const uint32_t block = first >> units_per_block_log2, in_block = first - (block << units_per_block_log2);
+  const uint32_t kept = keep[block];
+  if (!kept && in_block) return;
+  u32x4 x[UNROLL];
+  if (kept) {
+#pragma unroll
+    for (uint32_t i = 0; i < UNROLL; ++i)
+      if (tid + 256u * i < mine) x[i] = img[first + tid + 256u * i];
+  }
+  uint32_t sum = 0;
+  for (uint32_t i = tid * 4; i < block; i += 1024) {
+    u32x4 v = u32x4{0, 0, 0, 0};
+    if (i + 4 <= n_blocks) v = ld16_any<false>((const uint8_t *)(keep + i));
+    else
+      for (uint32_t e = 0; e < 3; ++e)
+        if (i + e < n_blocks) v[e] = keep[i + e];
+    sum += v.x + (i + 1 < block ? v.y : 0u) + (i + 2 < block ? v.z : 0u) + (i + 3 < block ? v.w : 0u);
+  }
+  sum = wave_inclusive_scan(sum);
+  if (lane == kWave - 1) wave_sum[tid / kWave] = sum;
+  __syncthreads();
+  const uint32_t slot = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+  if (tid == 0 && in_block == 0) {
+    pos[block] = slot;
+    if (block + 1 == n_blocks) pos[n_blocks] = slot + kept;
+  }
+  if (!kept) return;
+  __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(packed + ((uint64_t)slot << units_per_block_log2) + in_block,
+                                                                 0, (int)(mine * 16u), 0x00020000);
+#pragma unroll
+  for (uint32_t i = 0; i < UNROLL; ++i)
+    if (tid + 256u * i < mine)
+      __builtin_amdgcn_raw_buffer_store_b128(x[i], out, (int)(16u * (tid + 256u * i)), 0, kStorePolicySc0Sc1Nt);
+}
+
 }  // namespace
 
 extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_t block_bytes, uint32_t *keep_dev,
@@ -1683,7 +1775,10 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   const uint32_t ups_log2 = upb_log2 < kSegmentUnitsLog2 ? upb_log2 : kSegmentUnitsLog2;
   const uint64_t segments = (n_units + (1ull << ups_log2) - 1) >> ups_log2;
   const dim3 seg_grid((uint32_t)segments);
-  if (ups_log2 == upb_log2) {
+  if (ups_log2 < upb_log2 && upb_log2 <= kWholeBlockUnitsLog2 && nbytes <= kWholeBlocksBytes) {
+    hipLaunchKernelGGL(ds_constant_blocks_kernel, dim3((uint32_t)n_blocks), dim3(kBlockThreads), 0, st,
+                       (const u32x4 *)image_dev, n_units, upb_log2, keep_dev, (u32x4 *)patterns_dev);
+  } else if (ups_log2 == upb_log2) {
     hipLaunchKernelGGL(ds_constant_segments_kernel<true>, seg_grid, dim3(256), 0, st, (const u32x4 *)image_dev, n_units,
                        upb_log2, ups_log2, keep_dev, (u32x4 *)patterns_dev);
   } else {
@@ -1693,6 +1788,17 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
                        upb_log2, ups_log2, keep_dev, (u32x4 *)patterns_dev);
   }
   DS_HIP_TRY(hipGetLastError());
+  if (n_blocks <= kCountedBlocks && nbytes <= kCachedBytes) {
+    const auto launch = [&](auto kernel, uint32_t units) {
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)((n_units + units - 1) / units)), dim3(256), 0, st, (const u32x4 *)image_dev,
+                         (uint32_t)n_units, upb_log2, (const uint32_t *)keep_dev, pos_dev, (uint32_t)n_blocks,
+                         (u32x4 *)packed_dev);
+    };
+    if (nbytes <= kOneUnitBytes) launch(ds_count_and_pack_kernel<1>, 256);
+    else launch(ds_count_and_pack_kernel<4>, 1024);
+    DS_HIP_TRY(hipGetLastError());
+    return DS_OK;
+  }
   hipLaunchKernelGGL(ds_exclusive_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, keep_dev, pos_dev, n_blocks);
   DS_HIP_TRY(hipGetLastError());
   // (launches have less than 2^32 threads, and are rounded up to 8 MiB of image)

@@ -86,3 +86,33 @@ def test_the_largest_image_with_one_unit_per_thread_and_the_next(beyond):
     for i, k in enumerate(kept):
         assert torch.equal(packed[i * block:(i + 1) * block], img[k * block:(k + 1) * block])
     assert bool((packed[len(kept) * block:] == 0xCC).all())
+
+
+# (blocks, bytes of a block, bytes the last block lacks): on either side of what the pack counts itself, of its change from one
+# to four units per thread (8 MiB), of the blocks that one work-group looks at (16 MiB), and of the images it serves (64 MiB)
+@pytest.mark.parametrize("n_blocks,block,short", [
+    (1, 16384, 0), (1, 16384, 16368), (5, 1 << 20, 16), (3, 32768, 4096), (256, 32768, 0), (257, 32768, 32752), (1025, 16384, 48),
+    (2048, 16384, 16), (2049, 16384, 16), (2048, 32768, 0), (2047, 32768, 16), (129, 131072, 131056), (128, 131072, 16),
+    (16, 1 << 20, 0), (17, 1 << 20, (1 << 20) - 16), (64, 1 << 20, 0), (65, 1 << 20, (1 << 20) - 16), (9, 1 << 21, 64)])
+def test_blocks_counted_by_the_pack(n_blocks, block, short):
+    import torch
+    nbytes = n_blocks * block - short
+    gen = torch.Generator(device="cuda").manual_seed(n_blocks)
+    img = torch.randint(0, 1 << 30, (n_blocks, block // 4), dtype=torch.int32, device="cuda", generator=gen)
+    constant = torch.from_numpy(np.random.default_rng(n_blocks).random(n_blocks) < 0.4).cuda()
+    constant[-1] |= short == block - 16                   # one unit: constant whatever it holds
+    img[constant] = img[constant][:, :4].repeat(1, block // 16)
+    odd = torch.nonzero(~constant).flatten()[::2]          # of every other kept block the last unit alone differs
+    odd = odd[odd < n_blocks - 1]
+    img[odd] = img[odd][:, :4].repeat(1, block // 16)
+    img[odd, -1] += 1
+    flat = img.view(torch.uint8).reshape(-1)[:nbytes]
+    print(f"[case] compress {n_blocks} blocks of {block} less {short}", flush=True)
+    keep, pos, pats, packed = _run(flat, block)
+    want = (~constant).cpu().numpy().astype(np.int64)
+    assert np.array_equal(keep, want) and np.array_equal(pos, np.concatenate([[0], np.cumsum(want)]))
+    host = flat.cpu().numpy()
+    assert np.array_equal(pats, np.stack([host[k * block:k * block + 16] for k in range(n_blocks)]))
+    slots = [host[k * block:(k + 1) * block] for k in np.flatnonzero(want)]
+    kept = np.concatenate(slots) if slots else host[:0]
+    assert np.array_equal(packed[:kept.size], kept) and np.all(packed[kept.size:] == 0xCC)
