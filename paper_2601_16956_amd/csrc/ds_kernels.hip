@@ -1299,7 +1299,9 @@ int launch_several(const ds_plan *plan, bool pack, const LeanArgs &la, const Mov
 // every store that might have changed it, the table of such views of perf/cases.py took 93.4 us instead of 79.3 (gather).
 // That table: unit by unit 460 / 524 us, in narrow blocks 100 / 108, now 79 / 98; channels-last 14.1 / 14.5, now 10.8 /
 // 13.1; every second fp32 column 10.9 / 14.4, now 10.1 / 12.8; with the blocks in stripes over the XCDs (ds_perm_order) and
-// streaming loads (STREAM: images that no cache holds until the next pass) 63.2 / 68.8.  Streaming loads alone are worth, us:
+// streaming loads (STREAM: images that no cache holds until the next pass) 63.2 / 68.8, with short rows and short runs in larger
+// accesses (ds_perm_groups, ds_perm_runs) 61.5 / 67.2; the lines of which views hold parts, which the gather reads whole and a
+// scatter makes HBM read and write, leave 54 / 65 at the rate of a copy.  Streaming loads alone are worth, us:
 // gather, where no line of the tensor is another block's too (kPermOnce), bf16 4096 x 4096 62.4 / 59.5 (five of them), every
 // second column 86.5 / 80.6 (ten), channels-last 75.8 / 72.1; where lines are shared they cost (bytes 4096 x 4120 68 / 81);
 // the scatter's loads 62.4 / 57.9, but not beside wide blocks whose stores stay in the caches to meet their lines' other

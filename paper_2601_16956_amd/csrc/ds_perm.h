@@ -48,7 +48,8 @@ constexpr uint64_t kPermMinBytes = 1024;
 constexpr int kPermUnroll = 8;             // granules a thread has in flight
 
 enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11,
-                  kPermWide = 1u << 12, kPermStream = 1u << 13, kPermOnce = 1u << 14 };
+                  kPermWide = 1u << 12, kPermStream = 1u << 13, kPermOnce = 1u << 14,
+                  kPermGroups = 1u << 15 };
 
 // Wide blocks: views dense along a (16-byte loads of neighbours along a, transposed in registers), kPermWideA steps along a;
 // of each row 384 bytes where rows start at lines of the image, else up to 368, and a block writes the lines that start in
@@ -88,7 +89,8 @@ struct DsPerm {
                               // scatter's stores stream.  Streaming / cached, us: fp32 4096 x 4099 21.2 / 29.3, bytes
                               // 8192 x 8216 24.5 / 40.0; columns at multiples of 32 bytes 25.5 / 16.6, 109 / 86) |
                               // kPermOnce (a block's lines of the tensor are all its own, or nearly: the gather's loads
-                              // of them may stream)
+                              // of them may stream) | kPermGroups (flat and dense along a: 16 bytes of
+                              // neighbours along a at a time)
   uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
 static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
@@ -201,6 +203,36 @@ DS_PERM_FN void ds_perm_store(uint64_t base, uint32_t off, T v, uint32_t align) 
 #endif
   (void)align;
 }
+// 12 bytes at a multiple of 4
+struct DsPermRun {
+  uint32_t w[3];
+};
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef uint32_t DsPermThree __attribute__((ext_vector_type(3)));
+typedef DsPermThree DsPermThreeAny __attribute__((aligned(4)));
+#endif
+template <bool NT>
+DS_PERM_FN DsPermRun ds_perm_load_run(uint64_t base, uint32_t off) {
+  DS_PERM_TOUCH('r', base + off, 12, 4);
+  DsPermRun v;
+#if defined(__HIP_DEVICE_COMPILE__)
+  DsPermThree x;
+  if (NT) x = __builtin_nontemporal_load((const DS_PERM_GLOBAL DsPermThreeAny *)(base + off));
+  else x = *(const DS_PERM_GLOBAL DsPermThreeAny *)(base + off);
+  v = DsPermRun{{x.x, x.y, x.z}};
+#else
+  memcpy(v.w, (const void *)(uintptr_t)(base + off), 12);
+#endif
+  return v;
+}
+DS_PERM_FN void ds_perm_store_run(uint64_t base, uint32_t off, const DsPermRun &v) {
+  DS_PERM_TOUCH('w', base + off, 12, 4);
+#if defined(__HIP_DEVICE_COMPILE__)
+  *(DS_PERM_GLOBAL DsPermThreeAny *)(base + off) = DsPermThree{v.w[0], v.w[1], v.w[2]};
+#else
+  memcpy((void *)(uintptr_t)(base + off), v.w, 12);
+#endif
+}
 // Around streaming accesses: an opaque offset in front, a mark behind loads.  (Of two loops that differ in the cache policy
 // alone the compiler makes one, with cached accesses.)
 template <bool NT>
@@ -225,6 +257,23 @@ template <typename E>
 DS_PERM_FN void ds_perm_put(uint8_t *lds, uint32_t at, E v) {
   DS_PERM_TOUCH('l', at, sizeof(E), sizeof(E));
   *(E *)(lds + at) = v;
+}
+
+typedef uint32_t DsPermQuad __attribute__((vector_size(16)));
+// Element e of 16 bytes
+template <typename E>
+DS_PERM_FN E ds_perm_element(const DsPermQuad &v, uint32_t e) {
+  if (sizeof(E) == 8) return (E)(v[2 * e & 3] | (uint64_t)v[(2 * e + 1) & 3] << 32);
+  return (E)(v[e * sizeof(E) / 4] >> (8 * (e * sizeof(E) & 3)));
+}
+template <typename E>
+DS_PERM_FN void ds_perm_set_element(uint32_t *w, uint32_t e, E x) {
+  if (sizeof(E) == 8) {
+    w[2 * e & 3] = (uint32_t)x;
+    w[(2 * e + 1) & 3] = (uint32_t)((uint64_t)x >> 32);
+  } else {
+    w[e * sizeof(E) / 4] |= (uint32_t)x << (8 * (e * sizeof(E) & 3));
+  }
 }
 
 // Walk along a, the usual block: ds_perm_full_a<E>() steps along a, one granule per run.  Neighbouring threads take
@@ -340,12 +389,149 @@ DS_PERM_FN void ds_perm_along_b(const DS_PERM_TABLE DsPerm &d, const DsPermBlock
   }
 }
 
+// Walk along b, runs of 12 bytes: a run is one access, and its place takes one division and not two for each granule.
+// (150 MB of six of every sixteen bf16, us: granule by granule 103 / 192, now 97 / 190, in smaller blocks 87 / 181; 12 MB 12.0 /
+// 13.2, now 9.7 / 11.8.  As three accesses of 4 bytes, each on as many lines, 138; so runs of 3 granules of 2 bytes stay
+// granule by granule.)
+template <bool PACK, bool NT>
+DS_PERM_FN void ds_perm_runs(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  typedef uint32_t E;
+  constexpr int U = PACK ? 6 : 4;
+  const uint32_t per_row = PACK ? k.nbx : k.nb, total = k.na * per_row, m_row = ds_perm_magic(per_row > 1 ? per_row : 2);
+#pragma unroll 1
+  for (uint32_t i = tid; i < total; i += U * kPermThreads) {
+    uint32_t from[U], at[U], image[U];
+    DsPermRun v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const uint32_t x = ds_perm_min(i + (uint32_t)j * kPermThreads, total - 1);
+      const uint32_t a = ds_perm_div(x, per_row, m_row), c = x - a * per_row;
+      from[j] = a * k.sa + c * k.sb;
+      at[j] = ds_perm_row_lds(d, k, a) + c * 12;
+      image[j] = ds_perm_row_image(k, a) + c * 12;
+    }
+    if (PACK) {
+#pragma unroll
+      for (int j = 0; j < U; ++j) v[j] = ds_perm_load_run<NT>(k.src0, ds_perm_apart<NT>(from[j]));
+#pragma unroll
+      for (int j = 0; j < U; ++j)
+#pragma unroll
+        for (uint32_t g = 0; g < 3; ++g) ds_perm_put<E>(lds, at[j] + 4 * g, v[j].w[g]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < U; ++j)
+#pragma unroll
+        for (uint32_t g = 0; g < 3; ++g) v[j].w[g] = ds_perm_get<E>(lds, at[j] + 4 * g);
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        if (i + (uint32_t)j * kPermThreads >= total) break;
+        if (k.inside) {
+          ds_perm_store_run(k.src0, from[j], v[j]);
+        } else {
+#pragma unroll
+          for (uint32_t g = 0; g < 3; ++g)
+            if (image[j] + 4 * g >= k.lo && image[j] + 4 * g < k.hi) ds_perm_store<E>(k.src0, from[j] + 4 * g, v[j].w[g], 4);
+        }
+      }
+    }
+  }
+}
+
+// The first n < 16 bytes of w to p, as at most four pieces.  (The ends of rows that are not whole units; byte by byte
+// they were a chain of up to 15 loads and stores in each of a wavefront's eight rows: gather of 4096 transposed rows of 1000
+// bytes 8.2 us, now 7.6, in narrow blocks 7.2; 16 384 rows of 740 bytes 10.3, 9.1, 11.5.)
+template <char KIND, typename T>
+DS_PERM_FN void ds_perm_put_piece(uint64_t p, T v, uint32_t align) {
+  DS_PERM_TOUCH(KIND, p, sizeof(T), align);
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef T any __attribute__((aligned(1)));
+  *(DS_PERM_GLOBAL any *)p = v;
+#else
+  memcpy((void *)(uintptr_t)p, &v, sizeof(T));
+#endif
+  (void)align;
+}
+template <uint32_t S, char KIND = 'i'>
+DS_PERM_FN void ds_perm_put_bytes(uint64_t p, uint32_t n, const uint32_t *w) {
+  uint64_t v = w[0] | (uint64_t)w[1] << 32;
+  if (n & 8) {
+    ds_perm_put_piece<KIND, uint64_t>(p, v, S);
+    p += 8;
+    v = w[2] | (uint64_t)w[3] << 32;
+  }
+  if (S <= 4 && (n & 4)) {
+    ds_perm_put_piece<KIND, uint32_t>(p, (uint32_t)v, S);
+    p += 4;
+    v >>= 32;
+  }
+  if (S <= 2 && (n & 2)) {
+    ds_perm_put_piece<KIND, uint16_t>(p, (uint16_t)v, S);
+    p += 2;
+    v >>= 16;
+  }
+  if (S <= 1 && (n & 1)) ds_perm_put_piece<KIND, uint8_t>(p, (uint8_t)v, 1);
+}
+
+// ---- flat blocks dense along a (kPermGroups), tensor side ----
+// 16 bytes of neighbours along a at a time, group by group along a and column by column.  Gather: where the block is no
+// whole number of groups, each column's last one is pulled back and moves some elements twice; the scatter stores the
+// elements behind the last whole group, and in front of the view's cut unit, in at most four pieces.  As few blocks as 16 KiB allow, of equal length: in powers of two, one
+// element per thread and column, 536 x 536 x 9 fp32 channels-last (155 MB of them, us) 76.7 / 88.5, now 54.5 / 63.8 (a plain copy
+// 48.5), one of 10 MB 7.6 / 9.5, now 6.2 / 7.1; transposed bytes 256 x 265 (54 MB) 28.2 / 40.2, now 20.6 / 30.9.
+template <typename E, bool PACK, bool NT>
+DS_PERM_FN void ds_perm_groups(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
+  constexpr uint32_t S = (uint32_t)sizeof(E), G = 16 / S;
+  constexpr int U = PACK ? 4 : 2;
+  const uint32_t groups = (k.na + G - 1) / G, total = groups * k.nb, m = ds_perm_magic(groups > 1 ? groups : 2);
+#pragma unroll 1
+  for (uint32_t i = tid; i < total; i += U * kPermThreads) {
+    uint32_t from[U], at[U], a[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const uint32_t x = ds_perm_min(i + (uint32_t)j * kPermThreads, total - 1);
+      const uint32_t c = ds_perm_div(x, groups, m);
+      a[j] = (x - c * groups) * G;
+      if (PACK) a[j] = ds_perm_min(a[j], k.na - G);
+      from[j] = a[j] * S + c * k.sb;
+      at[j] = k.skew + a[j] * k.da + c * S;
+    }
+    if (PACK) {
+      DsPermQuad v[U];
+#pragma unroll
+      for (int j = 0; j < U; ++j) v[j] = ds_perm_load<DsPermQuad, NT>(k.src0, ds_perm_apart<NT>(from[j]), S);
+      ds_perm_loaded<NT>();
+#pragma unroll
+      for (int j = 0; j < U; ++j)
+#pragma unroll
+        for (uint32_t e = 0; e < G; ++e) ds_perm_put<E>(lds, at[j] + e * k.da, ds_perm_element<E>(v[j], e));
+    } else {
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        if (i + (uint32_t)j * kPermThreads >= total) break;
+        uint32_t n = ds_perm_min(k.na - a[j], G);
+        if (!k.inside) {  // (a row's elements are da apart in the image, none is cut by the range)
+          if (k.hi <= at[j]) continue;
+          n = ds_perm_min(n, (k.hi - at[j] + k.da - 1) / k.da);
+          if (k.lo > at[j]) {
+            for (uint32_t e = (k.lo - at[j] + k.da - 1) / k.da; e < n; ++e)
+              ds_perm_store<E>(k.src0, from[j] + e * S, ds_perm_get<E>(lds, at[j] + e * k.da), S);
+            continue;
+          }
+        }
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (uint32_t e = 0; e < G; ++e) ds_perm_set_element<E>(w, e, ds_perm_get<E>(lds, at[j] + ds_perm_min(e, n - 1) * k.da));
+        if (n == G) ds_perm_store<DsPermQuad>(k.src0, from[j], DsPermQuad{w[0], w[1], w[2], w[3]}, S);
+        else ds_perm_put_bytes<S, 'w'>(k.src0 + from[j], n * S, w);
+      }
+    }
+  }
+}
+
 // ---- wide blocks, tensor side ----
 // A thread takes 8 columns of 16 bytes along a and transposes them in registers: its loads, its stores and its accesses
 // of LDS are 16 bytes each (bytes: LDS 8).  In LDS row a starts at ds_perm_row_start: an odd number of 16-byte words
 // apart, one more after every fourth, which puts the words that 16 neighbouring lanes write into different banks.
-typedef uint32_t DsPermQuad __attribute__((vector_size(16)));
-
 // LDS accesses of type T at ALIGN bytes
 template <typename T, uint32_t ALIGN>
 DS_PERM_FN T ds_perm_lds_load(const uint8_t *lds, uint32_t at) {
@@ -477,7 +663,13 @@ DS_PERM_FN void ds_perm_tensor_side(const DS_PERM_TABLE DsPerm &d, const DsPermB
   constexpr uint32_t V = (uint32_t)(sizeof(W) / sizeof(E));
   constexpr bool NT = PACK && STREAM;
   const bool once = NT && (d.flags & kPermOnce);
-  if ((d.flags & kPermWide) && (PACK || k.inside)) {
+  if constexpr (sizeof(E) == 4)
+    if (!(d.flags & kPermAlongA) && d.run == 12) return ds_perm_runs<PACK, NT>(d, k, lds, tid);
+  if (d.flags & kPermGroups) {
+    if (PACK && k.na < 16 / sizeof(E)) ds_perm_along_b<E, PACK, NT>(d, k, lds, tid);
+    else if (once) ds_perm_groups<E, PACK, NT>(d, k, lds, tid);
+    else ds_perm_groups<E, PACK, false>(d, k, lds, tid);
+  } else if ((d.flags & kPermWide) && (PACK || k.inside)) {
     if (once) ds_perm_wide<E, PACK, NT>(d, k, lds, tid);
     else ds_perm_wide<E, PACK, false>(d, k, lds, tid);
   } else if (!(d.flags & kPermAlongA)) {
@@ -520,41 +712,6 @@ DS_PERM_FN void ds_perm_window(const DS_PERM_TABLE DsPerm &d, const DsPermBlock 
 struct DsPermUnit {
   uint32_t w[4];
 };
-
-// The first n < 16 bytes of w to the image, as at most four pieces.  (The ends of rows that are not whole units; byte by byte
-// they were a chain of up to 15 loads and stores in each of a wavefront's eight rows: gather of 4096 transposed rows of 1000
-// bytes 8.2 us, now 7.6, in narrow blocks 7.2; 16 384 rows of 740 bytes 10.3, 9.1, 11.5.)
-template <typename T>
-DS_PERM_FN void ds_perm_put_piece(uint64_t p, T v, uint32_t align) {
-  DS_PERM_TOUCH('i', p, sizeof(T), align);
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef T any __attribute__((aligned(1)));
-  *(DS_PERM_GLOBAL any *)p = v;
-#else
-  memcpy((void *)(uintptr_t)p, &v, sizeof(T));
-#endif
-  (void)align;
-}
-template <uint32_t S>
-DS_PERM_FN void ds_perm_put_bytes(uint64_t p, uint32_t n, const uint32_t *w) {
-  uint64_t v = w[0] | (uint64_t)w[1] << 32;
-  if (n & 8) {
-    ds_perm_put_piece<uint64_t>(p, v, S);
-    p += 8;
-    v = w[2] | (uint64_t)w[3] << 32;
-  }
-  if (S <= 4 && (n & 4)) {
-    ds_perm_put_piece<uint32_t>(p, (uint32_t)v, S);
-    p += 4;
-    v >>= 32;
-  }
-  if (S <= 2 && (n & 2)) {
-    ds_perm_put_piece<uint16_t>(p, (uint16_t)v, S);
-    p += 2;
-    v >>= 16;
-  }
-  if (S <= 1 && (n & 1)) ds_perm_put_piece<uint8_t>(p, (uint8_t)v, 1);
-}
 
 // Gather: LDS -> image, `img` pointing at image byte img_lo.
 // Wide blocks: 32 threads have room for a row's window, which is at most 31 units.
@@ -727,14 +884,29 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
     if (tb > d->eb) tb = d->eb;
     else if ((image_bits & 15) && tb * run >= 128) tb -= (uint32_t)((15 + run) / run);
   } else {
-    tb = (uint32_t)(4096 / run);
+    // 4096 granules at most, which is 16 per thread one batch behind the other: of a small view, whose blocks all run at
+    // once, that is the time (16 KiB / so, us: every second fp32, 500 KB, 5.3 / 3.9, scatter 5.8 / 4.2; six of every sixteen
+    // bytes, 100 KB, 6.6 / 4.4 and 7.7 / 5.2).  Cut at lines of the image, so that a line is one block's (150 MB of six of
+    // sixteen: bytes 108 / 90, at units 107; bf16 97 / 87, at units 93).
+    const uint32_t room = g == 1 ? 4096 : 8192;
+    tb = (uint32_t)((room < 4096 ? room : 4096) / run);
     if (tb > d->eb) tb = d->eb;
-    ta = (uint32_t)(16384 / (tb * run));
+    ta = (uint32_t)(room / (tb * run));
     if (ta > d->ea) ta = d->ea;
-    tb = (uint32_t)(16384 / (ta * run));
+    tb = (uint32_t)(room / (ta * run));
     if (tb > d->eb) tb = d->eb;
+    if (tb < d->eb) {
+      uint32_t whole = 1;  // steps that are whole lines, or whole units
+      while ((whole * run) & (image_bits & (kPermLine - 1) ? 15 : kPermLine - 1)) whole *= 2;
+      if (tb > whole) tb = tb / whole * whole;
+    }
   }
-  if (along_a) {  // a power of two, of at most one step along a per thread
+  // flat, dense along a: as few blocks as 16 KiB allow, of equal length, in whole groups of 16 bytes
+  const bool groups = flat && along_a && run == g && d->sa == g && d->ea >= 16 / g;
+  if (groups) {
+    const uint32_t G = 16 / g, most = ta / G * G, n = (d->ea + most - 1) / most;
+    ta = ((d->ea + n - 1) / n + G - 1) / G * G;
+  } else if (along_a) {  // a power of two, of at most one step along a per thread
     uint32_t p = 1;
     while (2 * p <= ta && 2 * p <= kPermThreads && p < d->ea) p *= 2;
     ta = p;
@@ -786,7 +958,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   const uint32_t units = (uint32_t)((flat ? kPermThreads * 16 : tb * run) / 16);
   while (d->lanes_log2 < 8 && (2u << d->lanes_log2) <= units) ++d->lanes_log2;  // (not used by wide blocks inside the range)
   d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
-             (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
+             (groups ? kPermGroups : 0u) | (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
              (wide && (columns & 63) == 0 ? kPermStream : 0u) |
              ((wide ? lines && g > 1 && (columns & (kPermLine - 1)) == 0 : ta * d->sa >= 4 * kPermLine) ? kPermOnce : 0u);
   const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
@@ -813,8 +985,8 @@ static inline void ds_perm_items(const DsPerm &d, uint32_t perm, uint32_t n, DsP
 // of 256 blocks 65.5 / 65.3, 128 63.2 / 62.8, 64 62.4 / 61.5, 32 62.1 / 60.9, single blocks 64.1 / 62.6; bytes of that shape
 // 72.8 / 83.2, with stripes of 64 68.3 / 73.6, with single blocks 93.0 / 72.9; the views of perf/cases.py 76.7 / 96.9, with
 // stripes 67.5 / 81.6 (kinds of views that take unequal time are dealt evenly too).
-// Gathers of less than 1536 blocks, all but a fifth of which run at once, have one stripe per XCD (1100 blocks of views of
-// bytes 15.7, in two 16.6; the scatter 20.3 and 17.0).
+// Launches of fewer blocks than about a round of them have one stripe per XCD (gather of 1558 blocks 15.5, in three stripes
+// 16.4, of 2035 blocks 19.6 and 20.9; scatter of 625 blocks 9.7, in two 10.9).
 struct DsPermOrder {
   uint32_t span;    // work-groups per XCD
   uint32_t stripe;  // blocks of a stripe, at least 2
@@ -823,7 +995,7 @@ struct DsPermOrder {
 constexpr uint32_t kPermOrdered = 1u << 27;
 static inline DsPermOrder ds_perm_order(uint32_t n, bool pack) {  // 0 < n < kPermOrdered
   const uint32_t blocks = 8 * (pack ? 64 : 48);
-  const uint32_t rounds = n < (pack ? 1536 : blocks) ? 1 : (n + blocks / 2) / blocks;
+  const uint32_t rounds = n < (pack ? 2048 : 768) ? 1 : (n + blocks / 2) / blocks;
   uint32_t stripe = (n + rounds * 8 - 1) / (rounds * 8);
   if (stripe < 2) stripe = 2;
   return {rounds * stripe, stripe, ds_perm_magic(stripe)};

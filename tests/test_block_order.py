@@ -21,7 +21,7 @@ def test_every_block_is_taken_once(tmp_path, pack):
                     os.path.join(ROOT, "tests", "c_abi", "order_host.cpp"), "-o", so], check=True)
     deal = ctypes.CDLL(so).order_host_deal
     deal.restype, deal.argtypes = ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_int, ctypes.c_void_p]
-    for n in [*range(1, 40), 383, 384, 385, 1535, 1536, 1537, *range(4096, 4110), 100003, (1 << 22) - 1, (1 << 27) - 1]:
+    for n in [*range(1, 40), 767, 768, 769, 2047, 2048, 2049, *range(4096, 4110), 100003, (1 << 22) - 1, (1 << 27) - 1]:
         hits = np.zeros(n, dtype=np.uint8)
         launched = deal(n, pack, hits.ctypes.data)
         assert hits.min() == hits.max() == 1
