@@ -1384,6 +1384,7 @@ __global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a, ImageArgs i
 }
 
 constexpr uint32_t kMixedChunks = 4096;  // other chunks up to which blocks and chunks share a launch
+constexpr uint32_t kMixedInPieces = 640; // ... and are moved 4 KiB per work-group
 
 // Blocks and the plan's other chunks in one launch: first the blocks, then the chunks, 16 KiB per work-group, which fill
 // the chip while the last blocks end.  A second launch costs 3 us and the ramps between the two; in exchange the chunks move at
@@ -1391,13 +1392,23 @@ constexpr uint32_t kMixedChunks = 4096;  // other chunks up to which blocks and 
 // (157 MB, 2048 chunks beside the blocks) 75.3 / 79.4 and 97.0 / 98.5, the same at a quarter of the columns 9.0 / 11.8 and
 // 9.7 / 13.7, at a sixteenth 6.9 / 9.9; one transposed matrix of 32 KB to 8 MB beside 32 MB 14.5 to 16.7 / 16.3 to 18.9;
 // beside 100 MB (6400 chunks) 40.9 / 41.5 and 40.3 / 39.3; 32 MB beside 400 MB 153.8 / 142.8 and 152.8 / 145.7.
-template <bool PACK, bool NTL, bool WIDE>
+// PIECES: few chunks, 4 KiB per work-group, one unit per thread.  All work-groups run at once then, and the launch takes as long
+// as the slowest, which is a chunk where several shards meet (the general path) or of a view of several dimensions.  Such
+// chunks whole, one unit per thread after the other / in pieces, us, gather and scatter: views of 592 columns of 8 bytes (10 MB)
+// 11.3 / 7.2 and 10.0 / 6.5, 2160 columns of f16 (43 MB) 22.2 / 17.6 and 26.2 / 21.5; 8 MB in tensors of 65 000 bytes beside a
+// view 7.5 / 5.5 and 6.7 / 5.1; 8 MB in one tensor 6.0 / 5.5.  Of more chunks the pieces cost more than they save (62 MB in one tensor
+// 20.5 / 20.7 and 20.1 / 22.3): whole, four units per thread in the general path too, the last chunks end sooner (the views
+// of perf/cases.py 61.3 / 58.9 and 66.2 / 64.5, 32 MB in tensors of 65 000 bytes 15.1 / 12.8 and 14.1 / 13.1; but 1000 views of 20 KB,
+// whose chunks hold little besides blocks, 10.9 / 12.1 and 12.4 / 13.6).
+template <bool PACK, bool NTL, bool PIECES, bool WIDE>
 __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsChunkRec *recs, const uint32_t *ids,
                                                           uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
   __shared__ union {
     __attribute__((aligned(16))) uint8_t block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
     GenLds tab;
   } s;
+  constexpr int UNITS = PIECES ? 1 : 4;                       // per thread
+  constexpr uint32_t kPerChunk = PIECES ? kUnitPieces : 1u;   // work-groups
   uint32_t wi = blockIdx.x;
   if (wi < a.xcd_span * 8u) {
     const uint32_t i = ds_perm_ordered(wi, a.stripe, a.magic);
@@ -1406,43 +1417,53 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsCh
   }
   wi -= a.xcd_span * 8u;
   uint64_t c;
-  uint32_t t0, t1;
+  uint32_t t0, t1, piece;
   if (wi < span * 8u) {
-    const uint32_t cm = (wi & 7u) * span + (wi >> 3);
+    const uint32_t cm = (wi & 7u) * span + (wi >> 3), rec = c_lo + cm / kPerChunk;
     if (cm >= n) return;
-    const DsChunkRec r = load_rec(recs, c_lo + cm);
-    c = load_id(ids, c_lo + cm);
+    piece = cm % kPerChunk * 4096;
+    const DsChunkRec r = load_rec(recs, rec);
+    c = load_id(ids, rec);
+    uint8_t *const img = ma.img + ((c << 14) - ma.img_lo);
     if ((r.kind & 0xFFu) < DS_CHUNK_GENERAL) {
-      lean_move<PACK, 256, 4, NTL, true, PACK>(r, ma.img + ((c << 14) - ma.img_lo), 0);
+      lean_move<PACK, 256, UNITS, NTL, true, PACK>(r, img + piece, piece);
       return;
     }
     if ((r.kind & 0xFFu) == DS_CHUNK_DIMS) {
+      if (PIECES) return dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, img + piece, piece);
 #pragma unroll 1
-      for (uint32_t piece = 0; piece < 16384; piece += 4096)
-        dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, ma.img + ((c << 14) - ma.img_lo) + piece, piece);
+      for (uint32_t p = 0; p < 16384; p += 4096) dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, img + p, p);
       return;
     }
     t0 = r.tile;
     t1 = r.tile + r.col0;
   } else {
-    c = ma.extra[wi - span * 8u];
+    const uint32_t x = wi - span * 8u;
+    c = ma.extra[x / kPerChunk];
+    piece = x % kPerChunk * 4096;
     cut_chunk_tiles(ma, c, t0, t1);
   }
-  general_chunk<PACK, 256, 1, NTL, true, PACK, kListed, true>(ma, c, 0, t0, t1, &s.tab);
+  general_chunk<PACK, 256, UNITS, NTL, true, PACK, kListed, !PIECES>(ma, c, piece, t0, t1, &s.tab);
 }
 
-template <bool PACK, bool NTL>
+template <bool PACK, bool NTL, bool PIECES>
 int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
-  const uint32_t span = (la.n_pieces + 7) / 8;
-  const dim3 grid(a.xcd_span * 8 + span * 8 + ma.n_extra);
+  constexpr uint32_t kPerChunk = PIECES ? kUnitPieces : 1u;
+  const uint32_t n = la.n_pieces * kPerChunk, span = (n + 7) / 8;
+  const dim3 grid(a.xcd_span * 8 + span * 8 + ma.n_extra * kPerChunk);
   if (plan->any_wide)
-    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, true>), grid, dim3(256), 0, stream, a, la.recs, la.ids, la.n_pieces, span,
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, true>), grid, dim3(256), 0, stream, a, la.recs, la.ids, n, span,
                        la.c_lo, ma);
   else
-    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, false>), grid, dim3(256), 0, stream, a, la.recs, la.ids, la.n_pieces, span,
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, false>), grid, dim3(256), 0, stream, a, la.recs, la.ids, n, span,
                        la.c_lo, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
+}
+template <bool PACK, bool NTL>
+int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
+  return la.n_pieces <= kMixedInPieces ? launch_mixed<PACK, NTL, true>(plan, a, la, ma, stream)
+                                       : launch_mixed<PACK, NTL, false>(plan, a, la, ma, stream);
 }
 
 template <bool PACK, bool STREAM>
