@@ -1399,7 +1399,8 @@ constexpr uint32_t kMixedInPieces = 640; // ... and are moved 4 KiB per work-gro
 // view 7.5 / 5.5 and 6.7 / 5.1; 8 MB in one tensor 6.0 / 5.5.  Of more chunks the pieces cost more than they save (62 MB in one tensor
 // 20.5 / 20.7 and 20.1 / 22.3): whole, four units per thread in the general path too, the last chunks end sooner (the views
 // of perf/cases.py 61.3 / 58.9 and 66.2 / 64.5, 32 MB in tensors of 65 000 bytes 15.1 / 12.8 and 14.1 / 13.1; but 1000 views of 20 KB,
-// whose chunks hold little besides blocks, 10.9 / 12.1 and 12.4 / 13.6).
+// whose chunks hold little besides blocks, 10.9 / 12.1 and 12.4 / 13.6), and so are views of several dimensions (62 MB in
+// runs of 1 KiB, a unit after the other 34.4 / 33.3, so 30.6 / 31.1).
 template <bool PACK, bool NTL, bool PIECES, bool WIDE>
 __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsChunkRec *recs, const uint32_t *ids,
                                                           uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
@@ -1430,9 +1431,7 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsCh
       return;
     }
     if ((r.kind & 0xFFu) == DS_CHUNK_DIMS) {
-      if (PIECES) return dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, img + piece, piece);
-#pragma unroll 1
-      for (uint32_t p = 0; p < 16384; p += 4096) dims_move<PACK, 256, 1, NTL, PACK>(r, ma.tiles, img + p, p);
+      dims_move<PACK, 256, UNITS, NTL, PACK>(r, ma.tiles, img + piece, piece);
       return;
     }
     t0 = r.tile;

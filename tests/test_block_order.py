@@ -66,3 +66,40 @@ def test_blocks_of_images_that_no_cache_holds(beside):
             assert gu.first_mismatch(dw.arena_host(), w.arena) is None
     finally:
         dw.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("beside", [0, 9 << 20, 12 << 20])
+def test_chunks_beside_blocks_in_pieces_and_whole(beside):
+    """Up to 640 chunks share the blocks' launch in pieces of 4 KiB, more of them whole: every kind of chunk, ends of shards
+    at every place in a piece, and ranges that cut pieces."""
+    import gpu_util as gu
+    rng = np.random.default_rng(beside >> 20)
+    views = [("bf16", (300, 203), (1, 301)), ("u8", (5, 40, 1000), (70000, 1500, 1)), ("u8", (3,), (1,)), ("u8", (41, 513), (700, 1)),
+             ("f32", (20, 300, 4), (300 * 8 + 4, 8, 1)), ("u8", (17000,), (1,)), ("i64", (130, 513), (1, 136)), ("u8", (90, 33, 17), (790, 23, 1)),
+             ("u8", (4097,), (1,)), ("bf16", (11, 7), (1, 13)), ("u8", (beside // 2 + 5,), (1,)), ("u8", (beside // 3000, 1000), (1012, 1)),
+             ("bf16", (beside // 12000, 5, 200), (1100, 216, 1)), ("f32", (333, 111), (222, 2))]
+    shards, at = [], 0
+    for k, (dtype, shape, strides) in enumerate(v for v in views if v[1][0]):
+        es = DTYPES[dtype][1]
+        at = -(-at // 64) * 64 + es * int(rng.integers(0, 3))
+        shards.append(Shard(f"b{k}", dtype, shape, strides, at, k))
+        at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    w = Workload("pieces", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print(f"[case] pieces beside blocks, {beside} bytes, image={dw.total}", flush=True)
+        cuts = [0, 16, 4096, 8208] + sorted(16 * int(x) for x in rng.integers(600, dw.total // 16, 6)) + [dw.total]
+        ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+        for lo, hi in [(0, dw.total)] + ranges:
+            assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        for parts in ([(0, dw.total)], ranges):
+            dw.arena.fill_(0x5A)
+            for lo, hi in parts:
+                dw.unpack(want, lo, hi)
+            assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+    finally:
+        dw.close()
