@@ -14,6 +14,8 @@ SOURCES = ["ds_plan.cpp", "ds_kernels.hip", "ds_engine.cpp", "ds_file.cpp", "ds_
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-pthread",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's first arguments that are no structures are in scalar registers when a wavefront starts, as many as 14 hold
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
 ]
 

@@ -72,6 +72,11 @@ constexpr uint32_t kUnitPieces = 4;       // work-groups of ds_unit_kernel per c
 constexpr uint64_t kCachedBytes = 64ull << 20;
 constexpr uint32_t kBigUnits = 512;       // N-D views: pieces of >= 8 KiB inside a chunk leave the scan
 
+// A kernel's arguments up to its first structure are in scalar registers when a wavefront starts (build.py asks for it, up to
+// 14 registers); the others it reads itself.  So what leads to a work-group's record or block comes first and by itself,
+// and what only some work-groups need is in structures.  Read / in registers, us: scatter of 23 MB in 106 tensors 8.8 / 8.3,
+// gather 8.6 / 8.5; 7.5 GB in 20 000 fragments 2316 / 2310; 8000 squares of 24 bf16 23.9 / 23.4 and 26.2 / 25.5; views of 592
+// columns of 8 bytes 7.4 / 7.1.
 struct MoveArgs {
   const DsTile *tiles;
   const DsTileHot *hot;  // n_tiles + 1 entries: the general path's compact copy of the tiles, and a sentinel
@@ -1120,8 +1125,10 @@ enum : int { kEvery = 0, kMulti = 1 };
 // Does a work-group of so many units take whole chunks (else pieces of them)?
 constexpr bool takes_whole_chunks(bool pack, int units) { return units >= (pack ? 512 : 1024); }
 template <bool PACK, int NT, int UNROLL, bool NTL, bool NTS, bool BUFST, int WAVES, int BLOCKS, int PATH, bool WALKS>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(LeanArgs la,
-                                                                                                     MoveArgs ma) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, WAVES))) void ds_move_kernel(
+    const DsChunkRec *recs, const uint32_t *ids, uint8_t *img, uint64_t img_lo, uint32_t chunk_log2, uint32_t c_lo,
+    uint32_t n_pieces, uint32_t xcd_span, MoveArgs ma) {
+  const LeanArgs la = {recs, ids, img, img_lo, chunk_log2, c_lo, n_pieces, xcd_span};
   __shared__ typename std::conditional<PATH == kMulti, MultiLds, GenLds>::type s_tab;
   const uint32_t n_lean = lean_items(la);
   constexpr bool WHOLE = takes_whole_chunks(PACK, NT * UNROLL);
@@ -1232,10 +1239,12 @@ int launch_pieces(LeanArgs la, MoveArgs ma, uint32_t grid_limit, hipStream_t str
   constexpr bool kWalks = PATH == kEvery && NTL && BUFST == PACK;
   if (kWalks && grid < items)
     hipLaunchKernelGGL((ds_move_kernel<PACK, NT, UNROLL, NTL, NTS, BUFST, WAVES, BLOCKS, PATH, kWalks>),
-                       dim3((uint32_t)grid), dim3(NT), 0, stream, la, ma);
+                       dim3((uint32_t)grid), dim3(NT), 0, stream, la.recs, la.ids, la.img, la.img_lo, la.chunk_log2, la.c_lo,
+                       la.n_pieces, la.xcd_span, ma);
   else
     hipLaunchKernelGGL((ds_move_kernel<PACK, NT, UNROLL, NTL, NTS, BUFST, WAVES, BLOCKS, PATH, false>),
-                       dim3((uint32_t)grid), dim3(NT), 0, stream, la, ma);
+                       dim3((uint32_t)grid), dim3(NT), 0, stream, la.recs, la.ids, la.img, la.img_lo, la.chunk_log2, la.c_lo,
+                       la.n_pieces, la.xcd_span, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
@@ -1372,7 +1381,9 @@ __device__ __forceinline__ void move_perm_item(const PermArgs &p, const ImageArg
 }
 
 template <bool PACK, bool STREAM, bool WIDE>
-__global__ __launch_bounds__(256, 5) void ds_perm_kernel(PermArgs a, ImageArgs image) {
+__global__ __launch_bounds__(256, 5) void ds_perm_kernel(const DsPerm *perms, const DsPermItem *items, uint32_t n_items,
+                                                         uint32_t xcd_span, uint32_t stripe, uint32_t magic, ImageArgs image) {
+  const PermArgs a = {perms, items, n_items, xcd_span, stripe, magic};
   __shared__ __attribute__((aligned(16))) uint8_t s_block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
   const uint32_t n = a.xcd_span ? a.xcd_span * 8u : a.n_items;
   for (uint32_t wi = blockIdx.x; wi < n; wi += gridDim.x) {
@@ -1402,8 +1413,10 @@ constexpr uint32_t kMixedInPieces = 640; // ... and are moved 4 KiB per work-gro
 // whose chunks hold little besides blocks, 10.9 / 12.1 and 12.4 / 13.6), and so are views of several dimensions (62 MB in
 // runs of 1 KiB, a unit after the other 34.4 / 33.3, so 30.6 / 31.1).
 template <bool PACK, bool NTL, bool PIECES, bool WIDE>
-__global__ __launch_bounds__(256, 5) void ds_mixed_kernel(PermArgs a, const DsChunkRec *recs, const uint32_t *ids,
-                                                          uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
+__global__ __launch_bounds__(256, 5) void ds_mixed_kernel(const DsPerm *perms, const DsPermItem *items, uint32_t n_items,
+                                                          uint32_t xcd_span, uint32_t stripe, uint32_t magic, const DsChunkRec *recs,
+                                                          const uint32_t *ids, uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
+  const PermArgs a = {perms, items, n_items, xcd_span, stripe, magic};
   __shared__ union {
     __attribute__((aligned(16))) uint8_t block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
     GenLds tab;
@@ -1451,11 +1464,11 @@ int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, con
   const uint32_t n = la.n_pieces * kPerChunk, span = (n + 7) / 8;
   const dim3 grid(a.xcd_span * 8 + span * 8 + ma.n_extra * kPerChunk);
   if (plan->any_wide)
-    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, true>), grid, dim3(256), 0, stream, a, la.recs, la.ids, n, span,
-                       la.c_lo, ma);
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, true>), grid, dim3(256), 0, stream, a.perms, a.items, a.n_items,
+                       a.xcd_span, a.stripe, a.magic, la.recs, la.ids, n, span, la.c_lo, ma);
   else
-    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, false>), grid, dim3(256), 0, stream, a, la.recs, la.ids, n, span,
-                       la.c_lo, ma);
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, false>), grid, dim3(256), 0, stream, a.perms, a.items, a.n_items,
+                       a.xcd_span, a.stripe, a.magic, la.recs, la.ids, n, span, la.c_lo, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
@@ -1470,8 +1483,10 @@ int launch_perm(const ds_plan *plan, const PermArgs &a, const ImageArgs &image, 
   uint32_t grid = a.xcd_span ? a.xcd_span * 8 : a.n_items;
   if (grid_limit && grid > grid_limit) grid = grid_limit;
   if (grid > kMaxGrid) grid = kMaxGrid;
-  if (plan->any_wide) hipLaunchKernelGGL((ds_perm_kernel<PACK, STREAM, true>), dim3(grid), dim3(256), 0, stream, a, image);
-  else hipLaunchKernelGGL((ds_perm_kernel<PACK, STREAM, false>), dim3(grid), dim3(256), 0, stream, a, image);
+  if (plan->any_wide) hipLaunchKernelGGL((ds_perm_kernel<PACK, STREAM, true>), dim3(grid), dim3(256), 0, stream, a.perms, a.items,
+                                          a.n_items, a.xcd_span, a.stripe, a.magic, image);
+  else hipLaunchKernelGGL((ds_perm_kernel<PACK, STREAM, false>), dim3(grid), dim3(256), 0, stream, a.perms, a.items, a.n_items,
+                          a.xcd_span, a.stripe, a.magic, image);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
@@ -1685,10 +1700,22 @@ __global__ __launch_bounds__(kScanThreads) void ds_exclusive_scan_kernel(const u
 // all of ds_image_compress: 305.6 us with four units at four wavefronts, now 299.3); launches of that shape have room for
 // images of up to 64 GiB, larger ones take four units per thread.
 constexpr uint32_t kStripeUnitsLog2 = 16;
+// (A structure, so that the arguments are not in registers from the start: work-groups of constant blocks are many, and
+// setting up 12 more scalar registers for each wavefront costs 2 of the 297 us.)
+struct KeptArgs {
+  const u32x4 *img;
+  uint64_t n_units;
+  uint32_t units_per_block_log2;
+  const uint32_t *keep, *pos;
+  u32x4 *packed;
+};
 template <int UNROLL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_pack_kept_blocks_kernel(
-    const u32x4 *__restrict__ img, uint64_t n_units, uint32_t units_per_block_log2, const uint32_t *__restrict__ keep,
-    const uint32_t *__restrict__ pos, u32x4 *__restrict__ packed) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_pack_kept_blocks_kernel(KeptArgs args) {
+  const u32x4 *__restrict__ const img = args.img;
+  const uint32_t *__restrict__ const keep = args.keep, *__restrict__ const pos = args.pos;
+  u32x4 *__restrict__ const packed = args.packed;
+  const uint64_t n_units = args.n_units;
+  const uint32_t units_per_block_log2 = args.units_per_block_log2;
   constexpr uint32_t kUnits = 256 * UNROLL, kGroupsLog2 = kStripeUnitsLog2 - __builtin_ctz(kUnits);
   // an XCD takes every eighth stripe of 1 MiB: neighbours share an L2, and runs of constant blocks, which leave
   // nothing to do, are dealt evenly (four units per thread 241 us; one contiguous eighth per XCD 271 us)
@@ -1719,8 +1746,8 @@ int launch_pack_kept(const u32x4 *img, uint64_t n_units, uint32_t upb_log2, cons
                      u32x4 *packed, hipStream_t stream) {
   const uint64_t stripes = ((n_units + (1u << kStripeUnitsLog2) - 1) >> kStripeUnitsLog2);
   const uint32_t grid = (uint32_t)((stripes + 7) / 8 * 8 << (kStripeUnitsLog2 - __builtin_ctz(256 * UNROLL)));
-  hipLaunchKernelGGL(ds_pack_kept_blocks_kernel<UNROLL>, dim3(grid), dim3(256), 0, stream, img, n_units, upb_log2, keep, pos,
-                     packed);
+  hipLaunchKernelGGL(ds_pack_kept_blocks_kernel<UNROLL>, dim3(grid), dim3(256), 0, stream,
+                     KeptArgs{img, n_units, upb_log2, keep, pos, packed});
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
