@@ -437,9 +437,7 @@ DS_PERM_FN void ds_perm_runs(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k
   }
 }
 
-// The first n < 16 bytes of w to p, as at most four pieces.  (The ends of rows that are not whole units; byte by byte
-// they were a chain of up to 15 loads and stores in each of a wavefront's eight rows: gather of 4096 transposed rows of 1000
-// bytes 8.2 us, now 7.6, in narrow blocks 7.2; 16 384 rows of 740 bytes 10.3, 9.1, 11.5.)
+// The first n < 16 bytes of w to p, as at most four pieces.  (The ends of rows that are not whole units.)
 template <char KIND, typename T>
 DS_PERM_FN void ds_perm_put_piece(uint64_t p, T v, uint32_t align) {
   DS_PERM_TOUCH(KIND, p, sizeof(T), align);
@@ -714,32 +712,47 @@ struct DsPermUnit {
 };
 
 // Gather: LDS -> image, `img` pointing at image byte img_lo.
-// Wide blocks: 32 threads have room for a row's window, which is at most 31 units.
+// Wide blocks: 32 threads have room for a row's window, which is at most 31 units; four rows' units are read before the first
+// is stored.  The parts of units at the ends of rows go last, one for each of two threads per row.  (Row after row, each with
+// its whole units or its parts, a block was a chain of eight such steps, which is what a small view takes: transposed bf16,
+// 512 x 519, 5.8 us, now 4.7, 512 x 512 4.6 and 4.4, 1000 x 1007 6.0 and 4.9, 80 of those 67.8 and 65.9, bytes 4096 x 4120 (169
+// MB) 68.0 and 65.7.)
 template <typename E, typename StoreUnit>
 DS_PERM_FN void ds_perm_wide_store(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, const uint8_t *lds, uint64_t base, uint32_t tid,
                                    StoreUnit store_unit) {
-  constexpr uint32_t S = (uint32_t)sizeof(E);
-#pragma unroll 2
-  for (uint32_t i = 0; i < kPermWideA / 8; ++i) {
-    const uint32_t a = tid / 32 + 8 * i;
-    if (a >= k.na) return;
-    const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew, row = ds_perm_row_start(d, a);
-    uint32_t w0, w1;
-    ds_perm_window(d, k, unit, skew, w0, w1);
-    const uint32_t x = (w0 & ~15u) + 16u * (tid & 31u);
-    if (x >= w0 && x + 16u <= w1) {
-      DsPermUnit v;
-      ds_perm_lds_words<S, 4>(lds, row + x - skew, v.w);
-      DS_PERM_TOUCH('i', base + (unit + x), 16, 16);
-      store_unit(base + (unit + x), v);
-    } else {
-      const uint32_t from = w0 > x ? w0 : x, to = ds_perm_min(w1, x + 16u);
-      if (from < to) {
-        DsPermUnit v;
-        ds_perm_lds_words<S, 4>(lds, row + from - skew, v.w);
-        ds_perm_put_bytes<S>(base + (unit + from), to - from, v.w);
-      }
+  constexpr uint32_t S = (uint32_t)sizeof(E), U = 4, kNone = ~0u;
+#pragma unroll 1
+  for (uint32_t first = tid / 32; first < k.na; first += 8 * U) {
+    DsPermUnit v[U];
+    uint32_t to[U];
+#pragma unroll
+    for (uint32_t i = 0; i < U; ++i) {
+      const uint32_t a = first + 8 * i;
+      const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew;
+      uint32_t w0, w1;
+      ds_perm_window(d, k, unit, skew, w0, w1);
+      const uint32_t x = (w0 & ~15u) + 16u * (tid & 31u);
+      to[i] = a < k.na && x >= w0 && x + 16u <= w1 ? unit + x : kNone;
+      if (to[i] != kNone) ds_perm_lds_words<S, 4>(lds, ds_perm_row_start(d, a) + x - skew, v[i].w);
     }
+#pragma unroll
+    for (uint32_t i = 0; i < U; ++i)
+      if (to[i] != kNone) {
+        DS_PERM_TOUCH('i', base + to[i], 16, 16);
+        store_unit(base + to[i], v[i]);
+      }
+  }
+  const uint32_t a = tid / 2;
+  if (a >= k.na) return;
+  const uint32_t at = ds_perm_row_image(k, a), skew = at & 15u, unit = at - skew;
+  uint32_t w0, w1;
+  ds_perm_window(d, k, unit, skew, w0, w1);
+  const uint32_t head = (w0 + 15u) & ~15u;  // where the first whole unit starts
+  const uint32_t from = tid & 1u ? (w1 & ~15u) : w0, to = tid & 1u ? w1 : ds_perm_min(head, w1);
+  if (from < to && (!(tid & 1u) || from >= head)) {
+    DsPermUnit v;
+    ds_perm_lds_words<S, 4>(lds, ds_perm_row_start(d, a) + from - skew, v.w);
+    ds_perm_put_bytes<S>(base + (unit + from), to - from, v.w);
   }
 }
 
