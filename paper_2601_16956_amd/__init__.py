@@ -147,7 +147,7 @@ def kernel_source_digest() -> str:
     with, so that a reader of a measurement can tell whether the profile still describes the kernels in use."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("ds_kernels.hip", "ds_splice.h", "ds_internal.h", "ds_perm.h"):
+    for name in ("ds_kernels.hip", "ds_blocks.h", "ds_splice.h", "ds_internal.h", "ds_perm.h"):
         with open(os.path.join(_HERE, "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -49,6 +49,7 @@
 #include <type_traits>
 
 #include "ds_internal.h"
+#include "ds_blocks.h"
 #include "ds_splice.h"
 
 namespace {
@@ -1573,8 +1574,8 @@ __global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *
   if (g >= segments) return;
   const uint64_t first = (uint64_t)g << units_per_segment_log2, left = n_units - first;
   const uint32_t n = left < (1ull << units_per_segment_log2) ? (uint32_t)left : 1u << units_per_segment_log2;
-  const uint64_t block = first >> units_per_block_log2, block_first = block << units_per_block_log2;
-  const u32x4 ref = img[block_first];
+  const auto [block, in_block] = ds_block_place(first, units_per_block_log2);
+  const u32x4 ref = img[first - in_block];
   u32x4 x = ref;
   if (tid < n) x = __builtin_nontemporal_load(img + first + tid);
   u32x4 d = x ^ ref;
@@ -1597,7 +1598,7 @@ __global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *
   if (tid == 0) {
     if (WHOLE) keep[block] = any ? 1u : 0u;
     else if (any) atomicOr(keep + block, 1u);
-    if (first == block_first) patterns[block] = ref;
+    if (in_block == 0) patterns[block] = ref;
   }
 }
 
@@ -1725,8 +1726,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
   if (first >= n_units) return;
   const uint64_t left = n_units - first;
   const uint32_t mine = left < kUnits ? (uint32_t)left : kUnits;
-  const uint64_t block = first >> units_per_block_log2;
-  const uint64_t in_block = first - (block << units_per_block_log2);
+  const auto [block, in_block] = ds_block_place(first, units_per_block_log2);
   const uint32_t slot = pos[block];
   if (!keep[block]) return;
   u32x4 x[UNROLL];
@@ -1769,7 +1769,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
   constexpr uint32_t kUnits = 256 * UNROLL;  // in one block (of a power of two of at least 16 KiB)
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
   const uint32_t first = blockIdx.x * kUnits, left = n_units - first, mine = left < kUnits ? left : kUnits;
-  const uint32_t block = first >> units_per_block_log2, in_block = first - (block << units_per_block_log2);
+  const DsBlockPlace place = ds_block_place(first, units_per_block_log2);
+  const uint32_t block = (uint32_t)place.block, in_block = (uint32_t)place.in_block;  // less than 2048, and 2^22
   const uint32_t kept = keep[block];
   if (!kept && in_block) return;
   u32x4 x[UNROLL];
