@@ -1,12 +1,13 @@
 // Host build of the block route for views with short runs (csrc/ds_perm.h, included unchanged): every block of a
 // view is moved thread by thread, phase by phase, and every access is counted, so that a CPU test can see that
-// exactly the bytes of the view and of the image range are read and written, and that LDS is not left.
+// exactly the bytes of the view and of the image range are read and written, and that the LDS of the kernel that runs the
+// block is not left.  The gather's side of the tensor runs as in small images and as in large ones (streaming loads).
 #include <stdint.h>
 
 #include <vector>
 
 static unsigned char *g_arena_hits, *g_image_hits;  // accesses per byte
-static uint64_t g_arena, g_arena_len, g_image, g_image_len;
+static uint64_t g_arena, g_arena_len, g_image, g_image_len, g_lds_len;
 static long g_bad;
 static void touch(char kind, uint64_t at, uint64_t n, uint64_t align);
 #define DS_PERM_TOUCH(kind, at, n, align) touch(kind, at, n, align)
@@ -14,7 +15,7 @@ static void touch(char kind, uint64_t at, uint64_t n, uint64_t align);
 
 static void touch(char kind, uint64_t at, uint64_t n, uint64_t align) {
   if (kind == 'l') {
-    if (at + n > kPermLdsBytes || at % align) ++g_bad;
+    if (at + n > g_lds_len || at % align) ++g_bad;
     return;
   }
   const bool arena = kind == 'r' || kind == 'w';
@@ -35,10 +36,17 @@ static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigne
     memcpy(v.w, (const void *)(uintptr_t)p, 16);
     return v;
   };
+  g_lds_len = d.flags & kPermWide ? kPermLdsBytes : kPermNarrowBytes;
   memset(lds, 0xCD, kPermLdsBytes);
   for (uint32_t t = 0; t < kPermThreads; ++t)
     if (pack) ds_perm_tensor_side<E, W, true>(d, k, lds, t);
     else ds_perm_image_load(d, k, lds, img, lo, t, load);
+  if (pack) {
+    alignas(16) static uint8_t streamed[kPermLdsBytes];
+    memset(streamed, 0xCD, kPermLdsBytes);
+    for (uint32_t t = 0; t < kPermThreads; ++t) ds_perm_tensor_side<E, W, true, true>(d, k, streamed, t);
+    if (memcmp(lds, streamed, kPermLdsBytes)) ++g_bad;
+  }
   for (uint32_t t = 0; t < kPermThreads; ++t)
     if (pack) ds_perm_image_store<E>(d, k, lds, img, lo, t, store);
     else ds_perm_tensor_side<E, W, false>(d, k, lds, t);
