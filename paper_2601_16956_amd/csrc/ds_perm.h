@@ -33,7 +33,7 @@
 #define DS_PERM_GLOBAL
 #define DS_PERM_TABLE
 #endif
-#ifndef DS_PERM_TOUCH  // the CPU test's hook: (kind, address or LDS offset, bytes, alignment)
+#ifndef DS_PERM_TOUCH  // the CPU test's hook: (kind, address or LDS offset, bytes, alignment); kind 's': a streaming load
 #define DS_PERM_TOUCH(kind, at, n, align)
 #endif
 
@@ -89,7 +89,7 @@ struct DsPerm {
                               // scatter's stores stream.  Streaming / cached, us: fp32 4096 x 4099 21.2 / 29.3, bytes
                               // 8192 x 8216 24.5 / 40.0; columns at multiples of 32 bytes 25.5 / 16.6, 109 / 86) |
                               // kPermOnce (a block's lines of the tensor are all its own, or nearly: the gather's loads
-                              // of them may stream) | kPermGroups (flat and dense along a: 16 bytes of
+                              // of them may stream; along b: its pieces of the tensor are four lines and more) | kPermGroups (flat and dense along a: 16 bytes of
                               // neighbours along a at a time)
   uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
@@ -179,7 +179,7 @@ DS_PERM_FN uint32_t ds_perm_row_lds(const DS_PERM_TABLE DsPerm &d, const DsPermB
 // moved twice, so that no load hangs on a condition.  Scatter: only what lies in [lo, hi) is stored.
 template <typename T, bool NT = false>
 DS_PERM_FN T ds_perm_load(uint64_t base, uint32_t off, uint32_t align) {
-  DS_PERM_TOUCH('r', base + off, sizeof(T), align);
+  DS_PERM_TOUCH(NT ? 's' : 'r', base + off, sizeof(T), align);
   T v;
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef T any __attribute__((aligned(1)));
@@ -213,7 +213,7 @@ typedef DsPermThree DsPermThreeAny __attribute__((aligned(4)));
 #endif
 template <bool NT>
 DS_PERM_FN DsPermRun ds_perm_load_run(uint64_t base, uint32_t off) {
-  DS_PERM_TOUCH('r', base + off, 12, 4);
+  DS_PERM_TOUCH(NT ? 's' : 'r', base + off, 12, 4);
   DsPermRun v;
 #if defined(__HIP_DEVICE_COMPILE__)
   DsPermThree x;
@@ -655,23 +655,31 @@ DS_PERM_FN void ds_perm_wide(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k
 }
 
 // STREAM: the image is one of those that no cache holds until the next pass (kCachedBytes); the gather's loads then stream
-// where no line of the tensor is another block's too.
+// where no line of the tensor is another block's too (kPermOnce).  Walks along b, streaming / cached, us: pieces of 8 bytes
+// that 16 blocks' lines hold (bf16 4096 x 4096 x 4 with strides of 8, 32768 and 2) 301 / 155, of 24 bytes (1500 x 3000 x 6
+// with strides of 16, 24 000 and 2) 189 / 108, of 16 bytes of bytes 127 / 90; long pieces, which share the lines at their
+// ends alone, 39.6 / 43.6 (fp32, every second of 1000 columns), 45.8 / 48.4 (bf16, of 1031), 44.0 / 48.7 (six of sixteen).
 template <typename E, typename W, bool PACK, bool STREAM = false>
 DS_PERM_FN void ds_perm_tensor_side(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
   constexpr uint32_t V = (uint32_t)(sizeof(W) / sizeof(E));
   constexpr bool NT = PACK && STREAM;
   const bool once = NT && (d.flags & kPermOnce);
   if constexpr (sizeof(E) == 4)
-    if (!(d.flags & kPermAlongA) && d.run == 12) return ds_perm_runs<PACK, NT>(d, k, lds, tid);
+    if (!(d.flags & kPermAlongA) && d.run == 12) {
+      if (once) ds_perm_runs<PACK, NT>(d, k, lds, tid);
+      else ds_perm_runs<PACK, false>(d, k, lds, tid);
+      return;
+    }
   if (d.flags & kPermGroups) {
-    if (PACK && k.na < 16 / sizeof(E)) ds_perm_along_b<E, PACK, NT>(d, k, lds, tid);
+    if (PACK && k.na < 16 / sizeof(E)) ds_perm_along_b<E, PACK, false>(d, k, lds, tid);
     else if (once) ds_perm_groups<E, PACK, NT>(d, k, lds, tid);
     else ds_perm_groups<E, PACK, false>(d, k, lds, tid);
   } else if ((d.flags & kPermWide) && (PACK || k.inside)) {
     if (once) ds_perm_wide<E, PACK, NT>(d, k, lds, tid);
     else ds_perm_wide<E, PACK, false>(d, k, lds, tid);
   } else if (!(d.flags & kPermAlongA)) {
-    ds_perm_along_b<E, PACK, NT>(d, k, lds, tid);
+    if (once) ds_perm_along_b<E, PACK, NT>(d, k, lds, tid);
+    else ds_perm_along_b<E, PACK, false>(d, k, lds, tid);
   } else if (!(d.flags & kPermFull)) {
     if (once) ds_perm_along_a<E, PACK, NT>(d, k, lds, tid);
     else ds_perm_along_a<E, PACK, false>(d, k, lds, tid);
@@ -973,7 +981,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
              (groups ? kPermGroups : 0u) | (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
              (wide && (columns & 63) == 0 ? kPermStream : 0u) |
-             ((wide ? lines && g > 1 && (columns & (kPermLine - 1)) == 0 : ta * d->sa >= 4 * kPermLine) ? kPermOnce : 0u);
+             ((wide ? lines && g > 1 && (columns & (kPermLine - 1)) == 0 : (along_a ? ta * d->sa : tb * d->sb) >= 4 * kPermLine) ? kPermOnce : 0u);
   const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
   return tiles < (1u << 31) ? (uint64_t)tiles : 0;
 }

@@ -8,6 +8,7 @@
 
 static unsigned char *g_arena_hits, *g_image_hits;  // accesses per byte
 static uint64_t g_arena, g_arena_len, g_image, g_image_len, g_lds_len;
+static uint64_t g_loads, g_streamed, g_large;  // loads of the tensor: all, streaming, by the gather as in large images
 static long g_bad;
 static void touch(char kind, uint64_t at, uint64_t n, uint64_t align);
 #define DS_PERM_TOUCH(kind, at, n, align) touch(kind, at, n, align)
@@ -18,7 +19,9 @@ static void touch(char kind, uint64_t at, uint64_t n, uint64_t align) {
     if (at + n > g_lds_len || at % align) ++g_bad;
     return;
   }
-  const bool arena = kind == 'r' || kind == 'w';
+  if (kind == 'r') ++g_loads;
+  if (kind == 's') ++g_loads, ++g_streamed;
+  const bool arena = kind == 'r' || kind == 's' || kind == 'w';
   const uint64_t base = arena ? g_arena : g_image, len = arena ? g_arena_len : g_image_len;
   if (at < base || at + n > base + len || at % align) {
     ++g_bad;
@@ -44,7 +47,9 @@ static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigne
   if (pack) {
     alignas(16) static uint8_t streamed[kPermLdsBytes];
     memset(streamed, 0xCD, kPermLdsBytes);
+    const uint64_t before = g_loads;
     for (uint32_t t = 0; t < kPermThreads; ++t) ds_perm_tensor_side<E, W, true, true>(d, k, streamed, t);
+    g_large += g_loads - before;
     if (memcmp(lds, streamed, kPermLdsBytes)) ++g_bad;
   }
   for (uint32_t t = 0; t < kPermThreads; ++t)
@@ -57,6 +62,9 @@ static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigne
 // range would have, which perm_host_launched counts.
 static uint64_t g_launched;
 extern "C" uint64_t perm_host_launched() { return g_launched; }
+// The loads of the tensor by gathers as in images that no cache holds, and how many of them streamed.
+extern "C" uint64_t perm_host_loads() { return g_large; }
+extern "C" uint64_t perm_host_streamed() { return g_streamed; }
 extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_t offset, uint64_t at, uint64_t nbytes,
                                uint64_t run, uint32_t n_outer, const uint64_t *extent, const uint64_t *stride, int pack,
                                uint64_t lo, uint64_t hi, unsigned char *img, unsigned char *arena_hits,

@@ -1,0 +1,47 @@
+"""Which of the block route's loads stream (csrc/ds_perm.h): in images that no cache holds those whose lines no other block
+reads."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from test_perm_blocks import _check
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("perm") / "perm_host.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-fPIC", "-shared", "-I",
+                    os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c_abi", "perm_host.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    u64, vp = ctypes.c_uint64, ctypes.c_void_p
+    lib.perm_host_move.restype = ctypes.c_long
+    lib.perm_host_move.argtypes = [vp, u64, u64, u64, u64, u64, ctypes.c_uint32, vp, vp, ctypes.c_int, u64, u64, vp, vp, vp]
+    lib.perm_host_loads.restype = lib.perm_host_streamed.restype = u64
+    return lib
+
+
+# (view, do the gather's loads stream?); walks along b: pieces of the tensor on either side of four lines, lines that
+# several blocks read, runs of 12 bytes, whole rows of units
+GATHERS = [
+    ("f32", (3000,), (2,), True), ("u8", (9000,), (3,), True), ("bf16", (40, 300), (800, 2), True),
+    ("f32", (20, 64), (1000, 2), True), ("f32", (20, 63), (1000, 2), False),
+    ("bf16", (200, 150, 4), (8, 1700, 2), False), ("bf16", (50, 100, 6), (16, 1000, 2), False),
+    ("u8", (60, 190, 8), (16, 1200, 2), False), ("bf16", (30, 40, 32), (64, 2000, 2), False),
+    ("f32", (40, 30, 4, 3), (16, 700, 4, 1), False), ("f32", (900, 3), (4, 1), True), ("f32", (9, 200, 3), (900, 4, 1), True),
+    # walks along a: columns of few lines and of many
+    ("bf16", (200, 9), (1, 200), False), ("f32", (512, 9), (1, 512), True)]
+
+
+@pytest.mark.parametrize("dtype,shape,strides,streams", GATHERS)
+def test_the_gather_streams_lines_of_one_block(lib, dtype, shape, strides, streams):
+    loads, streamed = lib.perm_host_loads(), lib.perm_host_streamed()
+    assert _check(lib.perm_host_move, dtype, shape, strides, 0, 512, np.random.default_rng(1)) > 0
+    loads, streamed = lib.perm_host_loads() - loads, lib.perm_host_streamed() - streamed
+    assert loads > 0
+    assert streamed == (loads if streams else 0)
