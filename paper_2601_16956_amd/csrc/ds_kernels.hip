@@ -1351,7 +1351,7 @@ __device__ __forceinline__ void move_perm_block(const DS_PERM_TABLE DsPerm &d, c
         st16_aligned<false>((uint8_t *)p, u32x4{v.w[0], v.w[1], v.w[2], v.w[3]});
       });
   } else {
-    if (STREAM && (d.flags & (kPermWide | kPermStream)) != kPermWide)
+    if (STREAM && (d.flags & kPermImageOnce))
       ds_perm_image_load(d, k, lds, a.img, a.img_lo, ds_perm_apart<true>(tid), [](uint64_t p) {
         const u32x4 v = ld16_aligned<true>((const uint8_t *)p);
         return DsPermUnit{{v.x, v.y, v.z, v.w}};

@@ -49,7 +49,7 @@ constexpr int kPermUnroll = 8;             // granules a thread has in flight
 
 enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11,
                   kPermWide = 1u << 12, kPermStream = 1u << 13, kPermOnce = 1u << 14,
-                  kPermGroups = 1u << 15 };
+                  kPermGroups = 1u << 15, kPermImageOnce = 1u << 16 };
 
 // Wide blocks: views dense along a (16-byte loads of neighbours along a, transposed in registers), kPermWideA steps along a;
 // of each row 384 bytes where rows start at lines of the image, else up to 368, and a block writes the lines that start in
@@ -89,8 +89,9 @@ struct DsPerm {
                               // scatter's stores stream.  Streaming / cached, us: fp32 4096 x 4099 21.2 / 29.3, bytes
                               // 8192 x 8216 24.5 / 40.0; columns at multiples of 32 bytes 25.5 / 16.6, 109 / 86) |
                               // kPermOnce (a block's lines of the tensor are all its own, or nearly: the gather's loads
-                              // of them may stream; along b: its pieces of the tensor are four lines and more) | kPermGroups (flat and dense along a: 16 bytes of
-                              // neighbours along a at a time)
+                              // of them may stream; along b: its pieces of the tensor are four lines and more) |
+                              // kPermGroups (flat and dense along a: 16 bytes of neighbours along a at a time) |
+                              // kPermImageOnce (the same of the image: the scatter's loads of it may stream)
   uint32_t n_slower;          // how many of the other dimensions are slower than a in the image
 };
 static_assert(sizeof(DsPerm) == 176, "eleven 16-byte words");
@@ -978,10 +979,19 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   d->tiles_b = (d->eb + tb - 1) / tb;
   const uint32_t units = (uint32_t)((flat ? kPermThreads * 16 : tb * run) / 16);
   while (d->lanes_log2 < 8 && (2u << d->lanes_log2) <= units) ++d->lanes_log2;  // (not used by wide blocks inside the range)
+  // Where the scatter's loads stream: wide blocks whose stores do; blocks that are one piece of the image; rows of whole
+  // lines, or of at least three.  Of shorter ones another block reads the lines at both ends again, from HBM.  Streaming
+  // / cached, scatter, us: rows of 112 bytes (bytes 2273 x 3283, 20 of them) 128 / 94, (5530 x 3933, five) 72 / 64, of 240
+  // bytes (bf16 332 941 x 214) 127 / 111, (fp32 37 x 96 x 2230 of 37 x 3552, five) 136 / 118, of 48 bytes (fp32 1000 x 1000
+  // x 4 x 3) 90 / 80, though of 240 bytes (fp32 1883 x 2672, five) 49 / 57 too; of 512 (i64 50 x 362, 500 of them) 0.74 of
+  // the time, (157 x 97 936) 0.86, of 496 (19 x 307) 0.92; pieces (fp32 660 343 x 6, five) 0.83, (25 x 372 x 372, five) 0.90.
+  const bool rows_of_lines = flat || ((image_bits | tb * run) & (kPermLine - 1)) == 0;
+  const bool image_once = wide ? (columns & 63) == 0 : rows_of_lines || tb * run >= 3 * kPermLine;
   d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
-             (groups ? kPermGroups : 0u) | (flat || ((image_bits | tb * run) & 127) == 0 ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
+             (groups ? kPermGroups : 0u) | (rows_of_lines ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
              (wide && (columns & 63) == 0 ? kPermStream : 0u) |
-             ((wide ? lines && g > 1 && (columns & (kPermLine - 1)) == 0 : (along_a ? ta * d->sa : tb * d->sb) >= 4 * kPermLine) ? kPermOnce : 0u);
+             ((wide ? lines && g > 1 && (columns & (kPermLine - 1)) == 0 : (along_a ? ta * d->sa : tb * d->sb) >= 4 * kPermLine) ? kPermOnce : 0u) |
+             (image_once ? kPermImageOnce : 0u);
   const unsigned __int128 tiles = (unsigned __int128)batches * d->tiles_a * d->tiles_b;
   return tiles < (1u << 31) ? (uint64_t)tiles : 0;
 }

@@ -57,14 +57,18 @@ static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigne
     else ds_perm_tensor_side<E, W, false>(d, k, lds, t);
 }
 
+static uint32_t g_flags;  // of the last view
+// The loads of the tensor by gathers as in images that no cache holds, and how many of them streamed.
+extern "C" uint64_t perm_host_loads() { return g_large; }
+extern "C" uint64_t perm_host_streamed() { return g_streamed; }
+// Do the scatter's loads of the image stream for the last view?
+extern "C" int perm_host_image_streams() { return (g_flags & kPermImageOnce) != 0; }
+
 // Moves image bytes [lo, hi) of one view at image offset `at`; `img` holds byte lo.  Returns the number of blocks
 // (0: not this route's), or -1 if an access was out of bounds or not aligned.  Runs the blocks that a launch for the
 // range would have, which perm_host_launched counts.
 static uint64_t g_launched;
 extern "C" uint64_t perm_host_launched() { return g_launched; }
-// The loads of the tensor by gathers as in images that no cache holds, and how many of them streamed.
-extern "C" uint64_t perm_host_loads() { return g_large; }
-extern "C" uint64_t perm_host_streamed() { return g_streamed; }
 extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_t offset, uint64_t at, uint64_t nbytes,
                                uint64_t run, uint32_t n_outer, const uint64_t *extent, const uint64_t *stride, int pack,
                                uint64_t lo, uint64_t hi, unsigned char *img, unsigned char *arena_hits,
@@ -79,6 +83,7 @@ extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_
   alignas(16) static uint8_t lds[kPermLdsBytes];
   DsPerm d;
   const uint64_t n = ds_perm_make(g_arena + offset, at, nbytes, run, n_outer, extent, stride, &d);
+  if (n) g_flags = d.flags;
   uint64_t first = 0, last = n;
   if (n) ds_perm_range(d, lo, hi, &first, &last);
   if (last > n) ++g_bad;

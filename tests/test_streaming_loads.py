@@ -45,3 +45,19 @@ def test_the_gather_streams_lines_of_one_block(lib, dtype, shape, strides, strea
     loads, streamed = lib.perm_host_loads() - loads, lib.perm_host_streamed() - streamed
     assert loads > 0
     assert streamed == (loads if streams else 0)
+
+
+# (view, image offset, do the scatter's loads stream?): rows on either side of three lines, rows of whole lines, pieces, wide
+# blocks
+SCATTERS = [
+    ("u8", (300, 3283), (1, 301), 512, False), ("bf16", (70, 1031), (1, 77), 512, False), ("f32", (37, 2230), (1, 37), 512, False),
+    ("f32", (70, 33, 4, 3), (16, 1120, 4, 1), 512, False), ("bf16", (70, 1024), (1, 77), 512, True),
+    ("bf16", (70, 1024), (1, 77), 16, False), ("i64", (50, 362), (1, 58), 64, True), ("i64", (50, 24), (1, 58), 64, False),
+    ("f32", (512, 9), (1, 512), 16, True), ("f32", (3000,), (2,), 16, True),
+    ("bf16", (64, 257), (1, 72), 512, False), ("bf16", (50, 16), (800, 2), 16, False)]
+
+
+@pytest.mark.parametrize("dtype,shape,strides,at,streams", SCATTERS)
+def test_the_scatter_streams_lines_of_one_block(lib, dtype, shape, strides, at, streams):
+    assert _check(lib.perm_host_move, dtype, shape, strides, 0, at, np.random.default_rng(1)) > 0
+    assert bool(lib.perm_host_image_streams()) == streams
