@@ -145,6 +145,7 @@ struct ds_plan {
   uint64_t n_one_by_one = 0;               // ... and those with (parts of) views of several outer dimensions
   uint64_t n_short_rows = 0;               // chunks of rows of at most 512 bytes
   bool any_wide = false;                   // does a view of `perms` move in wide blocks (ds_perm.h)?
+  uint64_t n_column_blocks = 0;            // blocks that are neither wide nor one piece of the image and go along a
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
   // The tables the kernels read, laid out one behind the other at these offsets (multiples of 128); the tables of
   // views moved in blocks come last.  `blob` is that layout on the host for tables of up to 256 KiB and for plans that
@@ -171,6 +172,8 @@ struct ds_plan {
     const uint64_t left_out = blocks ? n_perm_chunks : 0;
     return (n_general - left_out) * 2 > n_chunks() - left_out;
   }
+  // Are most blocks narrow ones along a (see ds_perm_order)?
+  bool mostly_columns() const { return n_column_blocks * 2 > perm_items.size(); }
   // Do most chunks of a launch hold several contiguous tensors, in a plan that has views too and an image of more than
   // 16 MiB?  They then take the general path with four units per thread, whose chain of dependent loads (record,
   // descriptors, data) one unit per thread, with a quarter of the bytes in flight, pays four times.  Four units / one, us,

@@ -1021,17 +1021,23 @@ static inline void ds_perm_items(const DsPerm &d, uint32_t perm, uint32_t n, DsP
 struct DsPermOrder {
   uint32_t span;    // work-groups per XCD
   uint32_t stripe;  // blocks of a stripe, at least 2
-  uint32_t magic;   // ds_perm_magic of it
+  uint32_t magic;   // ds_perm_magic of it; 0: one stripe per XCD
 };
 constexpr uint32_t kPermOrdered = 1u << 27;
-static inline DsPermOrder ds_perm_order(uint32_t n, bool pack) {  // 0 < n < kPermOrdered
+// `columns`: a launch whose blocks are mostly narrow ones along a keeps one stripe per XCD for the scatter, whose stores
+// of parts of lines wait in the L2 for the others: these are a few dozen blocks or the rest of a column further.
+// In stripes / one per XCD, scatter, us: fp32 37 x 96 x 2230 of 37 x 3552, five of them, 119 / 99, 1883 x 2672, five, 57 / 54,
+// bf16 332 941 x 214 111 / 105, bytes 2273 x 3283, 20 of them, 94 / 87; but bytes 15 298 x 194, five, 0.95 of the time.
+// (Wide blocks the other way round: i64 804 x 3735, five, 0.89, bf16 41 282 x 400, five, 0.90.)
+static inline DsPermOrder ds_perm_order(uint32_t n, bool pack, bool columns = false) {  // 0 < n < kPermOrdered
   const uint32_t blocks = 8 * (pack ? 64 : 48);
-  const uint32_t rounds = n < (pack ? 2048 : 768) ? 1 : (n + blocks / 2) / blocks;
+  const uint32_t rounds = n < (pack ? 2048 : 768) || (columns && !pack) ? 1 : (n + blocks / 2) / blocks;
   uint32_t stripe = (n + rounds * 8 - 1) / (rounds * 8);
   if (stripe < 2) stripe = 2;
-  return {rounds * stripe, stripe, ds_perm_magic(stripe)};
+  return {rounds * stripe, stripe, rounds == 1 ? 0 : ds_perm_magic(stripe)};
 }
-// The block that work-group w < 8 * span takes; n and more: none.  (w / 8 * stripe < 2^32: the quotient is exact.)
+// The block that work-group w < 8 * span takes; n and more: none.  (Of several stripes per XCD w / 8 * stripe < 2^32: the
+// quotient is exact.)
 DS_PERM_FN uint32_t ds_perm_ordered(uint32_t w, uint32_t stripe, uint32_t magic) {
   const uint32_t i = w >> 3, round = (uint32_t)(((uint64_t)i * magic) >> 32);
   return (round * 7u + (w & 7u)) * stripe + i;  // stripe 8 round + XCD, block i - round * stripe of it

@@ -487,6 +487,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
             p->perm_first.push_back((uint32_t)(before + blocks));
             p->perms.push_back(perm);
             p->any_wide |= (perm.flags & kPermWide) != 0;
+            if ((perm.flags & (kPermAlongA | kPermFlat | kPermWide)) == kPermAlongA) p->n_column_blocks += blocks;
             in_blocks.push_back((uint32_t)t);
             block_bytes += tl.nbytes;
           } else if (n_outer > 1 || (n_outer && tl.run_bytes < 16)) {
@@ -501,6 +502,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
         } else {
           p->perms.clear();
           p->perm_first.clear();
+          p->n_column_blocks = 0;
         }
         // what the general path is left with of views with short runs
         uint64_t one_element = 0;

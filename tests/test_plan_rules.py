@@ -12,7 +12,7 @@ from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
-         "in_pieces", "n_lanes", "n_dims", "mostly_several")
+         "in_pieces", "n_lanes", "n_dims", "mostly_several", "mostly_columns")
 
 
 @pytest.fixture(scope="module")
@@ -138,3 +138,15 @@ def test_which_plans_of_small_tensors_and_views_keep_four_units_per_thread(facts
     assert facts(_small(4200, small) + [_transposed(512)]).mostly_several               # beside blocks
     assert not facts(([("u8", (small,), (1,))] * 2 + [rows]) * 2500).mostly_several      # chunks that hold views
     assert not facts([("u8", (1 << 25,), (1,)), rows] + _small(100, small)).mostly_several
+
+
+def test_the_scatter_of_narrow_columns_keeps_one_stripe_per_xcd(facts):
+    """Blocks along a that are neither wide nor one piece of the image, when they are most of a launch's."""
+    narrow, wide, flat, along_b = (("bf16", (507, 2847), (1, 509)), ("bf16", (512, 2847), (1, 512)),
+                                   ("f32", (512, 513, 9), (513 * 9, 1, 513)), ("f32", (500000,), (2,)))
+    assert facts([narrow]).mostly_columns
+    for other in (wide, flat, along_b):
+        assert not facts([other]).mostly_columns
+    assert facts([narrow] * 3 + [wide, along_b]).mostly_columns
+    assert not facts([narrow, wide, wide, flat]).mostly_columns
+    assert not facts([("u8", (5000,), (1,))]).mostly_columns
