@@ -1561,7 +1561,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
 //
 // One work-group looks at one segment: a whole block of up to 64 KiB, or 64 KiB of a larger one (WHOLE = false; the
 // flags are cleared before).  keep[k] = 1 if some 16-byte unit of block k differs from the block's first unit.
-constexpr uint32_t kSegmentUnitsLog2 = 12;
 template <bool WHOLE>
 __global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *__restrict__ img, uint64_t n_units,
                                                                    uint32_t units_per_block_log2,
@@ -1602,14 +1601,13 @@ __global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *
   }
 }
 
-// The same for blocks of more than 64 KiB in images of up to 16 MiB: one work-group looks at a block, so that no flags have
+// The same for blocks of 128 and 256 KiB in images of up to 16 MiB: one work-group looks at a block, so that no flags have
 // to be cleared by a launch of their own.  Behind the block's first 16 KiB it takes 256 KiB at a time.  Bound by the latency
-// of those steps where blocks are constant; a constant block of 1 MiB takes 10 us, which is where the line for the block
-// size lies.  Images of 64 MB are a few us faster in segments (40 MB in blocks of 1 MiB 26.5 / 25.2 us, of 3 MB in blocks of
-// 128 KiB 7.9 / 10.2).
+// of those steps where blocks are constant, hence the line: one CU reads a constant block of 1 MiB in 20 us.  All of
+// ds_image_compress, us, so / in segments: 8 MB that no cache holds, all of it constant, in blocks of 128 KiB 8.2 / 11.5, of 256
+// KiB 9.4 / 11.6, of 512 KiB 14.3 / 11.5, of 1 MiB 23.9 / 11.4; in the caches 6.7 / 10.1, 6.3 / 10.2, 8.6 / 10.3 and 12.8 /
+// 10.3; nothing constant 6.2 / 10.3, 6.2 / 10.3, 7.8 / 10.1, 7.6 / 10.3.
 constexpr uint32_t kBlockThreads = 1024, kBlockUnroll = 16;
-constexpr uint64_t kWholeBlocksBytes = 16ull << 20;
-constexpr uint32_t kWholeBlockUnitsLog2 = 16;
 __global__ __launch_bounds__(kBlockThreads) void ds_constant_blocks_kernel(const u32x4 *__restrict__ img, uint64_t n_units,
                                                                            uint32_t units_per_block_log2,
                                                                            uint32_t *__restrict__ keep,
@@ -1756,10 +1754,13 @@ int launch_pack_kept(const u32x4 *img, uint64_t n_units, uint32_t upb_log2, cons
 // in front of its own, whose flags are at most 8 KiB in the L2, and the first of each block leaves the count in pos.
 // Small images are bound by the launches, each about 4 us of the caller's time, then by the chain flags -> count -> stores
 // behind the loads; from 8 MiB on by the caches and HBM, where four units per thread and ordinary loads are ahead.  All of
-// ds_image_compress with the scan of its own / so, us: 16 KB 10.2 / 6.0, 1 MB 10.1 / 6.1, 8 MB in blocks of 1 MiB 13.3 / 6.3 (no
+// ds_image_compress with the scan of its own / so, us: 16 KB 10.2 / 6.0, 1 MB 10.1 / 6.1, 8 MB in blocks of 256 KiB 13.7 / 6.2 (no
 // clearing launch either), 17 MB of which 30 % is constant 16.7 / 13.2 (one unit per thread 13.8), 34 MB in 2048 blocks 18.5 /
 // 14.1, 64 MB 27.7 / 25.8, none of it constant 32.9 / 21.9 (streaming loads 27.7).  Beyond: 134 MB in 2048 blocks 45.1 / 42.2,
 // none constant 49.5 / 51.7; 256 MB 78.3 / 82.5; 1 GiB in 1024 blocks 307 / 331.
+// Those are images that the last-level cache holds from the pass before.  Out of a rotation of 700 MB, blocks of 32 KiB, with
+// the scan / so / so with streaming loads: 16 MB 13.4 / 10.6 / 10.3, 34 MB 20.5 / 18.7 / 19.0, 64 MB 30.2 / 30.3 / 30.8; of
+// which 30 % is constant 15.0 / 12.4 / 11.7, 19.6 / 17.6 / 17.7, 27.7 / 26.5 / 25.9.
 constexpr uint64_t kCountedBlocks = 2048, kOneUnitBytes = 8ull << 20;
 template <int UNROLL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_count_and_pack_kernel(
@@ -1825,7 +1826,7 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   const uint32_t ups_log2 = upb_log2 < kSegmentUnitsLog2 ? upb_log2 : kSegmentUnitsLog2;
   const uint64_t segments = (n_units + (1ull << ups_log2) - 1) >> ups_log2;
   const dim3 seg_grid((uint32_t)segments);
-  if (ups_log2 < upb_log2 && upb_log2 <= kWholeBlockUnitsLog2 && nbytes <= kWholeBlocksBytes) {
+  if (ds_looks_at_whole_blocks(nbytes, upb_log2)) {
     hipLaunchKernelGGL(ds_constant_blocks_kernel, dim3((uint32_t)n_blocks), dim3(kBlockThreads), 0, st,
                        (const u32x4 *)image_dev, n_units, upb_log2, keep_dev, (u32x4 *)patterns_dev);
   } else if (ups_log2 == upb_log2) {

@@ -1,4 +1,5 @@
-"""ds_image_compress with blocks larger than the image, up to the largest power of two that 64 bits hold."""
+"""ds_image_compress with blocks larger than the image, up to the largest power of two that 64 bits hold; which blocks one
+work-group looks at."""
 import ctypes
 import os
 import subprocess
@@ -9,19 +10,32 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_place_of_a_unit_in_blocks_of_every_size(tmp_path):
-    so = str(tmp_path / "blocks_host.so")
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("blocks") / "blocks_host.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
                     os.path.join(ROOT, "tests", "c_abi", "blocks_host.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
     lib.blocks_host_place.restype = None
     lib.blocks_host_place.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_void_p]
+    lib.blocks_host_whole.argtypes = [ctypes.c_uint64, ctypes.c_uint32]
+    return lib
+
+
+def test_place_of_a_unit_in_blocks_of_every_size(lib):
     out = (ctypes.c_uint64 * 2)()
     for log2 in range(10, 60):
         for unit in (0, 1, 256, 1024, (1 << 22) - 256, (1 << 22) - 1, 1 << 31, 1 << 32, (1 << 32) + 1024, (1 << 36) + 7):
             lib.blocks_host_place(unit, log2, out)
             assert tuple(out) == divmod(unit, 1 << log2), (unit, log2)
+
+
+def test_constant_blocks_of_more_than_256_KiB_are_the_work_of_several_groups(lib):
+    for nbytes in (1 << 14, 1 << 20, 16 << 20):
+        assert [b for b in range(14, 64) if lib.blocks_host_whole(nbytes, b - 4)] == [17, 18]
+    for nbytes in ((16 << 20) + 16, 64 << 20, 1 << 40):
+        assert not any(lib.blocks_host_whole(nbytes, b - 4) for b in range(14, 64))
 
 
 @pytest.mark.gpu
@@ -53,3 +67,34 @@ def test_one_block_larger_than_the_image(block_log2, nbytes):
         assert torch.equal(pats[:-1], torch.stack([b[:16] for b in blocks])) and bool((pats[-1] == 0xCC).all())
         want = torch.cat([b for b, k in zip(blocks, kept) if k] + [img[:0]])
         assert torch.equal(packed[:want.numel()], want) and bool((packed[want.numel():] == 0xCC).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("block_log2", [16, 17, 18, 19, 20])
+def test_the_only_unit_that_differs(block_log2):
+    """On both sides of the blocks that one work-group looks at: the first unit behind the reference, those around its first 16
+    KiB and its steps, the last one; constant blocks between them; a short last block."""
+    import torch
+
+    import paper_2601_16956_amd as ds
+    block, units = 1 << block_log2, 1 << block_log2 - 4
+    at = sorted({u for u in (1, 1023, 1024, 4095, 4096, 16383, 16384, 17407, 17408, units - 1) if u < units})
+    rng = np.random.default_rng(block_log2)
+    img = np.repeat(rng.integers(0, 256, (2 * len(at) + 1, 1, 16), dtype=np.uint8), units, axis=1)
+    for k, u in enumerate(at):
+        img[2 * k, u, int(rng.integers(0, 16))] ^= 1
+    n_blocks, nbytes = len(img), img.size - block // 2
+    dev = torch.from_numpy(img.reshape(-1)).cuda()
+    keep = torch.full((n_blocks,), 9, dtype=torch.int32, device="cuda")
+    pos = torch.full((n_blocks + 1,), 9, dtype=torch.int32, device="cuda")
+    pats = torch.full((n_blocks, 16), 0xCC, dtype=torch.uint8, device="cuda")
+    packed = torch.full((n_blocks * block,), 0xCC, dtype=torch.uint8, device="cuda")
+    print(f"[case] compress {n_blocks} blocks of {block}", flush=True)
+    ds.ds_image_compress(dev.data_ptr(), nbytes, block, keep.data_ptr(), pos.data_ptr(), pats.data_ptr(), packed.data_ptr(),
+                         torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert keep.tolist() == [1, 0] * len(at) + [0]
+    assert pos.tolist() == [(k + 1) // 2 for k in range(2 * len(at))] + [len(at)] * 2
+    assert np.array_equal(pats.cpu().numpy(), img[:, 0])
+    assert np.array_equal(packed[:len(at) * block].cpu().numpy(), img[:-1:2].reshape(-1))
+    assert bool((packed[len(at) * block:] == 0xCC).all())
