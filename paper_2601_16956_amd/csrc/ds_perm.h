@@ -45,6 +45,9 @@ constexpr uint32_t kPermMaxBatch = 4;      // dimensions beside a and b (DS_MAX_
 // Gather of 20 000 square bf16 views, blocks / general path: of 512 bytes 62 / 40 us, of 1152 bytes 69 / 81, of 2048
 // bytes 76 / 92, of 4608 bytes 112 / 258; of 2000 views the blocks win from 512 bytes on (10.5 / 25 us).
 constexpr uint64_t kPermMinBytes = 1024;
+// Images of at most so many bytes have smaller blocks, which all run at once: what one takes is what the launch takes.  (Larger ones
+// have more blocks than run at once, and pay for each.)
+constexpr uint64_t kPermFewBytes = 2ull << 20;
 constexpr int kPermUnroll = 8;             // granules a thread has in flight
 
 enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11,
@@ -842,7 +845,7 @@ DS_PERM_FN void ds_perm_image_load(const DS_PERM_TABLE DsPerm &d, const DsPermBl
 // run, runs of 16 bytes and more (a unit then lies in at most two runs: the row and general paths move it with
 // whole 16-byte accesses), less than kPermMinBytes, extents that leave a block nearly empty or exceed 31 bits.
 static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes, uint64_t run, uint32_t n_outer,
-                                    const uint64_t *extent, const uint64_t *stride, DsPerm *d) {
+                                    const uint64_t *extent, const uint64_t *stride, uint64_t image_bytes, DsPerm *d) {
   if (n_outer == 0 || run >= 16 || nbytes < kPermMinBytes) return 0;
   uint64_t bits = src | run, columns = src;  // `columns`: where those of a view dense along a can start
   for (uint32_t j = 0; j < n_outer; ++j) {
@@ -891,6 +894,7 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   const uint64_t row_bytes = run * d->eb;
   const bool neighbours = a == n_outer || a + 1 == b;
   const bool flat = neighbours && row_bytes < 512 && ((row_bytes | img) & 15);
+  const bool few = image_bytes <= kPermFewBytes;
   uint32_t ta, tb;
   if (flat) {
     tb = d->eb;
@@ -906,16 +910,18 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
     if (tb > d->eb) tb = d->eb;
     else if ((image_bits & 15) && tb * run >= 128) tb -= (uint32_t)((15 + run) / run);
   } else {
-    // 4096 granules at most, which is 16 per thread one batch behind the other: of a small view, whose blocks all run at
-    // once, that is the time (16 KiB / so, us: every second fp32, 500 KB, 5.3 / 3.9, scatter 5.8 / 4.2; six of every sixteen
-    // bytes, 100 KB, 6.6 / 4.4 and 7.7 / 5.2).  Cut at lines of the image, so that a line is one block's (150 MB of six of
+    // 8 KiB; bytes, which are 32 granules per thread then, 4 KiB in small images.  us, 16 / 8 / 4 KiB, gather: every second
+    // byte, 100 KB 11.7 / 7.3 / 4.9, 2 MB 12.0 / 7.9 / 6.2, 8 MB 16.1 / 12.4 / 13.4, 64 MB 70 / 72 / 84; every third, 100 MB
+    // 112 / 110 / 132, scatter 157 / 150 / 143; 16 / 8 KiB: every second fp32, 500 KB 5.3 / 3.9, scatter 5.8 / 4.2, 64 MB in
+    // rows of 1000 41.1 / 39.6, scatter 82 / 79.  Rows of 1 KiB and more may be an eighth larger in all, so that a little
+    // less room than they take leaves no block nearly empty (every second fp32, 1031 columns, 16 MB: rows cut at 1024 17.5,
+    // whole 13.3; 100 MB 99 / 66).  Cut at lines of the image, so that a line is one block's (150 MB of six of
     // sixteen: bytes 108 / 90, at units 107; bf16 97 / 87, at units 93).
-    const uint32_t room = g == 1 ? 4096 : 8192;
-    tb = (uint32_t)((room < 4096 ? room : 4096) / run);
-    if (tb > d->eb) tb = d->eb;
-    ta = (uint32_t)(room / (tb * run));
+    const uint32_t room = g == 1 && few ? 4096 : 8192;
+    tb = row_bytes <= 4096 + 512 ? d->eb : (uint32_t)(4096 / run);
+    ta = (tb * run >= 1024 ? room + room / 8 : room) / (tb * (uint32_t)run);
     if (ta > d->ea) ta = d->ea;
-    tb = (uint32_t)(room / (ta * run));
+    if (tb < d->eb) tb = (uint32_t)(room / (ta * run));
     if (tb > d->eb) tb = d->eb;
     if (tb < d->eb) {
       uint32_t whole = 1;  // steps that are whole lines, or whole units
@@ -923,10 +929,13 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
       if (tb > whole) tb = tb / whole * whole;
     }
   }
-  // flat, dense along a: as few blocks as 16 KiB allow, of equal length, in whole groups of 16 bytes
+  // flat, dense along a: as few blocks as 16 KiB allow, in small images 8, of equal length, in whole groups of 16 bytes (us, 16
+  // / 8 KiB: fp32 with six columns, 1 MB, 3.4 / 3.1, scatter 3.8 / 3.1, 8 MB 4.5 / 4.8 and 5.8 / 5.9; bytes with 60, 350 KB
+  // 5.0 / 3.6 and 5.6 / 3.5; fp32 512 x 512 x 9, 9.4 MB, 5.3 / 6.3 and 7.1 / 7.3)
   const bool groups = flat && along_a && run == g && d->sa == g && d->ea >= 16 / g;
   if (groups) {
-    const uint32_t G = 16 / g, most = ta / G * G, n = (d->ea + most - 1) / most;
+    const uint32_t G = 16 / g, fit = few ? (uint32_t)(8192 / row_bytes) : ta, most = (fit < ta ? fit : ta) / G * G;
+    const uint32_t n = (d->ea + most - 1) / most;
     ta = ((d->ea + n - 1) / n + G - 1) / G * G;
   } else if (along_a) {  // a power of two, of at most one step along a per thread
     uint32_t p = 1;

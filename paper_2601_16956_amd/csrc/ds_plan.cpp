@@ -480,7 +480,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
           h.meta = n_outer | (tl.es_log2 << 8);
           DsPerm perm;
           const uint64_t blocks = ds_perm_make(tl.src, h.img_off, tl.nbytes, tl.run_bytes, tl.n_outer, tl.extent,
-                                               tl.stride, &perm);
+                                               tl.stride, p->total_bytes, &perm);
           const uint64_t before = p->perm_first.empty() ? 0 : p->perm_first.back();
           if (blocks && before + blocks < (1u << 31)) {
             if (p->perms.empty()) p->perm_first.push_back(0);

@@ -58,6 +58,8 @@ static void move_block(const DsPerm &d, const DsPermBlock &k, bool pack, unsigne
 }
 
 static uint32_t g_flags;  // of the last view
+static uint64_t g_image_bytes = 1 << 20;  // the whole image's, by which the plan chooses the size of some blocks
+extern "C" void perm_host_image_bytes(uint64_t n) { g_image_bytes = n; }
 // The loads of the tensor by gathers as in images that no cache holds, and how many of them streamed.
 extern "C" uint64_t perm_host_loads() { return g_large; }
 extern "C" uint64_t perm_host_streamed() { return g_streamed; }
@@ -82,7 +84,7 @@ extern "C" long perm_host_move(unsigned char *arena, uint64_t arena_len, uint64_
   g_bad = 0;
   alignas(16) static uint8_t lds[kPermLdsBytes];
   DsPerm d;
-  const uint64_t n = ds_perm_make(g_arena + offset, at, nbytes, run, n_outer, extent, stride, &d);
+  const uint64_t n = ds_perm_make(g_arena + offset, at, nbytes, run, n_outer, extent, stride, g_image_bytes, &d);
   if (n) g_flags = d.flags;
   uint64_t first = 0, last = n;
   if (n) ds_perm_range(d, lo, hi, &first, &last);
