@@ -144,6 +144,8 @@ struct ds_plan {
   uint64_t n_dims = 0;                     // ... of kind DS_CHUNK_DIMS
   uint64_t n_one_by_one = 0;               // ... and those with (parts of) views of several outer dimensions
   uint64_t n_short_rows = 0;               // chunks of rows of at most 512 bytes
+  uint64_t n_rests = 0;                    // chunks of kind DS_CHUNK_GENERAL and _MULTI, in plans with blocks
+  uint64_t rest_units = 0, rest_most = 0;  // ... their units that no block moves, and the most that one of them has
   bool any_wide = false;                   // does a view of `perms` move in wide blocks (ds_perm.h)?
   uint64_t n_column_blocks = 0;            // blocks that are neither wide nor one piece of the image and go along a
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
@@ -171,6 +173,13 @@ struct ds_plan {
   bool mostly_general(bool blocks) const {
     const uint64_t left_out = blocks ? n_perm_chunks : 0;
     return (n_general - left_out) * 2 > n_chunks() - left_out;
+  }
+  // Do the chunks beside the blocks hold little else than what blocks move: at most one unit for each thread of a work-group?
+  // (Three quarters of them, on average; each of them where few run at once and the launch takes as long as the slowest.)
+  // See ds_mixed_kernel.
+  static constexpr uint64_t kRestUnits = 256;
+  bool mostly_rests(bool at_once) const {
+    return n_rests * 4 > rest_recs.size() * 3 && (at_once ? rest_most <= kRestUnits : rest_units <= n_rests * kRestUnits);
   }
   // Are most blocks narrow ones along a (see ds_perm_order)?
   bool mostly_columns() const { return n_column_blocks * 2 > perm_items.size(); }

@@ -1404,16 +1404,21 @@ constexpr uint32_t kMixedInPieces = 640; // ... and are moved 4 KiB per work-gro
 // (157 MB, 2048 chunks beside the blocks) 75.3 / 79.4 and 97.0 / 98.5, the same at a quarter of the columns 9.0 / 11.8 and
 // 9.7 / 13.7, at a sixteenth 6.9 / 9.9; one transposed matrix of 32 KB to 8 MB beside 32 MB 14.5 to 16.7 / 16.3 to 18.9;
 // beside 100 MB (6400 chunks) 40.9 / 41.5 and 40.3 / 39.3; 32 MB beside 400 MB 153.8 / 142.8 and 152.8 / 145.7.
-// PIECES: few chunks, 4 KiB per work-group, one unit per thread.  All work-groups run at once then, and the launch takes as long
+// PIECES: up to 640 chunks, 4 KiB per work-group, one unit per thread.  All work-groups run at once then, and the launch takes as long
 // as the slowest, which is a chunk where several shards meet (the general path) or of a view of several dimensions.  Such
 // chunks whole, one unit per thread after the other / in pieces, us, gather and scatter: views of 592 columns of 8 bytes (10 MB)
 // 11.3 / 7.2 and 10.0 / 6.5, 2160 columns of f16 (43 MB) 22.2 / 17.6 and 26.2 / 21.5; 8 MB in tensors of 65 000 bytes beside a
 // view 7.5 / 5.5 and 6.7 / 5.1; 8 MB in one tensor 6.0 / 5.5.  Of more chunks the pieces cost more than they save (62 MB in one tensor
 // 20.5 / 20.7 and 20.1 / 22.3): whole, four units per thread in the general path too, the last chunks end sooner (the views
-// of perf/cases.py 61.3 / 58.9 and 66.2 / 64.5, 32 MB in tensors of 65 000 bytes 15.1 / 12.8 and 14.1 / 13.1; but 1000 views of 20 KB,
-// whose chunks hold little besides blocks, 10.9 / 12.1 and 12.4 / 13.6), and so are views of several dimensions (62 MB in
-// runs of 1 KiB, a unit after the other 34.4 / 33.3, so 30.6 / 31.1).
-template <bool PACK, bool NTL, bool PIECES, bool WIDE>
+// of perf/cases.py 61.3 / 58.9 and 66.2 / 64.5, 32 MB in tensors of 65 000 bytes 15.1 / 12.8 and 14.1 / 13.1), and so are views of
+// several dimensions (62 MB in runs of 1 KiB, a unit after the other 34.4 / 33.3, so 30.6 / 31.1).  In the gather without wide
+// blocks that takes 76 registers and leaves six work-groups per CU instead of seven.
+// RESTS: chunks that hold little besides blocks (mostly_rests) are moved whole, the general path's units one per thread: there
+// is nothing for more.  In pieces or with four units / so: 500 transposed bf16 of 100 x 102 7.7 / 6.1 and 8.2 / 6.7, 1000 of them 10.4 / 9.4
+// and 11.2 / 10.5, 3000 25.9 / 23.6 and 36.0 / 34.0, beside as many vectors of 1000 bytes 8.5 / 6.7 and 8.9 / 7.7, 500, 27.8 / 25.6 and
+// 38.9 / 37.4, 3000; 500 of every second of 9146 fp32 15.5 / 13.8 and 16.2 / 14.4.
+enum : int { kPieces, kWhole, kRests };
+template <bool PACK, bool NTL, int HOW, bool WIDE>
 __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(const DsPerm *perms, const DsPermItem *items, uint32_t n_items,
                                                           uint32_t xcd_span, uint32_t stripe, uint32_t magic, const DsChunkRec *recs,
                                                           const uint32_t *ids, uint32_t n, uint32_t span, uint32_t c_lo, MoveArgs ma) {
@@ -1422,8 +1427,8 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(const DsPerm *perms, c
     __attribute__((aligned(16))) uint8_t block[WIDE ? kPermLdsBytes : kPermNarrowBytes];
     GenLds tab;
   } s;
-  constexpr int UNITS = PIECES ? 1 : 4;                       // per thread
-  constexpr uint32_t kPerChunk = PIECES ? kUnitPieces : 1u;   // work-groups
+  constexpr int UNITS = HOW == kPieces ? 1 : 4;                      // per thread
+  constexpr uint32_t kPerChunk = HOW == kPieces ? kUnitPieces : 1u;  // work-groups
   uint32_t wi = blockIdx.x;
   if (wi < a.xcd_span * 8u) {
     const uint32_t i = ds_perm_ordered(wi, a.stripe, a.magic);
@@ -1456,27 +1461,29 @@ __global__ __launch_bounds__(256, 5) void ds_mixed_kernel(const DsPerm *perms, c
     piece = x % kPerChunk * 4096;
     cut_chunk_tiles(ma, c, t0, t1);
   }
-  general_chunk<PACK, 256, UNITS, NTL, true, PACK, kListed, !PIECES>(ma, c, piece, t0, t1, &s.tab);
+  general_chunk<PACK, 256, HOW == kWhole ? 4 : 1, NTL, true, PACK, kListed, HOW != kPieces>(ma, c, piece, t0, t1, &s.tab);
 }
 
-template <bool PACK, bool NTL, bool PIECES>
+template <bool PACK, bool NTL, int HOW>
 int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
-  constexpr uint32_t kPerChunk = PIECES ? kUnitPieces : 1u;
+  constexpr uint32_t kPerChunk = HOW == kPieces ? kUnitPieces : 1u;
   const uint32_t n = la.n_pieces * kPerChunk, span = (n + 7) / 8;
   const dim3 grid(a.xcd_span * 8 + span * 8 + ma.n_extra * kPerChunk);
   if (plan->any_wide)
-    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, true>), grid, dim3(256), 0, stream, a.perms, a.items, a.n_items,
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, HOW, true>), grid, dim3(256), 0, stream, a.perms, a.items, a.n_items,
                        a.xcd_span, a.stripe, a.magic, la.recs, la.ids, n, span, la.c_lo, ma);
   else
-    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, PIECES, false>), grid, dim3(256), 0, stream, a.perms, a.items, a.n_items,
+    hipLaunchKernelGGL((ds_mixed_kernel<PACK, NTL, HOW, false>), grid, dim3(256), 0, stream, a.perms, a.items, a.n_items,
                        a.xcd_span, a.stripe, a.magic, la.recs, la.ids, n, span, la.c_lo, ma);
   DS_HIP_TRY(hipGetLastError());
   return DS_OK;
 }
 template <bool PACK, bool NTL>
 int launch_mixed(const ds_plan *plan, const PermArgs &a, const LeanArgs &la, const MoveArgs &ma, hipStream_t stream) {
-  return la.n_pieces <= kMixedInPieces ? launch_mixed<PACK, NTL, true>(plan, a, la, ma, stream)
-                                       : launch_mixed<PACK, NTL, false>(plan, a, la, ma, stream);
+  const bool in_pieces = la.n_pieces <= kMixedInPieces;
+  return plan->mostly_rests(in_pieces) ? launch_mixed<PACK, NTL, kRests>(plan, a, la, ma, stream)
+         : in_pieces                   ? launch_mixed<PACK, NTL, kPieces>(plan, a, la, ma, stream)
+                                       : launch_mixed<PACK, NTL, kWhole>(plan, a, la, ma, stream);
 }
 
 template <bool PACK, bool STREAM>

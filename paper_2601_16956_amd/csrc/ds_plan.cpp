@@ -593,6 +593,19 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
                   r.run = (uint32_t)tl.run_bytes;
                 }
               }
+              if (!p->perms.empty() && (r.kind == DS_CHUNK_GENERAL || r.kind == DS_CHUNK_MULTI)) {
+                ++p->n_rests;
+                uint64_t units = 0;
+                for (uint32_t t2 = ti; t2 <= t1; ++t2) {
+                  uint64_t lo = p->tile_off[t2];
+                  if (p->hot[t2].meta & DS_HOT_PERM) lo += p->tiles[t2].nbytes & ~(uint64_t)15;
+                  lo = std::max(lo, cb);
+                  const uint64_t hi = std::min(p->tile_off[t2 + 1], c_end);
+                  if (lo < hi) units += (hi - lo) >> 4;
+                }
+                p->rest_units += units;
+                p->rest_most = std::max(p->rest_most, units);
+              }
             }
           }
           p->listed = p->n_perm_chunks && (n_chunks <= ds_plan::kListAlways ||

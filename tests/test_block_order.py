@@ -120,3 +120,37 @@ def test_chunks_beside_blocks_in_pieces_and_whole(beside):
             assert gu.first_mismatch(dw.arena_host(), w.arena) is None
     finally:
         dw.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("views", [60, 700, 3600])
+def test_chunks_that_hold_little_besides_blocks(views):
+    """Chunks of the ends of views and of small tensors between them: few, many, and in an image that no cache holds."""
+    import gpu_util as gu
+    rng = np.random.default_rng(views)
+    shards, at = [], 0
+    for k in range(views):
+        r, c, n = (int(rng.integers(lo, hi)) for lo, hi in ((80, 121), (90, 113), (1, 900)))
+        for dtype, shape, strides in (("bf16", (r, c), (1, r + k % 3)), ("u8", (n,), (1,))):
+            es = DTYPES[dtype][1]
+            at = -(-at // 16) * 16 + es * int(rng.integers(0, 3))
+            shards.append(Shard(f"r{len(shards)}", dtype, shape, strides, at, len(shards)))
+            at += (sum((e - 1) * s for e, s in zip(shape, strides)) + 1) * es
+    w = Workload("rests", 64, 0, rng.integers(0, 256, size=at + 64, dtype=np.uint8), shards)
+    want, offs, tab = gu.oracle_image(w)
+    dw = gu.DeviceWorkload(w)
+    try:
+        print(f"[case] rests of {views} views, image={dw.total}", flush=True)
+        cuts = [0] + sorted(16 * int(x) for x in rng.integers(1, dw.total // 16, 6)) + [dw.total]
+        ranges = [(lo, hi) for lo, hi in zip(cuts, cuts[1:]) if lo < hi]
+        for lo, hi in [(0, dw.total)] + ranges:
+            assert gu.first_mismatch(dw.pack(lo, hi), want[lo:hi]) is None, (lo, hi)
+        w.arena[:] = 0x5A
+        orc.unpack(tab, len(shards), want)
+        for parts in ([(0, dw.total)], ranges):
+            dw.arena.fill_(0x5A)
+            for lo, hi in parts:
+                dw.unpack(want, lo, hi)
+            assert gu.first_mismatch(dw.arena_host(), w.arena) is None
+    finally:
+        dw.close()

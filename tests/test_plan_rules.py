@@ -12,7 +12,7 @@ from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
-         "in_pieces", "n_lanes", "n_dims", "mostly_several", "mostly_columns")
+         "in_pieces", "n_lanes", "n_dims", "mostly_several", "mostly_columns", "rests_at_once", "rests")
 
 
 @pytest.fixture(scope="module")
@@ -150,3 +150,19 @@ def test_the_scatter_of_narrow_columns_keeps_one_stripe_per_xcd(facts):
     assert facts([narrow] * 3 + [wide, along_b]).mostly_columns
     assert not facts([narrow, wide, wide, flat]).mostly_columns
     assert not facts([("u8", (5000,), (1,))]).mostly_columns
+
+
+def test_chunks_that_hold_little_besides_blocks(facts):
+    """Ends of views and small tensors between them; not tensors that fill chunks, and where all chunks run at once not one of
+    them."""
+    view = ("bf16", (100, 102), (1, 100))
+    for table in ([view] * 30, [view, ("u8", (1000,), (1,))] * 40, [view] * 1000):
+        f = facts(table)
+        assert f.n_perms and f.rests and f.rests_at_once
+    f = facts([view] * 300 + [("u8", (65000,), (1,))])
+    assert f.rests and not f.rests_at_once
+    for table in ([view, ("u8", (16000,), (1,))] * 40, [view] * 30 + [("u8", (1 << 20,), (1,))], [view] * 3 + _small(400)):
+        f = facts(table)
+        assert f.n_perms and not f.rests and not f.rests_at_once
+    f = facts(_small(400, 20))
+    assert not f.n_perms and not f.rests
