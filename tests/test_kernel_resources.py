@@ -105,7 +105,9 @@ def test_one_unit_per_thread_runs_at_eight_wavefronts():
 
 
 def test_blocks_that_are_not_wide_have_seven_work_groups_per_CU():
-    """Wide blocks need LDS that leaves room for five; launches without them do not pay for it."""
+    """Wide blocks need LDS that leaves room for five; launches without them do not pay for it.  (The gather beside whole
+    chunks, ds_mixed_kernel<true, loads nt, 1, ...>, has registers for six.)"""
     for name in ("ds_perm_kernel", "ds_mixed_kernel"):
         for args, k in _kernels()[name]:
-            assert _waves(k) >= (5 if args[-1] == "true" else 6 if args[0] == "true" else 7), (name, args, k[".vgpr_count"])
+            six = name == "ds_mixed_kernel" and args[0] == "true" and args[2] == "1"
+            assert _waves(k) >= (5 if args[-1] == "true" else 6 if six else 7), (name, args, k[".vgpr_count"])
