@@ -148,6 +148,7 @@ struct ds_plan {
   uint64_t rest_units = 0, rest_most = 0;  // ... their units that no block moves, and the most that one of them has
   bool any_wide = false;                   // does a view of `perms` move in wide blocks (ds_perm.h)?
   uint64_t n_column_blocks = 0;            // blocks that are neither wide nor one piece of the image and go along a
+  uint64_t n_far_blocks = 0;               // blocks along b that read lines which blocks far on read too
   bool all_contiguous = false;             // no chunk needs the general path: every shard is one contiguous run
   // The tables the kernels read, laid out one behind the other at these offsets (multiples of 128); the tables of
   // views moved in blocks come last.  `blob` is that layout on the host for tables of up to 256 KiB and for plans that
@@ -181,8 +182,9 @@ struct ds_plan {
   bool mostly_rests(bool at_once) const {
     return n_rests * 4 > rest_recs.size() * 3 && (at_once ? rest_most <= kRestUnits : rest_units <= n_rests * kRestUnits);
   }
-  // Are most blocks narrow ones along a (see ds_perm_order)?
+  // Are most blocks narrow ones along a, or along b with lines that others far on read too (see ds_perm_order)?
   bool mostly_columns() const { return n_column_blocks * 2 > perm_items.size(); }
+  bool mostly_far() const { return n_far_blocks * 2 > perm_items.size(); }
   // Do most chunks of a launch hold several contiguous tensors, in a plan that has views too and an image of more than
   // 16 MiB?  They then take the general path with four units per thread, whose chain of dependent loads (record,
   // descriptors, data) one unit per thread, with a quarter of the bytes in flight, pays four times.  Four units / one, us,

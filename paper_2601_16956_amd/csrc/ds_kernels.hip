@@ -2031,7 +2031,7 @@ int launch_move_with(const ds_plan *plan, DeviceTables tb, bool pack, uint8_t *i
     a.items = tb.perm_items + first;
     a.n_items = (uint32_t)(last - first);
     if (variant != 3 && a.n_items < kPermOrdered) {
-      const DsPermOrder order = ds_perm_order(a.n_items, pack, plan->mostly_columns());
+      const DsPermOrder order = ds_perm_order(a.n_items, pack, pack ? plan->mostly_far() : plan->mostly_columns());
       a.xcd_span = order.span;
       a.stripe = order.stripe;
       a.magic = order.magic;

@@ -1033,14 +1033,19 @@ struct DsPermOrder {
   uint32_t magic;   // ds_perm_magic of it; 0: one stripe per XCD
 };
 constexpr uint32_t kPermOrdered = 1u << 27;
-// `columns`: a launch whose blocks are mostly narrow ones along a keeps one stripe per XCD for the scatter, whose stores
-// of parts of lines wait in the L2 for the others: these are a few dozen blocks or the rest of a column further.
-// In stripes / one per XCD, scatter, us: fp32 37 x 96 x 2230 of 37 x 3552, five of them, 119 / 99, 1883 x 2672, five, 57 / 54,
+// `together`: one stripe per XCD, for launches whose blocks share lines with blocks too far on for a stripe.
+// Scatters of mostly narrow blocks along a: their stores of parts of lines wait in the L2 for the others, which are a few
+// dozen blocks or the rest of a column further.  In stripes / one per XCD, scatter, us: fp32 37 x 96 x 2230 of 37 x 3552, five of them, 119 / 99, 1883 x 2672, five, 57 / 54,
 // bf16 332 941 x 214 111 / 105, bytes 2273 x 3283, 20 of them, 94 / 87; but bytes 15 298 x 194, five, 0.95 of the time.
 // (Wide blocks the other way round: i64 804 x 3735, five, 0.89, bf16 41 282 x 400, five, 0.90.)
-static inline DsPermOrder ds_perm_order(uint32_t n, bool pack, bool columns = false) {  // 0 < n < kPermOrdered
+// Gathers of mostly walks along b whose lines the next batches read too, kPermFarBlocks blocks and more further: in stripes / one
+// per XCD, us, bytes 186 x 37 605 x 9 with strides of 18, 3348 and 2, 21 blocks, 111 / 90, bf16 184 x 59 034 x 2, 15 blocks,
+// 140 / 125, 11 x 24 648 x 3, 20 of them, 10 blocks, 66 / 59, fp32 268 x 13 719 x 8, 54 blocks, 109 / 101; nearer ones: two
+// blocks, bytes 3000 x 3000 x 8, 90 / 114, bf16 4096 x 4096 x 4 156 / 154, four, fp32 2048 x 2048 x 4, 68 / 64.
+constexpr uint32_t kPermFarBlocks = 8;
+static inline DsPermOrder ds_perm_order(uint32_t n, bool pack, bool together = false) {  // 0 < n < kPermOrdered
   const uint32_t blocks = 8 * (pack ? 64 : 48);
-  const uint32_t rounds = n < (pack ? 2048 : 768) || (columns && !pack) ? 1 : (n + blocks / 2) / blocks;
+  const uint32_t rounds = n < (pack ? 2048 : 768) || together ? 1 : (n + blocks / 2) / blocks;
   uint32_t stripe = (n + rounds * 8 - 1) / (rounds * 8);
   if (stripe < 2) stripe = 2;
   return {rounds * stripe, stripe, rounds == 1 ? 0 : ds_perm_magic(stripe)};

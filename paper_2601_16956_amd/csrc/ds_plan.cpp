@@ -488,6 +488,8 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
             p->perms.push_back(perm);
             p->any_wide |= (perm.flags & kPermWide) != 0;
             if ((perm.flags & (kPermAlongA | kPermFlat | kPermWide)) == kPermAlongA) p->n_column_blocks += blocks;
+            if (!(perm.flags & (kPermAlongA | kPermOnce)) && perm.n_batch && perm.tiles_a * perm.tiles_b >= kPermFarBlocks)
+              p->n_far_blocks += blocks;
             in_blocks.push_back((uint32_t)t);
             block_bytes += tl.nbytes;
           } else if (n_outer > 1 || (n_outer && tl.run_bytes < 16)) {
@@ -502,7 +504,7 @@ int ds_plan_create_files(const ds_shard_desc *given, const uint32_t *file_of, si
         } else {
           p->perms.clear();
           p->perm_first.clear();
-          p->n_column_blocks = 0;
+          p->n_column_blocks = p->n_far_blocks = 0;
         }
         // what the general path is left with of views with short runs
         uint64_t one_element = 0;

@@ -11,10 +11,10 @@ static uint32_t deal(uint32_t n, const DsPermOrder &o, uint8_t *hits) {
 
 // Counts in `hits` how often each of n blocks is taken; returns the work-groups of the launch.
 extern "C" uint32_t order_host_deal(uint32_t n, int pack, uint8_t *hits) { return deal(n, ds_perm_order(n, pack != 0), hits); }
-extern "C" uint32_t order_host_deal_columns(uint32_t n, int pack, uint8_t *hits) {
+extern "C" uint32_t order_host_deal_together(uint32_t n, int pack, uint8_t *hits) {
   return deal(n, ds_perm_order(n, pack != 0, true), hits);
 }
 // Neighbouring blocks that an XCD takes one after the other.
-extern "C" uint32_t order_host_stripe(uint32_t n, int pack, int columns) {
-  return ds_perm_order(n, pack != 0, columns != 0).stripe;
+extern "C" uint32_t order_host_stripe(uint32_t n, int pack, int together) {
+  return ds_perm_order(n, pack != 0, together != 0).stripe;
 }

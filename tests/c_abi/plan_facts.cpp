@@ -17,6 +17,7 @@ extern "C" void plan_facts(const ds_plan *p, uint64_t *out) {
   out[11] = p->mostly_columns();
   out[12] = p->mostly_rests(true);
   out[13] = p->mostly_rests(false);
+  out[14] = p->mostly_far();
   out[8] = 0;  // views whose units in the general path are moved an element per lane
   for (const DsTileHot &h : p->hot) out[8] += (h.meta & DS_HOT_LANES) != 0;
 }

@@ -29,20 +29,20 @@ def test_every_block_is_taken_once(tmp_path, pack):
         assert launched <= max(16, n + 8 * (n // (8 * 48) + 1) + 8)
 
 
-def test_the_scatter_of_narrow_columns_has_one_stripe_per_xcd(tmp_path):
+def test_launches_whose_blocks_share_lines_far_on_have_one_stripe_per_xcd(tmp_path):
     so = str(tmp_path / "order_host.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-fPIC", "-shared", "-I",
                     os.path.join(ROOT, "paper_2601_16956_amd", "csrc"),
                     os.path.join(ROOT, "tests", "c_abi", "order_host.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
-    stripe, deal = lib.order_host_stripe, lib.order_host_deal_columns
+    stripe, deal = lib.order_host_stripe, lib.order_host_deal_together
     deal.restype, deal.argtypes = ctypes.c_uint32, [ctypes.c_uint32, ctypes.c_int, ctypes.c_void_p]
     for n in (16, 767, 768, 5000, 100003, 8 * 65536, 8 * 65537 + 1, 700001, (1 << 22) - 1, (1 << 27) - 8):
-        hits = np.zeros(n, dtype=np.uint8)
-        assert deal(n, 0, hits.ctypes.data) == 8 * -(-n // 8)
-        assert hits.min() == hits.max() == 1
-        assert stripe(n, 0, 1) == -(-n // 8)
-        assert stripe(n, 1, 1) == stripe(n, 1, 0)
+        for pack in (0, 1):
+            hits = np.zeros(n, dtype=np.uint8)
+            assert deal(n, pack, hits.ctypes.data) == 8 * -(-n // 8)
+            assert hits.min() == hits.max() == 1
+            assert stripe(n, pack, 1) == -(-n // 8)
     assert stripe(5000, 0, 0) < 64 and stripe(5000, 1, 0) < 128
 
 

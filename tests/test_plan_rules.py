@@ -12,7 +12,7 @@ from workloads.configs import DTYPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FACTS = ("n_chunks", "n_general", "n_perm_chunks", "n_perms", "n_blocks", "n_listed", "mostly_general",
-         "in_pieces", "n_lanes", "n_dims", "mostly_several", "mostly_columns", "rests_at_once", "rests")
+         "in_pieces", "n_lanes", "n_dims", "mostly_several", "mostly_columns", "rests_at_once", "rests", "mostly_far")
 
 
 @pytest.fixture(scope="module")
@@ -166,3 +166,13 @@ def test_chunks_that_hold_little_besides_blocks(facts):
         assert f.n_perms and not f.rests and not f.rests_at_once
     f = facts(_small(400, 20))
     assert not f.n_perms and not f.rests
+
+
+def test_the_gather_of_lines_that_blocks_far_on_share_keeps_one_stripe_per_xcd(facts):
+    """Walks along b in short pieces, with batches between the pieces of a line: from eight blocks to a batch on."""
+    far, near = ("u8", (20, 16384, 9), (18, 400, 2)), ("u8", (20, 3000, 8), (16, 400, 2))
+    assert facts([far]).mostly_far and facts([far] * 3 + [("f32", (50000,), (2,))]).mostly_far
+    for other in (near, ("f32", (500000,), (2,)), ("bf16", (900, 700), (1500, 2)), ("bf16", (512, 2847), (1, 512)),
+                  ("f32", (300, 300, 9), (2700, 1, 300))):
+        assert not facts([other]).mostly_far
+    assert not facts([far] + [("f32", (2000000,), (2,))]).mostly_far
