@@ -143,10 +143,12 @@ def hip_runtime_in_use() -> List[str]:
 
 
 def kernel_source_digest() -> str:
-    """SHA-256 (first 16 hex digits) over the kernel sources; a counter profile names the digest it was taken
-    with, so that a reader of a measurement can tell whether the profile still describes the kernels in use."""
+    """SHA-256 (first 16 hex digits) over the kernel sources and the compiler's flags; a counter profile names the digest it was
+    taken with, so that a reader of a measurement can tell whether the profile still describes the kernels in use."""
     import hashlib
-    h = hashlib.sha256()
+
+    from .build import HIPCC_FLAGS
+    h = hashlib.sha256("\0".join(HIPCC_FLAGS).encode())
     for name in ("ds_kernels.hip", "ds_blocks.h", "ds_splice.h", "ds_internal.h", "ds_perm.h"):
         with open(os.path.join(_HERE, "csrc", name), "rb") as f:
             h.update(f.read())

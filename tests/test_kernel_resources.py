@@ -111,3 +111,12 @@ def test_blocks_that_are_not_wide_have_seven_work_groups_per_CU():
         for args, k in _kernels()[name]:
             six = name == "ds_mixed_kernel" and args[0] == "true" and args[2] == "1"
             assert _waves(k) >= (5 if args[-1] == "true" else 6 if six else 7), (name, args, k[".vgpr_count"])
+
+
+def test_the_digest_that_profiles_name_covers_the_flags(monkeypatch):
+    import paper_2601_16956_amd as ds
+    from paper_2601_16956_amd import build
+    before = ds.kernel_source_digest()
+    assert ds.kernel_source_digest() == before
+    monkeypatch.setattr(build, "HIPCC_FLAGS", [f for f in build.HIPCC_FLAGS if "preload" not in f])
+    assert ds.kernel_source_digest() != before
