@@ -1310,13 +1310,14 @@ int launch_several(const ds_plan *plan, bool pack, const LeanArgs &la, const Mov
 // That table: unit by unit 460 / 524 us, in narrow blocks 100 / 108, now 79 / 98; channels-last 14.1 / 14.5, now 10.8 /
 // 13.1; every second fp32 column 10.9 / 14.4, now 10.1 / 12.8; with the blocks in stripes over the XCDs (ds_perm_order) and
 // streaming loads (STREAM: images that no cache holds until the next pass) 63.2 / 68.8, with short rows and short runs in larger
-// accesses (ds_perm_groups, ds_perm_runs) 61.5 / 67.2; the lines of which views hold parts, which the gather reads whole and a
-// scatter makes HBM read and write, leave 54 / 65 at the rate of a copy.  Streaming loads alone are worth, us:
+// accesses (ds_perm_groups, ds_perm_runs) 61.5 / 67.2, now 57.5 / 64.0; with the lines of which views hold parts, 38 MB that the
+// counters see the gather read and the scatter write, a plain copy would take 55.  Streaming loads alone are worth, us:
 // gather, where no line of the tensor is another block's too (kPermOnce), bf16 4096 x 4096 62.4 / 59.5 (five of them), every
 // second column 86.5 / 80.6 (ten), channels-last 75.8 / 72.1; where lines are shared they cost (bytes 4096 x 4120 68 / 81);
 // the scatter's loads 62.4 / 57.9, but not beside wide blocks whose stores stay in the caches to meet their lines' other
-// parts (1000 x 1007 75.4 / 82.1).  Images that the last-level cache holds lose (one of 33 MB 13.1 / 16.5).
-// Blocks are numbered along b first: along a first costs 15 % of the gather.  LDS has room for five work-groups per CU, in launches without wide blocks (WIDE = false) for seven:
+// parts (1000 x 1007 75.4 / 82.1), and not in short rows, whose lines several blocks read (kPermImageOnce).  Images that the last-level cache holds lose (one of 33 MB 13.1 / 16.5).
+// Blocks are numbered along b first: along a first costs 15 % of the gather.  LDS has room for five work-groups per CU, in
+// launches without wide blocks (WIDE = false) for seven:
 // 8000 squares of 24 bf16, gather / scatter, 30.4 / 32.0 with five, 27.1 / 28.8 with seven; a channels-last convolution of 46 MB
 // 24.0 / 28.5 and 21.7 / 26.1; three of every eight bytes 34.1 / 42.9 and 32.9 / 43.0.
 struct PermArgs {

@@ -477,8 +477,8 @@ DS_PERM_FN void ds_perm_put_bytes(uint64_t p, uint32_t n, const uint32_t *w) {
 // ---- flat blocks dense along a (kPermGroups), tensor side ----
 // 16 bytes of neighbours along a at a time, group by group along a and column by column.  Gather: where the block is no
 // whole number of groups, each column's last one is pulled back and moves some elements twice; the scatter stores the
-// elements behind the last whole group, and in front of the view's cut unit, in at most four pieces.  As few blocks as 16 KiB allow, of equal length: in powers of two, one
-// element per thread and column, 536 x 536 x 9 fp32 channels-last (155 MB of them, us) 76.7 / 88.5, now 54.5 / 63.8 (a plain copy
+// elements behind the last whole group, and in front of the view's cut unit, in at most four pieces.  Blocks of equal length, as
+// few as fit: in powers of two, one element per thread and column, 536 x 536 x 9 fp32 channels-last (155 MB of them, us) 76.7 / 88.5, now 54.5 / 63.8 (a plain copy
 // 48.5), one of 10 MB 7.6 / 9.5, now 6.2 / 7.1; transposed bytes 256 x 265 (54 MB) 28.2 / 40.2, now 20.6 / 30.9.
 template <typename E, bool PACK, bool NT>
 DS_PERM_FN void ds_perm_groups(const DS_PERM_TABLE DsPerm &d, const DsPermBlock &k, uint8_t *lds, uint32_t tid) {
@@ -1035,8 +1035,9 @@ struct DsPermOrder {
 constexpr uint32_t kPermOrdered = 1u << 27;
 // `together`: one stripe per XCD, for launches whose blocks share lines with blocks too far on for a stripe.
 // Scatters of mostly narrow blocks along a: their stores of parts of lines wait in the L2 for the others, which are a few
-// dozen blocks or the rest of a column further.  In stripes / one per XCD, scatter, us: fp32 37 x 96 x 2230 of 37 x 3552, five of them, 119 / 99, 1883 x 2672, five, 57 / 54,
-// bf16 332 941 x 214 111 / 105, bytes 2273 x 3283, 20 of them, 94 / 87; but bytes 15 298 x 194, five, 0.95 of the time.
+// dozen blocks or the rest of a column further.  In stripes / one per XCD, us: fp32 37 x 96 x 2230 of 37 x 3552, five of them,
+// 119 / 99, 1883 x 2672, five, 57 / 54, bf16 332 941 x 214 111 / 105, bytes 2273 x 3283, 20 of them, 94 / 87; but bytes 15 298 x
+// 194, five, 0.95 of the time.
 // (Wide blocks the other way round: i64 804 x 3735, five, 0.89, bf16 41 282 x 400, five, 0.90.)
 // Gathers of mostly walks along b whose lines the next batches read too, kPermFarBlocks blocks and more further: in stripes / one
 // per XCD, us, bytes 186 x 37 605 x 9 with strides of 18, 3348 and 2, 21 blocks, 111 / 90, bf16 184 x 59 034 x 2, 15 blocks,
