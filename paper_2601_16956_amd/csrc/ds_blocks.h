@@ -22,10 +22,11 @@ DS_BLOCKS_FN DsBlockPlace ds_block_place(uint64_t unit, uint32_t units_per_block
 
 // A look for a block that is not constant takes segments of up to 64 KiB ...
 constexpr uint32_t kSegmentUnitsLog2 = 12;
-// ... or, in images of up to 16 MiB, blocks of 128 and 256 KiB whole (ds_constant_blocks_kernel says what that saves and why not
-// larger ones).
+// ... or, in images of up to 16 MiB, blocks of 128 KiB to 1 MiB whole, by one work-group or four.  The work-groups per block, as
+// a power of two; -1: segments.  (ds_constant_blocks_kernel says why.)
 constexpr uint64_t kWholeBlocksBytes = 16ull << 20;
-constexpr uint32_t kWholeBlockUnitsLog2 = 14;
-DS_BLOCKS_FN bool ds_looks_at_whole_blocks(uint64_t nbytes, uint32_t units_per_block_log2) {
-  return units_per_block_log2 > kSegmentUnitsLog2 && units_per_block_log2 <= kWholeBlockUnitsLog2 && nbytes <= kWholeBlocksBytes;
+constexpr uint32_t kWholeBlockUnitsLog2 = 16, kOnePartUnitsLog2 = 14, kBlockPartsLog2 = 2;
+DS_BLOCKS_FN int ds_block_parts_log2(uint64_t nbytes, uint32_t units_per_block_log2) {
+  if (units_per_block_log2 <= kSegmentUnitsLog2 || units_per_block_log2 > kWholeBlockUnitsLog2 || nbytes > kWholeBlocksBytes) return -1;
+  return units_per_block_log2 <= kOnePartUnitsLog2 ? 0 : (int)kBlockPartsLog2;
 }

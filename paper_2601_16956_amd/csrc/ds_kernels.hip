@@ -1609,30 +1609,33 @@ __global__ __launch_bounds__(256) void ds_constant_segments_kernel(const u32x4 *
   }
 }
 
-// The same for blocks of 128 and 256 KiB in images of up to 16 MiB: one work-group looks at a block, so that no flags have
-// to be cleared by a launch of their own.  Behind the block's first 16 KiB it takes 256 KiB at a time.  Bound by the latency
-// of those steps where blocks are constant, hence the line: one CU reads a constant block of 1 MiB in 20 us.  All of
-// ds_image_compress, us, so / in segments: 8 MB that no cache holds, all of it constant, in blocks of 128 KiB 8.2 / 11.5, of 256
-// KiB 9.4 / 11.6, of 512 KiB 14.3 / 11.5, of 1 MiB 23.9 / 11.4; in the caches 6.7 / 10.1, 6.3 / 10.2, 8.6 / 10.3 and 12.8 /
-// 10.3; nothing constant 6.2 / 10.3, 6.2 / 10.3, 7.8 / 10.1, 7.6 / 10.3.
+// The same for blocks of 128 KiB to 1 MiB in images of up to 16 MiB: one work-group looks at a block of up to 256 KiB, four at a
+// larger one, so that no flags have to be cleared by a launch of their own.  Behind its first 16 KiB a work-group takes the rest
+// at once.  Bound by the latency of that where blocks are constant: one CU reads a constant block of 1 MiB in 20 us.
+// Four leave a byte of the block's flag each; ds_count_and_pack_kernel makes 1 of them.  All of ds_image_compress, us, one
+// work-group per block / in segments / now: 8 MB that no cache holds, all of it constant, in blocks of 128 KiB 8.2 / 11.5, of
+// 256 KiB 9.4 / 11.6, of 512 KiB 14.3 / 11.5 / 8.0, of 1 MiB 23.9 / 11.4 / 9.2; in the caches and in a captured graph 6.8 / 9.3,
+// 6.4 / 9.5, 8.5 / 9.4 / 6.2, 12.8 / 9.4 / 6.0; nothing constant 5.5 / 7.0, 5.4 / 7.1, 5.2 / 7.6 / 5.5, 5.2 / 7.5 / 5.3.
 constexpr uint32_t kBlockThreads = 1024, kBlockUnroll = 16;
+template <uint32_t PARTS_LOG2>
 __global__ __launch_bounds__(kBlockThreads) void ds_constant_blocks_kernel(const u32x4 *__restrict__ img, uint64_t n_units,
                                                                            uint32_t units_per_block_log2,
                                                                            uint32_t *__restrict__ keep,
                                                                            u32x4 *__restrict__ patterns) {
-  const uint32_t tid = threadIdx.x;
-  const uint64_t first = (uint64_t)blockIdx.x << units_per_block_log2, left = n_units - first;
-  const uint32_t n = left < (1ull << units_per_block_log2) ? (uint32_t)left : 1u << units_per_block_log2;
-  const u32x4 *const block = img + first;
-  const u32x4 ref = block[0];
-  u32x4 d = block[tid < n ? tid : 0] ^ ref;
+  const uint32_t tid = threadIdx.x, block = blockIdx.x >> PARTS_LOG2, part = blockIdx.x & ((1u << PARTS_LOG2) - 1);
+  const uint32_t units_log2 = units_per_block_log2 - PARTS_LOG2;  // of a work-group
+  const uint64_t first = (uint64_t)blockIdx.x << units_log2, left = first < n_units ? n_units - first : 0;
+  const uint32_t n = left < (1ull << units_log2) ? (uint32_t)left : 1u << units_log2;  // (0: behind the end of the image)
+  const u32x4 ref = img[(uint64_t)block << units_per_block_log2];
+  u32x4 d = u32x4{0, 0, 0, 0};
+  if (tid < n) d = img[first + tid] ^ ref;
   int any = __syncthreads_or((d.x | d.y | d.z | d.w) != 0);
   for (uint32_t base = kBlockThreads; base < n && !any; base += kBlockUnroll * kBlockThreads) {
     u32x4 y[kBlockUnroll];
 #pragma unroll
     for (uint32_t i = 0; i < kBlockUnroll; ++i) {
       const uint32_t u = base + kBlockThreads * i + tid;
-      y[i] = block[u < n ? u : n - 1];
+      y[i] = img[first + (u < n ? u : n - 1)];
     }
     uint32_t diff = 0;
 #pragma unroll
@@ -1643,8 +1646,9 @@ __global__ __launch_bounds__(kBlockThreads) void ds_constant_blocks_kernel(const
     any = __syncthreads_or(diff != 0);
   }
   if (tid == 0) {
-    keep[blockIdx.x] = any ? 1u : 0u;
-    patterns[blockIdx.x] = ref;
+    if (PARTS_LOG2) ((uint8_t *)keep)[blockIdx.x] = any ? 1 : 0;
+    else keep[block] = any ? 1u : 0u;
+    if (part == 0) patterns[block] = ref;
   }
 }
 
@@ -1769,18 +1773,29 @@ int launch_pack_kept(const u32x4 *img, uint64_t n_units, uint32_t upb_log2, cons
 // Those are images that the last-level cache holds from the pass before.  Out of a rotation of 700 MB, blocks of 32 KiB, with
 // the scan / so / so with streaming loads: 16 MB 13.4 / 10.6 / 10.3, 34 MB 20.5 / 18.7 / 19.0, 64 MB 30.2 / 30.3 / 30.8; of
 // which 30 % is constant 15.0 / 12.4 / 11.7, 19.6 / 17.6 / 17.7, 27.7 / 26.5 / 25.9.
-constexpr uint64_t kCountedBlocks = 2048, kOneUnitBytes = 8ull << 20;
-template <int UNROLL>
+// PARTS: of each block's flag four work-groups left a byte.  These are at most 32 blocks; a wavefront reads all the flags, and the
+// first work-group of a block leaves 1 in place of its bytes.  Others may still read them: whole words on either side,
+// neither of them 0.  (Such loads pass the caches by: four units per thread from 6 MiB on, 8 MB in blocks of 512 KiB, nothing
+// constant, 7.0 / 5.6; 6 MB, half of it constant, one 6.8, four 7.6.)
+constexpr uint64_t kCountedBlocks = 2048, kOneUnitBytes = 8ull << 20, kOneUnitPartsBytes = 6ull << 20;
+static_assert((kWholeBlocksBytes >> (4 + kOnePartUnitsLog2 + 1)) <= kWave, "a lane per block in parts");
+template <int UNROLL, bool PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void ds_count_and_pack_kernel(
-    const u32x4 *__restrict__ img, uint32_t n_units, uint32_t units_per_block_log2, const uint32_t *__restrict__ keep,
-    uint32_t *__restrict__ pos, uint32_t n_blocks, u32x4 *__restrict__ packed) {
+    const u32x4 *__restrict__ img, uint32_t n_units, uint32_t units_per_block_log2, uint32_t *keep, uint32_t *__restrict__ pos,
+    uint32_t n_blocks, u32x4 *__restrict__ packed) {
   __shared__ uint32_t wave_sum[256 / kWave];
   constexpr uint32_t kUnits = 256 * UNROLL;  // in one block (of a power of two of at least 16 KiB)
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
   const uint32_t first = blockIdx.x * kUnits, left = n_units - first, mine = left < kUnits ? left : kUnits;
   const DsBlockPlace place = ds_block_place(first, units_per_block_log2);
   const uint32_t block = (uint32_t)place.block, in_block = (uint32_t)place.in_block;  // less than 2048, and 2^22
-  const uint32_t kept = keep[block];
+  uint64_t flags = 0;
+  if (PARTS) {
+    uint32_t flag = 0;
+    if (lane < n_blocks) flag = __hip_atomic_load(keep + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    flags = __ballot(flag != 0);
+  }
+  const uint32_t kept = PARTS ? (uint32_t)(flags >> block) & 1u : keep[block];
   if (!kept && in_block) return;
   u32x4 x[UNROLL];
   if (kept) {
@@ -1788,19 +1803,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
     for (uint32_t i = 0; i < UNROLL; ++i)
       if (tid + 256u * i < mine) x[i] = img[first + tid + 256u * i];
   }
-  uint32_t sum = 0;
-  for (uint32_t i = tid * 4; i < block; i += 1024) {
-    u32x4 v = u32x4{0, 0, 0, 0};
-    if (i + 4 <= n_blocks) v = ld16_any<false>((const uint8_t *)(keep + i));
-    else
-      for (uint32_t e = 0; e < 3; ++e)
-        if (i + e < n_blocks) v[e] = keep[i + e];
-    sum += v.x + (i + 1 < block ? v.y : 0u) + (i + 2 < block ? v.z : 0u) + (i + 3 < block ? v.w : 0u);
+  uint32_t slot = 0;
+  if (PARTS) {
+    slot = (uint32_t)__popcll(flags & ((1ull << block) - 1));
+    if (tid == 0 && in_block == 0 && kept) __hip_atomic_store(keep + block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    uint32_t sum = 0;
+    for (uint32_t i = tid * 4; i < block; i += 1024) {
+      u32x4 v = u32x4{0, 0, 0, 0};
+      if (i + 4 <= n_blocks) v = ld16_any<false>((const uint8_t *)(keep + i));
+      else
+        for (uint32_t e = 0; e < 3; ++e)
+          if (i + e < n_blocks) v[e] = keep[i + e];
+      sum += v.x + (i + 1 < block ? v.y : 0u) + (i + 2 < block ? v.z : 0u) + (i + 3 < block ? v.w : 0u);
+    }
+    sum = wave_inclusive_scan(sum);
+    if (lane == kWave - 1) wave_sum[tid / kWave] = sum;
+    __syncthreads();
+    slot = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
   }
-  sum = wave_inclusive_scan(sum);
-  if (lane == kWave - 1) wave_sum[tid / kWave] = sum;
-  __syncthreads();
-  const uint32_t slot = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
   if (tid == 0 && in_block == 0) {
     pos[block] = slot;
     if (block + 1 == n_blocks) pos[n_blocks] = slot + kept;
@@ -1834,9 +1855,13 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   const uint32_t ups_log2 = upb_log2 < kSegmentUnitsLog2 ? upb_log2 : kSegmentUnitsLog2;
   const uint64_t segments = (n_units + (1ull << ups_log2) - 1) >> ups_log2;
   const dim3 seg_grid((uint32_t)segments);
-  if (ds_looks_at_whole_blocks(nbytes, upb_log2)) {
-    hipLaunchKernelGGL(ds_constant_blocks_kernel, dim3((uint32_t)n_blocks), dim3(kBlockThreads), 0, st,
+  const int parts_log2 = ds_block_parts_log2(nbytes, upb_log2);
+  if (parts_log2 == 0) {
+    hipLaunchKernelGGL(ds_constant_blocks_kernel<0>, dim3((uint32_t)n_blocks), dim3(kBlockThreads), 0, st,
                        (const u32x4 *)image_dev, n_units, upb_log2, keep_dev, (u32x4 *)patterns_dev);
+  } else if (parts_log2 > 0) {
+    hipLaunchKernelGGL(ds_constant_blocks_kernel<kBlockPartsLog2>, dim3((uint32_t)n_blocks << kBlockPartsLog2), dim3(kBlockThreads), 0,
+                       st, (const u32x4 *)image_dev, n_units, upb_log2, keep_dev, (u32x4 *)patterns_dev);
   } else if (ups_log2 == upb_log2) {
     hipLaunchKernelGGL(ds_constant_segments_kernel<true>, seg_grid, dim3(256), 0, st, (const u32x4 *)image_dev, n_units,
                        upb_log2, ups_log2, keep_dev, (u32x4 *)patterns_dev);
@@ -1850,11 +1875,11 @@ extern "C" int ds_image_compress(const void *image_dev, uint64_t nbytes, uint64_
   if (n_blocks <= kCountedBlocks && nbytes <= kCachedBytes) {
     const auto launch = [&](auto kernel, uint32_t units) {
       hipLaunchKernelGGL(kernel, dim3((uint32_t)((n_units + units - 1) / units)), dim3(256), 0, st, (const u32x4 *)image_dev,
-                         (uint32_t)n_units, upb_log2, (const uint32_t *)keep_dev, pos_dev, (uint32_t)n_blocks,
-                         (u32x4 *)packed_dev);
+                         (uint32_t)n_units, upb_log2, keep_dev, pos_dev, (uint32_t)n_blocks, (u32x4 *)packed_dev);
     };
-    if (nbytes <= kOneUnitBytes) launch(ds_count_and_pack_kernel<1>, 256);
-    else launch(ds_count_and_pack_kernel<4>, 1024);
+    const bool parts = parts_log2 > 0;
+    if (nbytes <= (parts ? kOneUnitPartsBytes : kOneUnitBytes)) launch(parts ? ds_count_and_pack_kernel<1, true> : ds_count_and_pack_kernel<1, false>, 256);
+    else launch(parts ? ds_count_and_pack_kernel<4, true> : ds_count_and_pack_kernel<4, false>, 1024);
     DS_HIP_TRY(hipGetLastError());
     return DS_OK;
   }

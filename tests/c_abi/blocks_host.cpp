@@ -7,6 +7,6 @@ extern "C" void blocks_host_place(uint64_t unit, uint32_t units_per_block_log2, 
   out[1] = p.in_block;
 }
 
-extern "C" int blocks_host_whole(uint64_t nbytes, uint32_t units_per_block_log2) {
-  return ds_looks_at_whole_blocks(nbytes, units_per_block_log2);
+extern "C" int blocks_host_parts_log2(uint64_t nbytes, uint32_t units_per_block_log2) {
+  return ds_block_parts_log2(nbytes, units_per_block_log2);
 }
