@@ -48,6 +48,7 @@ constexpr uint64_t kPermMinBytes = 1024;
 // Images of at most so many bytes have smaller blocks, which all run at once: what one takes is what the launch takes.  (Larger ones
 // have more blocks than run at once, and pay for each.)
 constexpr uint64_t kPermFewBytes = 2ull << 20;
+constexpr uint64_t kPermCacheBytes = 256ull << 20;  // the last-level cache
 constexpr int kPermUnroll = 8;             // granules a thread has in flight
 
 enum : uint32_t { kPermAlongA = 1u << 8, kPermFlat = 1u << 9, kPermFull = 1u << 10, kPermLines = 1u << 11,
@@ -994,8 +995,24 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   // bytes (bf16 332 941 x 214) 127 / 111, (fp32 37 x 96 x 2230 of 37 x 3552, five) 136 / 118, of 48 bytes (fp32 1000 x 1000
   // x 4 x 3) 90 / 80, though of 240 bytes (fp32 1883 x 2672, five) 49 / 57 too; of 512 (i64 50 x 362, 500 of them) 0.74 of
   // the time, (157 x 97 936) 0.86, of 496 (19 x 307) 0.92; pieces (fp32 660 343 x 6, five) 0.83, (25 x 372 x 372, five) 0.90.
+  // Narrow blocks along a store parts of lines of the tensor; beside them the loads stream only as long as the image and the
+  // tensors (as many bytes of them for each of the image as this view takes) fit the last-level cache, or seven eighths of it
+  // where rows do not start at lines.  Streaming / cached, us: together 144 MB (i64 50 x 362, 500 of them, columns of 50) 31.6 /
+  // 36.4, 202 MB (columns of 90) 35.2 / 48.1, 205 MB (24 x 65 537 of 25, eight) 54.8 / 64.0, 249 MB (33 x 515 of 34, 900) 80.3 / 73.6,
+  // 302 MB (157 x 20 001 of 158, six) 101.2 / 94.6, 331 MB (fp32 9 x 18 066 of 10, 241) 109 / 101; rows of lines, 246 MB (i64 157 x
+  // 97 936) 66.4 / 80.7, 258 MB (fp32 62 x 65 536 of 102, six) 66.5 / 74.4, 292 MB (i64 33 x 100 000 of 40, five) 98.7 / 92.3, 390 MB
+  // (33 x 512 of 73, 900) 96.1 / 91.7; but 277 MB (157 x 97 936 of 197) 74.5 / 83.6.
   const bool rows_of_lines = flat || ((image_bits | tb * run) & (kPermLine - 1)) == 0;
-  const bool image_once = wide ? (columns & 63) == 0 : rows_of_lines || tb * run >= 3 * kPermLine;
+  bool image_once = wide ? (columns & 63) == 0 : rows_of_lines || tb * run >= 3 * kPermLine;
+  if (along_a && !wide && !flat) {
+    uint64_t whole = run;  // bytes from the view's first to its last, or of its batches if these lie apart
+    for (uint32_t j = 0; j < n_outer; ++j)
+      if (extent[j] * stride[j] > whole) whole = extent[j] * stride[j];
+    const uint64_t parts = d->ea * d->sa > d->eb * d->sb ? d->ea * d->sa : d->eb * d->sb;
+    const double apart = (double)batches * (double)parts, span = apart < (double)whole ? apart : (double)whole;
+    const uint64_t room = rows_of_lines ? kPermCacheBytes : kPermCacheBytes / 8 * 7;
+    if ((double)image_bytes * (1.0 + span / (double)nbytes) > (double)room) image_once = false;
+  }
   d->flags = g_log2 | (along_a ? kPermAlongA : 0u) | (flat ? kPermFlat : 0u) | (full ? kPermFull : 0u) |
              (groups ? kPermGroups : 0u) | (rows_of_lines ? kPermLines : 0u) | (wide ? kPermWide : 0u) |
              (wide && (columns & 63) == 0 ? kPermStream : 0u) |

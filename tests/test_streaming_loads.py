@@ -61,3 +61,24 @@ SCATTERS = [
 def test_the_scatter_streams_lines_of_one_block(lib, dtype, shape, strides, at, streams):
     assert _check(lib.perm_host_move, dtype, shape, strides, 0, at, np.random.default_rng(1)) > 0
     assert bool(lib.perm_host_image_streams()) == streams
+
+
+# (view, bytes of the whole image, do the scatter's loads stream?): narrow blocks along a, image and tensors on either side of
+# 7/8 of 256 MiB, with rows of whole lines of 256 MiB, and of batches that lie apart; blocks that are not of that kind, whatever the image has
+CACHED = [
+    ("i64", (50, 362), (1, 50), 117 * 10**6, True), ("i64", (50, 362), (1, 50), 118 * 10**6, False),
+    ("i64", (50, 362), (1, 100), 78 * 10**6, True), ("i64", (50, 362), (1, 100), 79 * 10**6, False),
+    ("i64", (33, 512), (1, 33), 134 * 10**6, True), ("i64", (33, 512), (1, 33), 135 * 10**6, False),
+    ("i64", (3, 50, 362), (362 * 200, 1, 100), 78 * 10**6, True), ("i64", (3, 50, 362), (362 * 200, 1, 100), 79 * 10**6, False),
+    ("f32", (512, 9), (1, 512), 10**9, True), ("f32", (3000,), (2,), 10**9, True)]
+
+
+@pytest.mark.parametrize("dtype,shape,strides,image_bytes,streams", CACHED)
+def test_the_scatter_streams_beside_tensors_that_the_cache_holds(lib, dtype, shape, strides, image_bytes, streams):
+    image = ctypes.c_uint64(image_bytes)
+    lib.perm_host_image_bytes(image)
+    try:
+        assert _check(lib.perm_host_move, dtype, shape, strides, 0, 512, np.random.default_rng(1)) > 0
+        assert bool(lib.perm_host_image_streams()) == streams
+    finally:
+        lib.perm_host_image_bytes(ctypes.c_uint64(1 << 20))
