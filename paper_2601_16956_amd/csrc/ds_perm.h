@@ -933,12 +933,22 @@ static inline uint64_t ds_perm_make(uint64_t src, uint64_t img, uint64_t nbytes,
   // flat, dense along a: as few blocks as 16 KiB allow, in small images 8, of equal length, in whole groups of 16 bytes (us, 16
   // / 8 KiB: fp32 with six columns, 1 MB, 3.4 / 3.1, scatter 3.8 / 3.1, 8 MB 4.5 / 4.8 and 5.8 / 5.9; bytes with 60, 350 KB
   // 5.0 / 3.6 and 5.6 / 3.5; fp32 512 x 512 x 9, 9.4 MB, 5.3 / 6.3 and 7.1 / 7.3)
-  const bool groups = flat && along_a && run == g && d->sa == g && d->ea >= 16 / g;
+  // Neighbouring threads write LDS 16 bytes' worth of rows apart, which is 4 words for each of the columns: columns in multiples of
+  // 4 leave 4 banks or fewer.  That costs nothing where a block has few groups along a, three for each bank (four of
+  // 16-bit elements), and is still the better way for rows of 8 bytes or less on 4 banks.  One element per thread and column /
+  // groups, gather of 130 MB, us: bytes in 24 columns 77 / 220, 72 columns 72 / 110, 60 columns 67 / 75, 84 columns 0.79 of the time,
+  // 200 columns 69 / 52, 4 columns 0.51; bf16 in 20 columns 55 / 62, 28 columns 53 / 60, 100 columns 56 / 47, 4 columns 128 / 66; 12 MB
+  // of bf16 in 12 columns 8.4 / 9.6, bytes in 136 columns 1.22 of the time, bf16 in 68 the same.
+  bool groups = flat && along_a && run == g && d->sa == g && d->ea >= 16 / g;
   if (groups) {
     const uint32_t G = 16 / g, fit = few ? (uint32_t)(8192 / row_bytes) : ta, most = (fit < ta ? fit : ta) / G * G;
-    const uint32_t n = (d->ea + most - 1) / most;
-    ta = ((d->ea + n - 1) / n + G - 1) / G * G;
-  } else if (along_a) {  // a power of two, of at most one step along a per thread
+    const uint32_t n = (d->ea + most - 1) / most, even = ((d->ea + n - 1) / n + G - 1) / G;  // blocks, groups of each
+    uint32_t banks = 16;
+    for (uint32_t c = d->eb; banks > 1 && !(c & 1); c /= 2) banks /= 2;
+    if (banks <= 4 && (even < 64 ? even : 64) > (g == 1 ? 3 : 4) * banks && !(banks == 4 && row_bytes <= 8)) groups = false;
+    else ta = even * G;
+  }
+  if (!groups && along_a) {  // a power of two, of at most one step along a per thread
     uint32_t p = 1;
     while (2 * p <= ta && 2 * p <= kPermThreads && p < d->ea) p *= 2;
     ta = p;

@@ -63,6 +63,8 @@ extern "C" void perm_host_image_bytes(uint64_t n) { g_image_bytes = n; }
 // The loads of the tensor by gathers as in images that no cache holds, and how many of them streamed.
 extern "C" uint64_t perm_host_loads() { return g_large; }
 extern "C" uint64_t perm_host_streamed() { return g_streamed; }
+// Is the last view moved 16 bytes along the columns at a time?
+extern "C" int perm_host_groups() { return (g_flags & kPermGroups) != 0; }
 // Do the scatter's loads of the image stream for the last view?
 extern "C" int perm_host_image_streams() { return (g_flags & kPermImageOnce) != 0; }
 

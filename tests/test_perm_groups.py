@@ -1,10 +1,13 @@
 """Blocks of short rows that are dense along a (16 bytes of neighbours at a time) and runs of 12 bytes, thread by thread on
 the CPU and, in one table, on the GPU."""
+import ctypes
+
 import numpy as np
 import pytest
 
 from oracle import ds_oracle as orc
 from test_perm_blocks import _check, host  # noqa: F401  (the fixture)
+from test_streaming_loads import lib  # noqa: F401  (the fixture)
 from workloads.configs import DTYPES, Shard, Workload
 
 # whole groups and rests of each element size, last blocks of less than a group, one row to a block, batches; runs of 12
@@ -24,6 +27,25 @@ def test_blocks_move_exactly_the_view(host, k):  # noqa: F811
     rng = np.random.default_rng(k)
     for shift, at in ((0, 0), (1, 16), (2, 512), (4, 80)):
         assert _check(host, dtype, shape, strides, shift, at, rng) > 0
+
+
+# (view, 16 bytes along the columns at a time?): columns that leave 4 banks of LDS or fewer, on either side of the groups per block
+# that these serve, and rows of at most 8 bytes
+BANKS = [
+    ("u8", (3000, 24), (1, 3000), False), ("u8", (3000, 33), (1, 3000), True), ("u8", (3000, 34), (1, 3000), True),
+    ("u8", (3000, 60), (1, 3000), False), ("u8", (3000, 72), (1, 3000), False), ("u8", (900, 84), (1, 900), True),
+    ("u8", (3000, 76), (1, 3000), False), ("u8", (900, 136), (1, 900), False), ("u8", (900, 200), (1, 900), True),
+    ("u8", (9000, 4), (1, 9000), True), ("u8", (9000, 8), (1, 9000), False), ("u8", (9000, 12), (1, 9000), False),
+    ("bf16", (5000, 4), (1, 5000), True), ("bf16", (5000, 12), (1, 5000), False), ("bf16", (3000, 28), (1, 3000), False),
+    ("bf16", (900, 60), (1, 900), False), ("bf16", (900, 68), (1, 900), True), ("bf16", (3, 900, 20), (18000, 1, 900), False),
+    ("f32", (3000, 6), (1, 3000), True), ("i64", (900, 9), (1, 900), True)]
+
+
+@pytest.mark.parametrize("dtype,shape,strides,groups", BANKS)
+def test_groups_where_the_banks_allow(lib, dtype, shape, strides, groups):  # noqa: F811
+    lib.perm_host_image_bytes(ctypes.c_uint64(4 << 20))
+    assert _check(lib.perm_host_move, dtype, shape, strides, 0, 512, np.random.default_rng(1)) > 0
+    assert bool(lib.perm_host_groups()) == groups
 
 
 @pytest.mark.gpu
